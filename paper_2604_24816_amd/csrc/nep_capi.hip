@@ -145,6 +145,7 @@ struct nep_system {
   double* mparams64[2];
   Model64 m64[2];
   int nblocks = 1;
+  int ew_rows = 1;  // rows of energy and virial partials of the last evaluation
   // kernel timing with events (off unless nep_profile enables it)
   bool prof = false;
   std::vector<hipEvent_t> pool;
@@ -343,7 +344,7 @@ EvalBuffers eval_buffers(nep_system* s, int slot) {
   b.rec = s->rec;
   b.G = s->G;
   b.F = s->F[slot];
-  b.partial = s->partial;
+  b.ew = s->gpart;  // the gradient partials' buffer, free during an evaluation (256 doubles per tile are enough)
   b.flags = s->flags;
   b.flag_r = slot == 0 ? FLAG_BIN_R : FLAG_BIN_R1;
   b.flag_a = slot == 0 ? FLAG_BIN_A : FLAG_BIN_A1;
@@ -357,6 +358,7 @@ void prof_pair(nep_system* s, hipEvent_t* base, int a, int b, int group);
 int do_eval(nep_system* s, int slot, int prec) {
   hipEvent_t* ev = prof_take(s, 3);
   HIPCHK(launch_eval(s->mdev[slot], prec, eval_buffers(s, slot), s->st, ev));
+  s->ew_rows = eval_rows(s->N);
   if (ev) {
     prof_pair(s, ev, 0, 1, slot == 0 ? 0 : 4);
     prof_pair(s, ev, 1, 2, slot == 0 ? 1 : 5);
@@ -368,7 +370,7 @@ int do_eval(nep_system* s, int slot, int prec) {
 
 // Reduce energy + virial partials into res[base .. base+10).
 int reduce_ew(nep_system* s, int base) {
-  HIPCHK(launch_reduce_partials(s->partial, s->nblocks, P_ENERGY, 10, s->res + base, s->st));
+  HIPCHK(launch_reduce_partials(s->gpart, s->ew_rows, P_ENERGY, 10, s->res + base, s->st));
   return NEP_OK;
 }
 
@@ -795,6 +797,7 @@ int nep_compute_energy_forces_virial(nep_system* s, int32_t slot, int32_t precis
   double* F64 = s->x_alt;
   if (precision == NEP_FP64) {
     HIPCHK(launch_eval64(s->mdev[slot], s->m64[slot], eval_buffers(s, slot), U64, U64 + N, F64, s->st));
+    s->ew_rows = s->nblocks;
     s->force_valid[slot] = false;
   } else if ((st = do_eval(s, slot, precision))) {
     return st;
@@ -1130,6 +1133,7 @@ int nep_train_forward(nep_system* s, int32_t slot, const float* theta, double* e
   if (!s || !theta || !energy || slot < 0 || slot > 1 || !s->has_model[slot]) return fail(s, NEP_ERR_ARG, "bad argument");
   if (!s->have_list) return fail(s, NEP_ERR_STALE_LIST, "build the neighbour lists first");
   HIPCHK(launch_train_forward(s->mdev[slot], theta, eval_buffers(s, slot), s->st));
+  s->ew_rows = eval_rows(s->N);
   s->force_valid[slot] = false;
   int st;
   if ((st = reduce_ew(s, 0))) return st;
@@ -1169,6 +1173,7 @@ int nep_train_forward_params(nep_system* s, int32_t slot, const float* params, d
   if (!s || !params || !energy || slot < 0 || slot > 1 || !s->has_model[slot]) return fail(s, NEP_ERR_ARG, "bad argument");
   if (!s->have_list) return fail(s, NEP_ERR_STALE_LIST, "build the neighbour lists first");
   HIPCHK(launch_train_forward_params(s->mdev[slot], params, eval_buffers(s, slot), s->st));
+  s->ew_rows = eval_rows(s->N);
   s->force_valid[slot] = false;
   int st;
   if ((st = reduce_ew(s, 0))) return st;

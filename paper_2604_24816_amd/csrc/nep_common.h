@@ -252,7 +252,7 @@ struct EvalBuffers {
   uint4* rec;            // [N][4] neighbour records (written by the descriptor kernel)
   float* G;              // [nA * ncomp][N] dU/ds for the angular accumulators
   float* F;              // [3][N] forces (FP32 accumulation)
-  double* partial;       // [nblocks][kPartialStride]
+  double* ew;            // [eval_rows(N)][kPartialStride] energy and virial partials
   int32_t* flags;
   int flag_r, flag_a;    // flag words holding this model's last radial / angular bin
   int deterministic;     // 1: forces gathered in a fixed order, no atomics (k_force<..., true>)
@@ -267,7 +267,10 @@ hipError_t launch_derive_coeffs(int T, int nR, int kR, int nA, int kA, const flo
 // two kernels and after the force kernel.
 hipError_t launch_eval(const ModelDev& m, int precision, const EvalBuffers& b, hipStream_t st,
                        hipEvent_t* ev = nullptr);
-int eval_partial_blocks(int64_t N);
+// Lanes that share a center in the evaluation kernels for a system of N atoms, and the
+// rows of energy and virial partials (EvalBuffers::ew) an evaluation writes.
+int eval_lanes(int64_t N);
+int eval_rows(int64_t N);
 
 // MD and reductions (nep_md.hip)
 struct MassTable {

@@ -1,6 +1,8 @@
-// NEP energy/force evaluation on gfx950: two kernels per force evaluation.
+// NEP energy/force evaluation on gfx950: two kernels per force evaluation, one thread per
+// center, or in small systems L = 2 to 16 lanes per center that take its list entries in
+// turn (eval_lanes).
 //
-//   k_desc_net  (one thread per center, 256-thread workgroups)
+//   k_desc_net  (256-thread workgroups)
 //     1. radial descriptors q_n = sum_j g_n(r_ij) (Section III.B) and angular
 //        accumulators s_nlm = sum_j g_n(r_ij) P_lm(u_ij) for every channel n in one
 //        pass over the center's list with skin, each visited entry tested against
@@ -24,6 +26,7 @@
 //     wrote) and virial are summed per workgroup in FP64.
 //   Pair arithmetic in both comes from nep_fast.h.
 #include "nep_fast.h"
+#include <type_traits>
 
 namespace nep {
 namespace {
@@ -35,6 +38,7 @@ using namespace kern;
 // odd) and the MFMA operand and result patterns (lane (lr, lk) at 37 lr + lk and
 // 148 lk + lr) within two passes of the 64 LDS banks.
 constexpr int kNetStride = 37;
+constexpr int kBfStride = 40;  // bfloat16 weights staged in LDS: 16-byte aligned rows
 
 // The network's operand tiles are private to a wavefront, so its lanes only have to see
 // each other's LDS writes (wave_lds_sync), not a workgroup barrier: the wavefronts of a
@@ -183,6 +187,95 @@ __device__ __forceinline__ float network_wave(const ModelDev& m, const float* qs
   return U;
 }
 
+// ------------------------------------------------------------------------ shared centers
+// With L > 1 lanes to a center the part after the pair loop (descriptors from the sums,
+// network, dU/ds, record) would be repeated by every lane; it is spread over them instead:
+// lane l takes channels l, l + L, ... of the angular terms, every L-th activation and every
+// L-th coefficient, and the center's row of the operand tile carries the values between
+// lanes. The network's weights are staged in LDS while the pair loop runs, so that no global
+// load sits in this part. Both matter because a small system runs one short wavefront per
+// SIMD: 4,000 atoms at 16 lanes took 24 us with everything repeated and the weights
+// gathered from global memory.
+template <int PREC>
+struct NetLds {
+  float w[PREC == 0 ? 32 * 33 : 1];                      // W0 [hidden][descriptor], zero padded
+  alignas(16) uint16_t wb[PREC == 1 ? 32 * kBfStride : 8];  // the same as bfloat16
+  float b0[32], w1[32], sigma[32];
+};
+
+template <class S, int PREC>
+__device__ __forceinline__ void stage_network(const ModelDev& m, NetLds<PREC>& n) {
+  for (int t = threadIdx.x; t < 32 * 32; t += kBlock) {
+    const int hid = t >> 5, d = t & 31;
+    const bool in = hid < S::H && d < S::D;
+    if constexpr (PREC == 0) n.w[hid * 33 + d] = in ? m.W0[hid * S::D + d] : 0.f;
+    else n.wb[hid * kBfStride + d] = in ? m.W0bf[hid * S::D + d] : (uint16_t)0;
+  }
+  if (threadIdx.x < 32) {
+    const int t = threadIdx.x;
+    n.b0[t] = t < S::H ? m.b0[t] : 0.f;
+    n.w1[t] = t < S::H ? m.w1[t] : 0.f;
+    n.sigma[t] = t < S::D ? m.sigma[t] : 0.f;
+  }
+}
+
+// rows x 32 times W0^T (FORWARD: descriptors to hidden units) or W0 (hidden units to
+// descriptors), in place in the wavefront's operand tile of RT 16-row MFMA tiles. Rows that
+// belong to no center hold whatever the LDS held and are never read back.
+template <int PREC, int RT, bool FORWARD>
+__device__ __forceinline__ void net_product(float* lds, const NetLds<PREC>& n) {
+  const int lane = threadIdx.x & 63;
+  const int lr = lane & 15, lk = lane >> 4;
+  wave_lds_sync();
+  floatx4 acc[RT][2];
+#pragma unroll
+  for (int R = 0; R < RT; ++R)
+#pragma unroll
+    for (int C = 0; C < 2; ++C) acc[R][C] = floatx4{0.f, 0.f, 0.f, 0.f};
+  if constexpr (PREC == 0) {
+#pragma unroll
+    for (int kb = 0; kb < 8; ++kb) {
+      const int k = 4 * kb + lk;
+      float bop[2];
+#pragma unroll
+      for (int C = 0; C < 2; ++C) bop[C] = FORWARD ? n.w[(16 * C + lr) * 33 + k] : n.w[k * 33 + 16 * C + lr];
+#pragma unroll
+      for (int R = 0; R < RT; ++R) {
+        const float aop = lds[(16 * R + lr) * kNetStride + k];
+#pragma unroll
+        for (int C = 0; C < 2; ++C)
+          acc[R][C] = __builtin_amdgcn_mfma_f32_16x16x4f32(aop, bop[C], acc[R][C], 0, 0, 0);
+      }
+    }
+  } else {
+    bf16x8 bop[2];
+#pragma unroll
+    for (int C = 0; C < 2; ++C)
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        bop[C][e] = bits_to_bf16(FORWARD ? n.wb[(16 * C + lr) * kBfStride + 8 * lk + e]
+                                         : n.wb[(8 * lk + e) * kBfStride + 16 * C + lr]);
+#pragma unroll
+    for (int R = 0; R < RT; ++R) {
+      bf16x8 aop;
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        aop[e] = bits_to_bf16(f32_to_bf16_bits(lds[(16 * R + lr) * kNetStride + 8 * lk + e]));
+#pragma unroll
+      for (int C = 0; C < 2; ++C)
+        acc[R][C] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aop, bop[C], acc[R][C], 0, 0, 0);
+    }
+  }
+  wave_lds_sync();
+#pragma unroll
+  for (int R = 0; R < RT; ++R)
+#pragma unroll
+    for (int C = 0; C < 2; ++C)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) lds[(16 * R + 4 * lk + r) * kNetStride + 16 * C + lr] = acc[R][C][r];
+  wave_lds_sync();
+}
+
 // ------------------------------------------------------------------------ descriptors
 // The main loops only count the pairs inside the ZBL radius; a center with any visits its
 // whole radial list again afterwards (zbl_center), which keeps the loops free of slot
@@ -195,8 +288,10 @@ using EvalZbl = ZblSeen<0>;
 // descriptors are linear in the basis sums, q_n = sum_k c_nk sum_j f_k(r_ij), with
 // sum_j f_k = (sum_j f_c T_k + sum_j f_c) / 2, so a pair adds f_c and f_c T_k (k >= 1).
 // Returns the pair counts and the pairs inside the ZBL radius (zs).
-template <class S, bool MULTI>
-__device__ __forceinline__ void desc_pass(const ModelDev& m, const EvalBuffers& b, int64_t i, int ti, QPos qi,
+// With L > 1 this lane (l of the L that share the center) visits entries l, l + L, ... and
+// the sums over the lanes are formed at the end, in every lane.
+template <class S, bool MULTI, int L>
+__device__ __forceinline__ void desc_pass(const ModelDev& m, const EvalBuffers& b, int64_t i, int l, int ti, QPos qi,
                                           float* q, float* s, EvalZbl& zs, int& nr, int& na) {
   constexpr int NR = S::NR, NA = S::NA, NC = S::NC, KR = S::KR, KA = S::KA;
   const int64_t N = b.N;
@@ -259,10 +354,27 @@ __device__ __forceinline__ void desc_pass(const ModelDev& m, const EvalBuffers& 
     }
   };
   // the angular candidates are the list's prefix [0, kA)
-  if constexpr (MULTI)
+  if constexpr (L > 1)
+    for_each_rec_lanes<1, 1, L>(b.nbr, b.pos, N, i, l, kR, pair_both);
+  else if constexpr (MULTI)
     for_each_rec_span<1, S::DESC_AHEAD, 1>(b.nbr, b.pos, N, i, 0, kR, pair_both);
   else
     for_each_rec_fast<1, S::DESC_AHEAD, 1>(b.nbr, b.pos, N, i, 0, kR, pair_both);
+  if constexpr (L > 1) {
+    nr = lanes_sum<L>(nr);
+    na = lanes_sum<L>(na);
+    zs.n = lanes_sum<L>(zs.n);
+    if constexpr (MULTI) {
+#pragma unroll
+      for (int n = 0; n < NR; ++n) q[n] = lanes_sum<L>(q[n]);
+    } else {
+      Qf = lanes_sum<L>(Qf);
+#pragma unroll
+      for (int k = 1; k < KR; ++k) QT[k] = lanes_sum<L>(QT[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < NA * NC; ++k) s[k] = lanes_sum<L>(s[k]);
+  }
   if constexpr (!MULTI) {
     const cfloat_ptr c = uniform_coeffs(m.cR);
     float Qb[KR];
@@ -299,15 +411,165 @@ __device__ __forceinline__ void load_g_row(const float* row, float* g) {
   }
 }
 
+// The part of the descriptor kernel after the pair loop when L lanes share a center: q[0..NR)
+// and s hold the center's sums in every lane. lds: this wavefront's operand tile.
+template <class S, int PREC, bool MULTI, int L>
+__device__ __forceinline__ void finish_lanes(const ModelDev& m, const EvalBuffers& b, int64_t i, int l, bool valid,
+                                             int ti, const float* q, const float* s, const EvalZbl& zs, float* lds,
+                                             const NetLds<PREC>& net) {
+  constexpr int NR = S::NR, NA = S::NA, NC = S::NC, D = S::D, L3 = S::L3;
+  constexpr int RT = 64 / L >= 16 ? 64 / L / 16 : 1;
+  constexpr int ROUNDS = (NA + L - 1) / L;  // angular channels of a lane
+  const int64_t N = b.N;
+  float* row = lds + ((threadIdx.x & 63) / L) * kNetStride;
+  // scaled descriptors into the row
+#pragma unroll
+  for (int n = 0; n < NR; ++n)
+    if ((n & (L - 1)) == l) row[n] = q[n] * net.sigma[n];
+  for (int v = D + l; v < 32; v += L) row[v] = 0.f;
+  float sl[ROUNDS][NC];  // accumulators of channel n = l + r L
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    // picked by bit masks: a chain of selects becomes an indexed load of s, in scratch memory
+#pragma unroll
+    for (int lm = 0; lm < NC; ++lm) {
+      uint32_t v = 0;
+#pragma unroll
+      for (int n = 0; n < NA; ++n)
+        if (n / L == r) v |= __float_as_uint(s[n * NC + lm]) & (l == n % L ? 0xffffffffu : 0u);
+      sl[r][lm] = __uint_as_float(v);
+    }
+    const int n = l + r * L;
+    if (n < NA) {
+      float ql[L3];
+#pragma unroll
+      for (int k = 0; k < L3; ++k) ql[k] = 0.f;
+#pragma unroll
+      for (int lm = 0; lm < NC; ++lm)
+        ql[comp_l(lm) - 1] = fmaf(kW[lm], sl[r][lm] * sl[r][lm], ql[comp_l(lm) - 1]);
+#pragma unroll
+      for (int k = 0; k < L3; ++k) row[NR + k * NA + n] = ql[k] * net.sigma[NR + k * NA + n];
+      if constexpr (S::FB) row[NR + L3 * NA + n] = fourbody_q(sl[r]) * net.sigma[NR + L3 * NA + n];
+    }
+  }
+  net_product<PREC, RT, true>(lds, net);
+  float U = 0.f;
+#pragma unroll
+  for (int mu0 = 0; mu0 < 32; mu0 += L) {
+    const int mu = mu0 + l;
+    const float t = tanh_fast(row[mu] - net.b0[mu]), w = net.w1[mu];  // w1 = 0 beyond the last hidden unit
+    U = fmaf(w, t, U);
+    row[mu] = w * (1.f - t * t);
+  }
+  U = lanes_sum<L>(U) - m.b1[0];
+  net_product<PREC, RT, false>(lds, net);
+  if (!valid) return;
+  auto fp = [&](int v) { return row[v] * net.sigma[v]; };  // dU/dq_v
+  // the 64-byte record: position (0..2), radial coefficients t_0..t_8 (3..11), zeros
+  {
+    static_assert(S::KR == 9 && NR <= 5, "the record holds nine radial coefficients");
+    constexpr int TR = (9 + L - 1) / L;
+    float t[TR], sum = 0.f;
+#pragma unroll
+    for (int r = 0; r < TR; ++r) {
+      const int k = l + r * L;
+      t[r] = 0.f;
+      if (k < 9) {
+        if constexpr (MULTI) {
+          t[r] = k < NR ? fp(k) : 0.f;
+        } else {
+#pragma unroll
+          for (int n = 0; n < NR; ++n) t[r] = fmaf(fp(n), m.cR[n * S::KR + k], t[r]);
+        }
+      }
+      sum += t[r];
+    }
+    if constexpr (!MULTI) {
+      sum = lanes_sum<L>(sum);
+      if (l == 0) t[0] += sum;
+    }
+    float* rec = reinterpret_cast<float*>(b.rec + 4 * i);
+#pragma unroll
+    for (int r = 0; r < TR; ++r)
+      if (l + r * L < 9) rec[3 + l + r * L] = t[r];
+    const uint32_t* own = reinterpret_cast<const uint32_t*>(b.pos + i);
+    uint32_t* recu = reinterpret_cast<uint32_t*>(rec);
+#pragma unroll
+    for (int k0 = 0; k0 < 7; k0 += L) {  // words 0..2 and 12..15
+      const int k = k0 + l;
+      if (k < 3) recu[k] = own[k];
+      else if (k < 7) recu[9 + k] = 0u;
+    }
+  }
+  // dU/ds_nlm = dU/dq_nl * 2 W_lm s_nlm (+ four-body part for l = 2) of the lane's channels
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    const int n = l + r * L;
+    if (n < NA) {
+      float Gd[NC];
+#pragma unroll
+      for (int lm = 0; lm < NC; ++lm) Gd[lm] = fp(NR + (comp_l(lm) - 1) * NA + n) * 2.f * kW[lm] * sl[r][lm];
+      if constexpr (S::FB) {
+        float d5[5];
+        fourbody_ds(sl[r], d5);
+        const float f4 = fp(NR + L3 * NA + n);
+#pragma unroll
+        for (int k = 0; k < 5; ++k) Gd[3 + k] = fmaf(f4, d5[k], Gd[3 + k]);
+      }
+      if (b.deterministic) {
+        static_assert(NC % 4 == 0, "a channel of a row is written in 16-byte words");
+        float4* g4 = reinterpret_cast<float4*>(b.G + i * g_row<S>() + n * NC);
+#pragma unroll
+        for (int k = 0; k < NC / 4; ++k) g4[k] = make_float4(Gd[4 * k], Gd[4 * k + 1], Gd[4 * k + 2], Gd[4 * k + 3]);
+      } else {
+        float* g = b.G + (int64_t)n * NC * N + i;
+#pragma unroll
+        for (int lm = 0; lm < NC; ++lm) g[lm * N] = Gd[lm];
+      }
+    }
+  }
+  for (int c = l; c < 3; c += L) b.F[c * N + i] = 0.f;
+  if (zs.n) {  // ZBL energy (half of each close pair)
+    float uz = 0.f;
+    zbl_center<MULTI>(m, b, i, ti, b.x[i], b.x[N + i], b.x[2 * N + i], zs, &uz, nullptr, nullptr, l, L);
+    U += lanes_sum<L>(uz);
+  }
+  if (l == 0) b.U[i] = U;
+}
+
 // ------------------------------------------------------------------------ descriptor + network
-template <class S, int PREC, bool MULTI>
+template <class S, int PREC, bool MULTI, int L>
 __global__ void __launch_bounds__(kBlock, 2) k_desc_net(ModelDev m, EvalBuffers b) {
-  __shared__ float lds[kBlock / 64][64 * kNetStride];
+  __shared__ float lds[kBlock / 64][(64 / L >= 16 ? 64 / L : 16) * kNetStride];
   constexpr int NR = S::NR, NA = S::NA, NC = S::NC, D = S::D;
   const int64_t N = b.N;
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
-  const int64_t i = (int64_t)tile * kBlock + threadIdx.x;
+  const int64_t i = (int64_t)tile * (kBlock / L) + threadIdx.x / L;
+  const int l = threadIdx.x % L;
   const bool valid = i < N;
+  if constexpr (L > 1) {
+    __shared__ NetLds<PREC> net;
+    stage_network<S>(m, net);
+    float q[NR], s[NA * NC];
+#pragma unroll
+    for (int n = 0; n < NR; ++n) q[n] = 0.f;
+#pragma unroll
+    for (int k = 0; k < NA * NC; ++k) s[k] = 0.f;
+    const int ti = valid ? (MULTI ? b.type[i] : 0) : 0;
+    EvalZbl zs;
+    if (valid) {
+      const uint4 w0 = b.pos[i];
+      int nr = 0, na = 0;
+      desc_pass<S, MULTI, L>(m, b, i, l, ti, QPos{w0.x, w0.y, w0.z}, q, s, zs, nr, na);
+      if (l == 0) {
+        b.nactR[i] = nr;
+        b.nactA[i] = na;
+      }
+    }
+    __syncthreads();  // the staged weights
+    finish_lanes<S, PREC, MULTI, L>(m, b, i, l, valid, ti, q, s, zs, lds[threadIdx.x >> 6], net);
+    return;
+  }
 
   float q[D];
 #pragma unroll
@@ -321,7 +583,7 @@ __global__ void __launch_bounds__(kBlock, 2) k_desc_net(ModelDev m, EvalBuffers 
   if (valid) {
     const uint4 w0 = b.pos[i];
     int nr = 0, na = 0;
-    desc_pass<S, MULTI>(m, b, i, ti, QPos{w0.x, w0.y, w0.z}, q, s, zs, nr, na);
+    desc_pass<S, MULTI, 1>(m, b, i, 0, ti, QPos{w0.x, w0.y, w0.z}, q, s, zs, nr, na);
     b.nactR[i] = nr;
     b.nactA[i] = na;
     desc_finish<S>(s, q);
@@ -552,17 +814,23 @@ __device__ __forceinline__ void angular_pair_force(const ModelDev& m, const AngC
 // and the box-fraction pair vector of (j, i) is the exact negation of that of (i, j), so
 // both sides see the same r^2. The terms are bitwise those the scattering form adds, in
 // a fixed order.
-template <class S, bool MULTI, bool DET>
+template <class S, bool MULTI, bool DET, int L>
 __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, EvalBuffers b) {
   __shared__ double red[4 * 10];
   __shared__ HaloLds halo;
   constexpr int NR = S::NR, NA = S::NA, NC = S::NC;
   const int64_t N = b.N;
-  const int tile = xcd_tile(blockIdx.x, gridDim.x);
-  const int64_t i = (int64_t)tile * kBlock + threadIdx.x;
+  const int sub = xcd_tile(blockIdx.x, gridDim.x);  // L workgroups to a 256-atom tile
+  const int64_t i = (int64_t)sub * (kBlock / L) + threadIdx.x / L;
+  const int l = threadIdx.x % L;
   const bool valid = i < N;
   bool lds = false;
-  if constexpr (!DET) lds = load_halo(b, tile, halo);
+  int kR = 0, kA = 0;
+  if (valid) {
+    kR = radial_bound(b, i);
+    kA = angular_bound(b, i);
+  }
+  if constexpr (!DET) lds = load_halo(b, sub / L, halo);
   const double hx = box_quantum(b.box[0]), hy = box_quantum(b.box[1]), hz = box_quantum(b.box[2]);
   const float rcR_inv = 1.f / m.rcR;
   const CutConst cutR = cut_const(m.rcR);
@@ -592,7 +860,6 @@ __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, 
       for (int k = 0; k < NA * NC; ++k) G[k] = b.G[(int64_t)k * N + i];
     }
     const float rcR2 = (float)(m.rcR64 * m.rcR64), rcA2 = (float)(m.rcA64 * m.rcA64), zbl2 = (float)m.zbl_o2;
-    const int kR = radial_bound(b, i), kA = angular_bound(b, i);
     EvalZbl zs;  // pairs inside the ZBL radius
     // One entry: the radial term by gather, F_i += (dU_i/dr_ij + dU_j/dr_ji) along u, with
     // the neighbour's radial coefficients read from its record, the virial taking half of
@@ -672,13 +939,16 @@ __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, 
 #pragma unroll
         for (int c = 0; c < 3; ++c) w[a * 3 + c] = fmaf(d[a], nf[c], w[a * 3 + c]);
     };
-    if constexpr (MULTI)
+    if constexpr (L > 1)
+      for_each_rec_lanes<3, 4, L>(b.nbr, b.rec, N, i, l, kR, pair_both);
+    else if constexpr (MULTI)
       for_each_rec_span<3, 1, 4>(b.nbr, b.rec, N, i, 0, kR, pair_both);
     else
       for_each_rec_fast<3, 1, 4>(b.nbr, b.rec, N, i, 0, kR, pair_both);
+    if constexpr (L > 1) zs.n = lanes_sum<L>(zs.n);
     if (zs.n) {
       float f[3] = {fx, fy, fz};
-      zbl_center<MULTI>(m, b, i, ti, b.x[i], b.x[N + i], b.x[2 * N + i], zs, nullptr, f, w);
+      zbl_center<MULTI>(m, b, i, ti, b.x[i], b.x[N + i], b.x[2 * N + i], zs, nullptr, f, w, l, L);
       fx = f[0];
       fy = f[1];
       fz = f[2];
@@ -686,7 +956,7 @@ __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, 
     if constexpr (DET) {
       // the neighbours' angular terms on this atom, in list order
       const uint64_t n64 = (uint64_t)N;
-      for (int p = 0; p < kA; ++p) {
+      for (int p = l; p < kA; p += L) {
         const int32_t j = b.nbr[(uint64_t)(uint32_t)p * n64 + i];
         float dx, dy, dz;
         const float r2 = pair_vec_q(b.pos[j], qi, hx, hy, hz, dx, dy, dz);
@@ -703,18 +973,26 @@ __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, 
         fy += n1;
         fz += n2;
       }
-      b.F[i] = fx;
-      b.F[N + i] = fy;
-      b.F[2 * N + i] = fz;
-    } else if (lds) {
-      const int li = b.selfl[i];
-      atomicAdd(&halo.F[0][li], fx);
-      atomicAdd(&halo.F[1][li], fy);
-      atomicAdd(&halo.F[2][li], fz);
-    } else {
-      unsafeAtomicAdd(&b.F[i], fx);
-      unsafeAtomicAdd(&b.F[N + i], fy);
-      unsafeAtomicAdd(&b.F[2 * N + i], fz);
+    }
+    // the center's own force: the sum over its lanes, stored by the first
+    fx = lanes_sum<L>(fx);
+    fy = lanes_sum<L>(fy);
+    fz = lanes_sum<L>(fz);
+    if (l == 0) {
+      if constexpr (DET) {
+        b.F[i] = fx;
+        b.F[N + i] = fy;
+        b.F[2 * N + i] = fz;
+      } else if (lds) {
+        const int li = b.selfl[i];
+        atomicAdd(&halo.F[0][li], fx);
+        atomicAdd(&halo.F[1][li], fy);
+        atomicAdd(&halo.F[2][li], fz);
+      } else {
+        unsafeAtomicAdd(&b.F[i], fx);
+        unsafeAtomicAdd(&b.F[N + i], fy);
+        unsafeAtomicAdd(&b.F[2 * N + i], fz);
+      }
     }
   }
   if constexpr (!DET) {
@@ -725,29 +1003,40 @@ __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, 
   }
   // the tile's energy (the descriptor kernel's U_i, ZBL included) and virial in FP64
   double wd[10], ws[10];
-  wd[0] = valid ? (double)b.U[i] : 0.0;
+  wd[0] = valid && l == 0 ? (double)b.U[i] : 0.0;
 #pragma unroll
   for (int k = 0; k < 9; ++k) wd[1 + k] = (double)w[k];
   block_sum_n<10>(wd, ws, red);
   if (threadIdx.x == 0) {
-    b.partial[(int64_t)tile * kPartialStride + P_ENERGY] = ws[0];
+    b.ew[(int64_t)sub * kPartialStride + P_ENERGY] = ws[0];
 #pragma unroll
-    for (int k = 0; k < 9; ++k) b.partial[(int64_t)tile * kPartialStride + P_VIR + k] = ws[1 + k];
+    for (int k = 0; k < 9; ++k) b.ew[(int64_t)sub * kPartialStride + P_VIR + k] = ws[1 + k];
   }
+}
+
+template <class S, int PREC, bool MULTI, int L>
+hipError_t launch_lanes(const ModelDev& m, const EvalBuffers& b, hipStream_t st, hipEvent_t* ev) {
+  const int nb = grid_blocks(b.N, kBlock / L);
+  if (ev) (void)hipEventRecord(ev[0], st);
+  hipLaunchKernelGGL((k_desc_net<S, PREC, MULTI, L>), dim3(nb), dim3(kBlock), 0, st, m, b);
+  if (ev) (void)hipEventRecord(ev[1], st);
+  if (b.deterministic)
+    hipLaunchKernelGGL((k_force<S, MULTI, true, L>), dim3(nb), dim3(kBlock), 0, st, m, b);
+  else
+    hipLaunchKernelGGL((k_force<S, MULTI, false, L>), dim3(nb), dim3(kBlock), 0, st, m, b);
+  if (ev) (void)hipEventRecord(ev[2], st);
+  return hipGetLastError();
 }
 
 template <class S, int PREC, bool MULTI>
 hipError_t launch_pair(const ModelDev& m, const EvalBuffers& b, hipStream_t st, hipEvent_t* ev) {
-  const int nb = grid_blocks(b.N);
-  if (ev) (void)hipEventRecord(ev[0], st);
-  hipLaunchKernelGGL((k_desc_net<S, PREC, MULTI>), dim3(nb), dim3(kBlock), 0, st, m, b);
-  if (ev) (void)hipEventRecord(ev[1], st);
-  if (b.deterministic)
-    hipLaunchKernelGGL((k_force<S, MULTI, true>), dim3(nb), dim3(kBlock), 0, st, m, b);
-  else
-    hipLaunchKernelGGL((k_force<S, MULTI, false>), dim3(nb), dim3(kBlock), 0, st, m, b);
-  if (ev) (void)hipEventRecord(ev[2], st);
-  return hipGetLastError();
+  switch (eval_lanes(b.N)) {
+    case 16: return launch_lanes<S, PREC, MULTI, 16>(m, b, st, ev);
+    case 8: return launch_lanes<S, PREC, MULTI, 8>(m, b, st, ev);
+    case 4: return launch_lanes<S, PREC, MULTI, 4>(m, b, st, ev);
+    case 2: return launch_lanes<S, PREC, MULTI, 2>(m, b, st, ev);
+    default: return launch_lanes<S, PREC, MULTI, 1>(m, b, st, ev);
+  }
 }
 
 template <class S>
@@ -793,7 +1082,28 @@ hipError_t launch_derive_coeffs(int T, int nR, int kR, int nA, int kA, const flo
 
 bool eval_supported(const ModelDev& m) { return is_shape<FullShape>(m) || is_shape<SurShape>(m); }
 
-int eval_partial_blocks(int64_t N) { return grid_blocks(N); }
+// One thread per center fills the chip (1,024 SIMDs, two wavefronts each) from about 131,072
+// atoms on; below, a wavefront's own latency is the kernel's time (k_force 102 us from 256
+// to 32,000 atoms), so L lanes share a center, as many as keep N L <= 131072. On both sides
+// of that line, us of k_desc_net + k_force, one species:
+//   N         L = 1    2    4    8   16
+//   4,000       156  101   65   47   41
+//   13,500      160  102   67   61   85
+//   32,000      162  109   88  111  157
+//   62,500      176  143  158  198  284
+//   108,000     224  249  259  316  470
+// More lanes cost per wavefront (the sums over lanes, a halo to clear and flush per 256 / L
+// centers), fewer leave SIMDs idle.
+constexpr int64_t kFillLanes = 131072;
+constexpr int kMaxLanes = 16;
+
+int eval_lanes(int64_t N) {
+  int L = kMaxLanes;
+  while (L > 1 && N * L > kFillLanes) L /= 2;
+  return L;
+}
+
+int eval_rows(int64_t N) { return grid_blocks(N, kBlock / eval_lanes(N)); }
 
 hipError_t launch_eval(const ModelDev& m, int precision, const EvalBuffers& b, hipStream_t st,
                        hipEvent_t* ev) {

@@ -194,7 +194,7 @@ __global__ void __launch_bounds__(kBlock) k_desc64(ModelDev m, Model64 p, EvalBu
     U64[i] = U;
   }
   const double e = block_sum64(U, sh);
-  if (threadIdx.x == 0) b.partial[(int64_t)blockIdx.x * kPartialStride + P_ENERGY] = e;
+  if (threadIdx.x == 0) b.ew[(int64_t)blockIdx.x * kPartialStride + P_ENERGY] = e;
 }
 
 // Forces (F64 [3][N], zeroed before) and virial partials (FP64).
@@ -284,7 +284,7 @@ __global__ void __launch_bounds__(kBlock) k_force64(ModelDev m, Model64 p, EvalB
 #pragma unroll
   for (int k = 0; k < 9; ++k) {
     const double t = block_sum64(w[k], sh);
-    if (threadIdx.x == 0) b.partial[(int64_t)blockIdx.x * kPartialStride + P_VIR + k] = t;
+    if (threadIdx.x == 0) b.ew[(int64_t)blockIdx.x * kPartialStride + P_VIR + k] = t;
   }
 }
 

@@ -291,6 +291,68 @@ __device__ __forceinline__ void for_each_rec_fast(const int32_t* __restrict__ nb
   }
 }
 
+// The loop of one of the L lanes that share a center (lane l visits entries l, l + L, ...
+// below k1): the record of entry p + L and the index of entry p + 2 L are in flight while
+// the body of entry p runs. Loads past the last visited entry read that entry again, so
+// every address stays inside the list however far L reaches ahead.
+template <int W, int RS, int L, class Body>
+__device__ __forceinline__ void for_each_rec_lanes(const int32_t* __restrict__ nbr, const uint4* __restrict__ rec,
+                                                   int64_t N, int64_t i, int l, int k1, Body&& body) {
+  if (k1 <= 0) return;
+  auto index = [&](int p) { return nbr[(uint64_t)(uint32_t)(p < k1 ? p : k1 - 1) * (uint64_t)N + i]; };
+  auto record = [&](int32_t j, int w) { return rec[(uint64_t)(uint32_t)j * RS + w]; };
+  int32_t j0 = index(l), j1 = index(l + L);
+  uint4 rq[2][W];
+#pragma unroll
+  for (int w = 0; w < W; ++w) rq[0][w] = record(j0, w);
+  for (int p0 = l; p0 < k1; p0 += 2 * L) {
+#pragma unroll
+    for (int ph = 0; ph < 2; ++ph) {
+      const int p = p0 + ph * L;
+      if (p < k1) {
+        const int32_t j2 = index(p + 2 * L);
+#pragma unroll
+        for (int w = 0; w < W; ++w) rq[1 - ph][w] = record(j1, w);
+        body(p, j0, rq[ph]);
+        j0 = j1;
+        j1 = j2;
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------- lanes of one center
+// Sum over the L consecutive lanes (L = 1, 2, 4, 8 or 16, aligned) that share a center, in
+// every one of them: cross-lane additions inside a 16-lane row (two quad permutations, a
+// mirror of half a row, a mirror of the row). Each step adds two partial sums in both
+// orders, so all lanes hold the same bits and the order of the sum is fixed. All L lanes
+// must be active.
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {
+  return v + __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xf, 0xf, true));
+}
+template <int L>
+__device__ __forceinline__ float lanes_sum(float v) {
+  static_assert(L == 1 || L == 2 || L == 4 || L == 8 || L == 16, "lanes inside one 16-lane row");
+  if constexpr (L >= 2) v = dpp_add<0xb1>(v);    // quad_perm [1, 0, 3, 2]
+  if constexpr (L >= 4) v = dpp_add<0x4e>(v);    // quad_perm [2, 3, 0, 1]
+  if constexpr (L >= 8) v = dpp_add<0x141>(v);   // row_half_mirror
+  if constexpr (L >= 16) v = dpp_add<0x140>(v);  // row_mirror
+  return v;
+}
+template <int CTRL>
+__device__ __forceinline__ int dpp_add(int v) {
+  return v + __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+template <int L>
+__device__ __forceinline__ int lanes_sum(int v) {
+  if constexpr (L >= 2) v = dpp_add<0xb1>(v);
+  if constexpr (L >= 4) v = dpp_add<0x4e>(v);
+  if constexpr (L >= 8) v = dpp_add<0x141>(v);
+  if constexpr (L >= 16) v = dpp_add<0x140>(v);
+  return v;
+}
+
 // ---------------------------------------------------------------- structural zeros
 // Gradient components of the harmonic polynomials that vanish identically are passed as
 // Zero, so that their products drop out at compile time (an FP32 product with a literal

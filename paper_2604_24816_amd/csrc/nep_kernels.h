@@ -335,15 +335,17 @@ using ZblSeenFor = ZblSeen<MULTI ? 0 : 4>;
 // atoms' halves, along u) into f[3] and the virial of dU_i/dr_ij into w[9]. Called
 // only for centers that have such pairs, after the main loop: it visits the
 // recorded list positions, or the whole radial list when there were more.
+// (q0, qs): the first position and the stride of a lane that shares the center with others
+// (which then adds its part only).
 template <bool MULTI, int CAP>
 __device__ __forceinline__ void zbl_center(const ModelDev& m, const EvalBuffers& b, int64_t i, int ti, double xi,
                                         double yi, double zi, const ZblSeen<CAP>& seen, float* uz, float* f,
-                                        float* w) {
+                                        float* w, int q0 = 0, int qs = 1) {
   const int64_t N = b.N;
   const double Lx = b.box[0], Ly = b.box[1], Lz = b.box[2];
   const bool all = seen.n > CAP;
   const int kR = all ? radial_bound(b, i) : seen.n;
-  for (int q = 0; q < kR; ++q) {
+  for (int q = q0; q < kR; q += qs) {
     const int p = all ? q : (int)((seen.slots >> (16 * q)) & 0xffffu);
     const int32_t j = b.nbr[(int64_t)p * N + i];
     const double ex = min_image(b.x[j] - xi, Lx);
@@ -458,7 +460,15 @@ __device__ __forceinline__ Sym3 s_matrix(const float* sl) {
   return a;
 }
 
-// q_nl = sum_m W_lm s_nlm^2 and the four-body invariant tr(S^3) = 3 det S.
+// The four-body invariant tr(S^3) = 3 det S of one channel's accumulators.
+__device__ __forceinline__ float fourbody_q(const float* sl) {
+  const Sym3 a = s_matrix(sl);
+  const float det = a.xx * (a.yy * a.zz - a.yz * a.yz) - a.xy * (a.xy * a.zz - a.yz * a.xz) +
+                    a.xz * (a.xy * a.yz - a.yy * a.xz);
+  return 3.f * det;
+}
+
+// q_nl = sum_m W_lm s_nlm^2 and the four-body invariant.
 template <class S>
 __device__ __forceinline__ void desc_finish(const float* s, float* q) {
   constexpr int NR = S::NR, NA = S::NA, NC = S::NC;
@@ -471,12 +481,7 @@ __device__ __forceinline__ void desc_finish(const float* s, float* q) {
     }
   if constexpr (S::FB) {
 #pragma unroll
-    for (int n = 0; n < NA; ++n) {
-      const Sym3 a = s_matrix(s + n * NC);
-      const float det = a.xx * (a.yy * a.zz - a.yz * a.yz) - a.xy * (a.xy * a.zz - a.yz * a.xz) +
-                        a.xz * (a.xy * a.yz - a.yy * a.xz);
-      q[NR + S::L3 * NA + n] = 3.f * det;
-    }
+    for (int n = 0; n < NA; ++n) q[NR + S::L3 * NA + n] = fourbody_q(s + n * NC);
   }
 }
 

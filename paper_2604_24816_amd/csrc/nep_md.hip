@@ -8,20 +8,27 @@
 namespace nep {
 namespace {
 
-__global__ void k_reduce_partials(const double* __restrict__ partial, int nblocks, int first, int nvals,
-                                  double* __restrict__ out) {
-  __shared__ double sh[kBlock];
-  for (int k = 0; k < nvals; ++k) {
-    double s = 0.0;
-    for (int b = threadIdx.x; b < nblocks; b += kBlock) s += partial[(int64_t)b * kPartialStride + first + k];
-    __syncthreads();
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int off = kBlock / 2; off > 0; off >>= 1) {
-      if (threadIdx.x < (unsigned)off) sh[threadIdx.x] += sh[threadIdx.x + off];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) out[k] = sh[0];
+// Sums of slots first .. first + nvals - 1 over the rows of partials, one workgroup: 64
+// rows of 16 slots per pass (whole 128-byte rows, every slot at once), then the 64 row
+// groups of each slot in a fixed order.
+constexpr int kRedBlock = 1024;
+
+__global__ void __launch_bounds__(kRedBlock)
+k_reduce_partials(const double* __restrict__ partial, int nblocks, int first, int nvals, double* __restrict__ out) {
+  __shared__ double sh[kRedBlock];
+  constexpr int kRows = kRedBlock / kPartialStride;
+  const int slot = threadIdx.x % kPartialStride, row = threadIdx.x / kPartialStride;
+  double s = 0.0;
+#pragma unroll 4
+  for (int b = row; b < nblocks; b += kRows) s += partial[(int64_t)b * kPartialStride + slot];
+  sh[threadIdx.x] = s;
+  __syncthreads();
+  const int k = threadIdx.x - first;
+  if (k >= 0 && k < nvals) {
+    double t = 0.0;
+#pragma unroll 8
+    for (int r = 0; r < kRows; ++r) t += sh[r * kPartialStride + threadIdx.x];
+    out[k] = t;
   }
 }
 
@@ -313,7 +320,7 @@ __global__ void k_scatter_vec_f32(int64_t N, const int32_t* __restrict__ perm, c
 
 hipError_t launch_reduce_partials(const double* partial, int nblocks, int first, int nvals, double* out,
                                   hipStream_t st) {
-  hipLaunchKernelGGL(k_reduce_partials, dim3(1), dim3(kBlock), 0, st, partial, nblocks, first, nvals, out);
+  hipLaunchKernelGGL(k_reduce_partials, dim3(1), dim3(kRedBlock), 0, st, partial, nblocks, first, nvals, out);
   return hipGetLastError();
 }
 
