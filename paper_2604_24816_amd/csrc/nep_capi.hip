@@ -127,7 +127,7 @@ struct nep_system {
   // device buffers (inside the caller's workspace)
   double *x, *v, *x_alt, *v_alt, *x_build;
   int32_t *type, *type_alt, *perm, *perm_alt, *cellid, *cell_sorted, *src, *key;
-  int32_t *cell_count, *cell_start, *cell_fill, *scan_tmp;
+  int32_t *rank, *cell_count, *cell_start, *scan_tmp;
   int32_t *nbr, *cnt, *bp, *nactR, *nactA;
   uint16_t *nbrl, *selfl;
   BinEdges be;
@@ -169,6 +169,7 @@ int64_t layout(nep_system* s, char* base, int64_t N, int capR, int capA, int max
   S.x = c.take<double>(3 * N);
   S.v = c.take<double>(3 * N);
   S.x_alt = c.take<double>(3 * N);
+  S.rank = reinterpret_cast<int32_t*>(S.x_alt);  // read before a build writes x_alt
   S.v_alt = c.take<double>(3 * N);
   S.x_build = c.take<double>(3 * N);
   S.type = c.take<int32_t>(N);
@@ -181,7 +182,6 @@ int64_t layout(nep_system* s, char* base, int64_t N, int capR, int capA, int max
   S.key = c.take<int32_t>(N);
   S.cell_count = c.take<int32_t>(max_ncell);
   S.cell_start = c.take<int32_t>(max_ncell + 1);
-  S.cell_fill = c.take<int32_t>(max_ncell);
   S.scan_tmp = c.take<int32_t>(max_ncell / 1024 + 2);
   S.nbr = c.take<int32_t>((int64_t)(capR + kListPad) * N);
   S.cnt = c.take<int32_t>(N);
@@ -442,14 +442,16 @@ BinEdges make_bin_edges(const nep_hparams* hp0, const nep_hparams* hp1, double s
   return be;
 }
 
-int rebuild(nep_system* s, double skin, int force) {
+// Rebuild decision and rebuild: on a scheduled step, or when the nd2 displacement maxima of
+// the drift kernel (in s->partial) say so; reset clears the flag words first.
+int rebuild(nep_system* s, double skin, int scheduled, int reset, int nd2) {
   s->be = make_bin_edges(&s->model[0].hp, s->has_model[1] ? &s->model[1].hp : nullptr, skin);
   const ListOut lists{s->nbr, s->cnt, s->bp, s->nbrl, s->selfl};
-  HIPCHK(launch_rebuild(s->N, s->grid, s->be, s->capR, s->capA, s->x, s->v, s->type, s->perm, s->x_alt,
-                        s->v_alt, s->type_alt, s->perm_alt, s->x_build, s->cellid, s->cell_sorted, s->src,
-                        s->key, s->cell_count, s->cell_start, s->cell_fill, s->scan_tmp, s->pos, lists, s->ht, s->lsc,
+  const RebuildRule rule{scheduled, reset, 0.25 * skin * skin, skin, s->be};
+  HIPCHK(launch_rebuild(rule, s->partial, nd2, s->N, s->grid, s->capR, s->capA, s->x, s->v, s->type, s->perm,
+                        s->x_alt, s->v_alt, s->type_alt, s->perm_alt, s->x_build, s->cellid, s->cell_sorted, s->src,
+                        s->key, s->rank, s->cell_count, s->cell_start, s->scan_tmp, s->pos, lists, s->ht, s->lsc,
                         s->flags, s->st));
-  (void)force;
   return NEP_OK;
 }
 
@@ -668,6 +670,7 @@ int nep_system_create(const nep_model* full, const nep_model* sur, int64_t n_ato
     }
   }
   if (launch_zero_i32(s->flags, FLAG_COUNT, s->st) != hipSuccess ||
+      launch_zero_i32(s->cell_count, s->max_ncell, s->st) != hipSuccess ||
       launch_zero_i32(s->nbr, (int64_t)(cap_radial + kListPad) * n_atoms, s->st) != hipSuccess) {
     delete s;
     return NEP_ERR_HIP;
@@ -742,9 +745,7 @@ int nep_build_neighbors(nep_system* s, double skin) {
   for (int c = 0; c < 3; ++c)
     if (!(s->box[c] >= 2.0 * cut)) return fail(s, NEP_ERR_BOX_TOO_SMALL, "every box side must be >= 2 (rc + skin)");
   s->grid = make_grid(s->box, cut);
-  HIPCHK(launch_zero_i32(s->flags, FLAG_COUNT, s->st));
-  HIPCHK(launch_set_flag(s->flags, FLAG_REBUILD, 1, s->st));
-  int st = rebuild(s, skin, 1);
+  int st = rebuild(s, skin, 1, 1, 0);
   if (st) return st;
   st = check_flags(s);
   if (st) return st;
@@ -849,20 +850,17 @@ int thermo_row(nep_system* s, double* row, double err_rms, double err_max, int f
   return NEP_OK;
 }
 
-// One velocity-Verlet step with model `slot`. The rebuild flag is set on the device
-// for the scheduled steps and raised by the drift kernel when an atom has moved
-// more than skin/2 since the last build.
+// One velocity-Verlet step with model `slot`. The rebuild decision is taken on the device:
+// on the scheduled steps, and when an atom has moved more than skin/2 since the last build.
 int vv_step(nep_system* s, int slot, int prec, double dt, int rebuild_every, double skin) {
   const int64_t next = s->step + 1;
   const int scheduled = (rebuild_every > 0 && next % rebuild_every == 0) ? 1 : 0;
   hipEvent_t* ev = prof_take(s, 4);
   if (ev) HIPCHK(hipEventRecord(ev[0], s->st));
-  HIPCHK(launch_set_flag(s->flags, FLAG_REBUILD, scheduled, s->st));
   HIPCHK(launch_kick_drift(s->N, dt, s->grid, s->F[slot], s->type, s->mt, s->x, s->v, s->pos, s->x_build,
-                           0.25 * skin * skin, s->flags, s->partial, s->st));
-  HIPCHK(launch_select_bin(s->partial, kick_drift_blocks(s->N), s->flags, skin, s->be, s->st));
+                           s->partial, s->st));
   if (ev) HIPCHK(hipEventRecord(ev[1], s->st));
-  int st = rebuild(s, skin, 0);
+  int st = rebuild(s, skin, scheduled, 0, kick_drift_blocks(s->N));
   if (st) return st;
   if (ev) {
     HIPCHK(hipEventRecord(ev[2], s->st));
@@ -1328,6 +1326,7 @@ int nep_compute_energy_forces_virial_noalloc(const nep_model* model, int64_t n_a
   // state (device arrays in the caller's order), lists with skin, evaluation
   const CellGrid g = make_grid(s.box, model->hp.rc_radial);
   HIPCHK2(launch_zero_i32(s.flags, FLAG_COUNT, s.st));
+  HIPCHK2(launch_zero_i32(s.cell_count, s.max_ncell, s.st));
   HIPCHK2(launch_zero_i32(s.nbr, (int64_t)(cap_radial + kListPad) * n_atoms, s.st));
   HIPCHK2(launch_state_in(n_atoms, x, nullptr, types, s.n_types, g, s.x, s.v, s.type, s.perm, s.pos, s.flags, s.st));
   int32_t f[FLAG_COUNT];

@@ -15,7 +15,7 @@ constexpr int kNumXcd = 8;           // MI355X: 8 accelerator complex dies, one 
 constexpr int kPartialStride = 16;   // doubles per workgroup in reduction partials
 
 // Energy/virial partial slots.
-enum { P_ENERGY = 0, P_VIR = 1 /* 9 values */, P_KE = 10, P_ERR2 = 11, P_ERRMAX = 12, P_MAXD2 = 13, P_F2 = 14 };
+enum { P_ENERGY = 0, P_VIR = 1 /* 9 values */, P_KE = 10, P_ERR2 = 11, P_ERRMAX = 12, P_F2 = 14 };
 
 // Device flag words (int32).
 enum {
@@ -218,14 +218,19 @@ inline int grid_blocks(int64_t n, int block = kBlock) {
 // ---------------------------------------------------------------- launchers
 // Neighbour lists (nep_neighbors.hip)
 hipError_t launch_zero_i32(int32_t* p, int64_t n, hipStream_t st);
-hipError_t launch_zero_f32(float* p, int64_t n, hipStream_t st);
-hipError_t launch_zero_f64(double* p, int64_t n, hipStream_t st);
-hipError_t launch_rebuild(int64_t N, const CellGrid& g, const BinEdges& be, int capR, int capA,
-                          double* x, double* v, int32_t* type, int32_t* perm, double* x_alt,
-                          double* v_alt, int32_t* type_alt, int32_t* perm_alt, double* x_build,
-                          int32_t* cellid, int32_t* cell_sorted, int32_t* src, int32_t* key,
-                          int32_t* cell_count, int32_t* cell_start, int32_t* cell_fill,
-                          int32_t* scan_tmp, uint4* pos, const ListOut& lists, HaloTables ht,
+// What a step's rebuild decision needs: lists are rebuilt on a scheduled step, or when the
+// largest squared displacement since the build exceeds half_skin2 = (skin / 2)^2; reset
+// clears the flag words first (a build requested by the caller).
+struct RebuildRule {
+  int scheduled, reset;
+  double half_skin2, skin;
+  BinEdges be;
+};
+hipError_t launch_rebuild(const RebuildRule& rule, const double* d2, int nd2, int64_t N, const CellGrid& g, int capR,
+                          int capA, double* x, double* v, int32_t* type, int32_t* perm, double* x_alt, double* v_alt,
+                          int32_t* type_alt, int32_t* perm_alt, double* x_build, int32_t* cellid,
+                          int32_t* cell_sorted, int32_t* src, int32_t* key, int32_t* rank, int32_t* cell_count,
+                          int32_t* cell_start, int32_t* scan_tmp, uint4* pos, const ListOut& lists, HaloTables ht,
                           ListScratch sc, int32_t* flags, hipStream_t st);
 // Rows of original ids [o_lo, o_hi), ascending, into rows[(o - o_lo) * cap + k].
 hipError_t launch_export(int64_t N, const int32_t* perm, const int32_t* nbr, const int32_t* cnt,
@@ -281,15 +286,12 @@ hipError_t launch_reduce_partials(const double* partial, int nblocks, int first,
                                   double* out, hipStream_t st);
 hipError_t launch_max_partials(const double* partial, int nblocks, int slot, double* out,
                                hipStream_t st);
-hipError_t launch_kick_drift(int64_t N, double dt, CellGrid g, const float* F, const int32_t* type,
-                             MassTable mt, double* x, double* v, uint4* pos, const double* x_build,
-                             double half_skin2, int32_t* flags, double* partial, hipStream_t st);
-// FLAG_BIN_R / FLAG_BIN_A from the per-workgroup displacement maxima the drift
-// kernel left in partial.
-// workgroups of k_kick_drift, whose per-workgroup maxima launch_select_bin reads
+// Workgroups of k_kick_drift; each leaves the largest squared displacement since the build
+// of its atoms in d2 (1e300 for a non-finite one).
 int kick_drift_blocks(int64_t N);
-hipError_t launch_select_bin(const double* partial, int nblocks, int32_t* flags, double skin,
-                             const BinEdges& be, hipStream_t st);
+hipError_t launch_kick_drift(int64_t N, double dt, CellGrid g, const float* F, const int32_t* type,
+                             MassTable mt, double* x, double* v, uint4* pos, const double* x_build, double* d2,
+                             hipStream_t st);
 hipError_t launch_kick(int64_t N, double dt, const float* F, const int32_t* type, MassTable mt,
                        double* v, hipStream_t st);
 hipError_t launch_kick_diff(int64_t N, double dt, const float* Fa, const float* Fb,
@@ -328,7 +330,6 @@ hipError_t launch_kinetic(int64_t N, const double* v, const int32_t* type, MassT
                           double* partial, hipStream_t st);
 hipError_t launch_force_error(int64_t N, const float* Fa, const float* Fb, double* partial,
                               hipStream_t st);
-hipError_t launch_set_flag(int32_t* flags, int idx, int value, hipStream_t st);
 hipError_t launch_sum_i32(int64_t N, const int32_t* a, double* partial, int slot, hipStream_t st);
 hipError_t launch_state_in(int64_t N, const double* x_aos, const double* v_aos,
                            const int32_t* type_in, int n_types, CellGrid g, double* x, double* v,

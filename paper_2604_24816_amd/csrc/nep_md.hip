@@ -38,19 +38,17 @@ __device__ __forceinline__ double wrap_coord(double xv, double L) {
   return xv;
 }
 
-// v += dt/2 F/(m xi); x += dt v; wrap; flag a rebuild when |x - x_build| > skin/2.
-// Strides over a capped grid (kIntegrateGrid workgroups), so that the per-workgroup maxima
-// of the squared displacement that k_select_bin reads are few.
+// v += dt/2 F/(m xi); x += dt v; wrap; the largest squared displacement since the build per
+// workgroup, for the rebuild decision. Strides over a capped grid (kIntegrateGrid
+// workgroups), so that these maxima are few.
 constexpr int kIntegrateGrid = 8192;
 
 __global__ void k_kick_drift(int64_t N, double dt, CellGrid g, const float* __restrict__ F,
                              const int32_t* __restrict__ type, MassTable mt, double* __restrict__ x,
                              double* __restrict__ v, uint4* __restrict__ pos, const double* __restrict__ xb,
-                             double half_skin2,
-                             int32_t* __restrict__ flags, double* __restrict__ partial) {
+                             double* __restrict__ d2_out) {
   __shared__ double sh[kBlock / 64];
   double d2max = 0.0;
-  bool moved = false;
   for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < N; p += (int64_t)gridDim.x * blockDim.x) {
     const double inv = mt.inv_mxi[type[p]];
     double xn[3];
@@ -65,56 +63,14 @@ __global__ void k_kick_drift(int64_t N, double dt, CellGrid g, const float* __re
       d2 += d * d;
     }
     pos_put(pos, p, xn[0], xn[1], xn[2], g.box);
-    if (!(d2 <= half_skin2)) moved = true;  // also catches NaN
     if (!(d2 == d2)) d2 = 1e300;
     d2max = fmax(d2max, d2);
   }
-  if (moved) flags[FLAG_REBUILD] = 1;
-  // largest squared displacement since the build, per workgroup
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) d2max = fmax(d2max, __shfl_xor(d2max, off, 64));
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = d2max;
   __syncthreads();
-  if (threadIdx.x == 0)
-    partial[(int64_t)blockIdx.x * kPartialStride + P_MAXD2] =
-        fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
-}
-
-// k = first bin fraction with bin_frac(k) * skin >= 2 * (largest displacement since the
-// build); the evaluation visits the bins up to the edges rc_radial + f_k skin and
-// rc_angular + f_k skin. A rebuild later in the same step resets them to k = 0.
-constexpr int kSelBlock = 1024;  // one workgroup reads every partial: many loads in flight
-
-__global__ void __launch_bounds__(kSelBlock)
-k_select_bin(const double* __restrict__ partial, int nblocks, int32_t* flags, double skin, BinEdges be) {
-  __shared__ double sh[kSelBlock];
-  double m = 0.0;
-#pragma unroll 4
-  for (int b = threadIdx.x; b < nblocks; b += kSelBlock)
-    m = fmax(m, partial[(int64_t)b * kPartialStride + P_MAXD2]);
-  sh[threadIdx.x] = m;
-  __syncthreads();
-  for (int off = kSelBlock / 2; off > 0; off >>= 1) {
-    if (threadIdx.x < (unsigned)off) sh[threadIdx.x] = fmax(sh[threadIdx.x], sh[threadIdx.x + off]);
-    __syncthreads();
-  }
-  if (threadIdx.x != 0) return;
-  const double d = sqrt(sh[0]);
-  int k = kFracs - 1;
-  for (int j = kFracs - 1; j >= 0; --j)
-    if ((double)bin_frac(j) * skin >= 2.0 * d * (1.0 + 1e-12)) k = j;
-  int br0 = 0, ba0 = 0, br1 = 0, ba1 = 0;
-  for (int j = 0; j < kFracs; ++j)
-    if (j == k) {
-      br0 = be.idxR[0][j];
-      ba0 = be.idxA[0][j];
-      br1 = be.idxR[1][j];
-      ba1 = be.idxA[1][j];
-    }
-  flags[FLAG_BIN_R] = br0;
-  flags[FLAG_BIN_A] = ba0;
-  flags[FLAG_BIN_R1] = br1;
-  flags[FLAG_BIN_A1] = ba1;
+  if (threadIdx.x == 0) d2_out[blockIdx.x] = fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
 }
 
 __global__ void k_kick(int64_t N, double dt, const float* __restrict__ F, const int32_t* __restrict__ type,
@@ -246,10 +202,6 @@ __global__ void k_sum_i32(int64_t N, const int32_t* __restrict__ a, double* __re
   block_partial(p < N ? (double)a[p] : 0.0, sh, partial + (int64_t)blockIdx.x * kPartialStride + slot);
 }
 
-__global__ void k_set_flag(int32_t* flags, int idx, int value) {
-  if (threadIdx.x == 0) flags[idx] = value;
-}
-
 __global__ void k_state_in(int64_t N, const double* __restrict__ xa, const double* __restrict__ va,
                            const int32_t* __restrict__ tin, int n_types, CellGrid g, double* __restrict__ x,
                            double* __restrict__ v, int32_t* __restrict__ type, int32_t* __restrict__ perm,
@@ -335,16 +287,10 @@ int kick_drift_blocks(int64_t N) {
 }
 
 hipError_t launch_kick_drift(int64_t N, double dt, CellGrid g, const float* F, const int32_t* type,
-                             MassTable mt, double* x, double* v, uint4* pos, const double* x_build,
-                             double half_skin2, int32_t* flags, double* partial, hipStream_t st) {
+                             MassTable mt, double* x, double* v, uint4* pos, const double* x_build, double* d2,
+                             hipStream_t st) {
   hipLaunchKernelGGL(k_kick_drift, dim3(kick_drift_blocks(N)), dim3(kBlock), 0, st, N, dt, g, F, type, mt, x, v,
-                     pos, x_build, half_skin2, flags, partial);
-  return hipGetLastError();
-}
-
-hipError_t launch_select_bin(const double* partial, int nblocks, int32_t* flags, double skin,
-                             const BinEdges& be, hipStream_t st) {
-  hipLaunchKernelGGL(k_select_bin, dim3(1), dim3(kSelBlock), 0, st, partial, nblocks, flags, skin, be);
+                     pos, x_build, d2);
   return hipGetLastError();
 }
 
@@ -381,11 +327,6 @@ hipError_t launch_force_error(int64_t N, const float* Fa, const float* Fb, doubl
 
 hipError_t launch_sum_i32(int64_t N, const int32_t* a, double* partial, int slot, hipStream_t st) {
   hipLaunchKernelGGL(k_sum_i32, dim3(grid_blocks(N)), dim3(kBlock), 0, st, N, a, partial, slot);
-  return hipGetLastError();
-}
-
-hipError_t launch_set_flag(int32_t* flags, int idx, int value, hipStream_t st) {
-  hipLaunchKernelGGL(k_set_flag, dim3(1), dim3(64), 0, st, flags, idx, value);
   return hipGetLastError();
 }
 

@@ -18,19 +18,12 @@ __global__ void k_zero_i32(int32_t* p, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0;
 }
-__global__ void k_zero_f32(float* p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0.f;
-}
-__global__ void k_zero_f64(double* p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0.0;
-}
 
 // Workgroups of the rebuild kernels. Every rebuild kernel is enqueued each step and
-// returns at once when no rebuild is due, so the per-atom and per-cell ones stride over a
-// capped grid (a multiple of the 8 dies, so that a workgroup stays on its die): a step
-// without a rebuild then dispatches a few thousand workgroups, not one per cell or per
+// returns at once when no rebuild is due, so there are few of them (a dispatch that does
+// nothing still takes about 2 us of the step) and the per-atom and per-cell ones stride
+// over a capped grid (a multiple of the 8 dies, so that a workgroup stays on its die): a
+// step without a rebuild then dispatches a few thousand workgroups, not one per cell or per
 // 256 atoms.
 constexpr int kRebuildGrid = 8192;
 inline int rebuild_grid(int64_t nblocks) { return (int)(nblocks < kRebuildGrid ? nblocks : kRebuildGrid); }
@@ -42,113 +35,248 @@ __device__ __forceinline__ int cell_coord(double xv, double L, int n) {
   return c;
 }
 
-__global__ void k_bin(int64_t N, CellGrid g, const double* __restrict__ x, int32_t* __restrict__ cellid,
-                      int32_t* __restrict__ count, const int32_t* __restrict__ flags) {
-  if (flags[FLAG_REBUILD] == 0) return;
-  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < N; p += (int64_t)gridDim.x * blockDim.x) {
-    const int cx = cell_coord(x[p], g.box[0], g.nc[0]);
-    const int cy = cell_coord(x[N + p], g.box[1], g.nc[1]);
-    const int cz = cell_coord(x[2 * N + p], g.box[2], g.nc[2]);
-    const int c = cell_lin(g, cx, cy, cz);
-    cellid[p] = c;
-    atomicAdd(&count[c], 1);
+__device__ __forceinline__ int cell_of(const CellGrid& g, const double* __restrict__ x, int64_t N, int64_t p) {
+  return cell_lin(g, cell_coord(x[p], g.box[0], g.nc[0]), cell_coord(x[N + p], g.box[1], g.nc[1]),
+                  cell_coord(x[2 * N + p], g.box[2], g.nc[2]));
+}
+
+// Inclusive prefix sum over the lanes of a wavefront.
+__device__ __forceinline__ int wave_scan(int v) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(v, o, 64);
+    v += lane >= o ? t : 0;
+  }
+  return v;
+}
+
+// Exclusive prefix sum over a workgroup of WAVES wavefronts, the total in tot; sh holds
+// WAVES ints. Two barriers; sh may be reused after a further one.
+template <int WAVES>
+__device__ __forceinline__ int block_scan(int v, int* sh, int& tot) {
+  const int incl = wave_scan(v);
+  const int w = threadIdx.x >> 6;
+  __syncthreads();
+  if ((threadIdx.x & 63) == 63) sh[w] = incl;
+  __syncthreads();
+  int before = 0;
+  tot = 0;
+#pragma unroll
+  for (int k = 0; k < WAVES; ++k) {
+    const int t = sh[k];
+    before += k < w ? t : 0;
+    tot += t;
+  }
+  return before + incl - v;
+}
+
+// The step's rebuild decision and the distance bins its evaluations visit: from d2, the
+// largest squared displacement since the build. REBUILD is set on a scheduled step and when
+// an atom has moved more than skin / 2. k = first bin fraction with bin_frac(k) * skin >=
+// 2 sqrt(d2); the evaluation visits the bins up to the edges rc_radial + f_k skin and
+// rc_angular + f_k skin; after a build the displacements are 0, so k = 0. One thread.
+__device__ void select_bins(const RebuildRule& rule, double d2, int32_t* flags) {
+  if (rule.reset)
+    for (int k = 0; k < FLAG_COUNT; ++k) flags[k] = 0;
+  const int build = rule.scheduled || d2 > rule.half_skin2;
+  flags[FLAG_REBUILD] = build;
+  const double d = build ? 0.0 : sqrt(d2);
+  int k = kFracs - 1;
+  for (int j = kFracs - 1; j >= 0; --j)
+    if ((double)bin_frac(j) * rule.skin >= 2.0 * d * (1.0 + 1e-12)) k = j;
+  int br0 = 0, ba0 = 0, br1 = 0, ba1 = 0;
+  for (int j = 0; j < kFracs; ++j)
+    if (j == k) {
+      br0 = rule.be.idxR[0][j];
+      ba0 = rule.be.idxA[0][j];
+      br1 = rule.be.idxR[1][j];
+      ba1 = rule.be.idxA[1][j];
+    }
+  flags[FLAG_BIN_R] = br0;
+  flags[FLAG_BIN_A] = ba0;
+  flags[FLAG_BIN_R1] = br1;
+  flags[FLAG_BIN_A1] = ba1;
+  if (build) flags[FLAG_NBUILD] += 1;
+}
+
+// Largest of the n partial maxima over a workgroup of 1024 threads, valid in thread 0.
+constexpr int kSelBlock = 1024;
+__device__ __forceinline__ double block_max(const double* __restrict__ part, int n, double* sh) {
+  double m = 0.0;
+#pragma unroll 4
+  for (int b = threadIdx.x; b < n; b += kSelBlock) m = fmax(m, part[b]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    for (int k = 1; k < kSelBlock / 64; ++k) m = fmax(m, sh[k]);
+  return m;
+}
+
+__global__ void __launch_bounds__(kSelBlock)
+k_select(RebuildRule rule, const double* __restrict__ d2, int nd2, int32_t* __restrict__ flags) {
+  __shared__ double sh[kSelBlock / 64];
+  const double m = block_max(d2, nd2, sh);
+  if (threadIdx.x == 0) select_bins(rule, m, flags);
+}
+
+// Systems of up to kSortAtoms atoms in kSortCells cells: the decision, the binning, the
+// scan and the scatter in one workgroup, with the cell counts in LDS. One launch instead of
+// four; beyond these sizes one workgroup is slower than the launches it saves.
+constexpr int kSortAtoms = 16384, kSortCells = 2048;
+
+__global__ void __launch_bounds__(kSelBlock)
+k_select_sort(RebuildRule rule, const double* __restrict__ d2, int nd2, int64_t N, CellGrid g,
+              const double* __restrict__ x, const int32_t* __restrict__ perm, int32_t* __restrict__ start,
+              int32_t* __restrict__ src, int32_t* __restrict__ key, int32_t* __restrict__ flags) {
+  __shared__ double shd[kSelBlock / 64];
+  __shared__ int count[kSortCells], sh[kSelBlock / 64], build;
+  const int t = threadIdx.x;
+  const double m = block_max(d2, nd2, shd);
+  if (t == 0) {
+    select_bins(rule, m, flags);
+    build = rule.scheduled || m > rule.half_skin2;
+  }
+  for (int c = t; c < kSortCells; c += kSelBlock) count[c] = 0;
+  __syncthreads();
+  if (!build) return;
+  constexpr int PER = kSortAtoms / kSelBlock;
+  int cr[PER];  // cell | rank in the cell << 16
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int64_t p = t + (int64_t)u * kSelBlock;
+    cr[u] = 0;
+    if (p < N) {
+      const int c = cell_of(g, x, N, p);
+      cr[u] = c | atomicAdd(&count[c], 1) << 16;
+    }
+  }
+  __syncthreads();
+  constexpr int CPER = kSortCells / kSelBlock;
+  int v[CPER], sum = 0, tot;
+#pragma unroll
+  for (int k = 0; k < CPER; ++k) {
+    v[k] = count[CPER * t + k];
+    sum += v[k];
+  }
+  int run = block_scan<kSelBlock / 64>(sum, sh, tot);
+#pragma unroll
+  for (int k = 0; k < CPER; ++k) {
+    const int c = CPER * t + k;
+    count[c] = run;
+    if (c <= g.ncell) start[c] = run;  // start[ncell] = N: the cells past the grid are empty
+    run += v[k];
+  }
+  if (t == 0 && g.ncell == kSortCells) start[g.ncell] = tot;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int64_t p = t + (int64_t)u * kSelBlock;
+    if (p < N) {
+      const int pos = count[cr[u] & 0xffff] + (cr[u] >> 16);
+      src[pos] = (int32_t)p;
+      key[pos] = perm[p];
+    }
   }
 }
 
-// Exclusive scan, phase 1: each 256-thread block scans 1024 elements.
+// Cell of every atom and its rank among the cell's atoms in arrival order. count is zero
+// on entry (k_sort_permute clears it for the next build).
+__global__ void k_bin(int64_t N, CellGrid g, const double* __restrict__ x, int32_t* __restrict__ cellid,
+                      int32_t* __restrict__ rank, int32_t* __restrict__ count, const int32_t* __restrict__ flags) {
+  if (flags[FLAG_REBUILD] == 0) return;
+  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < N; p += (int64_t)gridDim.x * blockDim.x) {
+    const int c = cell_of(g, x, N, p);
+    cellid[p] = c;
+    rank[p] = atomicAdd(&count[c], 1);
+  }
+}
+
+// Exclusive scan of the cell counts: each workgroup scans 1024 cells and leaves its total;
+// k_scan_add then adds the totals of the workgroups before.
 constexpr int kScanPer = 4;
 constexpr int kScanTile = kBlock * kScanPer;
 
 __global__ void k_scan_tiles(const int32_t* __restrict__ in, int32_t* __restrict__ out, int n,
                              int32_t* __restrict__ tile_sums, const int32_t* __restrict__ flags) {
   if (flags[FLAG_REBUILD] == 0) return;
-  __shared__ int32_t s[kBlock];
+  __shared__ int sh[kBlock / 64];
   const int base = blockIdx.x * kScanTile + threadIdx.x * kScanPer;
   int32_t v[kScanPer];
-  int32_t sum = 0;
+  int sum = 0, tot;
   for (int k = 0; k < kScanPer; ++k) {
     v[k] = (base + k < n) ? in[base + k] : 0;
     sum += v[k];
   }
-  s[threadIdx.x] = sum;
-  __syncthreads();
-  for (int off = 1; off < kBlock; off <<= 1) {
-    int32_t t = (threadIdx.x >= (unsigned)off) ? s[threadIdx.x - off] : 0;
-    __syncthreads();
-    s[threadIdx.x] += t;
-    __syncthreads();
-  }
-  int32_t run = s[threadIdx.x] - sum;  // exclusive prefix of this thread
+  int run = block_scan<kBlock / 64>(sum, sh, tot);
   for (int k = 0; k < kScanPer; ++k) {
     if (base + k < n) out[base + k] = run;
     run += v[k];
   }
-  if (threadIdx.x == kBlock - 1) tile_sums[blockIdx.x] = s[kBlock - 1];
+  if (threadIdx.x == 0) tile_sums[blockIdx.x] = tot;
 }
 
-// Phase 2: one block scans the tile sums (any count) in chunks, exclusive.
-__global__ void k_scan_sums(int32_t* __restrict__ sums, int nt, int32_t* __restrict__ total,
-                            const int32_t* __restrict__ flags) {
+__global__ void __launch_bounds__(kScanTile)
+k_scan_add(int32_t* __restrict__ out, int n, int64_t N, const int32_t* __restrict__ sums,
+           const int32_t* __restrict__ flags) {
   if (flags[FLAG_REBUILD] == 0) return;
-  __shared__ int32_t s[kBlock];
-  int32_t carry = 0;
-  for (int base = 0; base < nt; base += kBlock) {
-    const int i = base + threadIdx.x;
-    const int32_t v = (i < nt) ? sums[i] : 0;
-    s[threadIdx.x] = v;
-    __syncthreads();
-    for (int off = 1; off < kBlock; off <<= 1) {
-      int32_t t = (threadIdx.x >= (unsigned)off) ? s[threadIdx.x - off] : 0;
-      __syncthreads();
-      s[threadIdx.x] += t;
-      __syncthreads();
-    }
-    if (i < nt) sums[i] = carry + s[threadIdx.x] - v;
-    const int32_t chunk = s[kBlock - 1];
-    __syncthreads();
-    carry += chunk;
-  }
-  if (threadIdx.x == 0) *total = carry;
+  __shared__ int sh[kScanTile / 64];
+  int s = 0, before;
+  for (int b = threadIdx.x; b < (int)blockIdx.x; b += kScanTile) s += sums[b];
+  block_scan<kScanTile / 64>(s, sh, before);
+  const int i = blockIdx.x * kScanTile + threadIdx.x;
+  if (i < n) out[i] += before;
+  if (i == n - 1) out[n] = (int32_t)N;
 }
 
-__global__ void k_scan_add(int32_t* __restrict__ out, int n, const int32_t* __restrict__ sums,
-                           const int32_t* __restrict__ flags) {
-  if (flags[FLAG_REBUILD] == 0) return;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] += sums[i / kScanTile];
-}
-
-__global__ void k_scatter(int64_t N, const int32_t* __restrict__ cellid, const int32_t* __restrict__ start,
-                          int32_t* __restrict__ fill, const int32_t* __restrict__ perm,
+__global__ void k_scatter(int64_t N, const int32_t* __restrict__ cellid, const int32_t* __restrict__ rank,
+                          const int32_t* __restrict__ start, const int32_t* __restrict__ perm,
                           int32_t* __restrict__ src, int32_t* __restrict__ key,
                           const int32_t* __restrict__ flags) {
   if (flags[FLAG_REBUILD] == 0) return;
   for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < N; p += (int64_t)gridDim.x * blockDim.x) {
-    const int c = cellid[p];
-    const int pos = start[c] + atomicAdd(&fill[c], 1);
+    const int pos = start[cellid[p]] + rank[p];
     src[pos] = (int32_t)p;
     key[pos] = perm[p];
   }
 }
 
-// Within each cell, order atoms by original id. One wavefront per cell: each lane holds
-// atoms of the cell, counts the cell's smaller keys (the keys are distinct original ids)
-// and moves its atom to that rank, so the result is the stable order whatever order the
-// scatter's atomics left. Cells of more than kSortMax atoms (none at metallic densities)
-// are sorted by one lane by insertion.
+// Within each cell, order atoms by original id and move their state there. One wavefront
+// per cell: each lane holds atoms of the cell, counts the cell's smaller keys (the keys are
+// distinct original ids) and moves its atom to that rank, so the result is the stable order
+// whatever order the scatter's atomics left. Cells of more than kSortMax atoms (none at
+// metallic densities) are sorted by one lane by insertion.
 constexpr int kSortMax = 256;
 constexpr int kSortWaves = kBlock / 64;
 
-__global__ void __launch_bounds__(kBlock) k_cell_sort(int ncell, const int32_t* __restrict__ start,
-                                                      int32_t* __restrict__ key, int32_t* __restrict__ src,
-                                                      const int32_t* __restrict__ flags) {
+__global__ void __launch_bounds__(kBlock)
+k_sort_permute(int64_t N, int ncell, const int32_t* __restrict__ start, int32_t* __restrict__ count,
+               int32_t* __restrict__ key, int32_t* __restrict__ src, const double* __restrict__ x,
+               const double* __restrict__ v, const int32_t* __restrict__ type, double* __restrict__ x2,
+               double* __restrict__ v2, int32_t* __restrict__ type2, int32_t* __restrict__ perm2,
+               double* __restrict__ xb, int32_t* __restrict__ cell_sorted, const int32_t* __restrict__ flags) {
   if (flags[FLAG_REBUILD] == 0) return;
   __shared__ int32_t kk[kSortWaves][kSortMax];
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   constexpr int U = kSortMax / 64;
   for (int c = blockIdx.x * kSortWaves + w; c < ncell; c += gridDim.x * kSortWaves) {  // wave-uniform
     const int a = start[c], n = start[c + 1] - a;
-    if (n <= 1) continue;
+    if (lane == 0) count[c] = 0;
+    if (n <= 0) continue;
+    // sorted atom p of the cell from atom s, original id k
+    auto move = [&](int64_t p, int64_t s, int32_t k) {
+      for (int d = 0; d < 3; ++d) {
+        const double xv = x[d * N + s];
+        x2[d * N + p] = xv;
+        xb[d * N + p] = xv;
+        v2[d * N + p] = v[d * N + s];
+      }
+      type2[p] = type[s];
+      perm2[p] = k;
+      cell_sorted[p] = c;
+    };
     if (n > kSortMax) {
       if (lane == 0) {
         for (int i = a + 1; i < a + n; ++i) {
@@ -162,6 +290,7 @@ __global__ void __launch_bounds__(kBlock) k_cell_sort(int ncell, const int32_t* 
           key[j + 1] = k;
           src[j + 1] = s0;
         }
+        for (int i = a; i < a + n; ++i) move(i, src[i], key[i]);
       }
       continue;
     }
@@ -183,161 +312,114 @@ __global__ void __launch_bounds__(kBlock) k_cell_sort(int ncell, const int32_t* 
       for (int u = 0; u < U; ++u) rank[u] += km < mk[u] ? 1 : 0;
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (lane + 64 * u < n) {
-        key[a + rank[u]] = mk[u];
-        src[a + rank[u]] = ms[u];
-      }
-    }
+    for (int u = 0; u < U; ++u)
+      if (lane + 64 * u < n) move(a + rank[u], ms[u], mk[u]);
     wave_lds_sync();
   }
-}
-
-__global__ void k_permute(int64_t N, const int32_t* __restrict__ src, const int32_t* __restrict__ cellid,
-                          const double* __restrict__ x, const double* __restrict__ v,
-                          const int32_t* __restrict__ type, const int32_t* __restrict__ perm,
-                          double* __restrict__ x2, double* __restrict__ v2, int32_t* __restrict__ type2,
-                          int32_t* __restrict__ perm2, double* __restrict__ xb,
-                          int32_t* __restrict__ cell_sorted, const int32_t* __restrict__ flags) {
-  if (flags[FLAG_REBUILD] == 0) return;
-  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < N; p += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t s = src[p];
-    for (int c = 0; c < 3; ++c) {
-      const double xv = x[c * N + s];
-      x2[c * N + p] = xv;
-      xb[c * N + p] = xv;
-      v2[c * N + p] = v[c * N + s];
-    }
-    type2[p] = type[s];
-    perm2[p] = perm[s];
-    cell_sorted[p] = cellid[s];
-  }
-}
-
-// Copy the permuted arrays back to the primary buffers.
-__global__ void k_copy_back(int64_t N, const double* __restrict__ x2, const double* __restrict__ v2,
-                            const int32_t* __restrict__ type2, const int32_t* __restrict__ perm2,
-                            double* __restrict__ x, double* __restrict__ v, int32_t* __restrict__ type,
-                            int32_t* __restrict__ perm, uint4* __restrict__ pos, CellGrid g,
-                            const int32_t* __restrict__ flags) {
-  if (flags[FLAG_REBUILD] == 0) return;
-  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < N; p += (int64_t)gridDim.x * blockDim.x) {
-    double xn[3];
-    for (int c = 0; c < 3; ++c) {
-      xn[c] = x2[c * N + p];
-      x[c * N + p] = xn[c];
-      v[c * N + p] = v2[c * N + p];
-    }
-    pos_put(pos, p, xn[0], xn[1], xn[2], g.box);
-    type[p] = type2[p];
-    perm[p] = perm2[p];
-  }
-}
-
-// Exclusive prefix sum over the workgroup; returns this thread's prefix, total in *tot.
-__device__ __forceinline__ int block_scan(int v, int* scan, int* tot) {
-  __syncthreads();
-  scan[threadIdx.x] = v;
-  __syncthreads();
-  for (int off = 1; off < kBlock; off <<= 1) {
-    const int t = threadIdx.x >= (unsigned)off ? scan[threadIdx.x - off] : 0;
-    __syncthreads();
-    scan[threadIdx.x] += t;
-    __syncthreads();
-  }
-  const int incl = scan[threadIdx.x];
-  *tot = scan[kBlock - 1];
-  return incl - v;
 }
 
 // One workgroup per 256-atom tile: the tile's force halo (every non-empty cell within
 // one cell, periodic, of a cell holding tile atoms), sorted by cell id, with local
 // offsets. ok = 0 when the tile or its halo exceeds the LDS tables of the force kernel.
+// The halo's cells are marked in a bitmap of the grid, which is then read in id order: no
+// duplicates and no sort. Grids of more than kMapCells cells (above eight million atoms at
+// metallic density), whose bitmap would not fit in LDS, sort the candidates instead (a
+// bitonic sort of up to 2,048 ids, whose 66 barriers made this kernel 30 us even for a
+// system of a few tiles).
+constexpr int kMapCells = 262144;
+
+__device__ void halo_none(int32_t* info) {
+  if (threadIdx.x < 4) info[threadIdx.x] = 0;
+}
+
+// Stencil cell o (0..26) of cell c_lo + t / 27, or -1 when that cell or the stencil cell is
+// empty.
+__device__ __forceinline__ int halo_cand(const CellGrid& g, const int32_t* __restrict__ cell_start, int c_lo, int t) {
+  const int c = c_lo + t / 27, o = t % 27;
+  int cx, cy, cz;
+  if (!(cell_start[c + 1] > cell_start[c] && cell_coords(g, c, cx, cy, cz))) return -1;
+  const int nx = (cx + o % 3 - 1 + g.nc[0]) % g.nc[0];
+  const int ny = (cy + (o / 3) % 3 - 1 + g.nc[1]) % g.nc[1];
+  const int nz = (cz + o / 9 - 1 + g.nc[2]) % g.nc[2];
+  const int v = cell_lin(g, nx, ny, nz);
+  return cell_start[v + 1] > cell_start[v] ? v : -1;
+}
+
+template <bool MAP>
 __device__ void halo_tile(int64_t N, const CellGrid& g, const int32_t* __restrict__ cell_sorted,
                           const int32_t* __restrict__ cell_start, const HaloTables& ht, int tile) {
-  __shared__ int cand[kCandMax];
-  __shared__ int scan[kBlock];
+  constexpr int kWords = MAP ? kMapCells / 32 : kCandMax;
+  __shared__ uint32_t buf[kWords];  // bitmap, or candidate ids to sort
+  __shared__ int scan[kBlock / 64];
   __shared__ int cnt[kHaloCellsMax];
   const int64_t t0 = (int64_t)tile * kBlock;
   const int64_t t1 = t0 + kBlock < N ? t0 + kBlock : N;
   int32_t* info = ht.info + 4 * tile;
   const int c_lo = cell_sorted[t0], c_hi = cell_sorted[t1 - 1];
   const int ncr = c_hi - c_lo + 1;
-  if (ncr > kTileCellsMax) {
-    if (threadIdx.x == 0) {
-      info[0] = 0;
-      info[1] = 0;
-      info[2] = 0;
-      info[3] = 0;
+  if (ncr > kTileCellsMax) return halo_none(info);
+  int n_list = 64;  // words of buf in use
+  if constexpr (MAP) {
+    n_list = (g.ncell + 31) / 32;
+    for (int t = threadIdx.x; t < n_list; t += kBlock) buf[t] = 0;
+    __syncthreads();
+    for (int t = threadIdx.x; t < 27 * ncr; t += kBlock) {
+      const int v = halo_cand(g, cell_start, c_lo, t);
+      if (v >= 0) atomicOr(&buf[v >> 5], 1u << (v & 31));
     }
-    return;
-  }
-  int n_sort = 64;
-  while (n_sort < 27 * ncr) n_sort <<= 1;
-  for (int t = threadIdx.x; t < n_sort; t += kBlock) {
-    int v = 0x7fffffff;
-    if (t < 27 * ncr) {
-      const int c = c_lo + t / 27, o = t % 27;
-      int cx, cy, cz;
-      if (cell_start[c + 1] > cell_start[c] && cell_coords(g, c, cx, cy, cz)) {
-        const int nx = (cx + o % 3 - 1 + g.nc[0]) % g.nc[0];
-        const int ny = (cy + (o / 3) % 3 - 1 + g.nc[1]) % g.nc[1];
-        const int nz = (cz + o / 9 - 1 + g.nc[2]) % g.nc[2];
-        v = cell_lin(g, nx, ny, nz);
-      }
-    }
-    cand[t] = v;
-  }
-  __syncthreads();
-  for (int k = 2; k <= n_sort; k <<= 1)
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int t = threadIdx.x; t < n_sort; t += kBlock) {
-        const int u = t ^ j;
-        if (u > t) {
-          const int a = cand[t], c = cand[u];
-          if ((a > c) == ((t & k) == 0)) {
-            cand[t] = c;
-            cand[u] = a;
+    __syncthreads();
+  } else {
+    while (n_list < 27 * ncr) n_list <<= 1;
+    for (int t = threadIdx.x; t < n_list; t += kBlock)
+      buf[t] = t < 27 * ncr ? (uint32_t)halo_cand(g, cell_start, c_lo, t) : ~0u;
+    __syncthreads();
+    for (int k = 2; k <= n_list; k <<= 1)
+      for (int j = k >> 1; j > 0; j >>= 1) {
+        for (int t = threadIdx.x; t < n_list; t += kBlock) {
+          const int u = t ^ j;
+          if (u > t) {
+            const uint32_t a = buf[t], c = buf[u];
+            if ((a > c) == ((t & k) == 0)) {
+              buf[t] = c;
+              buf[u] = a;
+            }
           }
         }
+        __syncthreads();
       }
-      __syncthreads();
+  }
+  // the thread's words, in id order: every halo cell once
+  const int per = (n_list + kBlock - 1) / kBlock;
+  const int e0 = threadIdx.x * per, e1 = e0 + per < n_list ? e0 + per : n_list;
+  auto each = [&](auto&& f) {
+    for (int e = e0; e < e1; ++e) {
+      if constexpr (MAP) {
+        for (uint32_t m = buf[e]; m; m &= m - 1) f(32 * e + __ffs(m) - 1);
+      } else {
+        const uint32_t c = buf[e];
+        if (c != ~0u && (e == 0 || buf[e - 1] != c)) f((int)c);
+      }
     }
-  const int per = (n_sort + kBlock - 1) / kBlock;
-  const int e0 = threadIdx.x * per;
+  };
   int mine = 0;
-  for (int e = e0; e < e0 + per && e < n_sort; ++e) {
-    const int c = cand[e];
-    if (c != 0x7fffffff && (e == 0 || cand[e - 1] != c) && cell_start[c + 1] > cell_start[c]) ++mine;
-  }
-  int ncells = 0;
-  int pos = block_scan(mine, scan, &ncells);
-  if (ncells > kHaloCellsMax) {
-    if (threadIdx.x == 0) {
-      info[0] = 0;
-      info[1] = 0;
-      info[2] = 0;
-      info[3] = 0;
-    }
-    return;
-  }
+  each([&](int) { ++mine; });
+  int ncells;
+  int pos = block_scan<kBlock / 64>(mine, scan, ncells);
+  if (ncells > kHaloCellsMax) return halo_none(info);
   int32_t* hs = ht.start + (int64_t)tile * kHaloCellsMax;
   int32_t* ho = ht.off + (int64_t)tile * (kHaloCellsMax + 1);
-  for (int e = e0; e < e0 + per && e < n_sort; ++e) {
-    const int c = cand[e];
-    if (c != 0x7fffffff && (e == 0 || cand[e - 1] != c) && cell_start[c + 1] > cell_start[c]) {
-      hs[pos] = cell_start[c];
-      cnt[pos] = cell_start[c + 1] - cell_start[c];
-      ++pos;
-    }
-  }
+  each([&](int c) {
+    hs[pos] = cell_start[c];
+    cnt[pos] = cell_start[c + 1] - cell_start[c];
+    ++pos;
+  });
   __syncthreads();
   const int per2 = (ncells + kBlock - 1) / kBlock;
   const int k0 = threadIdx.x * per2;
   int sum = 0;
   for (int k = k0; k < k0 + per2 && k < ncells; ++k) sum += cnt[k];
-  int natoms = 0;
-  int run = block_scan(sum, scan, &natoms);
+  int natoms;
+  int run = block_scan<kBlock / 64>(sum, scan, natoms);
   for (int k = k0; k < k0 + per2 && k < ncells; ++k) {
     ho[k] = run;
     run += cnt[k];
@@ -351,13 +433,31 @@ __device__ void halo_tile(int64_t N, const CellGrid& g, const int32_t* __restric
   }
 }
 
+// The tiles' halo tables; the sorted state, which k_sort_permute left in the alternate
+// buffers, goes back to the primary ones on the way.
+template <bool MAP>
 __global__ void __launch_bounds__(kBlock)
-k_halo_tables(int64_t N, CellGrid g, const int32_t* __restrict__ cell_sorted,
-              const int32_t* __restrict__ cell_start, HaloTables ht, const int32_t* __restrict__ flags) {
+k_halo_tables(int64_t N, CellGrid g, const double* __restrict__ x2, const double* __restrict__ v2,
+              const int32_t* __restrict__ type2, const int32_t* __restrict__ perm2, double* __restrict__ x,
+              double* __restrict__ v, int32_t* __restrict__ type, int32_t* __restrict__ perm, uint4* __restrict__ pos,
+              const int32_t* __restrict__ cell_sorted, const int32_t* __restrict__ cell_start, HaloTables ht,
+              const int32_t* __restrict__ flags) {
   if (flags[FLAG_REBUILD] == 0) return;
   const int ntiles = (int)((N + kBlock - 1) / kBlock);
   for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    halo_tile(N, g, cell_sorted, cell_start, ht, tile);
+    const int64_t p = (int64_t)tile * kBlock + threadIdx.x;
+    if (p < N) {
+      double xn[3];
+      for (int c = 0; c < 3; ++c) {
+        xn[c] = x2[c * N + p];
+        x[c * N + p] = xn[c];
+        v[c * N + p] = v2[c * N + p];
+      }
+      pos_put(pos, p, xn[0], xn[1], xn[2], g.box);
+      type[p] = type2[p];
+      perm[p] = perm2[p];
+    }
+    halo_tile<MAP>(N, g, cell_sorted, cell_start, ht, tile);
     __syncthreads();  // the LDS tables are reused by the next tile
   }
 }
@@ -390,48 +490,6 @@ __device__ __forceinline__ int bin_of(double r2, const BinEdges& be) {
 constexpr int kEdgesOne = 2 * kFracs - 1;
 constexpr int kEdgesTwo = kMaxBins - 1;
 
-// Pair vector x_q - x_p in FP64 followed by the periodic shift of the stencil cell
-// (-L, 0 or +L: the value the minimum-image rule subtracts for every pair that can
-// lie within the cutoff when the dimension holds at least three cells), or by the
-// minimum-image rule itself when some dimension has fewer cells (MINIMG);
-// r^2 = (dx*dx + dy*dy) + dz*dz without FMA.
-template <bool MINIMG>
-__device__ __forceinline__ double cand_r2(const double* __restrict__ x, int64_t N, int64_t q, double xi, double yi,
-                                          double zi, double sx, double sy, double sz, const CellGrid& g) {
-#pragma clang fp contract(off)
-  double dx = x[q] - xi, dy = x[N + q] - yi, dz = x[2 * N + q] - zi;
-  if constexpr (MINIMG) {
-    dx = g.nc[0] < 3 ? min_image(dx, g.box[0]) : dx + sx;
-    dy = g.nc[1] < 3 ? min_image(dy, g.box[1]) : dy + sy;
-    dz = g.nc[2] < 3 ? min_image(dz, g.box[2]) : dz + sz;
-  } else {
-    dx = dx + sx;
-    dy = dy + sy;
-    dz = dz + sz;
-  }
-  const double sxx = dx * dx;
-  const double syy = dy * dy;
-  const double szz = dz * dz;
-  const double sxy = sxx + syy;
-  return sxy + szz;
-}
-
-// Candidates of one stencil cell, four at a time (their positions are loaded
-// together before any is tested).
-template <bool MINIMG, class Visit>
-__device__ __forceinline__ void scan_cell(const double* __restrict__ x, int64_t N, int q0, int q1, int64_t p,
-                                          double xi, double yi, double zi, double sx, double sy, double sz,
-                                          const CellGrid& g, double cut2, Visit&& visit) {
-  for (int q = q0; q < q1; q += 4) {
-    double r2[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) r2[u] = cand_r2<MINIMG>(x, N, q + u < q1 ? q + u : q1 - 1, xi, yi, zi, sx, sy, sz, g);
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (q + u < q1 && q + u != p && r2[u] < cut2) visit(q + u, r2[u]);
-  }
-}
-
 // kMaxBins 16-bit counters packed in 64-bit registers: a counter update is a shift
 // and a few selects and adds instead of a select chain over kMaxBins registers.
 struct BinCounts {
@@ -450,211 +508,58 @@ struct BinCounts {
   }
 };
 
-// Per-thread staging of one scratch column in LDS: entries are collected sixteen
-// at a time (stride 17 words, no bank conflicts) and written out as one 64-byte
-// segment at [k / 16][atom][16] (or 32 bytes of 16-bit values), so the global
-// stores are whole segments even though the threads flush at different times.
-constexpr int kStage = 16;
-constexpr int kStageStride = kStage + 1;
+constexpr int kStage = 16;  // entries of a scratch segment
 
-__device__ __forceinline__ void stage_flush32(const uint32_t* st, uint4* col, int64_t N, int64_t p, int k) {
-  uint4* dst = col + ((int64_t)(k / kStage) * N + p) * (kStage / 4);
-#pragma unroll
-  for (int j = 0; j < kStage / 4; ++j)
-    dst[j] = make_uint4(st[4 * j], st[4 * j + 1], st[4 * j + 2], st[4 * j + 3]);
-}
-__device__ __forceinline__ void stage_flush16(const uint32_t* st, uint4* col, int64_t N, int64_t p, int k) {
-  uint4* dst = col + ((int64_t)(k / kStage) * N + p) * (kStage / 8);
-#pragma unroll
-  for (int j = 0; j < kStage / 8; ++j)
-    dst[j] = make_uint4((st[8 * j] & 0xffffu) | (st[8 * j + 1] << 16), (st[8 * j + 2] & 0xffffu) | (st[8 * j + 3] << 16),
-                        (st[8 * j + 4] & 0xffffu) | (st[8 * j + 5] << 16), (st[8 * j + 6] & 0xffffu) | (st[8 * j + 7] << 16));
-}
-
-// One thread per atom, one pass over the 27-cell stencil. Every candidate inside the
-// list cutoff is appended, in stencil order, to the atom's scratch column as
-// q | bin << 28 together with its halo-local index. Stencil cells whose nearest point
-// lies beyond the list cutoff (with a 1e-6 A margin) are skipped. k_place_lists then
-// counts the entries per bin and orders them by bin.
-// With MARKED, only the atoms that k_build_cells left to it (cnt = -1) are built.
-template <bool MINIMG, int NE, bool MARKED>
-__device__ void build_list_atom(int64_t N, const CellGrid& g, const double* __restrict__ x,
-                                const int32_t* __restrict__ start, const int32_t* __restrict__ cell_sorted,
-                                const BinEdges& be, int capR, const ListOut& lo_, const HaloTables& ht,
-                                const ListScratch& sc, int32_t* __restrict__ flags, int64_t p) {
-  if (p >= N) return;
-  if (MARKED && lo_.cnt[p] != -1) return;
-  const int tile = (int)(p / kBlock);
-  const bool hok = ht.info[4 * tile + 2] != 0;
-  const int hcells = ht.info[4 * tile + 0];
-  lo_.selfl[p] = hok ? (uint16_t)halo_index(ht, tile, hcells, (int)p) : kNoLocal;
-  const double cut2 = be.e2[be.nbins - 1];
-  const double xi = x[p], yi = x[N + p], zi = x[2 * N + p];
-  int cx, cy, cz;
-  cell_coords(g, cell_sorted[p], cx, cy, cz);
-  const int cc3[3] = {cx, cy, cz};
-  const double pos3[3] = {xi, yi, zi};
-  int lo[3], nof[3];
-  double dlo[3], dhi[3];  // distance from the atom to the lower / upper face of its cell
-  for (int d = 0; d < 3; ++d) {
-    lo[d] = g.nc[d] >= 3 ? -1 : 0;
-    nof[d] = g.nc[d] >= 3 ? 3 : g.nc[d];
-    const double h = g.box[d] / g.nc[d];
-    dlo[d] = fmax(pos3[d] - cc3[d] * h - 1e-6, 0.0);
-    dhi[d] = fmax((cc3[d] + 1) * h - pos3[d] - 1e-6, 0.0);
-  }
-  int n = 0;
-  __shared__ uint32_t stage_q[kBlock * kStageStride], stage_l[kBlock * kStageStride];
-  uint32_t* sq = stage_q + threadIdx.x * kStageStride;
-  uint32_t* sl = stage_l + threadIdx.x * kStageStride;
-  for (int a = 0; a < nof[2]; ++a) {
-    const int rz = cz + lo[2] + a;
-    const int zc = (rz + g.nc[2]) % g.nc[2];
-    const double sz = rz < 0 ? -g.box[2] : (rz >= g.nc[2] ? g.box[2] : 0.0);
-    const double gz = nof[2] < 3 ? 0.0 : (a == 0 ? dlo[2] : (a == 2 ? dhi[2] : 0.0));
-    for (int b = 0; b < nof[1]; ++b) {
-      const int ry = cy + lo[1] + b;
-      const int yc = (ry + g.nc[1]) % g.nc[1];
-      const double sy = ry < 0 ? -g.box[1] : (ry >= g.nc[1] ? g.box[1] : 0.0);
-      const double gy = nof[1] < 3 ? 0.0 : (b == 0 ? dlo[1] : (b == 2 ? dhi[1] : 0.0));
-      for (int e = 0; e < nof[0]; ++e) {
-        const int rx = cx + lo[0] + e;
-        const int xc = (rx + g.nc[0]) % g.nc[0];
-        const double sx = rx < 0 ? -g.box[0] : (rx >= g.nc[0] ? g.box[0] : 0.0);
-        const double gx = nof[0] < 3 ? 0.0 : (e == 0 ? dlo[0] : (e == 2 ? dhi[0] : 0.0));
-        if (gx * gx + gy * gy + gz * gz >= cut2) continue;
-        const int cc = cell_lin(g, xc, yc, zc);
-        const int q0 = start[cc], q1 = start[cc + 1];
-        if (q1 <= q0) continue;
-        // halo-local index of sorted atom q is loc0 + q (cells are contiguous in the halo)
-        const int loc0 = hok ? halo_index(ht, tile, hcells, q0) - q0 : 0;
-        scan_cell<MINIMG>(x, N, q0, q1, p, xi, yi, zi, sx, sy, sz, g, cut2, [&](int q, double r2) {
-          if (n < capR) {
-            sq[n % kStage] = (uint32_t)q | ((uint32_t)bin_of<NE>(r2, be) << 28);
-            sl[n % kStage] = hok ? (uint32_t)(loc0 + q) : (uint32_t)kNoLocal;
-            if (n % kStage == kStage - 1) {
-              stage_flush32(sq, sc.q, N, p, n);
-              stage_flush16(sl, sc.l, N, p, n);
-            }
-          }
-          ++n;
-        });
-      }
-    }
-  }
-  if (n < capR && n % kStage != 0) {
-    stage_flush32(sq, sc.q, N, p, n);
-    stage_flush16(sl, sc.l, N, p, n);
-  }
-  lo_.cnt[p] = n < capR ? n : capR;
-  if (n > capR) atomicMax(&flags[FLAG_OVF_R], n);
-}
-
-template <bool MINIMG, int NE, bool MARKED = false>
-__global__ void __launch_bounds__(kBlock)
-k_build_lists(int64_t N, CellGrid g, const double* __restrict__ x, const int32_t* __restrict__ start,
-              const int32_t* __restrict__ cell_sorted, BinEdges be, int capR, int capA, ListOut lo_,
-              HaloTables ht, ListScratch sc, int32_t* __restrict__ flags) {
-  if (flags[FLAG_REBUILD] == 0) return;
-  const int nblocks = (int)((N + kBlock - 1) / kBlock);
-  for (int b = blockIdx.x; b < nblocks; b += gridDim.x)
-    build_list_atom<MINIMG, NE, MARKED>(N, g, x, start, cell_sorted, be, capR, lo_, ht, sc, flags,
-                                        (int64_t)xcd_tile(b, nblocks) * kBlock + threadIdx.x);
-}
-
-// One workgroup per cell (boxes with at least three cells along every dimension):
-// the positions of the 27 stencil cells' atoms are staged in LDS once, in stencil
-// order and by sorted index inside a cell, and each wavefront takes the cell's atoms
-// in turn, its 64 lanes testing two chunks of 64 candidates at a time (their staged
-// positions read together, for the latency). The accepted candidates are
+// The list entries of a cell's atoms: PARTS workgroups to a cell (one in large systems, more
+// where one per cell would leave the chip idle). The positions of the stencil cells' atoms
+// (27 cells; along a dimension of one or two cells, each cell once) are staged in LDS once,
+// in stencil order and by sorted index inside a cell, and each wavefront takes the
+// workgroup's atoms in turn, its 64 lanes testing two chunks of 64 candidates at a time
+// (their staged positions read together, for the latency). The accepted candidates are
 // compacted (ballot and prefix count) into a per-wavefront LDS queue in candidate
 // order; only those are binned and written, 64 entries per pass, to the atom's
-// scratch column. The scratch therefore holds the same entries in the same order as
-// the per-atom kernel writes, with the FP64 distance computed the same way. Cells
-// whose stencil holds more than kCellCand atoms mark their atoms (cnt = -1) for
-// k_build_lists<false, NE, true>.
+// scratch column as q | bin << 28 with its halo-local index. Stencils of more than kCellCand
+// atoms (compressed boxes and dense clusters) are not staged: their candidates are read from
+// global memory, in the same order. Candidate vectors are x_q - x_p in FP64 plus the
+// periodic shift of the stencil cell (-L, 0 or +L: what the minimum-image rule gives every
+// pair that can lie within the cutoff when the dimension holds at least three cells), or the
+// minimum-image rule itself in a dimension of fewer cells; r^2 = (dx*dx + dy*dy) + dz*dz
+// without FMA.
 constexpr int kCellCand = 1024;  // stencil atoms a workgroup stages in LDS
 constexpr int kCellQueue = 192;  // accepted candidates queued per wavefront (two chunks past a drain)
 
-template <int NE>
-__device__ void build_cell(int64_t N, const CellGrid& g, const double* __restrict__ x,
-                           const int32_t* __restrict__ start, const BinEdges& be, int capR, const ListOut& lo_,
-                           const HaloTables& ht, const ListScratch& sc, int32_t* __restrict__ flags, int c) {
+struct CellStage {
+  double X[kCellCand], Y[kCellCand], Z[kCellCand];
+  int32_t Q[kCellCand];
+  uint8_t C[kCellCand];
+  int cq0[27], cum[28];
+  double shift[3][27];
+  uint32_t qk[kBlock / 64][kCellQueue];
+  double qr[kBlock / 64][kCellQueue];
+  int loc0s[2][27];  // halo offset of each stencil cell for the cell's first two tiles
+};
+
+// Atoms s0 + first, s0 + first + step, ... of the cell [s0, s1), whose own stencil cell is
+// `home`; nc candidates.
+template <int NE, bool STAGED, bool MINIMG>
+__device__ void build_atoms(int64_t N, const CellGrid& g, const double* __restrict__ x, const BinEdges& be, int capR,
+                            const ListOut& lo_, const HaloTables& ht, const ListScratch& sc,
+                            int32_t* __restrict__ flags, CellStage& S, int s0, int s1, int first, int step, int ns,
+                            int home, int nc, bool shifted) {
 #pragma clang fp contract(off)
-  const int s0 = start[c], s1 = start[c + 1];
-  if (s1 <= s0) return;  // empty cell or brick slot outside the grid
-  int cx, cy, cz;
-  cell_coords(g, c, cx, cy, cz);
-  __shared__ double X[kCellCand], Y[kCellCand], Z[kCellCand];
-  __shared__ int32_t Q[kCellCand];
-  __shared__ uint8_t C[kCellCand];
-  __shared__ int cq0[27], cum[28];
-  __shared__ double shift[3][27];
-  __shared__ uint32_t qk[kBlock / 64][kCellQueue];
-  __shared__ double qr[kBlock / 64][kCellQueue];
-  __shared__ int loc0s[2][27];  // halo offset of each stencil cell for the cell's first two tiles
-  const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int tile0 = s0 / kBlock;
-  int cnt_s = 0;
-  if (t < 27) {  // stencil cell t = 9 a + 3 b + e: z offset a - 1, y offset b - 1, x offset e - 1
-    const int r3[3] = {cx + t % 3 - 1, cy + (t / 3) % 3 - 1, cz + t / 9 - 1};
-    int w3[3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      w3[d] = (r3[d] + g.nc[d]) % g.nc[d];
-      shift[d][t] = r3[d] < 0 ? -g.box[d] : (r3[d] >= g.nc[d] ? g.box[d] : 0.0);
-    }
-    const int cc = cell_lin(g, w3[0], w3[1], w3[2]);
-    cq0[t] = start[cc];
-    cnt_s = start[cc + 1] - start[cc];
-    cum[t] = cnt_s;
-  }
-  __syncthreads();
-  if (t == 0) {
-    int acc = 0;
-    for (int k = 0; k < 27; ++k) {
-      const int v = cum[k];
-      cum[k] = acc;
-      acc += v;
-    }
-    cum[27] = acc;
-  }
-  __syncthreads();
-  const int nc = cum[27];
-  if (nc > kCellCand) {
-    for (int p = s0 + t; p < s1; p += kBlock) lo_.cnt[p] = -1;
-    return;
-  }
-  // halo-local offsets for the tile of the cell's first atom and the next tile if it
-  // holds atoms of the cell (other tiles, for cells of more than 256 atoms, are
-  // looked up when reached); computed while the positions load
-  if (t >= 64 && t < 64 + 54) {
-    const int u = t - 64, tl = tile0 + u / 27, sc = u % 27;
-    int v = 0;
-    if (tl * kBlock < s1 && ht.info[4 * tl + 2] != 0 && cum[sc + 1] > cum[sc])
-      v = halo_index(ht, tl, ht.info[4 * tl + 0], cq0[sc]) - cq0[sc];
-    loc0s[u / 27][sc] = v;
-  }
-  for (int k = t; k < nc; k += kBlock) {
-    int sidx = 0;
-#pragma unroll
-    for (int m = 1; m < 27; ++m) sidx += k >= cum[m] ? 1 : 0;
-    const int q = cq0[sidx] + (k - cum[sidx]);
-    X[k] = x[q];
-    Y[k] = x[N + q];
-    Z[k] = x[2 * N + q];
-    Q[k] = q;
-    C[k] = (uint8_t)sidx;
-  }
-  __syncthreads();
-  // a cell away from the periodic boundary has no image shifts
-  const bool shifted = cx == 0 || cy == 0 || cz == 0 || cx == g.nc[0] - 1 || cy == g.nc[1] - 1 ||
-                       cz == g.nc[2] - 1;
   const double cut2 = be.e2[be.nbins - 1];
   uint32_t* scq = reinterpret_cast<uint32_t*>(sc.q);
   uint16_t* scl = reinterpret_cast<uint16_t*>(sc.l);
+  auto cell_slot = [&](int k) {  // stencil cell of candidate k
+    if constexpr (STAGED) return (int)S.C[k];
+    int c = 0;
+    for (int m = 1; m < ns; ++m) c += k >= S.cum[m] ? 1 : 0;
+    return c;
+  };
   int cached_tile = -1, hok = 0, hcells = 0, loc0 = 0;  // loc0: of stencil cell `lane`, for the atom's tile
-  for (int p = s0 + w; p < s1; p += kBlock / 64) {  // wave-uniform
+  for (int p = s0 + first; p < s1; p += step) {  // wave-uniform
     const int tile = p / kBlock;
     if (tile != cached_tile) {
       cached_tile = tile;
@@ -662,30 +567,38 @@ __device__ void build_cell(int64_t N, const CellGrid& g, const double* __restric
       hok = ht.info[4 * tile + 2] != 0;
       loc0 = 0;
       if (tile - tile0 < 2) {
-        if (lane < 27) loc0 = loc0s[tile - tile0][lane];
-      } else if (hok && lane < 27 && cum[lane + 1] > cum[lane]) {
-        loc0 = halo_index(ht, tile, hcells, cq0[lane]) - cq0[lane];
+        if (lane < ns) loc0 = S.loc0s[tile - tile0][lane];
+      } else if (hok && lane < ns && S.cum[lane + 1] > S.cum[lane]) {
+        loc0 = halo_index(ht, tile, hcells, S.cq0[lane]) - S.cq0[lane];
       }
     }
-    // the atom lies in its own cell, stencil cell 13
-    const int self_off = __shfl(loc0, 13);
+    const int self_off = __shfl(loc0, home);
     if (lane == 0) lo_.selfl[p] = hok ? (uint16_t)(self_off + p) : kNoLocal;
-    const int ks = cum[13] + (p - s0);  // the atom's own slot (stencil cell 13 is its cell)
-    const double xi = X[ks], yi = Y[ks], zi = Z[ks];
+    const int ks = S.cum[home] + (p - s0);  // the atom's own slot
+    double xi, yi, zi;
+    if constexpr (STAGED) {
+      xi = S.X[ks];
+      yi = S.Y[ks];
+      zi = S.Z[ks];
+    } else {
+      xi = x[p];
+      yi = x[N + p];
+      zi = x[2 * N + p];
+    }
     int nw = 0, nq = 0;  // entries written, entries queued (wave-uniform)
     auto drain = [&]() {
       wave_lds_sync();
       for (int j0 = 0; j0 < nq; j0 += 64) {
         const int j = j0 + lane;
         const bool v = j < nq;
-        const int k = v ? (int)qk[w][j] : 0;
-        const int sidx = C[k];
+        const int k = v ? (int)S.qk[w][j] : 0;
+        const int sidx = cell_slot(k);
         const int lc = __shfl(loc0, sidx);
         const int e = nw + j;
         if (v && e < capR) {
-          const int q = Q[k];
+          const int q = STAGED ? S.Q[k] : S.cq0[sidx] + (k - S.cum[sidx]);
           const int64_t o = ((int64_t)(e / kStage) * N + p) * kStage + e % kStage;
-          scq[o] = (uint32_t)q | ((uint32_t)bin_of<NE>(qr[w][j], be) << 28);
+          scq[o] = (uint32_t)q | ((uint32_t)bin_of<NE>(S.qr[w][j], be) << 28);
           scl[o] = hok ? (uint16_t)(lc + q) : kNoLocal;
         }
       }
@@ -693,14 +606,31 @@ __device__ void build_cell(int64_t N, const CellGrid& g, const double* __restric
       nq = 0;
       wave_lds_sync();
     };
-    // the FP64 squared distance to stencil slot k, the expression of the per-atom build
     auto dist2 = [&](int k) {
-      double dx = X[k] - xi, dy = Y[k] - yi, dz = Z[k] - zi;
-      if (shifted) {
-        const int sidx = C[k];
-        dx = dx + shift[0][sidx];
-        dy = dy + shift[1][sidx];
-        dz = dz + shift[2][sidx];
+      double dx, dy, dz;
+      int sidx = 0;
+      if constexpr (STAGED) {
+        dx = S.X[k] - xi;
+        dy = S.Y[k] - yi;
+        dz = S.Z[k] - zi;
+      } else {
+        sidx = cell_slot(k);
+        const int64_t q = S.cq0[sidx] + (k - S.cum[sidx]);
+        dx = x[q] - xi;
+        dy = x[N + q] - yi;
+        dz = x[2 * N + q] - zi;
+      }
+      if (MINIMG || shifted) {
+        if constexpr (STAGED) sidx = S.C[k];
+        if constexpr (MINIMG) {
+          dx = g.nc[0] < 3 ? min_image(dx, g.box[0]) : dx + S.shift[0][sidx];
+          dy = g.nc[1] < 3 ? min_image(dy, g.box[1]) : dy + S.shift[1][sidx];
+          dz = g.nc[2] < 3 ? min_image(dz, g.box[2]) : dz + S.shift[2][sidx];
+        } else {
+          dx = dx + S.shift[0][sidx];
+          dy = dy + S.shift[1][sidx];
+          dz = dz + S.shift[2][sidx];
+        }
       }
       const double sxx = dx * dx;
       const double syy = dy * dy;
@@ -713,8 +643,8 @@ __device__ void build_cell(int64_t N, const CellGrid& g, const double* __restric
       const uint64_t m = __ballot(acc);
       const int pre = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
       if (acc) {
-        qk[w][nq + pre] = (uint32_t)k;
-        qr[w][nq + pre] = r2;
+        S.qk[w][nq + pre] = (uint32_t)k;
+        S.qr[w][nq + pre] = r2;
       }
       nq += __popcll(m);
     };
@@ -743,15 +673,107 @@ __device__ void build_cell(int64_t N, const CellGrid& g, const double* __restric
   }
 }
 
-template <int NE>
+template <int NE, bool MINIMG>
+__device__ void build_cell(int64_t N, const CellGrid& g, const double* __restrict__ x,
+                           const int32_t* __restrict__ start, const BinEdges& be, int capR, const ListOut& lo_,
+                           const HaloTables& ht, const ListScratch& sc, int32_t* __restrict__ flags, int c, int part,
+                           int parts, CellStage& S) {
+  const int s0 = start[c], s1 = start[c + 1];
+  constexpr int W = kBlock / 64;
+  if (s0 + part * W >= s1) return;  // empty cell, brick slot outside the grid, or no atom left for this part
+  int cx, cy, cz;
+  cell_coords(g, c, cx, cy, cz);
+  const int t = threadIdx.x, w = t >> 6;
+  const int tile0 = s0 / kBlock;
+  // stencil cells t = (a n1 + b) n0 + e: along a dimension of at least three cells the
+  // offsets -1, 0, 1, otherwise every cell once, starting with the cell's own
+  const int n0 = !MINIMG || g.nc[0] >= 3 ? 3 : g.nc[0], n1 = !MINIMG || g.nc[1] >= 3 ? 3 : g.nc[1],
+            n2 = !MINIMG || g.nc[2] >= 3 ? 3 : g.nc[2];
+  const int o0 = n0 == 3 ? 1 : 0, o1 = n1 == 3 ? 1 : 0, o2 = n2 == 3 ? 1 : 0;
+  const int ns = n0 * n1 * n2;
+  const int home = (o2 * n1 + o1) * n0 + o0;
+  if (t < ns) {
+    const int r3[3] = {cx + t % n0 - o0, cy + (t / n0) % n1 - o1, cz + t / (n0 * n1) - o2};
+    int w3[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      w3[d] = (r3[d] + g.nc[d]) % g.nc[d];
+      S.shift[d][t] = r3[d] < 0 ? -g.box[d] : (r3[d] >= g.nc[d] ? g.box[d] : 0.0);
+    }
+    const int cc = cell_lin(g, w3[0], w3[1], w3[2]);
+    S.cq0[t] = start[cc];
+    S.cum[t] = start[cc + 1] - start[cc];
+  }
+  __syncthreads();
+  if (t == 0) {
+    int acc = 0;
+    for (int k = 0; k < ns; ++k) {
+      const int v = S.cum[k];
+      S.cum[k] = acc;
+      acc += v;
+    }
+    S.cum[ns] = acc;
+  }
+  __syncthreads();
+  const int nc = S.cum[ns];
+  // halo-local offsets for the tile of the cell's first atom and the next tile if it
+  // holds atoms of the cell (other tiles, for cells of more than 256 atoms, are
+  // looked up when reached); computed while the positions load
+  if (t >= 64 && t < 64 + 2 * ns) {
+    const int u = t - 64, tl = tile0 + u / ns, sc0 = u % ns;
+    int v = 0;
+    if (tl * kBlock < s1 && ht.info[4 * tl + 2] != 0 && S.cum[sc0 + 1] > S.cum[sc0])
+      v = halo_index(ht, tl, ht.info[4 * tl + 0], S.cq0[sc0]) - S.cq0[sc0];
+    S.loc0s[u / ns][sc0] = v;
+  }
+  const bool staged = nc <= kCellCand;
+  if (staged) {
+    for (int k = t; k < nc; k += kBlock) {
+      int sidx = 0;
+#pragma unroll
+      for (int m = 1; m < 27; ++m) sidx += m < ns && k >= S.cum[m] ? 1 : 0;
+      const int q = S.cq0[sidx] + (k - S.cum[sidx]);
+      S.X[k] = x[q];
+      S.Y[k] = x[N + q];
+      S.Z[k] = x[2 * N + q];
+      S.Q[k] = q;
+      S.C[k] = (uint8_t)sidx;
+    }
+  }
+  __syncthreads();
+  // a cell away from the periodic boundary has no image shifts
+  const bool shifted = cx == 0 || cy == 0 || cz == 0 || cx == g.nc[0] - 1 || cy == g.nc[1] - 1 ||
+                       cz == g.nc[2] - 1;
+  if (staged)
+    build_atoms<NE, true, MINIMG>(N, g, x, be, capR, lo_, ht, sc, flags, S, s0, s1, part * W + w, parts * W, ns, home,
+                                  nc, shifted);
+  else
+    build_atoms<NE, false, MINIMG>(N, g, x, be, capR, lo_, ht, sc, flags, S, s0, s1, part * W + w, parts * W, ns,
+                                   home, nc, shifted);
+}
+
+template <int NE, bool MINIMG>
 __global__ void __launch_bounds__(kBlock)
 k_build_cells(int64_t N, CellGrid g, const double* __restrict__ x, const int32_t* __restrict__ start,
-              BinEdges be, int capR, ListOut lo_, HaloTables ht, ListScratch sc, int32_t* __restrict__ flags) {
+              BinEdges be, int capR, ListOut lo_, HaloTables ht, ListScratch sc, int parts,
+              int32_t* __restrict__ flags) {
   if (flags[FLAG_REBUILD] == 0) return;
-  for (int cb = blockIdx.x; cb < g.ncell; cb += gridDim.x) {
-    build_cell<NE>(N, g, x, start, be, capR, lo_, ht, sc, flags, xcd_tile(cb, g.ncell));
+  __shared__ CellStage S;
+  const int n = g.ncell * parts;
+  for (int cb = blockIdx.x; cb < n; cb += gridDim.x) {
+    const int u = xcd_tile(cb, n);
+    build_cell<NE, MINIMG>(N, g, x, start, be, capR, lo_, ht, sc, flags, u / parts, u % parts, parts, S);
     __syncthreads();  // the LDS staging is reused by the next cell
   }
+}
+
+// Workgroups to a cell: as many as give the chip's 256 compute units eight workgroups each,
+// up to one atom per wavefront of a 32-atom cell. Every workgroup of a cell stages the whole
+// stencil, so more of them only pay while compute units are idle: 4,000 atoms (125 cells)
+// took 52 us with one and take 30 with eight.
+inline int build_parts(int ncell) {
+  const int p = 2048 / ncell;
+  return p < 1 ? 1 : (p > 8 ? 8 : p);
 }
 
 // One wavefront per 16 atoms, four lanes per atom: counts each atom's scratch
@@ -923,17 +945,6 @@ k_place_lists(int64_t N, int nbins, int binA, int capR, int capA, ListOut lo_, L
   }
 }
 
-// After a build the positions equal the build positions: displacement 0, bin 0.
-__global__ void k_count_build(int32_t* flags, int bin_r0, int bin_a0, int bin_r1, int bin_a1) {
-  if (flags[FLAG_REBUILD] != 0 && threadIdx.x == 0) {
-    flags[FLAG_NBUILD] += 1;
-    flags[FLAG_BIN_R] = bin_r0;
-    flags[FLAG_BIN_A] = bin_a0;
-    flags[FLAG_BIN_R1] = bin_r1;
-    flags[FLAG_BIN_A1] = bin_a1;
-  }
-}
-
 // Lists in original ids, one row per original atom in [o_lo, o_hi), ascending.
 __global__ void k_export(int64_t N, const int32_t* __restrict__ perm, const int32_t* __restrict__ nbr,
                          const int32_t* __restrict__ cnt, int cap, int64_t o_lo, int64_t o_hi,
@@ -963,71 +974,52 @@ hipError_t launch_zero_i32(int32_t* p, int64_t n, hipStream_t st) {
   hipLaunchKernelGGL(k_zero_i32, dim3(grid_blocks(n)), dim3(kBlock), 0, st, p, n);
   return hipGetLastError();
 }
-hipError_t launch_zero_f32(float* p, int64_t n, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_zero_f32, dim3(grid_blocks(n)), dim3(kBlock), 0, st, p, n);
-  return hipGetLastError();
-}
-hipError_t launch_zero_f64(double* p, int64_t n, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_zero_f64, dim3(grid_blocks(n)), dim3(kBlock), 0, st, p, n);
-  return hipGetLastError();
-}
 
-// Every kernel below returns at once when flags[FLAG_REBUILD] == 0, so the whole
-// rebuild can be enqueued each step and skipped on the device without a host sync.
-hipError_t launch_rebuild(int64_t N, const CellGrid& g, const BinEdges& be, int capR, int capA,
-                          double* x, double* v, int32_t* type, int32_t* perm, double* x_alt,
-                          double* v_alt, int32_t* type_alt, int32_t* perm_alt, double* x_build,
-                          int32_t* cellid, int32_t* cell_sorted, int32_t* src, int32_t* key,
-                          int32_t* cell_count, int32_t* cell_start, int32_t* cell_fill,
-                          int32_t* scan_tmp, uint4* pos, const ListOut& lout, HaloTables ht,
+// The rebuild decision (see RebuildRule) from nd2 partial displacement maxima, then the
+// rebuild: every kernel after the decision returns at once when flags[FLAG_REBUILD] == 0,
+// so the whole rebuild can be enqueued each step and skipped on the device without a host
+// sync.
+hipError_t launch_rebuild(const RebuildRule& rule, const double* d2, int nd2, int64_t N, const CellGrid& g, int capR,
+                          int capA, double* x, double* v, int32_t* type, int32_t* perm, double* x_alt, double* v_alt,
+                          int32_t* type_alt, int32_t* perm_alt, double* x_build, int32_t* cellid,
+                          int32_t* cell_sorted, int32_t* src, int32_t* key, int32_t* rank, int32_t* cell_count,
+                          int32_t* cell_start, int32_t* scan_tmp, uint4* pos, const ListOut& lout, HaloTables ht,
                           ListScratch sc, int32_t* flags, hipStream_t st) {
   const int nb = grid_blocks(N);
   const int ncell = g.ncell;
-  hipError_t e;
-  if ((e = launch_zero_i32(cell_count, ncell, st)) != hipSuccess) return e;
-  if ((e = launch_zero_i32(cell_fill, ncell, st)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_bin, dim3(rebuild_grid(nb)), dim3(kBlock), 0, st, N, g, x, cellid, cell_count, flags);
-  const int ntiles = (ncell + kScanTile - 1) / kScanTile;
-  hipLaunchKernelGGL(k_scan_tiles, dim3(ntiles), dim3(kBlock), 0, st, cell_count, cell_start, ncell,
-                     scan_tmp, flags);
-  hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(kBlock), 0, st, scan_tmp, ntiles, cell_start + ncell,
-                     flags);
-  hipLaunchKernelGGL(k_scan_add, dim3(grid_blocks(ncell)), dim3(kBlock), 0, st, cell_start, ncell,
-                     scan_tmp, flags);
-  hipLaunchKernelGGL(k_scatter, dim3(rebuild_grid(nb)), dim3(kBlock), 0, st, N, cellid, cell_start, cell_fill, perm,
-                     src, key, flags);
-  hipLaunchKernelGGL(k_cell_sort, dim3(rebuild_grid(grid_blocks(ncell, kSortWaves))), dim3(kBlock), 0, st, ncell,
-                     cell_start, key, src, flags);
-  hipLaunchKernelGGL(k_permute, dim3(rebuild_grid(nb)), dim3(kBlock), 0, st, N, src, cellid, x, v, type, perm,
-                     x_alt, v_alt, type_alt, perm_alt, x_build, cell_sorted, flags);
-  hipLaunchKernelGGL(k_copy_back, dim3(rebuild_grid(nb)), dim3(kBlock), 0, st, N, x_alt, v_alt, type_alt, perm_alt,
-                     x, v, type, perm, pos, g, flags);
-  hipLaunchKernelGGL(k_halo_tables, dim3(rebuild_grid(nb)), dim3(kBlock), 0, st, N, g, cell_sorted, cell_start, ht, flags);
+  const BinEdges& be = rule.be;
+  if (N <= kSortAtoms && ncell <= kSortCells) {
+    hipLaunchKernelGGL(k_select_sort, dim3(1), dim3(kSelBlock), 0, st, rule, d2, nd2, N, g, x, perm,
+                       cell_start, src, key, flags);
+  } else {
+    hipLaunchKernelGGL(k_select, dim3(1), dim3(kSelBlock), 0, st, rule, d2, nd2, flags);
+    hipLaunchKernelGGL(k_bin, dim3(rebuild_grid(nb)), dim3(kBlock), 0, st, N, g, x, cellid, rank, cell_count, flags);
+    const int ntiles = (ncell + kScanTile - 1) / kScanTile;
+    hipLaunchKernelGGL(k_scan_tiles, dim3(ntiles), dim3(kBlock), 0, st, cell_count, cell_start, ncell, scan_tmp,
+                       flags);
+    hipLaunchKernelGGL(k_scan_add, dim3(ntiles), dim3(kScanTile), 0, st, cell_start, ncell, N, scan_tmp, flags);
+    hipLaunchKernelGGL(k_scatter, dim3(rebuild_grid(nb)), dim3(kBlock), 0, st, N, cellid, rank, cell_start, perm, src,
+                       key, flags);
+  }
+  hipLaunchKernelGGL(k_sort_permute, dim3(rebuild_grid(grid_blocks(ncell, kSortWaves))), dim3(kBlock), 0, st, N,
+                     ncell, cell_start, cell_count, key, src, x, v, type, x_alt, v_alt, type_alt, perm_alt, x_build,
+                     cell_sorted, flags);
+  auto halo = ncell <= kMapCells ? k_halo_tables<true> : k_halo_tables<false>;
+  hipLaunchKernelGGL(halo, dim3(rebuild_grid(nb)), dim3(kBlock), 0, st, N, g, x_alt, v_alt, type_alt, perm_alt, x, v,
+                     type, perm, pos, cell_sorted, cell_start, ht, flags);
   // the minimum-image rule inside the candidate loop only for boxes with fewer than
   // three cells along some dimension
   const bool small = g.nc[0] < 3 || g.nc[1] < 3 || g.nc[2] < 3;
   const bool one = be.nbins - 1 <= kEdgesOne;
-  if (small) {
-    auto kern = one ? k_build_lists<true, kEdgesOne> : k_build_lists<true, kEdgesTwo>;
-    hipLaunchKernelGGL(kern, dim3(rebuild_grid(nb)), dim3(kBlock), 0, st, N, g, x, cell_start, cell_sorted, be, capR, capA,
-                       lout, ht, sc, flags);
-  } else {
-    auto cells = one ? k_build_cells<kEdgesOne> : k_build_cells<kEdgesTwo>;
-    hipLaunchKernelGGL(cells, dim3(rebuild_grid(ncell)), dim3(kBlock), 0, st, N, g, x, cell_start, be, capR, lout, ht, sc,
-                       flags);
-    // atoms of cells whose stencil did not fit in LDS
-    auto rest = one ? k_build_lists<false, kEdgesOne, true> : k_build_lists<false, kEdgesTwo, true>;
-    hipLaunchKernelGGL(rest, dim3(rebuild_grid(nb)), dim3(kBlock), 0, st, N, g, x, cell_start, cell_sorted, be, capR, capA,
-                       lout, ht, sc, flags);
-  }
+  const int parts = build_parts(ncell);
+  auto cells = small ? (one ? k_build_cells<kEdgesOne, true> : k_build_cells<kEdgesTwo, true>)
+                     : (one ? k_build_cells<kEdgesOne, false> : k_build_cells<kEdgesTwo, false>);
+  hipLaunchKernelGGL(cells, dim3(rebuild_grid((int64_t)ncell * parts)), dim3(kBlock), 0, st, N, g, x, cell_start, be,
+                     capR, lout, ht, sc, parts, flags);
   const int place_groups = grid_blocks(N, kPlaceAtoms);
   hipLaunchKernelGGL(k_place_lists, dim3(place_groups < kPlaceGrid ? place_groups : kPlaceGrid), dim3(64), 0, st,
                      N, be.nbins,
                      be.idxA[0][kFracs - 1], capR, capA, lout, sc, flags);
-  hipLaunchKernelGGL(k_count_build, dim3(1), dim3(64), 0, st, flags, be.idxR[0][0], be.idxA[0][0], be.idxR[1][0],
-                     be.idxA[1][0]);
   return hipGetLastError();
 }
 
