@@ -342,6 +342,7 @@ EvalBuffers eval_buffers(nep_system* s, int slot) {
   b.U = s->U;
   b.pos = s->pos;
   b.rec = s->rec;
+  b.rec1 = s->lsc.q;  // at least 64 bytes per atom
   b.G = s->G;
   b.F = s->F[slot];
   b.ew = s->gpart;  // the gradient partials' buffer, free during an evaluation (256 doubles per tile are enough)

@@ -109,27 +109,30 @@ struct HaloTables {
 
 // Neighbour positions and records, laid out so that every writer stores whole cache
 // lines and every gather touches as few 16-byte words as possible:
-// pos [N] (16 bytes per atom) = (qx, qy, qz, 0): the position as three 32-bit fractions
+// pos [N] (16 bytes per atom) = (qx, qy, qz, species): the position as three 32-bit fractions
 //   of the box, q = round(x 2^32 / L) modulo 2^32, so that the two's-complement
 //   difference of two atoms' fractions is their minimum-image separation in units of
 //   L / 2^32 (the quantum: 1.7e-7 A in a 723 A box). Written by the integrator (and the
 //   state upload and list build), gathered by the descriptor pass.
 // rec [N][4] (64 bytes per atom), written whole by the descriptor kernel for its own atom
 //   and gathered by the force pass: word 0 = (qx, qy, qz, v), the position again and one
-//   radial force coefficient; words 1, 2 = eight more radial force coefficients; word 3
-//   is zero.
+//   radial force coefficient; words 1, 2 = eight more radial force coefficients; word 3 =
+//   (species, 0, 0, 0). With two species there are two planes of records, rec for the
+//   neighbours of species 0 and rec1 for those of species 1: an atom of species t gathers
+//   plane t, so that an entry still costs one 64-byte line (rec1 lies in the list build's
+//   scratch, free between builds).
 // The FP64 positions stay in the [3][N] position array (integration, list build, ZBL).
-// The coefficients are written by the descriptor kernel: for one species
-// v = w_0 + sum_k w_k and w_1..w_8 (w_k = sum_n (dU/dq_n) c_nk), with several species
-// dU/dq_0..dU/dq_4 in v, w_1..w_4.
+// The coefficients are written by the descriptor kernel: v = w_0 + sum_k w_k and w_1..w_8,
+// w_k = sum_n (dU/dq_n) c_nk with the coefficients c of (the atom's species, the plane's).
 __host__ __device__ inline double box_quantum(double L) { return L * (1.0 / 4294967296.0); }
 __device__ __forceinline__ uint32_t box_fraction(double x, double L) {
   const double f = rint(x * (4294967296.0 / L));  // in [0, 2^32] for x in [0, L)
   return (uint32_t)(uint64_t)f;                   // 2^32, the image of 0, wraps to 0
 }
 // Atom i's entry of the position array.
-__device__ __forceinline__ void pos_put(uint4* pos, int64_t i, double x, double y, double z, const double* box) {
-  pos[i] = make_uint4(box_fraction(x, box[0]), box_fraction(y, box[1]), box_fraction(z, box[2]), 0u);
+__device__ __forceinline__ void pos_put(uint4* pos, int64_t i, double x, double y, double z, int type,
+                                        const double* box) {
+  pos[i] = make_uint4(box_fraction(x, box[0]), box_fraction(y, box[1]), box_fraction(z, box[2]), (uint32_t)type);
 }
 
 // Outputs of the list build.
@@ -255,6 +258,7 @@ struct EvalBuffers {
   float* U;              // [N]
   uint4* pos;            // [N] box-fraction positions (read)
   uint4* rec;            // [N][4] neighbour records (written by the descriptor kernel)
+  uint4* rec1;           // [N][4] the records' second plane (two species)
   float* G;              // [nA * ncomp][N] dU/ds for the angular accumulators
   float* F;              // [3][N] forces (FP32 accumulation)
   double* ew;            // [eval_rows(N)][kPartialStride] energy and virial partials

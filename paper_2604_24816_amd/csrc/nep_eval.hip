@@ -284,18 +284,18 @@ using EvalZbl = ZblSeen<0>;
 
 // Radial descriptors q[0..NR) and angular accumulators s[NA][NC] of center i over the
 // pairs inside the true cutoffs, all channels in one pass over the list with skin
-// (geometry computed once per pair and reused for every n). One species: the radial
-// descriptors are linear in the basis sums, q_n = sum_k c_nk sum_j f_k(r_ij), with
-// sum_j f_k = (sum_j f_c T_k + sum_j f_c) / 2, so a pair adds f_c and f_c T_k (k >= 1).
-// Returns the pair counts and the pairs inside the ZBL radius (zs).
+// (geometry computed once per pair and reused for every n). The radial descriptors are
+// linear in the basis sums over the neighbours of each species t, q_n = sum_t sum_k c^t_nk
+// sum_j f_k(r_ij), with sum_j f_k = (sum_j f_c T_k + sum_j f_c) / 2, so a pair adds f_c and
+// f_c T_k (k >= 1). Returns the pair counts and the pairs inside the ZBL radius (zs).
 // With L > 1 this lane (l of the L that share the center) visits entries l, l + L, ... and
 // the sums over the lanes are formed at the end, in every lane.
 template <class S, bool MULTI, int L>
-__device__ __forceinline__ void desc_pass(const ModelDev& m, const EvalBuffers& b, int64_t i, int l, int ti, QPos qi,
-                                          float* q, float* s, EvalZbl& zs, int& nr, int& na) {
-  constexpr int NR = S::NR, NA = S::NA, NC = S::NC, KR = S::KR, KA = S::KA;
+__device__ __forceinline__ void desc_pass(const ModelDev& m, const EvalBuffers& b, const PairTab<S, MULTI>& tab,
+                                          int64_t i, int l, int ti, QPos qi, float* q, float* s, EvalZbl& zs, int& nr,
+                                          int& na) {
+  constexpr int NR = S::NR, NA = S::NA, NC = S::NC, KR = S::KR, KA = S::KA, TT = MULTI ? kMaxTypes : 1;
   const int64_t N = b.N;
-  const float rcR_inv = 1.f / m.rcR, rcA_inv = 1.f / m.rcA;
   const CutConst cutR = cut_const(m.rcR), cutA = cut_const(m.rcA);
   const float rcR2 = (float)(m.rcR64 * m.rcR64), rcA2 = (float)(m.rcA64 * m.rcA64), zbl2 = (float)m.zbl_o2;
   const bool zbl_on = m.zbl_o2 > 0.0;
@@ -303,33 +303,13 @@ __device__ __forceinline__ void desc_pass(const ModelDev& m, const EvalBuffers& 
   nr = 0;
   na = 0;
   const int kR = radial_bound(b, i), kA = angular_bound(b, i);
-  float Qf = 0.f, QT[KR];  // sum_j f_c and sum_j f_c T_k (one species)
+  float Qf[TT], QT[TT][KR];  // sum_j f_c and sum_j f_c T_k
 #pragma unroll
-  for (int k = 0; k < KR; ++k) QT[k] = 0.f;
-  // the radial term of a pair inside rc_radial
-  auto radial_term = [&](int p, int32_t j, float r2, float r) {
-    ++nr;
-    zs.n += (zbl_on && r2 < zbl2) ? 1 : 0;
-    if constexpr (MULTI) {
-      float g[NR];
-      radial_g<NR, KR>(r, rcR_inv, m.cR + (ti * m.T + b.type[j]) * NR * KR, g);
+  for (int t = 0; t < TT; ++t) {
+    Qf[t] = 0.f;
 #pragma unroll
-      for (int n = 0; n < NR; ++n) q[n] += g[n];
-    } else {
-      // T_k by the recurrence T_{k+1} = 2x T_k - T_{k-1}
-      const RadialGeo ra = radial_geo<false>(r, cutR);
-      Qf += ra.fc;
-      const float x2 = ra.x + ra.x;
-      float Tm = 1.f, T = ra.x;
-#pragma unroll
-      for (int k = 1; k < KR; ++k) {
-        QT[k] = fmaf(ra.fc, T, QT[k]);
-        const float Tn = fmaf(x2, T, -Tm);
-        Tm = T;
-        T = Tn;
-      }
-    }
-  };
+    for (int k = 0; k < KR; ++k) QT[t][k] = 0.f;
+  }
   // one entry: the radial term, and for the angular candidates inside rc_angular the angular one
   auto pair_both = [&](int p, int32_t j, const uint4* w) {
     float dx, dy, dz;
@@ -337,14 +317,38 @@ __device__ __forceinline__ void desc_pass(const ModelDev& m, const EvalBuffers& 
     if (!(r2 < rcR2)) return;
     float r, rinv;
     r_of_r2(r2, r, rinv);
-    radial_term(p, j, r2, r);
+    const int tj = MULTI ? (int)w[0].w : 0;
+    ++nr;
+    zs.n += (zbl_on && r2 < zbl2) ? 1 : 0;
+    {
+      // T_k by the recurrence T_{k+1} = 2x T_k - T_{k-1}
+      const RadialGeo ra = radial_geo<false>(r, cutR);
+      float ft[TT];  // f_c for the neighbour's species, 0 for the others
+#pragma unroll
+      for (int t = 0; t < TT; ++t) {
+        ft[t] = !MULTI || tj == t ? ra.fc : 0.f;
+        Qf[t] += ft[t];
+      }
+      const float x2 = ra.x + ra.x;
+      float Tm = 1.f, T = ra.x;
+#pragma unroll
+      for (int k = 1; k < KR; ++k) {
+#pragma unroll
+        for (int t = 0; t < TT; ++t) QT[t][k] = fmaf(ft[t], T, QT[t][k]);
+        const float Tn = fmaf(x2, T, -Tm);
+        Tm = T;
+        T = Tn;
+      }
+    }
     if (p < kA && r2 < rcA2) {
       ++na;
       float g[NA];
+      const RadialGeo ra = radial_geo<false>(r, cutA);
       if constexpr (MULTI) {
-        radial_g<NA, KA>(r, rcA_inv, m.cA + (ti * m.T + b.type[j]) * NA * KA, g);
+        radial_cd_tab<S, false>(ra.x, ang_tab(tab, ti, tj), g, nullptr);
+#pragma unroll
+        for (int n = 0; n < NA; ++n) g[n] *= ra.fc;
       } else {
-        const RadialGeo ra = radial_geo<false>(r, cutA);
         radial_g_fast<NA, KA>(ra.fc, ra.x, uniform_coeffs(m.hA), g);
       }
       for_each_poly<NC>(dx * rinv, dy * rinv, dz * rinv, [&](int lm, float P) {
@@ -356,38 +360,38 @@ __device__ __forceinline__ void desc_pass(const ModelDev& m, const EvalBuffers& 
   // the angular candidates are the list's prefix [0, kA)
   if constexpr (L > 1)
     for_each_rec_lanes<1, 1, L>(b.nbr, b.pos, N, i, l, kR, pair_both);
-  else if constexpr (MULTI)
-    for_each_rec_span<1, S::DESC_AHEAD, 1>(b.nbr, b.pos, N, i, 0, kR, pair_both);
   else
     for_each_rec_fast<1, S::DESC_AHEAD, 1>(b.nbr, b.pos, N, i, 0, kR, pair_both);
   if constexpr (L > 1) {
     nr = lanes_sum<L>(nr);
     na = lanes_sum<L>(na);
     zs.n = lanes_sum<L>(zs.n);
-    if constexpr (MULTI) {
 #pragma unroll
-      for (int n = 0; n < NR; ++n) q[n] = lanes_sum<L>(q[n]);
-    } else {
-      Qf = lanes_sum<L>(Qf);
+    for (int t = 0; t < TT; ++t) {
+      Qf[t] = lanes_sum<L>(Qf[t]);
 #pragma unroll
-      for (int k = 1; k < KR; ++k) QT[k] = lanes_sum<L>(QT[k]);
+      for (int k = 1; k < KR; ++k) QT[t][k] = lanes_sum<L>(QT[t][k]);
     }
 #pragma unroll
     for (int k = 0; k < NA * NC; ++k) s[k] = lanes_sum<L>(s[k]);
   }
-  if constexpr (!MULTI) {
-    const cfloat_ptr c = uniform_coeffs(m.cR);
+#pragma unroll
+  for (int t = 0; t < TT; ++t) {
     float Qb[KR];
-    Qb[0] = Qf;
+    Qb[0] = Qf[t];
 #pragma unroll
-    for (int k = 1; k < KR; ++k) Qb[k] = 0.5f * (QT[k] + Qf);
+    for (int k = 1; k < KR; ++k) Qb[k] = 0.5f * (QT[t][k] + Qf[t]);
+    auto add = [&](auto c) {
 #pragma unroll
-    for (int n = 0; n < NR; ++n) {
-      float a = 0.f;
+      for (int n = 0; n < NR; ++n) {
+        float a = 0.f;
 #pragma unroll
-      for (int k = 0; k < KR; ++k) a = fmaf(c[n * KR + k], Qb[k], a);
-      q[n] += a;
-    }
+        for (int k = 0; k < KR; ++k) a = fmaf(c[n * KR + k], Qb[k], a);
+        q[n] += a;
+      }
+    };
+    if constexpr (MULTI) add(tab.rad + (ti * kMaxTypes + t) * (NR * KR));
+    else add(uniform_coeffs(m.cR));
   }
 }
 
@@ -416,7 +420,7 @@ __device__ __forceinline__ void load_g_row(const float* row, float* g) {
 template <class S, int PREC, bool MULTI, int L>
 __device__ __forceinline__ void finish_lanes(const ModelDev& m, const EvalBuffers& b, int64_t i, int l, bool valid,
                                              int ti, const float* q, const float* s, const EvalZbl& zs, float* lds,
-                                             const NetLds<PREC>& net) {
+                                             const NetLds<PREC>& net, const PairTab<S, MULTI>& tab) {
   constexpr int NR = S::NR, NA = S::NA, NC = S::NC, D = S::D, L3 = S::L3;
   constexpr int RT = 64 / L >= 16 ? 64 / L / 16 : 1;
   constexpr int ROUNDS = (NA + L - 1) / L;  // angular channels of a lane
@@ -465,39 +469,37 @@ __device__ __forceinline__ void finish_lanes(const ModelDev& m, const EvalBuffer
   net_product<PREC, RT, false>(lds, net);
   if (!valid) return;
   auto fp = [&](int v) { return row[v] * net.sigma[v]; };  // dU/dq_v
-  // the 64-byte record: position (0..2), radial coefficients t_0..t_8 (3..11), zeros
-  {
+  // the 64-byte records: position (words 0..2), radial coefficients (3..11), species, zeros
+#pragma unroll
+  for (int t = 0; t < (MULTI ? kMaxTypes : 1); ++t) {
     static_assert(S::KR == 9 && NR <= 5, "the record holds nine radial coefficients");
     constexpr int TR = (9 + L - 1) / L;
-    float t[TR], sum = 0.f;
+    float w[TR], sum = 0.f;
 #pragma unroll
     for (int r = 0; r < TR; ++r) {
       const int k = l + r * L;
-      t[r] = 0.f;
+      w[r] = 0.f;
       if (k < 9) {
-        if constexpr (MULTI) {
-          t[r] = k < NR ? fp(k) : 0.f;
-        } else {
 #pragma unroll
-          for (int n = 0; n < NR; ++n) t[r] = fmaf(fp(n), m.cR[n * S::KR + k], t[r]);
+        for (int n = 0; n < NR; ++n) {
+          const float c = MULTI ? tab.rad[(ti * kMaxTypes + t) * (NR * S::KR) + n * S::KR + k] : m.cR[n * S::KR + k];
+          w[r] = fmaf(fp(n), c, w[r]);
         }
       }
-      sum += t[r];
+      sum += w[r];
     }
-    if constexpr (!MULTI) {
-      sum = lanes_sum<L>(sum);
-      if (l == 0) t[0] += sum;
-    }
-    float* rec = reinterpret_cast<float*>(b.rec + 4 * i);
+    sum = lanes_sum<L>(sum);
+    if (l == 0) w[0] += sum;
+    float* rec = reinterpret_cast<float*>((t == 0 ? b.rec : b.rec1) + 4 * i);
 #pragma unroll
     for (int r = 0; r < TR; ++r)
-      if (l + r * L < 9) rec[3 + l + r * L] = t[r];
+      if (l + r * L < 9) rec[3 + l + r * L] = w[r];
     const uint32_t* own = reinterpret_cast<const uint32_t*>(b.pos + i);
     uint32_t* recu = reinterpret_cast<uint32_t*>(rec);
 #pragma unroll
-    for (int k0 = 0; k0 < 7; k0 += L) {  // words 0..2 and 12..15
+    for (int k0 = 0; k0 < 7; k0 += L) {  // words 0..2, 12 (species) and 13..15
       const int k = k0 + l;
-      if (k < 3) recu[k] = own[k];
+      if (k < 4) recu[k < 3 ? k : 12] = own[k];
       else if (k < 7) recu[9 + k] = 0u;
     }
   }
@@ -547,6 +549,11 @@ __global__ void __launch_bounds__(kBlock, 2) k_desc_net(ModelDev m, EvalBuffers 
   const int64_t i = (int64_t)tile * (kBlock / L) + threadIdx.x / L;
   const int l = threadIdx.x % L;
   const bool valid = i < N;
+  __shared__ PairTab<S, MULTI> tab;
+  if constexpr (MULTI) {
+    stage_pairs<S>(m, tab);
+    __syncthreads();
+  }
   if constexpr (L > 1) {
     __shared__ NetLds<PREC> net;
     stage_network<S>(m, net);
@@ -560,14 +567,14 @@ __global__ void __launch_bounds__(kBlock, 2) k_desc_net(ModelDev m, EvalBuffers 
     if (valid) {
       const uint4 w0 = b.pos[i];
       int nr = 0, na = 0;
-      desc_pass<S, MULTI, L>(m, b, i, l, ti, QPos{w0.x, w0.y, w0.z}, q, s, zs, nr, na);
+      desc_pass<S, MULTI, L>(m, b, tab, i, l, ti, QPos{w0.x, w0.y, w0.z}, q, s, zs, nr, na);
       if (l == 0) {
         b.nactR[i] = nr;
         b.nactA[i] = na;
       }
     }
     __syncthreads();  // the staged weights
-    finish_lanes<S, PREC, MULTI, L>(m, b, i, l, valid, ti, q, s, zs, lds[threadIdx.x >> 6], net);
+    finish_lanes<S, PREC, MULTI, L>(m, b, i, l, valid, ti, q, s, zs, lds[threadIdx.x >> 6], net, tab);
     return;
   }
 
@@ -583,7 +590,7 @@ __global__ void __launch_bounds__(kBlock, 2) k_desc_net(ModelDev m, EvalBuffers 
   if (valid) {
     const uint4 w0 = b.pos[i];
     int nr = 0, na = 0;
-    desc_pass<S, MULTI, 1>(m, b, i, 0, ti, QPos{w0.x, w0.y, w0.z}, q, s, zs, nr, na);
+    desc_pass<S, MULTI, 1>(m, b, tab, i, 0, ti, QPos{w0.x, w0.y, w0.z}, q, s, zs, nr, na);
     b.nactR[i] = nr;
     b.nactA[i] = na;
     desc_finish<S>(s, q);
@@ -597,35 +604,32 @@ __global__ void __launch_bounds__(kBlock, 2) k_desc_net(ModelDev m, EvalBuffers 
   for (int v = 0; v < D; ++v) fp[v] *= m.sigma[v];  // dU/dq = sigma * dU/dq~
 
   if (valid) {
-    {
-      // neighbour record words 0.w, 1, 2: for one species v = w_0 + sum_k w_k and w_1..w_8 with
-      // w_k = sum_n (dU/dq_n) c_nk (the radial force of a pair is then a Chebyshev series in
-      // w_i + w_j), dU/dq_0..dU/dq_4 for several species
-      static_assert(S::KR == 9 && S::NR <= 5, "the record holds nine radial coefficients");
-      float t[9];
-      if constexpr (MULTI) {
+    // the whole 64-byte record of each plane: position, v = w_0 + sum_k w_k and w_1..w_8 with
+    // w_k = sum_n (dU/dq_n) c_nk (the radial force of a pair is then a Chebyshev series in
+    // w_i + w_j), species
+    const uint4 own = b.pos[i];
 #pragma unroll
-        for (int k = 0; k < 9; ++k) t[k] = k < NR ? fp[k] : 0.f;
-      } else {
-        const cfloat_ptr c = uniform_coeffs(m.cR);
-        float sum = 0.f;
+    for (int t = 0; t < (MULTI ? kMaxTypes : 1); ++t) {
+      static_assert(S::KR == 9, "the record holds nine radial coefficients");
+      float w[9], sum = 0.f;
+      auto form = [&](auto c) {
 #pragma unroll
         for (int k = 0; k < 9; ++k) {
           float a = 0.f;
 #pragma unroll
           for (int n = 0; n < NR; ++n) a = fmaf(fp[n], c[n * S::KR + k], a);
-          t[k] = a;
+          w[k] = a;
           sum += a;
         }
-        t[0] += sum;
-      }
-      // the whole 64-byte record: position, the nine coefficients, a zero word
-      const uint4 own = b.pos[i];
-      uint4* r = b.rec + 4 * i;
-      r[0] = make_uint4(own.x, own.y, own.z, __float_as_uint(t[0]));
-      reinterpret_cast<float4*>(r + 1)[0] = make_float4(t[1], t[2], t[3], t[4]);
-      reinterpret_cast<float4*>(r + 2)[0] = make_float4(t[5], t[6], t[7], t[8]);
-      r[3] = make_uint4(0u, 0u, 0u, 0u);
+      };
+      if constexpr (MULTI) form(tab.rad + (ti * kMaxTypes + t) * (NR * S::KR));
+      else form(uniform_coeffs(m.cR));
+      w[0] += sum;
+      uint4* r = (t == 0 ? b.rec : b.rec1) + 4 * i;
+      r[0] = make_uint4(own.x, own.y, own.z, __float_as_uint(w[0]));
+      reinterpret_cast<float4*>(r + 1)[0] = make_float4(w[1], w[2], w[3], w[4]);
+      reinterpret_cast<float4*>(r + 2)[0] = make_float4(w[5], w[6], w[7], w[8]);
+      r[3] = make_uint4(own.w, 0u, 0u, 0u);
     }
     // 4. dU/ds_nlm = dU/dq_nl * 2 W_lm s_nlm (+ four-body part for l = 2)
     float Gd[NA * NC];
@@ -727,14 +731,12 @@ constexpr int force_waves() { return S::L3 <= 2 ? 3 : 2; }
 
 // Constants of the angular pair force (uniform over a launch).
 struct AngConst {
-  float rcA_inv;
   CutConst cutA;
   float kDA;  // f_c' = kDA c (angular cutoff)
   float kYA;  // x' = kYA y
 };
 __device__ __forceinline__ AngConst ang_const(const ModelDev& m) {
   AngConst a;
-  a.rcA_inv = 1.f / m.rcA;
   a.cutA = cut_const(m.rcA);
   a.kDA = -0.5f * kPiF * a.cutA.rc_inv;
   a.kYA = 4.f * a.cutA.rc_inv;
@@ -747,60 +749,40 @@ __device__ __forceinline__ AngConst ang_const(const ModelDev& m) {
 // F_ck = sum_lm [ A_lm P_lm u + B_lm (grad P_lm - l P_lm u) / r ] with A_lm = sum_n G_nlm g'_n
 // and B_lm = sum_n G_nlm g_n; the l P B terms are summed per l and scaled once.
 template <class S, bool MULTI, class GF>
-__device__ __forceinline__ void angular_pair_force(const ModelDev& m, const AngConst& ac, GF&& Gc, int tc, int tk,
-                                                   float ux, float uy, float uz, float r, float rinv, float& n0,
-                                                   float& n1, float& n2) {
+__device__ __forceinline__ void angular_pair_force(const ModelDev& m, const AngConst& ac, const PairTab<S, MULTI>& tab,
+                                                   GF&& Gc, int tc, int tk, float ux, float uy, float uz, float r,
+                                                   float rinv, float& n0, float& n1, float& n2) {
   constexpr int NA = S::NA, NC = S::NC, KA = S::KA;
-  float sc, vx = 0.f, vy = 0.f, vz = 0.f, vscale;
-  if constexpr (MULTI) {
-    float g[NA], dg[NA];
-    radial_g_dg<NA, KA>(r, ac.rcA_inv, m.cA + (tc * m.T + tk) * NA * KA, g, dg);
-    float sA = 0.f;
-    float sB[4] = {0.f, 0.f, 0.f, 0.f};
-    for_each_poly_grad<NC>(ux, uy, uz, [&](int lm, float P, auto px, auto py, auto pz) {
-      float A = Gc(lm) * dg[0], B = Gc(lm) * g[0];
-#pragma unroll
-      for (int n = 1; n < NA; ++n) {
-        A = fmaf(Gc(n * NC + lm), dg[n], A);
-        B = fmaf(Gc(n * NC + lm), g[n], B);
-      }
-      sA = fmaf(P, A, sA);
-      sB[comp_l(lm) - 1] = fmaf(P, B, sB[comp_l(lm) - 1]);
-      vx = fmac(B, px, vx);
-      vy = fmac(B, py, vy);
-      vz = fmac(B, pz, vz);
-    });
-    const float lPB = fmaf(4.f, sB[3], fmaf(3.f, sB[2], fmaf(2.f, sB[1], sB[0])));
-    sc = fmaf(-rinv, lPB, sA);
-    vscale = rinv;
-  } else {
-    // With g_n = f_c C_n and g'_n = f_c' C_n + f_c x' D_n: B_lm = f_c E_lm and
-    // A_lm = f_c' E_lm + f_c x' H_lm for E_lm = sum_n G_nlm C_n, H_lm = sum_n G_nlm D_n,
-    // so f_c, f_c' and f_c x' are applied once to the sums over lm.
-    const RadialGeo rb = radial_geo<true>(r, ac.cutA);
-    float Cn[NA], Dn[NA];
+  float vx = 0.f, vy = 0.f, vz = 0.f;
+  // With g_n = f_c C_n and g'_n = f_c' C_n + f_c x' D_n: B_lm = f_c E_lm and
+  // A_lm = f_c' E_lm + f_c x' H_lm for E_lm = sum_n G_nlm C_n, H_lm = sum_n G_nlm D_n,
+  // so f_c, f_c' and f_c x' are applied once to the sums over lm.
+  const RadialGeo rb = radial_geo<true>(r, ac.cutA);
+  float Cn[NA], Dn[NA];
+  if constexpr (MULTI)
+    radial_cd_tab<S, true>(rb.x, ang_tab(tab, tc, tk), Cn, Dn);
+  else
     radial_cd_fast<NA, KA>(rb.x, uniform_coeffs(m.hA), Cn, Dn);
-    float sH = 0.f;
-    float sE[4] = {0.f, 0.f, 0.f, 0.f};
-    for_each_poly_grad<NC>(ux, uy, uz, [&](int lm, float P, auto px, auto py, auto pz) {
-      float E = Gc(lm) * Cn[0], H = Gc(lm) * Dn[0];
+  float sH = 0.f;
+  float sE[4] = {0.f, 0.f, 0.f, 0.f};
+  for_each_poly_grad<NC>(ux, uy, uz, [&](int lm, float P, auto px, auto py, auto pz) {
+    float E = Gc(lm) * Cn[0], H = Gc(lm) * Dn[0];
 #pragma unroll
-      for (int n = 1; n < NA; ++n) {
-        E = fmaf(Gc(n * NC + lm), Cn[n], E);
-        H = fmaf(Gc(n * NC + lm), Dn[n], H);
-      }
-      sH = fmaf(P, H, sH);
-      sE[comp_l(lm) - 1] = fmaf(P, E, sE[comp_l(lm) - 1]);
-      vx = fmac(E, px, vx);
-      vy = fmac(E, py, vy);
-      vz = fmac(E, pz, vz);
-    });
-    const float sPE = (sE[0] + sE[1]) + (sE[2] + sE[3]);
-    const float lPE = fmaf(4.f, sE[3], fmaf(3.f, sE[2], fmaf(2.f, sE[1], sE[0])));
-    const float sA = fmaf(ac.kDA * rb.c, sPE, (rb.fc * (ac.kYA * rb.y)) * sH);
-    vscale = rb.fc * rinv;
-    sc = fmaf(-vscale, lPE, sA);
-  }
+    for (int n = 1; n < NA; ++n) {
+      E = fmaf(Gc(n * NC + lm), Cn[n], E);
+      H = fmaf(Gc(n * NC + lm), Dn[n], H);
+    }
+    sH = fmaf(P, H, sH);
+    sE[comp_l(lm) - 1] = fmaf(P, E, sE[comp_l(lm) - 1]);
+    vx = fmac(E, px, vx);
+    vy = fmac(E, py, vy);
+    vz = fmac(E, pz, vz);
+  });
+  const float sPE = (sE[0] + sE[1]) + (sE[2] + sE[3]);
+  const float lPE = fmaf(4.f, sE[3], fmaf(3.f, sE[2], fmaf(2.f, sE[1], sE[0])));
+  const float sA = fmaf(ac.kDA * rb.c, sPE, (rb.fc * (ac.kYA * rb.y)) * sH);
+  const float vscale = rb.fc * rinv;
+  const float sc = fmaf(-vscale, lPE, sA);
   // n = -dU_c/dr_ck (sign folded into the operands)
   n0 = fmaf(-ux, sc, -(vx * vscale));
   n1 = fmaf(-uy, sc, -(vy * vscale));
@@ -818,7 +800,13 @@ template <class S, bool MULTI, bool DET, int L>
 __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, EvalBuffers b) {
   __shared__ double red[4 * 10];
   __shared__ HaloLds halo;
-  constexpr int NR = S::NR, NA = S::NA, NC = S::NC;
+  __shared__ PairTab<S, MULTI> tab;
+  // two species, full shape: the thread's own coefficients towards each species in LDS, 18
+  // registers that its pair loop does not have (864,000 atoms: 1,429 us with them spilled,
+  // 1,327 in LDS); the l <= 2 shapes have them, and their third workgroup needs the LDS
+  constexpr bool OWN = MULTI && S::L3 > 2;
+  __shared__ float own[OWN ? kMaxTypes : 1][OWN ? S::KR : 1][OWN ? kBlock : 1];
+  constexpr int NA = S::NA, NC = S::NC;
   const int64_t N = b.N;
   const int sub = xcd_tile(blockIdx.x, gridDim.x);  // L workgroups to a 256-atom tile
   const int64_t i = (int64_t)sub * (kBlock / L) + threadIdx.x / L;
@@ -830,11 +818,14 @@ __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, 
     kR = radial_bound(b, i);
     kA = angular_bound(b, i);
   }
+  if constexpr (MULTI) {
+    stage_pairs<S>(m, tab);
+    if (DET) __syncthreads();  // load_halo has barriers of its own
+  }
   if constexpr (!DET) lds = load_halo(b, sub / L, halo);
   const double hx = box_quantum(b.box[0]), hy = box_quantum(b.box[1]), hz = box_quantum(b.box[2]);
-  const float rcR_inv = 1.f / m.rcR;
   const CutConst cutR = cut_const(m.rcR);
-  const float kXR = -0.25f * kPiF * cutR.rc_inv;  // X = kXR Z for the radial series (one species)
+  const float kXR = -0.25f * kPiF * cutR.rc_inv;  // X = kXR Z for the radial series
   const AngConst ac = ang_const(m);
   const bool zbl_on = m.zbl_o2 > 0.0;
   float fx = 0.f, fy = 0.f, fz = 0.f;
@@ -845,12 +836,25 @@ __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, 
     const uint4* ri = b.rec + 4 * i;
     const uint4 r0 = ri[0], r1 = ri[1], r2w = ri[2];
     const QPos qi{r0.x, r0.y, r0.z};
-    const int ti = MULTI ? b.type[i] : 0;
-    // own radial coefficients (v = w_0 + sum_k w_k and w_1..w_8 for one species, dU/dq_n for
-    // several)
+    const int ti = MULTI ? (int)ri[3].x : 0;
+    const uint4* plane = MULTI && ti ? b.rec1 : b.rec;  // the neighbours' coefficients towards this species
+    // own radial coefficients (v = w_0 + sum_k w_k and w_1..w_8) towards each species
     const float wi[9] = {__uint_as_float(r0.w),  __uint_as_float(r1.x),  __uint_as_float(r1.y),
                          __uint_as_float(r1.z),  __uint_as_float(r1.w),  __uint_as_float(r2w.x),
                          __uint_as_float(r2w.y), __uint_as_float(r2w.z), __uint_as_float(r2w.w)};
+    float wi1[9];
+    if constexpr (MULTI) {
+      const float* rf = reinterpret_cast<const float*>(b.rec1 + 4 * i) + 3;
+#pragma unroll
+      for (int k = 0; k < 9; ++k) {
+        if constexpr (OWN) {
+          own[0][k][threadIdx.x] = wi[k];
+          own[1][k][threadIdx.x] = rf[k];
+        } else {
+          wi1[k] = rf[k];
+        }
+      }
+    }
     constexpr int KR = S::KR;
     float G[NA * NC];
     if constexpr (DET) {
@@ -875,30 +879,20 @@ __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, 
       const int lj = (!DET && ang && lds) ? (int)b.nbrl[(int64_t)p * N + i] : 0;
       float r, rinv;
       r_of_r2(r2, r, rinv);
-      const int tj = MULTI ? b.type[j] : 0;
+      const int tj = MULTI ? (int)rw[3].x : 0;
       const float wj[9] = {__uint_as_float(rw[0].w), __uint_as_float(rw[1].x), __uint_as_float(rw[1].y),
                            __uint_as_float(rw[1].z), __uint_as_float(rw[1].w), __uint_as_float(rw[2].x),
                            __uint_as_float(rw[2].y), __uint_as_float(rw[2].z), __uint_as_float(rw[2].w)};
-      float sr;  // (dU_i/dr_ij + dU_j/dr_ji) / r: the pair force is sr (x_j - x_i)
-      if constexpr (MULTI) {
-        float g[NR], dg[NR], g2[NR], dg2[NR];
-        radial_g_dg<NR, KR>(r, rcR_inv, m.cR + (ti * m.T + tj) * NR * KR, g, dg);
-        radial_g_dg<NR, KR>(r, rcR_inv, m.cR + (tj * m.T + ti) * NR * KR, g2, dg2);
-        float si = 0.f, sj = 0.f;
+      // (dU_i/dr_ij + dU_j/dr_ji) / r, the radial parts: sum_k (w_ik + w_jk) f_k'(r) / r; the
+      // pair force is sr (x_j - x_i)
+      const RadialGeo ra = radial_geo<true>(r, cutR);
+      float W[KR];
 #pragma unroll
-        for (int n = 0; n < NR; ++n) {
-          si = fmaf(wi[n], dg[n], si);
-          sj = fmaf(wj[n], dg2[n], sj);
-        }
-        sr = (si + sj) * rinv;
-      } else {
-        // one species: sum_k (w_ik + w_jk) f_k'(r)
-        const RadialGeo ra = radial_geo<true>(r, cutR);
-        float W[KR];
-#pragma unroll
-        for (int k = 1; k < KR; ++k) W[k] = wi[k] + wj[k];
-        sr = radial_series_z<KR>(ra, W, wi[0] + wj[0]) * (kXR * rinv);
+      for (int k = 0; k < KR; ++k) {
+        if constexpr (OWN) W[k] = own[tj][k][threadIdx.x] + wj[k];
+        else W[k] = (MULTI && tj ? wi1[k] : wi[k]) + wj[k];
       }
+      const float sr = radial_series_z<KR>(ra, W, W[0]) * (kXR * rinv);
       zs.n += (zbl_on && r2 < zbl2) ? 1 : 0;
       fx = fmaf(sr, dx, fx);
       fy = fmaf(sr, dy, fy);
@@ -917,7 +911,7 @@ __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, 
       if (!ang) return;
       const float ux = dx * rinv, uy = dy * rinv, uz = dz * rinv;
       float n0, n1, n2;  // -dU_i/dr_ij, the force on the neighbour
-      angular_pair_force<S, MULTI>(m, ac, [&](int q) { return G[q]; }, ti, tj, ux, uy, uz, r, rinv, n0, n1, n2);
+      angular_pair_force<S, MULTI>(m, ac, tab, [&](int q) { return G[q]; }, ti, tj, ux, uy, uz, r, rinv, n0, n1, n2);
       fx -= n0;
       fy -= n1;
       fz -= n2;
@@ -939,12 +933,11 @@ __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, 
 #pragma unroll
         for (int c = 0; c < 3; ++c) w[a * 3 + c] = fmaf(d[a], nf[c], w[a * 3 + c]);
     };
+    constexpr int W = MULTI ? 4 : 3;  // words of a record: with several species also the species
     if constexpr (L > 1)
-      for_each_rec_lanes<3, 4, L>(b.nbr, b.rec, N, i, l, kR, pair_both);
-    else if constexpr (MULTI)
-      for_each_rec_span<3, 1, 4>(b.nbr, b.rec, N, i, 0, kR, pair_both);
+      for_each_rec_lanes<W, 4, L>(b.nbr, plane, N, i, l, kR, pair_both);
     else
-      for_each_rec_fast<3, 1, 4>(b.nbr, b.rec, N, i, 0, kR, pair_both);
+      for_each_rec_fast<W, 1, 4>(b.nbr, plane, N, i, 0, kR, pair_both);
     if constexpr (L > 1) zs.n = lanes_sum<L>(zs.n);
     if (zs.n) {
       float f[3] = {fx, fy, fz};
@@ -959,15 +952,16 @@ __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, 
       for (int p = l; p < kA; p += L) {
         const int32_t j = b.nbr[(uint64_t)(uint32_t)p * n64 + i];
         float dx, dy, dz;
-        const float r2 = pair_vec_q(b.pos[j], qi, hx, hy, hz, dx, dy, dz);
+        const uint4 pj = b.pos[j];
+        const float r2 = pair_vec_q(pj, qi, hx, hy, hz, dx, dy, dz);
         if (!(r2 < rcR2 && r2 < rcA2)) continue;
         float r, rinv;
         r_of_r2(r2, r, rinv);
-        const int tj = MULTI ? b.type[j] : 0;
+        const int tj = MULTI ? (int)pj.w : 0;
         float Gj[NA * NC];
         load_g_row<S>(b.G + (int64_t)j * g_row<S>(), Gj);
         float n0, n1, n2;  // -dU_j/dr_ji, the force of center j's angular term on this atom
-        angular_pair_force<S, MULTI>(m, ac, [&](int q) { return Gj[q]; }, tj, ti, -(dx * rinv), -(dy * rinv),
+        angular_pair_force<S, MULTI>(m, ac, tab, [&](int q) { return Gj[q]; }, tj, ti, -(dx * rinv), -(dy * rinv),
                                      -(dz * rinv), r, rinv, n0, n1, n2);
         fx += n0;
         fy += n1;

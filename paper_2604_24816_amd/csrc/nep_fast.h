@@ -1,8 +1,8 @@
 // Pair arithmetic of the evaluation kernels (k_desc_net, k_force), written for the
 // fewest VALU instructions per pair: the cutoff function from short Taylor series on
 // the one interval it needs, the Chebyshev basis through the recurrences of both kinds
-// with model-derived coefficient tables, the single-species radial force by Clenshaw's
-// recurrence, and a neighbour loop whose prefetch buffers rotate without copies.
+// with model-derived coefficient tables, the radial force by Clenshaw's recurrence, and
+// a neighbour loop whose prefetch buffers rotate without copies.
 // The training kernels keep the direct forms of nep_kernels.h.
 #pragma once
 
@@ -128,7 +128,74 @@ __device__ __forceinline__ void radial_cd_fast(float x, CP h, float* C, float* D
   }
 }
 
-// Radial pair force of one species. The r-derivative of sum_k W_k f_k(r), for
+// ---------------------------------------------------------------- two species
+// With two species the coefficients depend on the pair's species, which differ from lane to
+// lane, so a pair's table is read from LDS (at most four distinct addresses per load, on
+// different banks) instead of held in scalar registers: ang, the angular derived tables of
+// each (center, neighbour) species pair, term by term ([k] (h_0k .. h_4k, d_0k .. d_4k, 0, 0),
+// three wide loads per term of both sums); rad, the radial coefficients c_nk. Gathering the
+// tables from global memory made the two-species kernels 2.2 (k_force) and 2.6 (k_desc_net)
+// times slower than the one-species ones.
+template <class S, bool MULTI>
+struct PairTab {
+  static constexpr int kTerm = 12;
+  static constexpr int kAng = S::KA * kTerm, kRad = S::NR * S::KR;
+  static constexpr int kPairs = MULTI ? kMaxTypes * kMaxTypes : 0;
+  static_assert(2 * S::NA <= kTerm, "a term of both sums fits its slot");
+  alignas(16) float ang[kPairs * kAng + 4];
+  float rad[kPairs * kRad + 4];
+};
+// Filled by the whole workgroup; a barrier must follow.
+template <class S>
+__device__ __forceinline__ void stage_pairs(const ModelDev& m, PairTab<S, true>& t) {
+  using P = PairTab<S, true>;
+  constexpr int NA = S::NA, KA = S::KA;
+  for (int e = threadIdx.x; e < m.T * m.T * KA * 2 * NA; e += kBlock) {
+    const int pr = e / (KA * 2 * NA), k = e / (2 * NA) % KA, c = e % (2 * NA), n = c % NA;
+    const float* h = m.hA + (int64_t)pr * derived_block<NA, KA>();
+    float v = 0.f;
+    if (c < NA) v = h[n * KA + k];
+    else if (k > 0) v = h[NA * KA + n * (KA - 1) + k - 1];
+    t.ang[(pr / m.T * kMaxTypes + pr % m.T) * P::kAng + k * P::kTerm + c] = v;
+  }
+  for (int e = threadIdx.x; e < m.T * m.T * P::kRad; e += kBlock) {
+    const int pr = e / P::kRad;
+    t.rad[(pr / m.T * kMaxTypes + pr % m.T) * P::kRad + e % P::kRad] = m.cR[e];
+  }
+}
+template <class S>
+__device__ __forceinline__ const float* ang_tab(const PairTab<S, true>& t, int tc, int tk) {
+  return t.ang + (tc * kMaxTypes + tk) * PairTab<S, true>::kAng;
+}
+
+// The channel sums C_n (and with DERIV D_n) from a species pair's table.
+template <class S, bool DERIV>
+__device__ __forceinline__ void radial_cd_tab(float x, const float* tab, float* C, float* D) {
+  constexpr int NA = S::NA, KA = S::KA, kTerm = PairTab<S, true>::kTerm;
+  const float x2 = x + x;
+  float Tm = 0.f, T = 1.f;  // T_{k-1}, T_k
+  float Um = 0.f, U = 0.f;  // U_{k-2}, U_{k-1}
+#pragma unroll
+  for (int k = 0; k < KA; ++k) {
+#pragma unroll
+    for (int n = 0; n < NA; ++n) C[n] = k == 0 ? tab[n] : fmaf(tab[k * kTerm + n], T, C[n]);
+    if (DERIV && k > 0) {
+#pragma unroll
+      for (int n = 0; n < NA; ++n) {
+        const float d = tab[k * kTerm + NA + n];
+        D[n] = k == 1 ? d : fmaf(d, U, D[n]);
+      }
+    }
+    const float Tn = k == 0 ? x : fmaf(x2, T, -Tm);
+    Tm = T;
+    T = Tn;
+    const float Un = k == 0 ? 1.f : (k == 1 ? x2 : fmaf(x2, U, -Um));
+    Um = U;
+    U = Un;
+  }
+}
+
+// Radial pair force. The r-derivative of sum_k W_k f_k(r), for
 // f_k = f_c (T_k(x) + 1) / 2, is X = (f_c' (C + sum_k W_k) + f_c x' C'(x)) / 2 with the
 // Chebyshev series C(x) = sum_k W_k T_k(x); with f_c' and x' from the pair geometry,
 //   X = -(pi / (4 r_c)) Z,   Z = c (C + sum_k W_k) + f_c y S C'(x),   S = -8 / pi.
@@ -201,7 +268,7 @@ __device__ __forceinline__ void r_of_r2(float r2, float& r, float& rinv) {
 }
 
 // ---------------------------------------------------------------- neighbour loops
-// Both visit entries [k0, k1) of atom i's slot-major list, calling body(p, j, w) with the
+// Visits entries [k0, k1) of atom i's slot-major list, calling body(p, j, w) with the
 // first W 16-byte words of neighbour j's entry in rec (RS words per atom: the position
 // array with RS = 1, the 64-byte records with RS = 4). The records of entries p + 1 .. p + AHEAD
 // and the index of entry p + AHEAD + 1 are in flight while the body of entry p runs, so
@@ -211,48 +278,8 @@ __device__ __forceinline__ void r_of_r2(float r2, float& r, float& rinv) {
 // which hold indices of atoms of the system, so every address stays inside the list and
 // the records; the index loads walk down the column by a pointer step of one row.
 //
-// for_each_rec_span moves the queue along by register copies; for_each_rec_fast is
-// unrolled AHEAD + 1 times so that each record is loaded straight into the buffer the
-// body later reads (a rotation by index, not by copies), at the cost of a few more live
-// registers.
-template <int W, int AHEAD, int RS, class Body>
-__device__ __forceinline__ void for_each_rec_span(const int32_t* __restrict__ nbr, const uint4* __restrict__ rec,
-                                                  int64_t N, int64_t i, int k0, int k1, Body&& body) {
-  static_assert(AHEAD >= 1 && AHEAD + 1 <= kListPad, "prefetch depth within the list's padding");
-  if (k1 <= k0) return;
-  const uint64_t n64 = (uint64_t)N;
-  const int32_t* __restrict__ col = nbr + i + (uint64_t)(uint32_t)k0 * n64;  // entry k0
-  auto record = [&](int32_t j, int w) { return rec[(uint64_t)(uint32_t)j * RS + w]; };
-  int32_t jq[AHEAD + 1];  // indices of entries p .. p + AHEAD
-#pragma unroll
-  for (int a = 0; a <= AHEAD; ++a) {
-    jq[a] = *col;
-    col += n64;
-  }
-  uint4 rq[AHEAD][W];  // records of entries p .. p + AHEAD - 1
-#pragma unroll
-  for (int a = 0; a < AHEAD; ++a)
-#pragma unroll
-    for (int w = 0; w < W; ++w) rq[a][w] = record(jq[a], w);
-  for (int p = k0; p < k1; ++p) {
-    const int32_t jn = *col;  // entry p + AHEAD + 1
-    col += n64;
-    uint4 rn[W];
-#pragma unroll
-    for (int w = 0; w < W; ++w) rn[w] = record(jq[AHEAD], w);
-    body(p, jq[0], rq[0]);
-#pragma unroll
-    for (int a = 0; a < AHEAD; ++a) jq[a] = jq[a + 1];
-    jq[AHEAD] = jn;
-#pragma unroll
-    for (int a = 0; a + 1 < AHEAD; ++a)
-#pragma unroll
-      for (int w = 0; w < W; ++w) rq[a][w] = rq[a + 1][w];
-#pragma unroll
-    for (int w = 0; w < W; ++w) rq[AHEAD - 1][w] = rn[w];
-  }
-}
-
+// The loop is unrolled AHEAD + 1 times so that each record is loaded straight into the
+// buffer the body later reads (a rotation by index, not by copies).
 template <int W, int AHEAD, int RS, class Body>
 __device__ __forceinline__ void for_each_rec_fast(const int32_t* __restrict__ nbr, const uint4* __restrict__ rec,
                                                   int64_t N, int64_t i, int k0, int k1, Body&& body) {

@@ -50,7 +50,8 @@ __global__ void k_kick_drift(int64_t N, double dt, CellGrid g, const float* __re
   __shared__ double sh[kBlock / 64];
   double d2max = 0.0;
   for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < N; p += (int64_t)gridDim.x * blockDim.x) {
-    const double inv = mt.inv_mxi[type[p]];
+    const int32_t tp = type[p];
+    const double inv = mt.inv_mxi[tp];
     double xn[3];
     double d2 = 0.0;
     for (int c = 0; c < 3; ++c) {
@@ -62,7 +63,7 @@ __global__ void k_kick_drift(int64_t N, double dt, CellGrid g, const float* __re
       const double d = min_image(xx - xb[c * N + p], g.box[c]);
       d2 += d * d;
     }
-    pos_put(pos, p, xn[0], xn[1], xn[2], g.box);
+    pos_put(pos, p, xn[0], xn[1], xn[2], tp, g.box);
     if (!(d2 == d2)) d2 = 1e300;
     d2max = fmax(d2max, d2);
   }
@@ -222,10 +223,11 @@ __global__ void k_state_in(int64_t N, const double* __restrict__ xa, const doubl
     if (!isfinite(vv)) flags[FLAG_NONFINITE] = 1;
     v[c * N + p] = vv;
   }
-  pos_put(pos, p, xn[0], xn[1], xn[2], g.box);
   const int t = tin[p];
-  if (t < 0 || t >= n_types) flags[FLAG_TYPE] = 1;
-  type[p] = (t < 0 || t >= n_types) ? 0 : t;
+  const bool bad = t < 0 || t >= n_types;
+  if (bad) flags[FLAG_TYPE] = 1;
+  pos_put(pos, p, xn[0], xn[1], xn[2], bad ? 0 : t, g.box);
+  type[p] = bad ? 0 : t;
   perm[p] = (int32_t)p;
 }
 

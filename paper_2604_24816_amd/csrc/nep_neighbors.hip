@@ -453,8 +453,9 @@ k_halo_tables(int64_t N, CellGrid g, const double* __restrict__ x2, const double
         x[c * N + p] = xn[c];
         v[c * N + p] = v2[c * N + p];
       }
-      pos_put(pos, p, xn[0], xn[1], xn[2], g.box);
-      type[p] = type2[p];
+      const int32_t tp = type2[p];
+      pos_put(pos, p, xn[0], xn[1], xn[2], tp, g.box);
+      type[p] = tp;
       perm[p] = perm2[p];
     }
     halo_tile<MAP>(N, g, cell_sorted, cell_start, ht, tile);
