@@ -135,7 +135,7 @@ struct nep_system {
   ListScratch lsc;
   float *F[2], *U, *G;
   uint4 *pos, *rec;
-  float *gF, *vjp, *qs;
+  float* gF;
   double *partial, *gpart, *res, *staging;
   int32_t* flags;
   float* mparams[2];
@@ -157,7 +157,7 @@ struct nep_system {
 
 namespace {
 
-constexpr int kGradMax = 32 * 32 + 2 * 32 + 1;  // equals train_grad_stride()
+constexpr int kGradMax = 1408;                  // equals train_grad_stride()
 constexpr int kDerivedMax = 10;                 // channels and basis functions the derived tables hold
 
 // Lays out every buffer; with base == nullptr it only measures.
@@ -169,17 +169,16 @@ int64_t layout(nep_system* s, char* base, int64_t N, int capR, int capA, int max
   S.x = c.take<double>(3 * N);
   S.v = c.take<double>(3 * N);
   S.x_alt = c.take<double>(3 * N);
-  S.rank = reinterpret_cast<int32_t*>(S.x_alt);  // read before a build writes x_alt
+  // cell and rank of each atom, read before a build writes x_alt
+  S.rank = reinterpret_cast<int32_t*>(S.x_alt);
+  S.cellid = S.rank + N;
   S.v_alt = c.take<double>(3 * N);
   S.x_build = c.take<double>(3 * N);
   S.type = c.take<int32_t>(N);
   S.type_alt = c.take<int32_t>(N);
   S.perm = c.take<int32_t>(N);
   S.perm_alt = c.take<int32_t>(N);
-  S.cellid = c.take<int32_t>(N);
   S.cell_sorted = c.take<int32_t>(N);
-  S.src = c.take<int32_t>(N);
-  S.key = c.take<int32_t>(N);
   S.cell_count = c.take<int32_t>(max_ncell);
   S.cell_start = c.take<int32_t>(max_ncell + 1);
   S.scan_tmp = c.take<int32_t>(max_ncell / 1024 + 2);
@@ -210,6 +209,9 @@ int64_t layout(nep_system* s, char* base, int64_t N, int capR, int capA, int max
   S.gpart = c.take<double>((int64_t)nb * kGradMax);
   S.res = c.take<double>(kResults);
   S.staging = c.take<double>(3 * N);
+  // sort keys and sources of a build, outside any call's use of the staging buffer
+  S.src = reinterpret_cast<int32_t*>(S.staging);
+  S.key = S.src + N;
   S.flags = c.take<int32_t>(FLAG_COUNT);
   S.nhc = c.take<double>(kNhcDoubles);
   // derived radial tables: at most kMaxTypes^2 species pairs of kDerivedMax channels and basis functions
@@ -221,8 +223,6 @@ int64_t layout(nep_system* s, char* base, int64_t N, int capR, int capA, int max
     S.mbf[k] = c.take<uint16_t>(HD[k] > 0 ? HD[k] : 1);
     S.mparams64[k] = c.take<double>(np[k] > 0 ? np[k] : 1);
   }
-  S.vjp = nullptr;
-  S.qs = nullptr;
   S.nblocks = nb;
   return (c.off + 255) & ~int64_t(255);
 }
@@ -1153,13 +1153,9 @@ int nep_train_backward(nep_system* s, int32_t slot, const float* theta, double g
   t.e = eval_buffers(s, slot);
   t.theta = theta;
   t.gE = gE;
-  t.gF = nullptr;
-  if (gF) {
-    HIPCHK(launch_gather_vec_f32(s->N, s->perm, gF, s->gF, s->st));
-    t.gF = s->gF;
-  }
-  t.vjp = nullptr;
-  t.qs = nullptr;
+  t.perm = s->perm;
+  t.gF = gF;
+  t.w = s->gF;
   t.gpart = s->gpart;
   t.grad = grad;
   t.accumulate = accumulate ? 1 : 0;
@@ -1193,13 +1189,9 @@ int nep_train_backward_params(nep_system* s, int32_t slot, const float* params, 
   t.e = eval_buffers(s, slot);
   t.theta = params;
   t.gE = gE;
-  t.gF = nullptr;
-  if (gF) {
-    HIPCHK(launch_gather_vec_f32(s->N, s->perm, gF, s->gF, s->st));
-    t.gF = s->gF;
-  }
-  t.vjp = nullptr;
-  t.qs = nullptr;
+  t.perm = s->perm;
+  t.gF = gF;
+  t.w = s->gF;
   t.gpart = s->gpart;
   t.grad = grad;
   t.accumulate = accumulate ? 1 : 0;

@@ -344,8 +344,6 @@ hipError_t launch_forces_out(int64_t N, const int32_t* perm, const float* F, dou
                              hipStream_t st);
 hipError_t launch_scalar_out(int64_t N, const int32_t* perm, const float* U, double* out,
                              hipStream_t st);
-hipError_t launch_gather_vec_f32(int64_t N, const int32_t* perm, const float* aos_orig,
-                                 float* soa_sorted, hipStream_t st);
 hipError_t launch_scatter_vec_f32(int64_t N, const int32_t* perm, const float* soa_sorted,
                                   float* aos_orig, hipStream_t st);
 
@@ -353,11 +351,11 @@ hipError_t launch_scatter_vec_f32(int64_t N, const int32_t* perm, const float* s
 struct TrainBuffers {
   EvalBuffers e;
   const float* theta;    // network parameters, packed W0, b0, w1, b1
-  const float* gF;       // [3][N] sorted order, may be null
+  const int32_t* perm;   // [N] sorted -> original
+  const float* gF;       // [N][3] original order, may be null
+  float* w;              // [N][3] scratch: gF in sorted order
   double gE;
-  float* vjp;            // [D][N] scratch
-  float* qs;             // [D][N] scratch
-  double* gpart;         // [nblocks][train_grad_stride()] FP64 partial gradients
+  double* gpart;         // [tiles of 256 atoms][train_grad_stride()] FP64 gradient sums
   float* grad;           // [G] output
   int accumulate;        // 1: grad += result
 };
@@ -369,7 +367,6 @@ hipError_t launch_train_backward(const ModelDev& m, const TrainBuffers& t, hipSt
 hipError_t launch_train_forward_params(const ModelDev& m, const float* params, const EvalBuffers& b,
                                        hipStream_t st);
 hipError_t launch_train_backward_params(const ModelDev& m, const TrainBuffers& t, hipStream_t st);
-int train_partial_blocks(int64_t N);
 int train_grad_stride();
 hipError_t launch_adam(float* theta, const float* g, float* m1, float* m2, int64_t n, int64_t t,
                        double lr, double b1, double b2, double eps, hipStream_t st);

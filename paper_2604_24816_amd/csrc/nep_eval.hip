@@ -34,12 +34,6 @@ namespace {
 using namespace kern;
 
 // ------------------------------------------------------------------------ network
-// Row stride of the per-wavefront operand tile: 37 words keep a lane's own row (stride
-// odd) and the MFMA operand and result patterns (lane (lr, lk) at 37 lr + lk and
-// 148 lk + lr) within two passes of the 64 LDS banks.
-constexpr int kNetStride = 37;
-constexpr int kBfStride = 40;  // bfloat16 weights staged in LDS: 16-byte aligned rows
-
 // The network's operand tiles are private to a wavefront, so its lanes only have to see
 // each other's LDS writes (wave_lds_sync), not a workgroup barrier: the wavefronts of a
 // workgroup leave their descriptor loops independently.
@@ -187,112 +181,20 @@ __device__ __forceinline__ float network_wave(const ModelDev& m, const float* qs
   return U;
 }
 
-// ------------------------------------------------------------------------ shared centers
-// With L > 1 lanes to a center the part after the pair loop (descriptors from the sums,
-// network, dU/ds, record) would be repeated by every lane; it is spread over them instead:
-// lane l takes channels l, l + L, ... of the angular terms, every L-th activation and every
-// L-th coefficient, and the center's row of the operand tile carries the values between
-// lanes. The network's weights are staged in LDS while the pair loop runs, so that no global
-// load sits in this part. Both matter because a small system runs one short wavefront per
-// SIMD: 4,000 atoms at 16 lanes took 24 us with everything repeated and the weights
-// gathered from global memory.
-template <int PREC>
-struct NetLds {
-  float w[PREC == 0 ? 32 * 33 : 1];                      // W0 [hidden][descriptor], zero padded
-  alignas(16) uint16_t wb[PREC == 1 ? 32 * kBfStride : 8];  // the same as bfloat16
-  float b0[32], w1[32], sigma[32];
-};
-
-template <class S, int PREC>
-__device__ __forceinline__ void stage_network(const ModelDev& m, NetLds<PREC>& n) {
-  for (int t = threadIdx.x; t < 32 * 32; t += kBlock) {
-    const int hid = t >> 5, d = t & 31;
-    const bool in = hid < S::H && d < S::D;
-    if constexpr (PREC == 0) n.w[hid * 33 + d] = in ? m.W0[hid * S::D + d] : 0.f;
-    else n.wb[hid * kBfStride + d] = in ? m.W0bf[hid * S::D + d] : (uint16_t)0;
-  }
-  if (threadIdx.x < 32) {
-    const int t = threadIdx.x;
-    n.b0[t] = t < S::H ? m.b0[t] : 0.f;
-    n.w1[t] = t < S::H ? m.w1[t] : 0.f;
-    n.sigma[t] = t < S::D ? m.sigma[t] : 0.f;
-  }
-}
-
-// rows x 32 times W0^T (FORWARD: descriptors to hidden units) or W0 (hidden units to
-// descriptors), in place in the wavefront's operand tile of RT 16-row MFMA tiles. Rows that
-// belong to no center hold whatever the LDS held and are never read back.
-template <int PREC, int RT, bool FORWARD>
-__device__ __forceinline__ void net_product(float* lds, const NetLds<PREC>& n) {
-  const int lane = threadIdx.x & 63;
-  const int lr = lane & 15, lk = lane >> 4;
-  wave_lds_sync();
-  floatx4 acc[RT][2];
-#pragma unroll
-  for (int R = 0; R < RT; ++R)
-#pragma unroll
-    for (int C = 0; C < 2; ++C) acc[R][C] = floatx4{0.f, 0.f, 0.f, 0.f};
-  if constexpr (PREC == 0) {
-#pragma unroll
-    for (int kb = 0; kb < 8; ++kb) {
-      const int k = 4 * kb + lk;
-      float bop[2];
-#pragma unroll
-      for (int C = 0; C < 2; ++C) bop[C] = FORWARD ? n.w[(16 * C + lr) * 33 + k] : n.w[k * 33 + 16 * C + lr];
-#pragma unroll
-      for (int R = 0; R < RT; ++R) {
-        const float aop = lds[(16 * R + lr) * kNetStride + k];
-#pragma unroll
-        for (int C = 0; C < 2; ++C)
-          acc[R][C] = __builtin_amdgcn_mfma_f32_16x16x4f32(aop, bop[C], acc[R][C], 0, 0, 0);
-      }
-    }
-  } else {
-    bf16x8 bop[2];
-#pragma unroll
-    for (int C = 0; C < 2; ++C)
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        bop[C][e] = bits_to_bf16(FORWARD ? n.wb[(16 * C + lr) * kBfStride + 8 * lk + e]
-                                         : n.wb[(8 * lk + e) * kBfStride + 16 * C + lr]);
-#pragma unroll
-    for (int R = 0; R < RT; ++R) {
-      bf16x8 aop;
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        aop[e] = bits_to_bf16(f32_to_bf16_bits(lds[(16 * R + lr) * kNetStride + 8 * lk + e]));
-#pragma unroll
-      for (int C = 0; C < 2; ++C)
-        acc[R][C] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aop, bop[C], acc[R][C], 0, 0, 0);
-    }
-  }
-  wave_lds_sync();
-#pragma unroll
-  for (int R = 0; R < RT; ++R)
-#pragma unroll
-    for (int C = 0; C < 2; ++C)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) lds[(16 * R + 4 * lk + r) * kNetStride + 16 * C + lr] = acc[R][C][r];
-  wave_lds_sync();
-}
-
 // ------------------------------------------------------------------------ descriptors
-// The main loops only count the pairs inside the ZBL radius; a center with any visits its
-// whole radial list again afterwards (zbl_center), which keeps the loops free of slot
-// bookkeeping for the common case of no close pairs.
-using EvalZbl = ZblSeen<0>;
-
 // Radial descriptors q[0..NR) and angular accumulators s[NA][NC] of center i over the
 // pairs inside the true cutoffs, all channels in one pass over the list with skin
 // (geometry computed once per pair and reused for every n). The radial descriptors are
 // linear in the basis sums over the neighbours of each species t, q_n = sum_t sum_k c^t_nk
 // sum_j f_k(r_ij), with sum_j f_k = (sum_j f_c T_k + sum_j f_c) / 2, so a pair adds f_c and
-// f_c T_k (k >= 1). Returns the pair counts and the pairs inside the ZBL radius (zs).
+// f_c T_k (k >= 1). Returns the pair counts and the number of pairs inside the
+// ZBL radius (nz), which the loops only count; a center with any visits its radial list again
+// afterwards (zbl_center).
 // With L > 1 this lane (l of the L that share the center) visits entries l, l + L, ... and
 // the sums over the lanes are formed at the end, in every lane.
 template <class S, bool MULTI, int L>
 __device__ __forceinline__ void desc_pass(const ModelDev& m, const EvalBuffers& b, const PairTab<S, MULTI>& tab,
-                                          int64_t i, int l, int ti, QPos qi, float* q, float* s, EvalZbl& zs, int& nr,
+                                          int64_t i, int l, int ti, QPos qi, float* q, float* s, int& nz, int& nr,
                                           int& na) {
   constexpr int NR = S::NR, NA = S::NA, NC = S::NC, KR = S::KR, KA = S::KA, TT = MULTI ? kMaxTypes : 1;
   const int64_t N = b.N;
@@ -319,7 +221,7 @@ __device__ __forceinline__ void desc_pass(const ModelDev& m, const EvalBuffers& 
     r_of_r2(r2, r, rinv);
     const int tj = MULTI ? (int)w[0].w : 0;
     ++nr;
-    zs.n += (zbl_on && r2 < zbl2) ? 1 : 0;
+    nz += (zbl_on && r2 < zbl2) ? 1 : 0;
     {
       // T_k by the recurrence T_{k+1} = 2x T_k - T_{k-1}
       const RadialGeo ra = radial_geo<false>(r, cutR);
@@ -365,7 +267,7 @@ __device__ __forceinline__ void desc_pass(const ModelDev& m, const EvalBuffers& 
   if constexpr (L > 1) {
     nr = lanes_sum<L>(nr);
     na = lanes_sum<L>(na);
-    zs.n = lanes_sum<L>(zs.n);
+    nz = lanes_sum<L>(nz);
 #pragma unroll
     for (int t = 0; t < TT; ++t) {
       Qf[t] = lanes_sum<L>(Qf[t]);
@@ -419,7 +321,7 @@ __device__ __forceinline__ void load_g_row(const float* row, float* g) {
 // and s hold the center's sums in every lane. lds: this wavefront's operand tile.
 template <class S, int PREC, bool MULTI, int L>
 __device__ __forceinline__ void finish_lanes(const ModelDev& m, const EvalBuffers& b, int64_t i, int l, bool valid,
-                                             int ti, const float* q, const float* s, const EvalZbl& zs, float* lds,
+                                             int ti, const float* q, const float* s, int nz, float* lds,
                                              const NetLds<PREC>& net, const PairTab<S, MULTI>& tab) {
   constexpr int NR = S::NR, NA = S::NA, NC = S::NC, D = S::D, L3 = S::L3;
   constexpr int RT = 64 / L >= 16 ? 64 / L / 16 : 1;
@@ -456,7 +358,7 @@ __device__ __forceinline__ void finish_lanes(const ModelDev& m, const EvalBuffer
       if constexpr (S::FB) row[NR + L3 * NA + n] = fourbody_q(sl[r]) * net.sigma[NR + L3 * NA + n];
     }
   }
-  net_product<PREC, RT, true>(lds, net);
+  net_product<PREC, RT, true>(lds, lds, net);
   float U = 0.f;
 #pragma unroll
   for (int mu0 = 0; mu0 < 32; mu0 += L) {
@@ -466,7 +368,7 @@ __device__ __forceinline__ void finish_lanes(const ModelDev& m, const EvalBuffer
     row[mu] = w * (1.f - t * t);
   }
   U = lanes_sum<L>(U) - m.b1[0];
-  net_product<PREC, RT, false>(lds, net);
+  net_product<PREC, RT, false>(lds, lds, net);
   if (!valid) return;
   auto fp = [&](int v) { return row[v] * net.sigma[v]; };  // dU/dq_v
   // the 64-byte records: position (words 0..2), radial coefficients (3..11), species, zeros
@@ -531,9 +433,9 @@ __device__ __forceinline__ void finish_lanes(const ModelDev& m, const EvalBuffer
     }
   }
   for (int c = l; c < 3; c += L) b.F[c * N + i] = 0.f;
-  if (zs.n) {  // ZBL energy (half of each close pair)
+  if (nz) {  // ZBL energy (half of each close pair)
     float uz = 0.f;
-    zbl_center<MULTI>(m, b, i, ti, b.x[i], b.x[N + i], b.x[2 * N + i], zs, &uz, nullptr, nullptr, l, L);
+    zbl_center<MULTI>(m, b, i, ti, b.x[i], b.x[N + i], b.x[2 * N + i], &uz, nullptr, nullptr, l, L);
     U += lanes_sum<L>(uz);
   }
   if (l == 0) b.U[i] = U;
@@ -563,18 +465,18 @@ __global__ void __launch_bounds__(kBlock, 2) k_desc_net(ModelDev m, EvalBuffers 
 #pragma unroll
     for (int k = 0; k < NA * NC; ++k) s[k] = 0.f;
     const int ti = valid ? (MULTI ? b.type[i] : 0) : 0;
-    EvalZbl zs;
+    int nz = 0;
     if (valid) {
       const uint4 w0 = b.pos[i];
       int nr = 0, na = 0;
-      desc_pass<S, MULTI, L>(m, b, tab, i, l, ti, QPos{w0.x, w0.y, w0.z}, q, s, zs, nr, na);
+      desc_pass<S, MULTI, L>(m, b, tab, i, l, ti, QPos{w0.x, w0.y, w0.z}, q, s, nz, nr, na);
       if (l == 0) {
         b.nactR[i] = nr;
         b.nactA[i] = na;
       }
     }
     __syncthreads();  // the staged weights
-    finish_lanes<S, PREC, MULTI, L>(m, b, i, l, valid, ti, q, s, zs, lds[threadIdx.x >> 6], net, tab);
+    finish_lanes<S, PREC, MULTI, L>(m, b, i, l, valid, ti, q, s, nz, lds[threadIdx.x >> 6], net, tab);
     return;
   }
 
@@ -585,12 +487,12 @@ __global__ void __launch_bounds__(kBlock, 2) k_desc_net(ModelDev m, EvalBuffers 
 #pragma unroll
   for (int k = 0; k < NA * NC; ++k) s[k] = 0.f;
   const int ti = valid ? (MULTI ? b.type[i] : 0) : 0;
-  EvalZbl zs;  // pairs inside the ZBL radius
+  int nz = 0;  // pairs inside the ZBL radius
 
   if (valid) {
     const uint4 w0 = b.pos[i];
     int nr = 0, na = 0;
-    desc_pass<S, MULTI, 1>(m, b, tab, i, 0, ti, QPos{w0.x, w0.y, w0.z}, q, s, zs, nr, na);
+    desc_pass<S, MULTI, 1>(m, b, tab, i, 0, ti, QPos{w0.x, w0.y, w0.z}, q, s, nz, nr, na);
     b.nactR[i] = nr;
     b.nactA[i] = na;
     desc_finish<S>(s, q);
@@ -665,7 +567,7 @@ __global__ void __launch_bounds__(kBlock, 2) k_desc_net(ModelDev m, EvalBuffers 
     b.F[N + i] = 0.f;
     b.F[2 * N + i] = 0.f;
     // ZBL energy (half of each close pair), after the descriptors are no longer live
-    if (zs.n) zbl_center<MULTI>(m, b, i, ti, b.x[i], b.x[N + i], b.x[2 * N + i], zs, &U, nullptr, nullptr);
+    if (nz) zbl_center<MULTI>(m, b, i, ti, b.x[i], b.x[N + i], b.x[2 * N + i], &U, nullptr, nullptr);
     b.U[i] = U;
   }
 }
@@ -864,7 +766,7 @@ __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, 
       for (int k = 0; k < NA * NC; ++k) G[k] = b.G[(int64_t)k * N + i];
     }
     const float rcR2 = (float)(m.rcR64 * m.rcR64), rcA2 = (float)(m.rcA64 * m.rcA64), zbl2 = (float)m.zbl_o2;
-    EvalZbl zs;  // pairs inside the ZBL radius
+    int nz = 0;  // pairs inside the ZBL radius
     // One entry: the radial term by gather, F_i += (dU_i/dr_ij + dU_j/dr_ji) along u, with
     // the neighbour's radial coefficients read from its record, the virial taking half of
     // that pair term (the lists are symmetric, so the pair's other half comes from j); and
@@ -893,7 +795,7 @@ __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, 
         else W[k] = (MULTI && tj ? wi1[k] : wi[k]) + wj[k];
       }
       const float sr = radial_series_z<KR>(ra, W, W[0]) * (kXR * rinv);
-      zs.n += (zbl_on && r2 < zbl2) ? 1 : 0;
+      nz += (zbl_on && r2 < zbl2) ? 1 : 0;
       fx = fmaf(sr, dx, fx);
       fy = fmaf(sr, dy, fy);
       fz = fmaf(sr, dz, fz);
@@ -938,10 +840,10 @@ __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, 
       for_each_rec_lanes<W, 4, L>(b.nbr, plane, N, i, l, kR, pair_both);
     else
       for_each_rec_fast<W, 1, 4>(b.nbr, plane, N, i, 0, kR, pair_both);
-    if constexpr (L > 1) zs.n = lanes_sum<L>(zs.n);
-    if (zs.n) {
+    if constexpr (L > 1) nz = lanes_sum<L>(nz);
+    if (nz) {
       float f[3] = {fx, fy, fz};
-      zbl_center<MULTI>(m, b, i, ti, b.x[i], b.x[N + i], b.x[2 * N + i], zs, nullptr, f, w, l, L);
+      zbl_center<MULTI>(m, b, i, ti, b.x[i], b.x[N + i], b.x[2 * N + i], nullptr, f, w, l, L);
       fx = f[0];
       fy = f[1];
       fz = f[2];

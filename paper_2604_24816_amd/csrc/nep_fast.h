@@ -371,6 +371,14 @@ template <int CTRL>
 __device__ __forceinline__ int dpp_add(int v) {
   return v + __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
 }
+// Sum over the whole wavefront, valid in lane 63: the row sums, then rows 0 -> 1 and 2 -> 3
+// and rows 0-1 -> 2-3 by row broadcasts. All 64 lanes must be active.
+__device__ __forceinline__ float wave_sum_last(float v) {
+  v = dpp_add<0x140>(dpp_add<0x141>(dpp_add<0x4e>(dpp_add<0xb1>(v))));
+  v += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x142, 0xa, 0xf, false));
+  v += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x143, 0xc, 0xf, false));
+  return v;
+}
 template <int L>
 __device__ __forceinline__ int lanes_sum(int v) {
   if constexpr (L >= 2) v = dpp_add<0xb1>(v);
@@ -378,6 +386,101 @@ __device__ __forceinline__ int lanes_sum(int v) {
   if constexpr (L >= 8) v = dpp_add<0x141>(v);
   if constexpr (L >= 16) v = dpp_add<0x140>(v);
   return v;
+}
+
+// ---------------------------------------------------------------- network of shared centers
+// Row stride of the per-wavefront operand tile: 37 words keep a lane's own row (stride
+// odd) and the MFMA operand and result patterns (lane (lr, lk) at 37 lr + lk and
+// 148 lk + lr) within two passes of the 64 LDS banks.
+constexpr int kNetStride = 37;
+constexpr int kBfStride = 40;  // bfloat16 weights staged in LDS: 16-byte aligned rows
+
+// With L > 1 lanes to a center the part after the pair loop (descriptors from the sums,
+// network, dU/ds, record) would be repeated by every lane; it is spread over them instead:
+// lane l takes channels l, l + L, ... of the angular terms, every L-th activation and every
+// L-th coefficient, and the center's row of the operand tile carries the values between
+// lanes. The network's weights are staged in LDS while the pair loop runs, so that no global
+// load sits in this part. Both matter because a small system runs one short wavefront per
+// SIMD: 4,000 atoms at 16 lanes took 24 us with everything repeated and the weights
+// gathered from global memory.
+template <int PREC>
+struct NetLds {
+  float w[PREC == 0 ? 32 * 33 : 1];                      // W0 [hidden][descriptor], zero padded
+  alignas(16) uint16_t wb[PREC == 1 ? 32 * kBfStride : 8];  // the same as bfloat16
+  float b0[32], w1[32], sigma[32];
+};
+
+template <class S, int PREC>
+__device__ __forceinline__ void stage_network(const ModelDev& m, NetLds<PREC>& n) {
+  for (int t = threadIdx.x; t < 32 * 32; t += kBlock) {
+    const int hid = t >> 5, d = t & 31;
+    const bool in = hid < S::H && d < S::D;
+    if constexpr (PREC == 0) n.w[hid * 33 + d] = in ? m.W0[hid * S::D + d] : 0.f;
+    else n.wb[hid * kBfStride + d] = in ? m.W0bf[hid * S::D + d] : (uint16_t)0;
+  }
+  if (threadIdx.x < 32) {
+    const int t = threadIdx.x;
+    n.b0[t] = t < S::H ? m.b0[t] : 0.f;
+    n.w1[t] = t < S::H ? m.w1[t] : 0.f;
+    n.sigma[t] = t < S::D ? m.sigma[t] : 0.f;
+  }
+}
+
+// rows x 32 times W0^T (FORWARD: descriptors to hidden units) or W0 (hidden units to
+// descriptors) of a wavefront's operand tile of RT 16-row MFMA tiles, into dst (which may be
+// the same tile). Rows that belong to no center hold whatever the LDS held and are never read back.
+template <int PREC, int RT, bool FORWARD>
+__device__ __forceinline__ void net_product(const float* src, float* dst, const NetLds<PREC>& n) {
+  const int lane = threadIdx.x & 63;
+  const int lr = lane & 15, lk = lane >> 4;
+  wave_lds_sync();
+  floatx4 acc[RT][2];
+#pragma unroll
+  for (int R = 0; R < RT; ++R)
+#pragma unroll
+    for (int C = 0; C < 2; ++C) acc[R][C] = floatx4{0.f, 0.f, 0.f, 0.f};
+  if constexpr (PREC == 0) {
+#pragma unroll
+    for (int kb = 0; kb < 8; ++kb) {
+      const int k = 4 * kb + lk;
+      float bop[2];
+#pragma unroll
+      for (int C = 0; C < 2; ++C) bop[C] = FORWARD ? n.w[(16 * C + lr) * 33 + k] : n.w[k * 33 + 16 * C + lr];
+#pragma unroll
+      for (int R = 0; R < RT; ++R) {
+        const float aop = src[(16 * R + lr) * kNetStride + k];
+#pragma unroll
+        for (int C = 0; C < 2; ++C)
+          acc[R][C] = __builtin_amdgcn_mfma_f32_16x16x4f32(aop, bop[C], acc[R][C], 0, 0, 0);
+      }
+    }
+  } else {
+    bf16x8 bop[2];
+#pragma unroll
+    for (int C = 0; C < 2; ++C)
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        bop[C][e] = bits_to_bf16(FORWARD ? n.wb[(16 * C + lr) * kBfStride + 8 * lk + e]
+                                         : n.wb[(8 * lk + e) * kBfStride + 16 * C + lr]);
+#pragma unroll
+    for (int R = 0; R < RT; ++R) {
+      bf16x8 aop;
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        aop[e] = bits_to_bf16(f32_to_bf16_bits(src[(16 * R + lr) * kNetStride + 8 * lk + e]));
+#pragma unroll
+      for (int C = 0; C < 2; ++C)
+        acc[R][C] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aop, bop[C], acc[R][C], 0, 0, 0);
+    }
+  }
+  wave_lds_sync();
+#pragma unroll
+  for (int R = 0; R < RT; ++R)
+#pragma unroll
+    for (int C = 0; C < 2; ++C)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) dst[(16 * R + 4 * lk + r) * kNetStride + 16 * C + lr] = acc[R][C][r];
+  wave_lds_sync();
 }
 
 // ---------------------------------------------------------------- structural zeros

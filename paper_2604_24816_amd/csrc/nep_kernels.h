@@ -1,6 +1,6 @@
-// Device helpers shared by the evaluation and training kernels: radial basis,
-// pair vectors, workgroup reductions, model shapes, and the descriptor
-// accumulation of one center (radial q_n, angular s_nlm, q_nl, four-body).
+// Device helpers shared by the evaluation and training kernels: pair vectors, workgroup
+// reductions, model shapes, the ZBL term, and the descriptors of one center from its
+// accumulators (q_nl, four-body).
 #pragma once
 
 #include "nep_common.h"
@@ -29,136 +29,6 @@ __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
 }
 
 __device__ __forceinline__ __bf16 bits_to_bf16(uint16_t b) { return __builtin_bit_cast(__bf16, b); }
-
-// Chebyshev-based radial basis f_k(r) = (T_k(x) + 1) f_c(r) / 2 with
-// x = 2 (r/rc - 1)^2 - 1 and f_c = (1 + cos(pi r / rc)) / 2 (published NEP form).
-// Returns g_n = sum_k c_nk f_k.
-template <int N, int K, class CP>
-__device__ __forceinline__ void radial_g(float r, float rc_inv, CP c, float* g) {
-  float sn, cs;
-  sincospif(r * rc_inv, &sn, &cs);
-  const float fc = 0.5f * (1.f + cs);
-  const float y = r * rc_inv - 1.f;
-  const float x = 2.f * y * y - 1.f;
-  float Tm1 = 1.f, T = x;
-  float fk[K];
-  fk[0] = 1.f;
-  fk[1] = 0.5f * (x + 1.f);
-#pragma unroll
-  for (int k = 2; k < K; ++k) {
-    const float Tn = 2.f * x * T - Tm1;
-    Tm1 = T;
-    T = Tn;
-    fk[k] = 0.5f * (Tn + 1.f);
-  }
-#pragma unroll
-  for (int n = 0; n < N; ++n) {
-    float a = 0.f;
-#pragma unroll
-    for (int k = 0; k < K; ++k) a = fmaf(c[n * K + k], fk[k], a);
-    g[n] = a * fc;
-  }
-}
-
-// g_n and dg_n/dr.
-template <int N, int K, class CP>
-__device__ __forceinline__ void radial_g_dg(float r, float rc_inv, CP c, float* g, float* dg) {
-  float sn, cs;
-  sincospif(r * rc_inv, &sn, &cs);
-  const float fc = 0.5f * (1.f + cs);
-  const float dfc = -0.5f * kPiF * rc_inv * sn;
-  const float y = r * rc_inv - 1.f;
-  const float x = 2.f * y * y - 1.f;
-  const float dx = 4.f * y * rc_inv;
-  float hk[K], dk[K];  // (T_k + 1)/2 and T_k'/2
-  float Tm1 = 1.f, T = x, dTm1 = 0.f, dT = 1.f;
-  hk[0] = 1.f;
-  dk[0] = 0.f;
-  hk[1] = 0.5f * (x + 1.f);
-  dk[1] = 0.5f;
-#pragma unroll
-  for (int k = 2; k < K; ++k) {
-    const float Tn = 2.f * x * T - Tm1;
-    const float dTn = 2.f * T + 2.f * x * dT - dTm1;
-    Tm1 = T;
-    T = Tn;
-    dTm1 = dT;
-    dT = dTn;
-    hk[k] = 0.5f * (Tn + 1.f);
-    dk[k] = 0.5f * dTn;
-  }
-  const float fcdx = fc * dx;
-#pragma unroll
-  for (int n = 0; n < N; ++n) {
-    float a = 0.f, b = 0.f;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      a = fmaf(c[n * K + k], hk[k], a);
-      b = fmaf(c[n * K + k], dk[k], b);
-    }
-    g[n] = a * fc;
-    dg[n] = fmaf(b, fcdx, a * dfc);
-  }
-}
-
-// The radial basis itself, f_k = f_c (T_k + 1)/2 for k < K. For one species the
-// radial descriptors are linear in it, q_n = sum_k c_nk sum_j f_k(r_ij), so a center
-// accumulates the K basis sums and contracts with c once.
-template <int K>
-__device__ __forceinline__ void radial_basis(float r, float rc_inv, float* f) {
-  float sn, cs;
-  sincospif(r * rc_inv, &sn, &cs);
-  const float fc = 0.5f * (1.f + cs);
-  const float y = r * rc_inv - 1.f;
-  const float x = 2.f * y * y - 1.f;
-  const float hf = 0.5f * fc;
-  float Tm1 = 1.f, T = x;
-  f[0] = fc;
-  f[1] = fmaf(hf, x, hf);
-#pragma unroll
-  for (int k = 2; k < K; ++k) {
-    const float Tn = 2.f * x * T - Tm1;
-    Tm1 = T;
-    T = Tn;
-    f[k] = fmaf(hf, Tn, hf);
-  }
-}
-
-// e_k = d f_k / dr. For one species dU_i/dr_ij = sum_k w_ik e_k(r_ij) with
-// w_ik = sum_n (dU_i/dq_n) c_nk formed once per center.
-template <int K>
-__device__ __forceinline__ void radial_basis_deriv(float r, float rc_inv, float* e) {
-  float sn, cs;
-  sincospif(r * rc_inv, &sn, &cs);
-  const float fc = 0.5f * (1.f + cs);
-  const float dfc = -0.5f * kPiF * rc_inv * sn;
-  const float y = r * rc_inv - 1.f;
-  const float x = 2.f * y * y - 1.f;
-  const float hfd = 2.f * y * rc_inv * fc;  // (f_c / 2) dx/dr
-  const float hdf = 0.5f * dfc;
-  float Tm1 = 1.f, T = x, dTm1 = 0.f, dT = 1.f;
-  e[0] = dfc;
-  e[1] = fmaf(hdf, x + 1.f, hfd);
-#pragma unroll
-  for (int k = 2; k < K; ++k) {
-    const float Tn = 2.f * x * T - Tm1;
-    const float dTn = 2.f * T + 2.f * x * dT - dTm1;
-    Tm1 = T;
-    T = Tn;
-    dTm1 = dT;
-    dT = dTn;
-    e[k] = fmaf(hdf, Tn + 1.f, hfd * dTn);
-  }
-}
-
-// FP64 minimum-image pair vector, rounded to FP32 after the subtraction.
-__device__ __forceinline__ void pair_vec(const double* __restrict__ x, int64_t N, int64_t j, double xi,
-                                         double yi, double zi, double Lx, double Ly, double Lz, float& dx,
-                                         float& dy, float& dz) {
-  dx = (float)min_image(x[j] - xi, Lx);
-  dy = (float)min_image(x[N + j] - yi, Ly);
-  dz = (float)min_image(x[2 * N + j] - zi, Lz);
-}
 
 // Deterministic FP64 sums of K values over a 256-thread workgroup: a butterfly over the
 // 64 lanes of each wavefront (cross-lane moves, no barrier), then the four wavefront
@@ -204,44 +74,12 @@ struct Shape {
 using FullShape = Shape<5, 9, 5, 9, 4, true, 30>;
 using SurShape = Shape<5, 9, 5, 9, 2, false, 8>;
 
-constexpr int kLdsStride = 33;  // 32 columns + 1 pad word against bank conflicts
-
 
 // r and 1/r of an FP32 pair vector (hardware reciprocal square root, 1 ulp).
 __device__ __forceinline__ void pair_r(float dx, float dy, float dz, float& r, float& rinv) {
   const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
   rinv = __builtin_amdgcn_rsqf(r2);
   r = r2 * rinv;
-}
-
-// Pair test for an entry whose position is already loaded: FP64 minimum-image
-// vector, kept when r^2 < cut2; rounded to FP32 after the subtraction.
-__device__ __forceinline__ bool inside(double xj, double yj, double zj, double xi, double yi, double zi,
-                                       double Lx, double Ly, double Lz, double cut2, float& dx, float& dy,
-                                       float& dz) {
-  const double ex = min_image(xj - xi, Lx);
-  const double ey = min_image(yj - yi, Ly);
-  const double ez = min_image(zj - zi, Lz);
-  if (!(ex * ex + ey * ey + ez * ez < cut2)) return false;
-  dx = (float)ex;
-  dy = (float)ey;
-  dz = (float)ez;
-  return true;
-}
-
-// Pair test for one entry of a list with skin: FP64 minimum-image vector, kept when
-// r^2 < cut2 (the true cutoff); the vector is rounded to FP32 after the subtraction.
-__device__ __forceinline__ bool pair_inside(const double* __restrict__ x, int64_t N, int32_t j, double xi,
-                                            double yi, double zi, double Lx, double Ly, double Lz, double cut2,
-                                            float& dx, float& dy, float& dz) {
-  const double ex = min_image(x[j] - xi, Lx);
-  const double ey = min_image(x[N + j] - yi, Ly);
-  const double ez = min_image(x[2 * N + j] - zi, Lz);
-  if (!(ex * ex + ey * ey + ez * ez < cut2)) return false;
-  dx = (float)ex;
-  dy = (float)ey;
-  dz = (float)ez;
-  return true;
 }
 
 // Number of list entries of atom i the current evaluation must visit for radial
@@ -312,41 +150,20 @@ __device__ __forceinline__ double pair_r2_64(double xj, double yj, double zj, do
   return ex * ex + ey * ey + ez * ez;
 }
 
-// Close pairs (inside the outer ZBL radius) seen by a main loop: their count and
-// the list positions of the first CAP of them, 16 bits each (CAP = 0: count only,
-// for kernels with no registers to spare).
-template <int CAP>
-struct ZblSeen {
-  static_assert(CAP >= 0 && CAP <= 4, "four 16-bit slots");
-  int n = 0;
-  uint64_t slots = 0;
-  __device__ __forceinline__ void add(int p) {
-    if constexpr (CAP > 0) {
-      if (n < CAP) slots |= (uint64_t)p << (16 * n);
-    }
-    ++n;
-  }
-};
-template <bool MULTI>
-using ZblSeenFor = ZblSeen<MULTI ? 0 : 4>;
-
 // ZBL terms of center i (the pairs with r^2 < zbl_o2): half of each pair's energy
 // into uz, and, when f is given, the force on i (the whole pair derivative, both
 // atoms' halves, along u) into f[3] and the virial of dU_i/dr_ij into w[9]. Called
-// only for centers that have such pairs, after the main loop: it visits the
-// recorded list positions, or the whole radial list when there were more.
+// only for centers that have such pairs, after the main loop: it visits the radial list.
 // (q0, qs): the first position and the stride of a lane that shares the center with others
 // (which then adds its part only).
-template <bool MULTI, int CAP>
+template <bool MULTI>
 __device__ __forceinline__ void zbl_center(const ModelDev& m, const EvalBuffers& b, int64_t i, int ti, double xi,
-                                        double yi, double zi, const ZblSeen<CAP>& seen, float* uz, float* f,
-                                        float* w, int q0 = 0, int qs = 1) {
+                                        double yi, double zi, float* uz, float* f, float* w, int q0 = 0,
+                                        int qs = 1) {
   const int64_t N = b.N;
   const double Lx = b.box[0], Ly = b.box[1], Lz = b.box[2];
-  const bool all = seen.n > CAP;
-  const int kR = all ? radial_bound(b, i) : seen.n;
-  for (int q = q0; q < kR; q += qs) {
-    const int p = all ? q : (int)((seen.slots >> (16 * q)) & 0xffffu);
+  const int kR = radial_bound(b, i);
+  for (int p = q0; p < kR; p += qs) {
     const int32_t j = b.nbr[(int64_t)p * N + i];
     const double ex = min_image(b.x[j] - xi, Lx);
     const double ey = min_image(b.x[N + j] - yi, Ly);
@@ -367,79 +184,6 @@ __device__ __forceinline__ void zbl_center(const ModelDev& m, const EvalBuffers&
 #pragma unroll
         for (int c = 0; c < 3; ++c) w[a * 3 + c] += (float)(-d[a] * 0.5 * de * d[c] / r);
       }
-    }
-  }
-}
-
-// Radial descriptors q[0..NR) and angular accumulators s[NA][NC] of center i over
-// the pairs inside the true cutoffs, all channels in one pass over the neighbours
-// (geometry computed once per pair and reused for every n). Returns the pair counts
-// and the pairs inside the ZBL radius (zs).
-template <class S, bool MULTI>
-__device__ __forceinline__ void desc_accumulate(const ModelDev& m, const EvalBuffers& b, int64_t i, int ti,
-                                                double xi, double yi, double zi, double Lx, double Ly,
-                                                double Lz, float* q, float* s, ZblSeenFor<MULTI>& zs, int& nr,
-                                                int& na) {
-  constexpr int NR = S::NR, NA = S::NA, NC = S::NC;
-  const int64_t N = b.N;
-  const float rcR_inv = 1.f / m.rcR, rcA_inv = 1.f / m.rcA;
-  const double rcR2 = m.rcR64 * m.rcR64, rcA2 = m.rcA64 * m.rcA64;
-  const double iLx = 1.0 / Lx, iLy = 1.0 / Ly, iLz = 1.0 / Lz;
-  nr = 0;
-  na = 0;
-  const float* cR = m.cR + (MULTI ? 0 : (ti * m.T) * NR * S::KR);
-  const float* cA = m.cA + (MULTI ? 0 : (ti * m.T) * NA * S::KA);
-  const int kR = radial_bound(b, i), kA = angular_bound(b, i);
-  float Qb[S::KR];  // basis sums (one species)
-#pragma unroll
-  for (int k = 0; k < S::KR; ++k) Qb[k] = 0.f;
-  // one pass over the list: radial terms for every pair inside rc_radial, angular
-  // terms for the pairs of the angular prefix inside rc_angular; FP64 positions from
-  // the position array (these kernels serve training, not the MD step)
-  for (int p = 0; p < kR; ++p) {
-    const int32_t j = b.nbr[(int64_t)p * N + i];
-    double ex, ey, ez;
-    const double r2 = pair_r2_64(b.x[j], b.x[N + j], b.x[2 * N + j], xi, yi, zi, Lx, Ly, Lz, iLx, iLy, iLz, ex,
-                                 ey, ez);
-    if (!(r2 < rcR2)) continue;
-    const float dx = (float)ex, dy = (float)ey, dz = (float)ez;
-    ++nr;
-    float r, rinv;
-    pair_r(dx, dy, dz, r, rinv);
-    const int tj = MULTI ? b.type[j] : 0;
-    if (r2 < m.zbl_o2) zs.add(p);
-    if constexpr (MULTI) {
-      float g[NR];
-      radial_g<NR, S::KR>(r, rcR_inv, m.cR + (ti * m.T + tj) * NR * S::KR, g);
-#pragma unroll
-      for (int n = 0; n < NR; ++n) q[n] += g[n];
-    } else {
-      float f[S::KR];
-      radial_basis<S::KR>(r, rcR_inv, f);
-#pragma unroll
-      for (int k = 0; k < S::KR; ++k) Qb[k] += f[k];
-    }
-    if (p < kA && r2 < rcA2) {
-      ++na;
-      float g[NA];
-      if constexpr (MULTI)
-        radial_g<NA, S::KA>(r, rcA_inv, m.cA + (ti * m.T + tj) * NA * S::KA, g);
-      else
-        radial_g<NA, S::KA>(r, rcA_inv, uniform_coeffs(cA), g);
-      for_each_poly<NC>(dx * rinv, dy * rinv, dz * rinv, [&](int lm, float P) {
-#pragma unroll
-        for (int n = 0; n < NA; ++n) s[n * NC + lm] = fmaf(g[n], P, s[n * NC + lm]);
-      });
-    }
-  }
-  if constexpr (!MULTI) {
-    const cfloat_ptr c = uniform_coeffs(cR);
-#pragma unroll
-    for (int n = 0; n < NR; ++n) {
-      float a = 0.f;
-#pragma unroll
-      for (int k = 0; k < S::KR; ++k) a = fmaf(c[n * S::KR + k], Qb[k], a);
-      q[n] += a;
     }
   }
 }

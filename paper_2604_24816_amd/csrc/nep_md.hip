@@ -254,14 +254,6 @@ __global__ void k_scalar_out(int64_t N, const int32_t* __restrict__ perm, const 
   out[perm[p]] = (double)U[p];
 }
 
-__global__ void k_gather_vec_f32(int64_t N, const int32_t* __restrict__ perm, const float* __restrict__ a,
-                                 float* __restrict__ s) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= N) return;
-  const int64_t o = perm[p];
-  for (int c = 0; c < 3; ++c) s[c * N + p] = a[3 * o + c];
-}
-
 __global__ void k_scatter_vec_f32(int64_t N, const int32_t* __restrict__ perm, const float* __restrict__ s,
                                   float* __restrict__ a) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -352,13 +344,6 @@ hipError_t launch_forces_out(int64_t N, const int32_t* perm, const float* F, dou
 
 hipError_t launch_scalar_out(int64_t N, const int32_t* perm, const float* U, double* out, hipStream_t st) {
   hipLaunchKernelGGL(k_scalar_out, dim3(grid_blocks(N)), dim3(kBlock), 0, st, N, perm, U, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_gather_vec_f32(int64_t N, const int32_t* perm, const float* aos_orig, float* soa_sorted,
-                                 hipStream_t st) {
-  hipLaunchKernelGGL(k_gather_vec_f32, dim3(grid_blocks(N)), dim3(kBlock), 0, st, N, perm, aos_orig,
-                     soa_sorted);
   return hipGetLastError();
 }
 

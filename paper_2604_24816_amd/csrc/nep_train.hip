@@ -7,231 +7,10 @@
 // Writing q~ = sigma q, v~ = sigma v, h = W0 q~ - b0, t = tanh h, d = 1 - t^2 and
 // z = W0 v~, the per-atom contributions are
 //   dL/dW0 = alpha q~^T - beta v~^T,  alpha = gE w1 d + 2 z w1 t d,  beta = w1 d
-//   dL/db0 = -alpha,  dL/dw1 = gE t - z d,  dL/db1 = -gE,
-// summed over atoms. k_train_backward recomputes the descriptors of each center,
-// evaluates the JVP over the same pair lists as the force kernel, and reduces
-// the outer products over the 64 centers of a wavefront with FP32 MFMA
-// (atoms as the K dimension), then over workgroups in FP64.
-#include "nep_kernels.h"
-
-namespace nep {
-namespace {
-
-using namespace kern;
-
-constexpr int kGW = 32 * 32;        // gW0 tile, hidden-major, padded
-constexpr int kGB0 = kGW;           // 32 sums of alpha
-constexpr int kGW1 = kGW + 32;      // 32 sums of gE t - z d
-constexpr int kGradStride = kGW + 64 + 1;
-
-template <class S, bool MULTI>
-__global__ void __launch_bounds__(kBlock, 1)
-k_train_backward(ModelDev m, EvalBuffers b, const float* __restrict__ gF, double gE,
-                 double* __restrict__ gpart) {
-  __shared__ float tA[kBlock / 64][64 * kLdsStride];
-  __shared__ float tB[kBlock / 64][64 * kLdsStride];
-  constexpr int NR = S::NR, NA = S::NA, NC = S::NC, D = S::D, H = S::H;
-  const int64_t N = b.N;
-  const int tile = xcd_tile(blockIdx.x, gridDim.x);
-  const int64_t i = (int64_t)tile * kBlock + threadIdx.x;
-  const bool valid = i < N;
-  const double* __restrict__ x = b.x;
-  const double Lx = b.box[0], Ly = b.box[1], Lz = b.box[2];
-  const float rcR_inv = 1.f / m.rcR, rcA_inv = 1.f / m.rcA;
-
-  float q[D], v[D];
-#pragma unroll
-  for (int k = 0; k < D; ++k) {
-    q[k] = 0.f;
-    v[k] = 0.f;
-  }
-  if (valid) {
-    float s[NA * NC];
-#pragma unroll
-    for (int k = 0; k < NA * NC; ++k) s[k] = 0.f;
-    const int ti = MULTI ? b.type[i] : 0;
-    const double xi = x[i], yi = x[N + i], zi = x[2 * N + i];
-    int nr = 0, na = 0;
-    ZblSeenFor<MULTI> zs;  // the ZBL terms do not depend on the parameters
-    desc_accumulate<S, MULTI>(m, b, i, ti, xi, yi, zi, Lx, Ly, Lz, q, s, zs, nr, na);
-    const double rcR2 = m.rcR64 * m.rcR64, rcA2 = m.rcA64 * m.rcA64;
-    desc_finish<S>(s, q);
-    if (gF) {
-      const float wi0 = gF[i], wi1 = gF[N + i], wi2 = gF[2 * N + i];
-      // radial JVP: dq_n/dr_ij . w = g_n'(r) (u . w)
-      const int kR = radial_bound(b, i);
-      for (int p = 0; p < kR; ++p) {
-        const int32_t j = b.nbr[(int64_t)p * N + i];
-        float dx, dy, dz;
-        if (!pair_inside(x, N, j, xi, yi, zi, Lx, Ly, Lz, rcR2, dx, dy, dz)) continue;
-        const float r = sqrtf(dx * dx + dy * dy + dz * dz);
-        const float rinv = 1.f / r;
-        const int tj = MULTI ? b.type[j] : 0;
-        float g[NR], dg[NR];
-        radial_g_dg<NR, S::KR>(r, rcR_inv, m.cR + (ti * m.T + tj) * NR * S::KR, g, dg);
-        const float uw = ((gF[j] - wi0) * dx + (gF[N + j] - wi1) * dy + (gF[2 * N + j] - wi2) * dz) * rinv;
-#pragma unroll
-        for (int n = 0; n < NR; ++n) v[n] = fmaf(dg[n], uw, v[n]);
-      }
-      // angular JVP: dq_nl = sum_m 2 W_lm s_nlm ds_nlm, dq4_n = sum_k (d q4/d s_k) ds_k, with
-      // ds_nlm = g_n' (u.w) P_lm + g_n (grad P_lm . w - l P_lm (u.w)) / r
-      float d4[S::FB ? NA * 5 : 1];
-      if constexpr (S::FB) {
-#pragma unroll
-        for (int n = 0; n < NA; ++n) fourbody_ds(s + n * NC, d4 + 5 * n);
-      }
-#pragma unroll
-      for (int n = 0; n < NA; ++n)
-#pragma unroll
-        for (int lm = 0; lm < NC; ++lm) s[n * NC + lm] *= 2.f * kW[lm];
-      const int kA = angular_bound(b, i);
-      for (int p = 0; p < kA; ++p) {
-        const int32_t j = b.nbr[(int64_t)p * N + i];
-        float dx, dy, dz;
-        if (!pair_inside(x, N, j, xi, yi, zi, Lx, Ly, Lz, rcA2, dx, dy, dz)) continue;
-        const float r = sqrtf(dx * dx + dy * dy + dz * dz);
-        const float rinv = 1.f / r;
-        const int tj = MULTI ? b.type[j] : 0;
-        float g[NA], dg[NA];
-        radial_g_dg<NA, S::KA>(r, rcA_inv, m.cA + (ti * m.T + tj) * NA * S::KA, g, dg);
-        const float w0 = gF[j] - wi0, w1 = gF[N + j] - wi1, w2 = gF[2 * N + j] - wi2;
-        const float ux = dx * rinv, uy = dy * rinv, uz = dz * rinv;
-        const float uw = ux * w0 + uy * w1 + uz * w2;
-        for_each_poly_grad<NC>(ux, uy, uz, [&](int lm, float P, float px, float py, float pz) {
-          const int l = comp_l(lm);
-          const float a = uw * P;
-          const float bb = (px * w0 + py * w1 + pz * w2 - (float)l * P * uw) * rinv;
-#pragma unroll
-          for (int n = 0; n < NA; ++n) {
-            const float t = fmaf(dg[n], a, g[n] * bb);
-            v[NR + (l - 1) * NA + n] = fmaf(s[n * NC + lm], t, v[NR + (l - 1) * NA + n]);
-            if constexpr (S::FB) {
-              if (l == 2) v[NR + S::L3 * NA + n] = fmaf(d4[5 * n + lm - 3], t, v[NR + S::L3 * NA + n]);
-            }
-          }
-        });
-      }
-    }
-  }
-  // per-atom gradient terms (VALU); invalid lanes contribute zeros
-  float qs[D], vs[D];
-#pragma unroll
-  for (int k = 0; k < D; ++k) {
-    qs[k] = valid ? q[k] * m.sigma[k] : 0.f;
-    vs[k] = valid ? v[k] * m.sigma[k] : 0.f;
-  }
-  const int wave = threadIdx.x >> 6;
-  const int lane = threadIdx.x & 63;
-  const int lr = lane & 15, lk = lane >> 4;
-  float* A = tA[wave];
-  float* B = tB[wave];
-  float alpha[H], beta[H], gw1c[H];
-  const float gEf = (float)gE;
-#pragma unroll
-  for (int mu = 0; mu < H; ++mu) {
-    float h = -m.b0[mu], z = 0.f;
-#pragma unroll
-    for (int k = 0; k < D; ++k) {
-      h = fmaf(m.W0[mu * D + k], qs[k], h);
-      z = fmaf(m.W0[mu * D + k], vs[k], z);
-    }
-    const float t = tanhf(h);
-    const float d = 1.f - t * t;
-    const float w1d = m.w1[mu] * d;
-    alpha[mu] = valid ? fmaf(gEf, w1d, 2.f * z * m.w1[mu] * t * d) : 0.f;
-    beta[mu] = valid ? w1d : 0.f;
-    gw1c[mu] = valid ? fmaf(gEf, t, -z * d) : 0.f;
-  }
-  floatx4 acc[2][2];
-#pragma unroll
-  for (int R = 0; R < 2; ++R)
-#pragma unroll
-    for (int C = 0; C < 2; ++C) acc[R][C] = floatx4{0.f, 0.f, 0.f, 0.f};
-  // sum over the wavefront's 64 atoms of alpha q~^T - beta v~^T on MFMA
-#pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 32; ++k) {
-      A[lane * kLdsStride + k] = k < H ? (pass == 0 ? alpha[k] : -beta[k]) : 0.f;
-      B[lane * kLdsStride + k] = k < D ? (pass == 0 ? qs[k] : vs[k]) : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kb = 0; kb < 16; ++kb) {
-      const int atom = 4 * kb + lk;
-      float aop[2], bop[2];
-#pragma unroll
-      for (int R = 0; R < 2; ++R) aop[R] = A[atom * kLdsStride + 16 * R + lr];
-#pragma unroll
-      for (int C = 0; C < 2; ++C) bop[C] = B[atom * kLdsStride + 16 * C + lr];
-#pragma unroll
-      for (int R = 0; R < 2; ++R)
-#pragma unroll
-        for (int C = 0; C < 2; ++C)
-          acc[R][C] = __builtin_amdgcn_mfma_f32_16x16x4f32(aop[R], bop[C], acc[R][C], 0, 0, 0);
-    }
-  }
-  // column sums of alpha and of gE t - z d over the wavefront
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < 32; ++k) {
-    A[lane * kLdsStride + k] = k < H ? alpha[k] : 0.f;
-    B[lane * kLdsStride + k] = k < H ? gw1c[k] : 0.f;
-  }
-  __syncthreads();
-  float ca = 0.f, cb = 0.f;
-  if (lane < 32) {
-    for (int a = 0; a < 64; ++a) {
-      ca += A[a * kLdsStride + lane];
-      cb += B[a * kLdsStride + lane];
-    }
-  }
-  __syncthreads();
-  // combine the 4 wavefronts in FP64; tA is reused as [4][kGW + 64] floats
-  float* red = &tA[0][0];
-  constexpr int kW4 = kGW + 64;
-#pragma unroll
-  for (int R = 0; R < 2; ++R)
-#pragma unroll
-    for (int C = 0; C < 2; ++C)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) red[wave * kW4 + (16 * R + 4 * lk + r) * 32 + 16 * C + lr] = acc[R][C][r];
-  if (lane < 32) {
-    red[wave * kW4 + kGB0 + lane] = ca;
-    red[wave * kW4 + kGW1 + lane] = cb;
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < kW4; e += kBlock) {
-    double sum = 0.0;
-#pragma unroll
-    for (int w = 0; w < kBlock / 64; ++w) sum += (double)red[w * kW4 + e];
-    gpart[(int64_t)tile * kGradStride + e] = sum;
-  }
-}
-
-// Sum of v over the wavefront, added by its first lane to an LDS word.
-__device__ __forceinline__ void wave_add_lds(float v, float* dst) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  if ((threadIdx.x & 63) == 0) atomicAdd(dst, v);
-}
-
-// Adds v for centers of species ti into dst[ti * stride] (one species: dst).
-template <bool MULTI>
-__device__ __forceinline__ void wave_add_by_type(float v, int ti, int T, float* dst, int stride) {
-  if constexpr (MULTI) {
-    for (int t = 0; t < T; ++t) wave_add_lds(ti == t ? v : 0.f, dst + t * stride);
-  } else {
-    wave_add_lds(v, dst);
-  }
-}
-
-// Gradient of L = gE * E + sum_i gF_i . F_i with respect to the expansion
-// coefficients c of the radial functions (Section III.B) and the descriptor
-// scaler sigma. Each center contributes L_i = gE U_i - Fp_i . v_i (v_i: the
-// descriptor JVP along gF). With alpha and beta as in k_train_backward,
-// rho = sigma * (W0^T alpha) is dL_i/dq and -Fp = -sigma * (W0^T beta) is dL_i/dv.
+//   dL/db0 = -alpha,  dL/dw1 = gE t - z d,  dL/db1 = -gE.
+// With rho = sigma * (W0^T alpha) = dL/dq and -Fp = -sigma * (W0^T beta) = dL/dv
+// (Section III.B names the expansion coefficients c trainable):
+//  * scaler: dL/dsigma_k = q_k (W0^T alpha)_k - v_k (W0^T beta)_k;
 //  * radial: q_n and v_n are linear in c through the basis sums over the neighbours
 //    j of each species t, F_k = sum f_k(r_ij) and E_k = sum f'_k(r_ij) (u.w), so
 //    dL/dc^{t_i t}_{nk} += rho_n F_k - Fp_n E_k;
@@ -240,32 +19,109 @@ __device__ __forceinline__ void wave_add_by_type(float v, int ti, int T, float* 
 //    (plus, for the four-body term, Fp4 dq4/ds in A and rho4 dq4/ds - Fp4 (d^2q4/ds^2) sd
 //    in C), and each pair adds f_k (X_n - Z_n) - f'_k (u.w) Y_n to dL/dc_nk, with
 //    X_n = sum_lm C_nlm P_lm, Y_n = sum_lm A_nlm P_lm and
-//    Z_n = sum_lm A_nlm (grad P_lm . w - l P_lm (u.w)) / r;
-//  * scaler: dL/dsigma_k += q_k (W0^T alpha)_k - v_k (W0^T beta)_k.
-// Sums over the workgroup run in FP32 (wavefront shuffles, then LDS atomics); each
-// workgroup writes its sums as FP64 in the packed order [cR | cA | sigma].
-template <class S, bool MULTI>
+//    Z_n = sum_lm A_nlm (grad P_lm . w - l P_lm (u.w)) / r.
+#include "nep_fast.h"
+
+namespace nep {
+namespace {
+
+using namespace kern;
+
+// A row of gradient sums: [W0 sums (hidden-major) | alpha | gE t - z d | cR | cA | sigma].
+constexpr int kGradStride = 1408;
+constexpr int kGradRows = 64;   // rows that the workgroups share
+inline int grad_rows(int64_t N) {
+  const int nb = grid_blocks(N);
+  return nb < kGradRows ? nb : kGradRows;
+}
+
+// The force weights in sorted order, [N][3], and the rows cleared.
+__global__ void k_train_prep(int64_t N, const int32_t* __restrict__ perm, const float* __restrict__ gF,
+                             float* __restrict__ w, double* __restrict__ rows, int64_t nrow) {
+  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (int64_t k = p; k < nrow; k += (int64_t)gridDim.x * blockDim.x) rows[k] = 0.0;
+  if (!gF || p >= N) return;
+  const int64_t o = perm[p];
+  for (int c = 0; c < 3; ++c) w[3 * p + c] = gF[3 * o + c];
+}
+
+// The neighbours of one lane of a center: entries l, l + L, ... below k1, each with its FP64
+// position, force weight and species loaded while the entry before is worked on.
+template <bool MULTI, int L, class Body>
+__device__ __forceinline__ void for_each_train(const EvalBuffers& b, const float* __restrict__ w, int64_t i, int l,
+                                               int k1, Body&& body) {
+  if (k1 <= 0) return;
+  struct Item {
+    double x, y, z;
+    float w0, w1, w2;
+    int t;
+  };
+  const int64_t N = b.N;
+  auto load = [&](int p) {
+    const int32_t j = b.nbr[(uint64_t)(uint32_t)(p < k1 ? p : k1 - 1) * (uint64_t)N + i];
+    Item q;
+    q.x = b.x[j];
+    q.y = b.x[N + j];
+    q.z = b.x[2 * N + j];
+    q.w0 = w ? w[3 * (int64_t)j] : 0.f;
+    q.w1 = w ? w[3 * (int64_t)j + 1] : 0.f;
+    q.w2 = w ? w[3 * (int64_t)j + 2] : 0.f;
+    q.t = MULTI ? b.type[j] : 0;
+    return q;
+  };
+  Item q = load(l);
+  for (int p = l; p < k1; p += L) {
+    const Item n = load(p + L);
+    body(p, q);
+    q = n;
+  }
+}
+
+// Gradients of the network parameters and, with COEF, of the coefficients and the scaler,
+// summed over centers into `rows`. L lanes share a center: one pass over its list gives the
+// basis sums, the accumulators s and their JVP sd together (two accumulators per harmonic
+// and channel: one wavefront per SIMD); the network runs on MFMA with the wavefront's
+// centers as rows, as does the sum of the outer products over them; the angular
+// coefficients take a second pass. Sums over a wavefront are FP32, over wavefronts and
+// workgroups FP64.
+// A thread per center, with the descriptors, the radial and the angular JVP each in a pass
+// of their own and the descriptors computed again for the coefficients, took 287 us for
+// the network's gradient of 32,000 atoms and 57 + 89 us for both of 4,000 atoms (l <= 2
+// shape); with sincospi and coefficient gathers per pair in place of the tables.
+template <class S, bool MULTI, bool COEF, int L>
 __global__ void __launch_bounds__(kBlock, 1)
-k_train_cgrad(ModelDev m, EvalBuffers b, const float* __restrict__ gF, double gE, double* __restrict__ gpart) {
+k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, double* __restrict__ rows, int nrows) {
   constexpr int NR = S::NR, NA = S::NA, NC = S::NC, D = S::D, H = S::H, KR = S::KR, KA = S::KA;
   constexpr int TT = MULTI ? kMaxTypes : 1;
-  static_assert(kMaxTypes * kMaxTypes * (NR * KR + NA * KA) + D <= kGradStride, "partial row too short");
-  __shared__ float red[kMaxTypes * kMaxTypes * (NR * KR + NA * KA) + D];
-  const int T = MULTI ? m.T : 1;
-  const int oA = T * T * NR * KR, oS = oA + T * T * NA * KA;
-  const int nred = oS + D;
-  for (int e = threadIdx.x; e < nred; e += kBlock) red[e] = 0.f;
+  constexpr int CW = 64 / L;                      // centers of a wavefront
+  constexpr int RT = CW >= 16 ? CW / 16 : 1;      // their 16-row tiles
+  constexpr int TILE = 16 * RT * kNetStride;
+  constexpr int NCOEF = TT * TT * (NR * KR + NA * KA) + D;
+  constexpr int kNet = 32 * 32 + 2 * 32;          // a wavefront's network sums
+  static_assert(H * D + 2 * H + NCOEF <= kGradStride, "row too short");
+  static_assert(5 * TILE >= kNet, "the tiles hold a wavefront's network sums");
+  __shared__ NetLds<0> net;
+  __shared__ PairTab<S, MULTI> tab;
+  __shared__ float tiles[kBlock / 64][5 * TILE];  // q~, v~, h (alpha), z (beta), gE t - z d
+  __shared__ float red[kBlock / 64][COEF ? NCOEF : 1];
+  stage_network<S>(m, net);
+  if constexpr (MULTI) stage_pairs<S>(m, tab);
   __syncthreads();
   const int64_t N = b.N;
-  const int tile = xcd_tile(blockIdx.x, gridDim.x);
-  const int64_t i = (int64_t)tile * kBlock + threadIdx.x;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int lr = lane & 15, lk = lane >> 4;
+  const int64_t i = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * (kBlock / L) + threadIdx.x / L;
+  const int l = threadIdx.x % L;
   const bool valid = i < N;
-  const double* __restrict__ x = b.x;
-  const double Lx = b.box[0], Ly = b.box[1], Lz = b.box[2];
-  const float rcR_inv = 1.f / m.rcR, rcA_inv = 1.f / m.rcA;
+  const CutConst cutR = cut_const(m.rcR), cutA = cut_const(m.rcA);
+  const float kDR = -0.5f * kPiF * cutR.rc_inv, kYR = 4.f * cutR.rc_inv;
+  const float kDA = -0.5f * kPiF * cutA.rc_inv, kYA = 4.f * cutA.rc_inv;
   const double rcR2 = m.rcR64 * m.rcR64, rcA2 = m.rcA64 * m.rcA64;
+  const double Lx = b.box[0], Ly = b.box[1], Lz = b.box[2];
+  const double iLx = 1.0 / Lx, iLy = 1.0 / Ly, iLz = 1.0 / Lz;
 
-  float q[D], v[D], s[NA * NC], sd[NA * NC], Fk[TT][KR], Ek[TT][KR];
+  float q[D], v[D], s[NA * NC], sd[NA * NC];
+  float Fk[TT][KR], Ek[TT][KR];  // this lane's part of the basis sums per neighbour species
 #pragma unroll
   for (int k = 0; k < D; ++k) q[k] = v[k] = 0.f;
 #pragma unroll
@@ -274,258 +130,351 @@ k_train_cgrad(ModelDev m, EvalBuffers b, const float* __restrict__ gF, double gE
   for (int t = 0; t < TT; ++t)
 #pragma unroll
     for (int k = 0; k < KR; ++k) Fk[t][k] = Ek[t][k] = 0.f;
-  int ti = 0;
+  int ti = 0, kA = 0;
   double xi = 0, yi = 0, zi = 0;
   float wi0 = 0.f, wi1 = 0.f, wi2 = 0.f;
   if (valid) {
     ti = MULTI ? b.type[i] : 0;
-    xi = x[i];
-    yi = x[N + i];
-    zi = x[2 * N + i];
-    int nr = 0, na = 0;
-    ZblSeenFor<MULTI> zs;  // the ZBL terms do not depend on the parameters
-    desc_accumulate<S, MULTI>(m, b, i, ti, xi, yi, zi, Lx, Ly, Lz, q, s, zs, nr, na);
-    desc_finish<S>(s, q);
-    if (gF) {
-      wi0 = gF[i];
-      wi1 = gF[N + i];
-      wi2 = gF[2 * N + i];
+    xi = b.x[i];
+    yi = b.x[N + i];
+    zi = b.x[2 * N + i];
+    if (w) {
+      wi0 = w[3 * i];
+      wi1 = w[3 * i + 1];
+      wi2 = w[3 * i + 2];
     }
-    // radial basis sums per neighbour species
-    const int kR = radial_bound(b, i);
-    for (int p = 0; p < kR; ++p) {
-      const int32_t j = b.nbr[(int64_t)p * N + i];
-      float dx, dy, dz;
-      if (!pair_inside(x, N, j, xi, yi, zi, Lx, Ly, Lz, rcR2, dx, dy, dz)) continue;
-      const float r = sqrtf(dx * dx + dy * dy + dz * dz);
-      const float rinv = 1.f / r;
-      const int tj = MULTI ? b.type[j] : 0;
-      float f[KR], e[KR];
-      radial_basis<KR>(r, rcR_inv, f);
-      float uw = 0.f;
-      if (gF) {
-        radial_basis_deriv<KR>(r, rcR_inv, e);
-        uw = ((gF[j] - wi0) * dx + (gF[N + j] - wi1) * dy + (gF[2 * N + j] - wi2) * dz) * rinv;
-      } else {
+    kA = angular_bound(b, i);
+    // Fk, Ek hold sum f_c T_k and sum (f_c T_k)' (u.w) (k >= 1) and the k = 0 sums of f_c
+    for_each_train<MULTI, L>(b, w, i, l, radial_bound(b, i), [&](int p, const auto& e) {
+      double ex, ey, ez;
+      const double r2 = pair_r2_64(e.x, e.y, e.z, xi, yi, zi, Lx, Ly, Lz, iLx, iLy, iLz, ex, ey, ez);
+      if (!(r2 < rcR2)) return;
+      const float dx = (float)ex, dy = (float)ey, dz = (float)ez;
+      float r, rinv;
+      pair_r(dx, dy, dz, r, rinv);
+      const float w0 = e.w0 - wi0, w1 = e.w1 - wi1, w2 = e.w2 - wi2;
+      const float ux = dx * rinv, uy = dy * rinv, uz = dz * rinv;
+      const float uw = ux * w0 + uy * w1 + uz * w2;
+      {
+        const RadialGeo g = radial_geo<true>(r, cutR);
+        const float df = kDR * g.c * uw, xf = g.fc * (kYR * g.y) * uw;
+        float ft[TT], dt[TT], xt[TT];  // the factors for the neighbour's species, 0 for the others
 #pragma unroll
-        for (int k = 0; k < KR; ++k) e[k] = 0.f;
-      }
+        for (int t = 0; t < TT; ++t) {
+          const bool on = !MULTI || e.t == t;
+          ft[t] = on ? g.fc : 0.f;
+          dt[t] = on ? df : 0.f;
+          xt[t] = on ? xf : 0.f;
+          Fk[t][0] += ft[t];
+          Ek[t][0] += dt[t];
+        }
+        const float x2 = g.x + g.x;
+        float Tm = 1.f, T = g.x, Um = 0.f, U = 1.f;  // T_{k-1}, T_k, U_{k-2}, U_{k-1}
 #pragma unroll
-      for (int t = 0; t < TT; ++t) {
-        const bool on = !MULTI || tj == t;
+        for (int k = 1; k < KR; ++k) {
+          const float kU = (float)k * U;  // T_k'
 #pragma unroll
-        for (int k = 0; k < KR; ++k) {
-          Fk[t][k] += on ? f[k] : 0.f;
-          Ek[t][k] = fmaf(on ? e[k] : 0.f, uw, Ek[t][k]);
+          for (int t = 0; t < TT; ++t) {
+            Fk[t][k] = fmaf(ft[t], T, Fk[t][k]);
+            Ek[t][k] = fmaf(dt[t], T, fmaf(xt[t], kU, Ek[t][k]));
+          }
+          const float Tn = fmaf(x2, T, -Tm), Un = fmaf(x2, U, -Um);
+          Tm = T;
+          T = Tn;
+          Um = U;
+          U = Un;
         }
       }
-    }
-    if (gF) {
-      // radial JVP v_n = sum_t sum_k c^{t_i t}_{nk} E_k
+      if (p < kA && r2 < rcA2) {
+        // ds_nlm . w = g_n' (u.w) P_lm + g_n (grad P_lm . w - l P_lm (u.w)) / r
+        const RadialGeo g = radial_geo<true>(r, cutA);
+        float gn[NA], gu[NA];
+        if constexpr (MULTI) radial_cd_tab<S, true>(g.x, ang_tab(tab, ti, e.t), gn, gu);
+        else radial_cd_fast<NA, KA>(g.x, uniform_coeffs(m.hA), gn, gu);
+        const float df = kDA * g.c * uw, xf = g.fc * (kYA * g.y) * uw;
 #pragma unroll
-      for (int t = 0; t < TT; ++t) {
-        if (t >= T) break;
-        const float* c = m.cR + (ti * T + t) * NR * KR;
+        for (int n = 0; n < NA; ++n) {
+          gu[n] = fmaf(df, gn[n], xf * gu[n]);
+          gn[n] *= g.fc;
+        }
+        for_each_poly_grad<NC>(ux, uy, uz, [&](int lm, float P, auto px, auto py, auto pz) {
+          const float bb = fmac(w0, px, fmac(w1, py, fmac(w2, pz, -(float)comp_l(lm) * P * uw))) * rinv;
+#pragma unroll
+          for (int n = 0; n < NA; ++n) {
+            s[n * NC + lm] = fmaf(gn[n], P, s[n * NC + lm]);
+            sd[n * NC + lm] = fmaf(gu[n], P, fmaf(gn[n], bb, sd[n * NC + lm]));
+          }
+        });
+      }
+    });
+#pragma unroll
+    for (int t = 0; t < TT; ++t) {
+      // sum f_k = (sum f_c T_k + sum f_c) / 2, and its derivative likewise
+#pragma unroll
+      for (int k = 1; k < KR; ++k) {
+        Fk[t][k] = 0.5f * (Fk[t][k] + Fk[t][0]);
+        Ek[t][k] = 0.5f * (Ek[t][k] + Ek[t][0]);
+      }
+      auto add = [&](auto c) {
 #pragma unroll
         for (int n = 0; n < NR; ++n)
 #pragma unroll
-          for (int k = 0; k < KR; ++k) v[n] = fmaf(c[n * KR + k], Ek[t][k], v[n]);
-      }
-      // angular JVP sd_nlm = sum_j [g_n' (u.w) P_lm + g_n (grad P_lm . w - l P_lm (u.w)) / r]
-      const int kA = angular_bound(b, i);
-      for (int p = 0; p < kA; ++p) {
-        const int32_t j = b.nbr[(int64_t)p * N + i];
-        float dx, dy, dz;
-        if (!pair_inside(x, N, j, xi, yi, zi, Lx, Ly, Lz, rcA2, dx, dy, dz)) continue;
-        const float r = sqrtf(dx * dx + dy * dy + dz * dz);
-        const float rinv = 1.f / r;
-        const int tj = MULTI ? b.type[j] : 0;
-        float g[NA], dg[NA];
-        radial_g_dg<NA, KA>(r, rcA_inv, m.cA + (ti * m.T + tj) * NA * KA, g, dg);
-        const float w0 = gF[j] - wi0, w1 = gF[N + j] - wi1, w2 = gF[2 * N + j] - wi2;
-        const float ux = dx * rinv, uy = dy * rinv, uz = dz * rinv;
-        const float uw = ux * w0 + uy * w1 + uz * w2;
-        for_each_poly_grad<NC>(ux, uy, uz, [&](int lm, float P, float px, float py, float pz) {
-          const float a = uw * P;
-          const float bb = (px * w0 + py * w1 + pz * w2 - (float)comp_l(lm) * P * uw) * rinv;
-#pragma unroll
-          for (int n = 0; n < NA; ++n) sd[n * NC + lm] = fmaf(dg[n], a, fmaf(g[n], bb, sd[n * NC + lm]));
-        });
-      }
-#pragma unroll
-      for (int n = 0; n < NA; ++n)
-#pragma unroll
-        for (int lm = 0; lm < NC; ++lm) {
-          const int k = NR + (comp_l(lm) - 1) * NA + n;
-          v[k] = fmaf(2.f * kW[lm] * s[n * NC + lm], sd[n * NC + lm], v[k]);
-        }
-      if constexpr (S::FB) {
-#pragma unroll
-        for (int n = 0; n < NA; ++n) {
-          float d4[5];
-          fourbody_ds(s + n * NC, d4);
-#pragma unroll
-          for (int c = 0; c < 5; ++c) v[NR + S::L3 * NA + n] = fmaf(d4[c], sd[n * NC + 3 + c], v[NR + S::L3 * NA + n]);
-        }
-      }
-    }
-  }
-  // network: rho = sigma W0^T alpha, Fp = sigma W0^T beta
-  float al[H], be[H];
-  const float gEf = (float)gE;
-#pragma unroll
-  for (int mu = 0; mu < H; ++mu) {
-    float h = -m.b0[mu], z = 0.f;
-#pragma unroll
-    for (int k = 0; k < D; ++k) {
-      h = fmaf(m.W0[mu * D + k], q[k] * m.sigma[k], h);
-      z = fmaf(m.W0[mu * D + k], v[k] * m.sigma[k], z);
-    }
-    const float t = tanhf(h);
-    const float d = 1.f - t * t;
-    be[mu] = m.w1[mu] * d;
-    al[mu] = fmaf(gEf, be[mu], 2.f * z * m.w1[mu] * t * d);
-  }
-  float rho[D], fp[D];
-#pragma unroll
-  for (int k = 0; k < D; ++k) {
-    float sa = 0.f, sb = 0.f;
-#pragma unroll
-    for (int mu = 0; mu < H; ++mu) {
-      sa = fmaf(m.W0[mu * D + k], al[mu], sa);
-      sb = fmaf(m.W0[mu * D + k], be[mu], sb);
-    }
-    rho[k] = m.sigma[k] * sa;
-    fp[k] = m.sigma[k] * sb;
-    wave_add_lds(valid ? q[k] * sa - v[k] * sb : 0.f, red + oS + k);
-  }
-  // radial coefficients
-#pragma unroll
-  for (int t = 0; t < TT; ++t) {
-    if (t >= T) break;
-#pragma unroll
-    for (int n = 0; n < NR; ++n)
-#pragma unroll
-      for (int k = 0; k < KR; ++k)
-        wave_add_by_type<MULTI>(valid ? rho[n] * Fk[t][k] - fp[n] * Ek[t][k] : 0.f, ti, T,
-                                red + (t * NR + n) * KR + k, T * NR * KR);
-  }
-  // angular coefficients A (in place of s) and C (in place of sd)
-  if constexpr (S::FB) {
-#pragma unroll
-    for (int n = 0; n < NA; ++n) {
-      float d4[5], h4[5];
-      fourbody_ds(s + n * NC, d4);
-      fourbody_ds_dir(s + n * NC, sd + n * NC, h4);
-      const int k4 = NR + S::L3 * NA + n;
-#pragma unroll
-      for (int c = 0; c < 5; ++c) {
-        const int lm = 3 + c;
-        const int k = NR + NA + n;  // l = 2
-        const float a = 2.f * kW[lm] * fp[k] * s[n * NC + lm] + fp[k4] * d4[c];
-        const float cc = 2.f * kW[lm] * (rho[k] * s[n * NC + lm] - fp[k] * sd[n * NC + lm]) + rho[k4] * d4[c] -
-                         fp[k4] * h4[c];
-        s[n * NC + lm] = a;
-        sd[n * NC + lm] = cc;
-      }
-    }
-  }
-#pragma unroll
-  for (int n = 0; n < NA; ++n)
-#pragma unroll
-    for (int lm = 0; lm < NC; ++lm) {
-      if (S::FB && comp_l(lm) == 2) continue;
-      const int k = NR + (comp_l(lm) - 1) * NA + n;
-      const float a = 2.f * kW[lm] * fp[k] * s[n * NC + lm];
-      const float cc = 2.f * kW[lm] * (rho[k] * s[n * NC + lm] - fp[k] * sd[n * NC + lm]);
-      s[n * NC + lm] = a;
-      sd[n * NC + lm] = cc;
-    }
-  for (int t = 0; t < TT; ++t) {
-    if (t >= T) break;
-    float acc[NA * KA];
-#pragma unroll
-    for (int k = 0; k < NA * KA; ++k) acc[k] = 0.f;
-    if (valid) {
-      const int kA = angular_bound(b, i);
-      for (int p = 0; p < kA; ++p) {
-        const int32_t j = b.nbr[(int64_t)p * N + i];
-        float dx, dy, dz;
-        if (!pair_inside(x, N, j, xi, yi, zi, Lx, Ly, Lz, rcA2, dx, dy, dz)) continue;
-        if (MULTI && b.type[j] != t) continue;
-        const float r = sqrtf(dx * dx + dy * dy + dz * dz);
-        const float rinv = 1.f / r;
-        const float ux = dx * rinv, uy = dy * rinv, uz = dz * rinv;
-        float w0 = 0.f, w1 = 0.f, w2 = 0.f;
-        if (gF) {
-          w0 = gF[j] - wi0;
-          w1 = gF[N + j] - wi1;
-          w2 = gF[2 * N + j] - wi2;
-        }
-        const float uw = ux * w0 + uy * w1 + uz * w2;
-        float X[NA], Y[NA], Z[NA];
-#pragma unroll
-        for (int n = 0; n < NA; ++n) X[n] = Y[n] = Z[n] = 0.f;
-        for_each_poly_grad<NC>(ux, uy, uz, [&](int lm, float P, float px, float py, float pz) {
-          const float bb = (px * w0 + py * w1 + pz * w2 - (float)comp_l(lm) * P * uw) * rinv;
-#pragma unroll
-          for (int n = 0; n < NA; ++n) {
-            X[n] = fmaf(sd[n * NC + lm], P, X[n]);
-            Y[n] = fmaf(s[n * NC + lm], P, Y[n]);
-            Z[n] = fmaf(s[n * NC + lm], bb, Z[n]);
+          for (int k = 0; k < KR; ++k) {
+            q[n] = fmaf(c[n * KR + k], Fk[t][k], q[n]);
+            v[n] = fmaf(c[n * KR + k], Ek[t][k], v[n]);
           }
-        });
-        float f[KA], e[KA];
-        radial_basis<KA>(r, rcA_inv, f);
-        radial_basis_deriv<KA>(r, rcA_inv, e);
-#pragma unroll
-        for (int n = 0; n < NA; ++n) {
-          const float xz = X[n] - Z[n], yu = Y[n] * uw;
-#pragma unroll
-          for (int k = 0; k < KA; ++k) acc[n * KA + k] = fmaf(f[k], xz, fmaf(-e[k], yu, acc[n * KA + k]));
-        }
-      }
+      };
+      if constexpr (MULTI) add(tab.rad + (ti * kMaxTypes + t) * (NR * KR));
+      else add(uniform_coeffs(m.cR));
     }
+#pragma unroll
+    for (int n = 0; n < NR; ++n) {
+      q[n] = lanes_sum<L>(q[n]);
+      v[n] = lanes_sum<L>(v[n]);
+    }
+#pragma unroll
+    for (int k = 0; k < NA * NC; ++k) {
+      s[k] = lanes_sum<L>(s[k]);
+      sd[k] = lanes_sum<L>(sd[k]);
+    }
+    desc_finish<S>(s, q);
 #pragma unroll
     for (int n = 0; n < NA; ++n)
 #pragma unroll
-      for (int k = 0; k < KA; ++k)
-        wave_add_by_type<MULTI>(valid ? acc[n * KA + k] : 0.f, ti, T, red + oA + (t * NA + n) * KA + k,
-                                T * NA * KA);
+      for (int lm = 0; lm < NC; ++lm) {
+        const int k = NR + (comp_l(lm) - 1) * NA + n;
+        v[k] = fmaf(2.f * kW[lm] * s[n * NC + lm], sd[n * NC + lm], v[k]);
+      }
+    if constexpr (S::FB) {
+#pragma unroll
+      for (int n = 0; n < NA; ++n) {
+        float d4[5];
+        fourbody_ds(s + n * NC, d4);
+#pragma unroll
+        for (int c = 0; c < 5; ++c) v[NR + S::L3 * NA + n] = fmaf(d4[c], sd[n * NC + 3 + c], v[NR + S::L3 * NA + n]);
+      }
+    }
+  }
+  // network: rows of q~ and v~, then h and z, then alpha and beta (zero for the rows of no center)
+  float* tq = tiles[wave];
+  float* tv = tq + TILE;
+  float* ta = tq + 2 * TILE;
+  float* tb = tq + 3 * TILE;
+  float* tg = tq + 4 * TILE;
+  const int row = (lane / L) * kNetStride;
+#pragma unroll
+  for (int k = 0; k < 32; ++k)
+    if ((k & (L - 1)) == l) {
+      tq[row + k] = k < D ? q[k < D ? k : 0] * net.sigma[k] : 0.f;
+      tv[row + k] = k < D ? v[k < D ? k : 0] * net.sigma[k] : 0.f;
+    }
+  net_product<0, RT, true>(tq, ta, net);
+  net_product<0, RT, true>(tv, tb, net);
+  const float gEf = (float)gE;
+#pragma unroll
+  for (int mu0 = 0; mu0 < 32; mu0 += L) {
+    const int mu = mu0 + l;
+    const float t = tanhf(ta[row + mu] - net.b0[mu]), z = tb[row + mu], w1 = net.w1[mu];
+    const float d = 1.f - t * t, w1d = w1 * d;
+    ta[row + mu] = valid ? fmaf(gEf, w1d, 2.f * z * w1 * t * d) : 0.f;
+    tb[row + mu] = valid ? w1d : 0.f;
+    tg[row + mu] = valid ? fmaf(gEf, t, -z * d) : 0.f;
+  }
+  wave_lds_sync();
+  // sum over the wavefront's centers of alpha q~^T - beta v~^T, and of alpha and gE t - z d
+  floatx4 acc[2][2];
+#pragma unroll
+  for (int R = 0; R < 2; ++R)
+#pragma unroll
+    for (int C = 0; C < 2; ++C) acc[R][C] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int pass = 0; pass < 2; ++pass)
+#pragma unroll
+    for (int kb = 0; kb < CW / 4; ++kb) {
+      const int c0 = (4 * kb + lk) * kNetStride;
+      float aop[2], bop[2];
+#pragma unroll
+      for (int R = 0; R < 2; ++R) aop[R] = pass == 0 ? ta[c0 + 16 * R + lr] : -tb[c0 + 16 * R + lr];
+#pragma unroll
+      for (int C = 0; C < 2; ++C) bop[C] = pass == 0 ? tq[c0 + 16 * C + lr] : tv[c0 + 16 * C + lr];
+#pragma unroll
+      for (int R = 0; R < 2; ++R)
+#pragma unroll
+        for (int C = 0; C < 2; ++C)
+          acc[R][C] = __builtin_amdgcn_mfma_f32_16x16x4f32(aop[R], bop[C], acc[R][C], 0, 0, 0);
+    }
+  float ca = 0.f, cb = 0.f;
+  if (lane < 32)
+    for (int c = 0; c < CW; ++c) {
+      ca += ta[c * kNetStride + lane];
+      cb += tg[c * kNetStride + lane];
+    }
+  if constexpr (COEF) {
+    constexpr int oA = TT * TT * NR * KR, oS = oA + TT * TT * NA * KA;
+    float* rw = red[wave];
+    // the sum of x over the wavefront's lanes whose center has species tc, to entry e
+    auto total = [&](float x, int e) {
+      x = wave_sum_last(x);
+      if (lane == 63) rw[e] = x;
+    };
+    auto total_by_type = [&](float x, int e, int stride) {
+      if constexpr (MULTI) {
+#pragma unroll
+        for (int tc = 0; tc < TT; ++tc) total(ti == tc ? x : 0.f, e + tc * stride);
+      } else {
+        total(x, e);
+      }
+    };
+    net_product<0, RT, false>(ta, ta, net);
+    net_product<0, RT, false>(tb, tb, net);
+    // dL/dq and dU/dq of the lane's center (zero where there is none)
+    float rho[D], fp[D];
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+      const float sa = ta[row + k], sb = tb[row + k];
+      rho[k] = net.sigma[k] * sa;
+      fp[k] = net.sigma[k] * sb;
+      total((k & (L - 1)) == l ? q[k] * sa - v[k] * sb : 0.f, oS + k);
+    }
+    // radial coefficients [t_i][t][n][k], linear in the lanes' parts of the basis sums
+#pragma unroll
+    for (int t = 0; t < TT; ++t)
+#pragma unroll
+      for (int n = 0; n < NR; ++n)
+#pragma unroll
+        for (int k = 0; k < KR; ++k)
+          total_by_type(rho[n] * Fk[t][k] - fp[n] * Ek[t][k], (t * NR + n) * KR + k, TT * NR * KR);
+    // angular coefficients A (in place of s) and C (in place of sd)
+#pragma unroll
+    for (int n = 0; n < NA; ++n) {
+      float d4[5] = {}, h4[5] = {};
+      if constexpr (S::FB) {
+        fourbody_ds(s + n * NC, d4);
+        fourbody_ds_dir(s + n * NC, sd + n * NC, h4);
+      }
+#pragma unroll
+      for (int lm = 0; lm < NC; ++lm) {
+        const int k = NR + (comp_l(lm) - 1) * NA + n;
+        float a = 2.f * kW[lm] * fp[k] * s[n * NC + lm];
+        float c = 2.f * kW[lm] * (rho[k] * s[n * NC + lm] - fp[k] * sd[n * NC + lm]);
+        if constexpr (S::FB) {
+          if (comp_l(lm) == 2) {
+            const int k4 = NR + S::L3 * NA + n;
+            a = fmaf(fp[k4], d4[lm - 3], a);
+            c += rho[k4] * d4[lm - 3] - fp[k4] * h4[lm - 3];
+          }
+        }
+        s[n * NC + lm] = a;
+        sd[n * NC + lm] = c;
+      }
+    }
+    float gc[TT][NA * KA];
+#pragma unroll
+    for (int t = 0; t < TT; ++t)
+#pragma unroll
+      for (int k = 0; k < NA * KA; ++k) gc[t][k] = 0.f;
+    for_each_train<MULTI, L>(b, w, i, l, kA, [&](int, const auto& e) {
+      double ex, ey, ez;
+      const double r2 = pair_r2_64(e.x, e.y, e.z, xi, yi, zi, Lx, Ly, Lz, iLx, iLy, iLz, ex, ey, ez);
+      if (!(r2 < rcA2)) return;
+      const float dx = (float)ex, dy = (float)ey, dz = (float)ez;
+      float r, rinv;
+      pair_r(dx, dy, dz, r, rinv);
+      const float w0 = e.w0 - wi0, w1 = e.w1 - wi1, w2 = e.w2 - wi2;
+      const float ux = dx * rinv, uy = dy * rinv, uz = dz * rinv;
+      const float uw = ux * w0 + uy * w1 + uz * w2;
+      float X[NA], Y[NA], Z[NA];
+#pragma unroll
+      for (int n = 0; n < NA; ++n) X[n] = Y[n] = Z[n] = 0.f;
+      for_each_poly_grad<NC>(ux, uy, uz, [&](int lm, float P, auto px, auto py, auto pz) {
+        const float bb = fmac(w0, px, fmac(w1, py, fmac(w2, pz, -(float)comp_l(lm) * P * uw))) * rinv;
+#pragma unroll
+        for (int n = 0; n < NA; ++n) {
+          X[n] = fmaf(sd[n * NC + lm], P, X[n]);
+          Y[n] = fmaf(s[n * NC + lm], P, Y[n]);
+          Z[n] = fmaf(s[n * NC + lm], bb, Z[n]);
+        }
+      });
+      const RadialGeo g = radial_geo<true>(r, cutA);
+      // f_k and f'_k (u.w), from T_k and T_k' = k U_{k-1}
+      const float df = kDA * g.c * uw, xf = g.fc * (kYA * g.y) * uw;
+      const float x2 = g.x + g.x;
+      float Tm = 0.f, T = 1.f, Um = 0.f, U = 0.f;
+#pragma unroll
+      for (int k = 0; k < KA; ++k) {
+        const float f = 0.5f * g.fc * (T + 1.f);
+        const float fd = 0.5f * fmaf(df, T + 1.f, xf * ((float)k * U));
+#pragma unroll
+        for (int n = 0; n < NA; ++n) {
+          const float t1 = fmaf(f, X[n] - Z[n], -fd * Y[n]);
+#pragma unroll
+          for (int t = 0; t < TT; ++t) gc[t][n * KA + k] += !MULTI || e.t == t ? t1 : 0.f;
+        }
+        const float Tn = k == 0 ? g.x : fmaf(x2, T, -Tm);
+        const float Un = k == 0 ? 1.f : (k == 1 ? x2 : fmaf(x2, U, -Um));
+        Tm = T;
+        T = Tn;
+        Um = U;
+        U = Un;
+      }
+    });
+#pragma unroll
+    for (int t = 0; t < TT; ++t)
+#pragma unroll
+      for (int n = 0; n < NA; ++n)
+#pragma unroll
+        for (int k = 0; k < KA; ++k)
+          total_by_type(gc[t][n * KA + k], oA + (t * NA + n) * KA + k, TT * NA * KA);
+  }
+  // the four wavefronts in FP64, then the workgroup's row
+  __syncthreads();
+#pragma unroll
+  for (int R = 0; R < 2; ++R)
+#pragma unroll
+    for (int C = 0; C < 2; ++C)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) tq[(16 * R + 4 * lk + r) * 32 + 16 * C + lr] = acc[R][C][r];
+  if (lane < 32) {
+    tq[32 * 32 + lane] = ca;
+    tq[32 * 32 + 32 + lane] = cb;
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < nred; e += kBlock) gpart[(int64_t)tile * kGradStride + e] = (double)red[e];
-}
-
-// grad[e] for e < n (the [cR | cA | sigma] block) = sum over workgroups (FP64).
-__global__ void k_cgrad_reduce(const double* __restrict__ gpart, int nblocks, int n, float* __restrict__ grad,
-                               int accumulate) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
-  double sum = 0.0;
-  for (int blk = 0; blk < nblocks; ++blk) sum += gpart[(int64_t)blk * kGradStride + e];
-  grad[e] = accumulate ? (float)((double)grad[e] + sum) : (float)sum;
-}
-
-// grad[theta] = sum over workgroups (FP64), in theta's packed order.
-__global__ void k_grad_reduce(const double* __restrict__ gpart, int nblocks, int H, int D, double gE, int64_t N,
-                              float* __restrict__ grad, int accumulate) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  const int G = H * D + 2 * H + 1;
-  if (e >= G) return;
-  double out;
-  if (e == G - 1) {
-    out = -gE * (double)N;
-  } else {
-    int src;
-    double sign = 1.0;
-    if (e < H * D) src = (e / D) * 32 + (e % D);
-    else if (e < H * D + H) { src = kGB0 + (e - H * D); sign = -1.0; }
-    else src = kGW1 + (e - H * D - H);
-    double sum = 0.0;
-    for (int blk = 0; blk < nblocks; ++blk) sum += gpart[(int64_t)blk * kGradStride + src];
-    out = sign * sum;
+  double* out = rows + (int64_t)(blockIdx.x % nrows) * kGradStride;
+  auto add = [&](int e, float a0, float a1, float a2, float a3) {
+    unsafeAtomicAdd(out + e, ((double)a0 + (double)a1) + ((double)a2 + (double)a3));
+  };
+  for (int e = threadIdx.x; e < H * D + 2 * H; e += kBlock) {
+    const int u = e - H * D;
+    const int src = u < 0 ? (e / D) * 32 + e % D : (u < H ? 32 * 32 + u : 32 * 32 + 32 + u - H);
+    add(e, tiles[0][src], tiles[1][src], tiles[2][src], tiles[3][src]);
   }
+  if constexpr (COEF)
+    for (int e = threadIdx.x; e < NCOEF; e += kBlock)
+      add(H * D + 2 * H + e, red[0][e], red[1][e], red[2][e], red[3][e]);
+}
+
+// The gradient from the rows, in packed order: [cR | cA | sigma] first when ncoef > 0, then
+// [W0 | b0 | w1 | b1]. Four threads to an entry, each a quarter of the rows.
+__global__ void __launch_bounds__(kBlock)
+k_grad_finish(const double* __restrict__ rows, int nrows, int H, int D, int ncoef, double gE, int64_t N,
+              float* __restrict__ grad, int accumulate) {
+  __shared__ double sh[kBlock];
+  const int e = blockIdx.x * (kBlock / 4) + threadIdx.x % (kBlock / 4), part = threadIdx.x / (kBlock / 4);
+  const int G = H * D + 2 * H + 1;
+  const int u = e - ncoef;  // entry of the network block
+  const int src = u < 0 ? G - 1 + e : u;
+  double sum = 0.0;
+  if (e < ncoef + G - 1) {
+#pragma unroll 4
+    for (int r = part; r < nrows; r += 4) sum += rows[(int64_t)r * kGradStride + src];
+  }
+  sh[threadIdx.x] = sum;
+  __syncthreads();
+  if (part != 0 || e >= ncoef + G) return;
+  const int t = threadIdx.x;
+  double out = (sh[t] + sh[t + kBlock / 4]) + (sh[t + kBlock / 2] + sh[t + 3 * (kBlock / 4)]);
+  if (u >= H * D && u < H * D + H) out = -out;  // dL/db0 = -sum alpha
+  if (u == G - 1) out = -gE * (double)N;
   grad[e] = accumulate ? (float)((double)grad[e] + out) : (float)out;
 }
 
@@ -542,29 +491,45 @@ __global__ void k_adam(float* __restrict__ theta, const float* __restrict__ g, f
   theta[k] = (float)((double)theta[k] - lr * (a / c1) / (sqrt(b / c2) + eps));
 }
 
+// Lanes per center: as many as keep one wavefront (what the full shape's registers allow)
+// on each of the chip's 1,024 SIMDs; above that the fewest, since every lane more costs its
+// share of the sums over lanes. The l <= 2 shapes fit two wavefronts and stay at four lanes.
+// us of a backward call, network and coefficients:
+//             full shape, L = 2     4    16    l <= 2, L = 2     4    16
+//   4,000                   149    95    53               43    36    30
+//   8,788                   142    87   125               43    35    48
+//   32,000                  150   168   307               45    43    92
+//   256,000                1081  1244  2359              272   231   623
 template <class S>
-hipError_t launch_backward_shape(const ModelDev& m, const TrainBuffers& t, hipStream_t st) {
-  const int nb = grid_blocks(t.e.N);
-  if (m.T > 1)
-    hipLaunchKernelGGL((k_train_backward<S, true>), dim3(nb), dim3(kBlock), 0, st, m, t.e, t.gF, t.gE, t.gpart);
-  else
-    hipLaunchKernelGGL((k_train_backward<S, false>), dim3(nb), dim3(kBlock), 0, st, m, t.e, t.gF, t.gE, t.gpart);
-  const int G = m.H * m.D + 2 * m.H + 1;
-  hipLaunchKernelGGL(k_grad_reduce, dim3(grid_blocks(G)), dim3(kBlock), 0, st, t.gpart, nb, m.H, m.D, t.gE,
-                     t.e.N, t.grad, t.accumulate);
-  return hipGetLastError();
+int train_lanes(int64_t N) {
+  constexpr int64_t kLanes = 65536;
+  return N * 16 <= kLanes ? 16 : (N * 4 <= kLanes || S::L3 <= 2 ? 4 : 2);
 }
 
-template <class S>
-hipError_t launch_cgrad_shape(const ModelDev& m, const TrainBuffers& t, hipStream_t st) {
-  const int nb = grid_blocks(t.e.N);
-  if (m.T > 1)
-    hipLaunchKernelGGL((k_train_cgrad<S, true>), dim3(nb), dim3(kBlock), 0, st, m, t.e, t.gF, t.gE, t.gpart);
-  else
-    hipLaunchKernelGGL((k_train_cgrad<S, false>), dim3(nb), dim3(kBlock), 0, st, m, t.e, t.gF, t.gE, t.gpart);
-  const int n = m.T * m.T * (m.nR * m.kR + m.nA * m.kA) + m.D;
-  hipLaunchKernelGGL(k_cgrad_reduce, dim3(grid_blocks(n)), dim3(kBlock), 0, st, t.gpart, nb, n, t.grad,
-                     t.accumulate);
+template <class S, bool MULTI, bool COEF>
+void launch_grad(const ModelDev& m, const TrainBuffers& t, int nrows, hipStream_t st) {
+  const float* w = t.gF ? t.w : nullptr;
+  const int L = train_lanes<S>(t.e.N);
+  const dim3 nb(grid_blocks(t.e.N, kBlock / L));
+  if (L == 16)
+    hipLaunchKernelGGL((k_train_grad<S, MULTI, COEF, 16>), nb, dim3(kBlock), 0, st, m, t.e, w, t.gE, t.gpart, nrows);
+  else if (L == 4)
+    hipLaunchKernelGGL((k_train_grad<S, MULTI, COEF, 4>), nb, dim3(kBlock), 0, st, m, t.e, w, t.gE, t.gpart, nrows);
+  else if constexpr (S::L3 > 2)
+    hipLaunchKernelGGL((k_train_grad<S, MULTI, COEF, 2>), nb, dim3(kBlock), 0, st, m, t.e, w, t.gE, t.gpart, nrows);
+}
+
+template <class S, bool COEF>
+hipError_t launch_backward_shape(const ModelDev& m, const TrainBuffers& t, hipStream_t st) {
+  const int nrows = grad_rows(t.e.N);
+  hipLaunchKernelGGL(k_train_prep, dim3(grid_blocks(t.gF ? t.e.N : (int64_t)nrows * kGradStride)), dim3(kBlock), 0, st,
+                     t.e.N, t.perm, t.gF, t.w, t.gpart, (int64_t)nrows * kGradStride);
+  if (m.T > 1) launch_grad<S, true, COEF>(m, t, nrows, st);
+  else launch_grad<S, false, COEF>(m, t, nrows, st);
+  const int ncoef = COEF ? m.T * m.T * (m.nR * m.kR + m.nA * m.kA) + m.D : 0;
+  const int G = m.H * m.D + 2 * m.H + 1;
+  hipLaunchKernelGGL(k_grad_finish, dim3(grid_blocks(ncoef + G, kBlock / 4)), dim3(kBlock), 0, st, t.gpart, nrows,
+                     m.H, m.D, ncoef, t.gE, t.e.N, t.grad, t.accumulate);
   return hipGetLastError();
 }
 
@@ -603,50 +568,41 @@ hipError_t launch_adam(float* theta, const float* g, float* m1, float* m2, int64
   return hipGetLastError();
 }
 
-int train_partial_blocks(int64_t N) { return grid_blocks(N); }
 int train_grad_stride() { return kGradStride; }
 
 hipError_t launch_train_forward(const ModelDev& m, const float* theta, const EvalBuffers& b, hipStream_t st) {
   return launch_eval(with_theta(m, theta), 0, b, st);
 }
 
-int param_block_offset(const ModelDev& m) {
-  return m.T * m.T * (m.nR * m.kR + m.nA * m.kA) + m.D;
+// The model with every parameter taken from `params` and its derived radial tables, which the
+// kernels read the coefficients through, built from this vector.
+static hipError_t params_model(const ModelDev& m, const float* params, ModelDev& mp, hipStream_t st) {
+  mp = with_params(m, params);
+  mp.hR = m.hscratch;
+  mp.hA = m.hscratch + (int64_t)m.T * m.T * m.nR * (2 * m.kR - 1);
+  return launch_derive_coeffs(m.T, m.nR, m.kR, m.nA, m.kA, mp.cR, mp.cA, m.hscratch, const_cast<float*>(mp.hA), st);
 }
 
 hipError_t launch_train_forward_params(const ModelDev& m, const float* params, const EvalBuffers& b,
                                        hipStream_t st) {
-  // the evaluation kernels read the radial coefficients through their derived tables:
-  // build them from this vector's coefficients
-  ModelDev mp = with_params(m, params);
-  mp.hR = m.hscratch;
-  mp.hA = m.hscratch + (int64_t)m.T * m.T * m.nR * (2 * m.kR - 1);
-  hipError_t e = launch_derive_coeffs(m.T, m.nR, m.kR, m.nA, m.kA, mp.cR, mp.cA, m.hscratch,
-                                      const_cast<float*>(mp.hA), st);
-  if (e != hipSuccess) return e;
-  return launch_eval(mp, 0, b, st);
+  ModelDev mp;
+  const hipError_t e = params_model(m, params, mp, st);
+  return e != hipSuccess ? e : launch_eval(mp, 0, b, st);
 }
 
 hipError_t launch_train_backward_params(const ModelDev& m, const TrainBuffers& t, hipStream_t st) {
-  const ModelDev mp = with_params(m, t.theta);
-  TrainBuffers tn = t;
-  tn.grad = t.grad + param_block_offset(m);
-  hipError_t e;
-  if (is_shape<FullShape>(mp)) {
-    if ((e = launch_backward_shape<FullShape>(mp, tn, st)) != hipSuccess) return e;
-    return launch_cgrad_shape<FullShape>(mp, t, st);
-  }
-  if (is_shape<SurShape>(mp)) {
-    if ((e = launch_backward_shape<SurShape>(mp, tn, st)) != hipSuccess) return e;
-    return launch_cgrad_shape<SurShape>(mp, t, st);
-  }
+  ModelDev mp;
+  const hipError_t e = params_model(m, t.theta, mp, st);
+  if (e != hipSuccess) return e;
+  if (is_shape<FullShape>(mp)) return launch_backward_shape<FullShape, true>(mp, t, st);
+  if (is_shape<SurShape>(mp)) return launch_backward_shape<SurShape, true>(mp, t, st);
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_train_backward(const ModelDev& m, const TrainBuffers& t, hipStream_t st) {
   const ModelDev mt = with_theta(m, t.theta);
-  if (is_shape<FullShape>(mt)) return launch_backward_shape<FullShape>(mt, t, st);
-  if (is_shape<SurShape>(mt)) return launch_backward_shape<SurShape>(mt, t, st);
+  if (is_shape<FullShape>(mt)) return launch_backward_shape<FullShape, false>(mt, t, st);
+  if (is_shape<SurShape>(mt)) return launch_backward_shape<SurShape, false>(mt, t, st);
   return hipErrorInvalidValue;
 }
 
