@@ -799,7 +799,7 @@ int nep_compute_energy_forces_virial(nep_system* s, int32_t slot, int32_t precis
   double* F64 = s->x_alt;
   if (precision == NEP_FP64) {
     HIPCHK(launch_eval64(s->mdev[slot], s->m64[slot], eval_buffers(s, slot), U64, U64 + N, F64, s->st));
-    s->ew_rows = s->nblocks;
+    s->ew_rows = eval64_rows(N);
     s->force_valid[slot] = false;
   } else if ((st = do_eval(s, slot, precision))) {
     return st;

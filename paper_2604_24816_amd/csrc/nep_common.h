@@ -315,6 +315,8 @@ struct Model64 {
 // U64 [N] and Fp64 [D][N] are its per-atom energies and dU/dq.
 hipError_t launch_eval64(const ModelDev& m, const Model64& p, const EvalBuffers& b, double* U64, double* Fp64,
                          double* F64, hipStream_t st);
+// Rows of energy and virial partials it writes.
+int eval64_rows(int64_t N);
 hipError_t launch_scalar_out64(int64_t N, const int32_t* perm, const double* u, double* out, hipStream_t st);
 // FP64 gradient of gE E + sum gF . F with respect to the packed parameters (n_params
 // values, overwritten), gF_sorted [3][N] in sorted order or null.
