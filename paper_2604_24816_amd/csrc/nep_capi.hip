@@ -359,7 +359,7 @@ void prof_pair(nep_system* s, hipEvent_t* base, int a, int b, int group);
 int do_eval(nep_system* s, int slot, int prec) {
   hipEvent_t* ev = prof_take(s, 3);
   HIPCHK(launch_eval(s->mdev[slot], prec, eval_buffers(s, slot), s->st, ev));
-  s->ew_rows = eval_rows(s->N);
+  s->ew_rows = eval_rows(s->mdev[slot], s->N);
   if (ev) {
     prof_pair(s, ev, 0, 1, slot == 0 ? 0 : 4);
     prof_pair(s, ev, 1, 2, slot == 0 ? 1 : 5);
@@ -1132,7 +1132,7 @@ int nep_train_forward(nep_system* s, int32_t slot, const float* theta, double* e
   if (!s || !theta || !energy || slot < 0 || slot > 1 || !s->has_model[slot]) return fail(s, NEP_ERR_ARG, "bad argument");
   if (!s->have_list) return fail(s, NEP_ERR_STALE_LIST, "build the neighbour lists first");
   HIPCHK(launch_train_forward(s->mdev[slot], theta, eval_buffers(s, slot), s->st));
-  s->ew_rows = eval_rows(s->N);
+  s->ew_rows = eval_rows(s->mdev[slot], s->N);
   s->force_valid[slot] = false;
   int st;
   if ((st = reduce_ew(s, 0))) return st;
@@ -1168,7 +1168,7 @@ int nep_train_forward_params(nep_system* s, int32_t slot, const float* params, d
   if (!s || !params || !energy || slot < 0 || slot > 1 || !s->has_model[slot]) return fail(s, NEP_ERR_ARG, "bad argument");
   if (!s->have_list) return fail(s, NEP_ERR_STALE_LIST, "build the neighbour lists first");
   HIPCHK(launch_train_forward_params(s->mdev[slot], params, eval_buffers(s, slot), s->st));
-  s->ew_rows = eval_rows(s->N);
+  s->ew_rows = eval_rows(s->mdev[slot], s->N);
   s->force_valid[slot] = false;
   int st;
   if ((st = reduce_ew(s, 0))) return st;

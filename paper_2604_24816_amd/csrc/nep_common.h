@@ -261,7 +261,7 @@ struct EvalBuffers {
   uint4* rec1;           // [N][4] the records' second plane (two species)
   float* G;              // [nA * ncomp][N] dU/ds for the angular accumulators
   float* F;              // [3][N] forces (FP32 accumulation)
-  double* ew;            // [eval_rows(N)][kPartialStride] energy and virial partials
+  double* ew;            // [eval_rows()][kPartialStride] energy and virial partials
   int32_t* flags;
   int flag_r, flag_a;    // flag words holding this model's last radial / angular bin
   int deterministic;     // 1: forces gathered in a fixed order, no atomics (k_force<..., true>)
@@ -276,10 +276,8 @@ hipError_t launch_derive_coeffs(int T, int nR, int kR, int nA, int kA, const flo
 // two kernels and after the force kernel.
 hipError_t launch_eval(const ModelDev& m, int precision, const EvalBuffers& b, hipStream_t st,
                        hipEvent_t* ev = nullptr);
-// Lanes that share a center in the evaluation kernels for a system of N atoms, and the
-// rows of energy and virial partials (EvalBuffers::ew) an evaluation writes.
-int eval_lanes(int64_t N);
-int eval_rows(int64_t N);
+// Rows of energy and virial partials (EvalBuffers::ew) an evaluation writes.
+int eval_rows(const ModelDev& m, int64_t N);
 
 // MD and reductions (nep_md.hip)
 struct MassTable {

@@ -1,6 +1,6 @@
 // NEP energy/force evaluation on gfx950: two kernels per force evaluation, one thread per
 // center, or in small systems L = 2 to 16 lanes per center that take its list entries in
-// turn (eval_lanes).
+// turn (desc_lanes, force_lanes).
 //
 //   k_desc_net  (256-thread workgroups)
 //     1. radial descriptors q_n = sum_j g_n(r_ij) (Section III.B) and angular
@@ -26,7 +26,6 @@
 //     wrote) and virial are summed per workgroup in FP64.
 //   Pair arithmetic in both comes from nep_fast.h.
 #include "nep_fast.h"
-#include <type_traits>
 
 namespace nep {
 namespace {
@@ -911,28 +910,71 @@ __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, 
 }
 
 template <class S, int PREC, bool MULTI, int L>
-hipError_t launch_lanes(const ModelDev& m, const EvalBuffers& b, hipStream_t st, hipEvent_t* ev) {
-  const int nb = grid_blocks(b.N, kBlock / L);
-  if (ev) (void)hipEventRecord(ev[0], st);
-  hipLaunchKernelGGL((k_desc_net<S, PREC, MULTI, L>), dim3(nb), dim3(kBlock), 0, st, m, b);
-  if (ev) (void)hipEventRecord(ev[1], st);
-  if (b.deterministic)
-    hipLaunchKernelGGL((k_force<S, MULTI, true, L>), dim3(nb), dim3(kBlock), 0, st, m, b);
-  else
-    hipLaunchKernelGGL((k_force<S, MULTI, false, L>), dim3(nb), dim3(kBlock), 0, st, m, b);
-  if (ev) (void)hipEventRecord(ev[2], st);
-  return hipGetLastError();
+void launch_desc(const ModelDev& m, const EvalBuffers& b, hipStream_t st) {
+  hipLaunchKernelGGL((k_desc_net<S, PREC, MULTI, L>), dim3(grid_blocks(b.N, kBlock / L)), dim3(kBlock), 0, st, m, b);
+}
+template <class S, bool MULTI, int L>
+void launch_force(const ModelDev& m, const EvalBuffers& b, hipStream_t st) {
+  const dim3 nb(grid_blocks(b.N, kBlock / L));
+  if (b.deterministic) hipLaunchKernelGGL((k_force<S, MULTI, true, L>), nb, dim3(kBlock), 0, st, m, b);
+  else hipLaunchKernelGGL((k_force<S, MULTI, false, L>), nb, dim3(kBlock), 0, st, m, b);
 }
 
+// One thread per center fills the chip (1,024 SIMDs, two wavefronts each) from about 131,072
+// atoms on; below, a wavefront's own latency is the kernel's time (k_force 102 us from 256
+// to 32,000 atoms), so L lanes share a center, as many as keep N L <= 131072. On both sides
+// of that line, us of k_desc_net + k_force, one species:
+//   N         L = 1    2    4    8   16
+//   4,000       156  101   65   47   41
+//   13,500      160  102   67   61   85
+//   32,000      162  109   88  111  157
+//   62,500      176  143  158  198  284
+//   108,000     224  249  259  316  470
+// More lanes cost per wavefront (the sums over lanes, a halo to clear and flush per 256 / L
+// centers), fewer leave SIMDs idle.
+constexpr int64_t kFillLanes = 131072;
+constexpr int kMaxLanes = 16;
+int desc_lanes(int64_t N) {
+  int L = kMaxLanes;
+  while (L > 1 && N * L > kFillLanes) L /= 2;
+  return L;
+}
+// The force kernel of the full shape also takes four lanes where that makes two or three
+// short rounds of workgroups in place of one that leaves a quarter to a half of the chip
+// idle: up to 3/4 of 65,536 and of 131,072 atoms. us, one species / two / two deterministic:
+//   N         L = 1         2              4
+//   46,000      111 133 220   90 105 166    87 109 134
+//   62,500      115 135 220   92 106 169   100 115 161
+//   80,000      155 192 341  146 198 250   146 166 205
+//   120,000     154 192 354  167 197 312   185 215 298
+// Both modes take the same lanes, since the virial's partial sums follow them.
+int force_lanes(const ModelDev& m, int64_t N) {
+  if (m.L3 > 2 && ((N > 32768 && N <= 49152) || (N > 65536 && N <= 98304))) return 4;
+  return desc_lanes(N);
+}
+
+// ev (nullable): three events recorded before the descriptor kernel, between the two
+// kernels and after the force kernel.
 template <class S, int PREC, bool MULTI>
 hipError_t launch_pair(const ModelDev& m, const EvalBuffers& b, hipStream_t st, hipEvent_t* ev) {
-  switch (eval_lanes(b.N)) {
-    case 16: return launch_lanes<S, PREC, MULTI, 16>(m, b, st, ev);
-    case 8: return launch_lanes<S, PREC, MULTI, 8>(m, b, st, ev);
-    case 4: return launch_lanes<S, PREC, MULTI, 4>(m, b, st, ev);
-    case 2: return launch_lanes<S, PREC, MULTI, 2>(m, b, st, ev);
-    default: return launch_lanes<S, PREC, MULTI, 1>(m, b, st, ev);
+  if (ev) (void)hipEventRecord(ev[0], st);
+  switch (desc_lanes(b.N)) {
+    case 16: launch_desc<S, PREC, MULTI, 16>(m, b, st); break;
+    case 8: launch_desc<S, PREC, MULTI, 8>(m, b, st); break;
+    case 4: launch_desc<S, PREC, MULTI, 4>(m, b, st); break;
+    case 2: launch_desc<S, PREC, MULTI, 2>(m, b, st); break;
+    default: launch_desc<S, PREC, MULTI, 1>(m, b, st); break;
   }
+  if (ev) (void)hipEventRecord(ev[1], st);
+  switch (force_lanes(m, b.N)) {
+    case 16: launch_force<S, MULTI, 16>(m, b, st); break;
+    case 8: launch_force<S, MULTI, 8>(m, b, st); break;
+    case 4: launch_force<S, MULTI, 4>(m, b, st); break;
+    case 2: launch_force<S, MULTI, 2>(m, b, st); break;
+    default: launch_force<S, MULTI, 1>(m, b, st); break;
+  }
+  if (ev) (void)hipEventRecord(ev[2], st);
+  return hipGetLastError();
 }
 
 template <class S>
@@ -978,28 +1020,7 @@ hipError_t launch_derive_coeffs(int T, int nR, int kR, int nA, int kA, const flo
 
 bool eval_supported(const ModelDev& m) { return is_shape<FullShape>(m) || is_shape<SurShape>(m); }
 
-// One thread per center fills the chip (1,024 SIMDs, two wavefronts each) from about 131,072
-// atoms on; below, a wavefront's own latency is the kernel's time (k_force 102 us from 256
-// to 32,000 atoms), so L lanes share a center, as many as keep N L <= 131072. On both sides
-// of that line, us of k_desc_net + k_force, one species:
-//   N         L = 1    2    4    8   16
-//   4,000       156  101   65   47   41
-//   13,500      160  102   67   61   85
-//   32,000      162  109   88  111  157
-//   62,500      176  143  158  198  284
-//   108,000     224  249  259  316  470
-// More lanes cost per wavefront (the sums over lanes, a halo to clear and flush per 256 / L
-// centers), fewer leave SIMDs idle.
-constexpr int64_t kFillLanes = 131072;
-constexpr int kMaxLanes = 16;
-
-int eval_lanes(int64_t N) {
-  int L = kMaxLanes;
-  while (L > 1 && N * L > kFillLanes) L /= 2;
-  return L;
-}
-
-int eval_rows(int64_t N) { return grid_blocks(N, kBlock / eval_lanes(N)); }
+int eval_rows(const ModelDev& m, int64_t N) { return grid_blocks(N, kBlock / force_lanes(m, N)); }
 
 hipError_t launch_eval(const ModelDev& m, int precision, const EvalBuffers& b, hipStream_t st,
                        hipEvent_t* ev) {

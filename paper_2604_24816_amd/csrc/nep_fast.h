@@ -131,17 +131,19 @@ __device__ __forceinline__ void radial_cd_fast(float x, CP h, float* C, float* D
 // ---------------------------------------------------------------- two species
 // With two species the coefficients depend on the pair's species, which differ from lane to
 // lane, so a pair's table is read from LDS (at most four distinct addresses per load, on
-// different banks) instead of held in scalar registers: ang, the angular derived tables of
-// each (center, neighbour) species pair, term by term ([k] (h_0k .. h_4k, d_0k .. d_4k, 0, 0),
-// three wide loads per term of both sums); rad, the radial coefficients c_nk. Gathering the
-// tables from global memory made the two-species kernels 2.2 (k_force) and 2.6 (k_desc_net)
-// times slower than the one-species ones.
+// different banks) instead of held in scalar registers: ang, the coefficients h_nk of the
+// angular derived table of each (center, neighbour) species pair, as 16-byte words
+// ([k] h_0k .. h_3k, then h_40 .. h_48: twelve loads for both sums, which share them, since
+// d_n(k-1) = k h_nk); rad, the radial coefficients c_nk. Gathering the tables from global
+// memory made the two-species kernels 2.2 (k_force) and 2.6 (k_desc_net) times slower than
+// the one-species ones. The force kernel's atomics keep the LDS busy, so its reads count:
+// with the d table read as well (27 loads) it took 1,333 us for the 820,800-atom alloy.
 template <class S, bool MULTI>
 struct PairTab {
-  static constexpr int kTerm = 12;
-  static constexpr int kAng = S::KA * kTerm, kRad = S::NR * S::KR;
+  static_assert(S::NA == 5, "a term is one 16-byte word and a scalar");
+  static constexpr int kLast = 4 * S::KA;  // h_40 ..
+  static constexpr int kAng = (5 * S::KA + 3) / 4 * 4, kRad = S::NR * S::KR;
   static constexpr int kPairs = MULTI ? kMaxTypes * kMaxTypes : 0;
-  static_assert(2 * S::NA <= kTerm, "a term of both sums fits its slot");
   alignas(16) float ang[kPairs * kAng + 4];
   float rad[kPairs * kRad + 4];
 };
@@ -150,13 +152,10 @@ template <class S>
 __device__ __forceinline__ void stage_pairs(const ModelDev& m, PairTab<S, true>& t) {
   using P = PairTab<S, true>;
   constexpr int NA = S::NA, KA = S::KA;
-  for (int e = threadIdx.x; e < m.T * m.T * KA * 2 * NA; e += kBlock) {
-    const int pr = e / (KA * 2 * NA), k = e / (2 * NA) % KA, c = e % (2 * NA), n = c % NA;
-    const float* h = m.hA + (int64_t)pr * derived_block<NA, KA>();
-    float v = 0.f;
-    if (c < NA) v = h[n * KA + k];
-    else if (k > 0) v = h[NA * KA + n * (KA - 1) + k - 1];
-    t.ang[(pr / m.T * kMaxTypes + pr % m.T) * P::kAng + k * P::kTerm + c] = v;
+  for (int e = threadIdx.x; e < m.T * m.T * NA * KA; e += kBlock) {
+    const int pr = e / (NA * KA), n = e / KA % NA, k = e % KA;
+    t.ang[(pr / m.T * kMaxTypes + pr % m.T) * P::kAng + (n < 4 ? 4 * k + n : P::kLast + k)] =
+        m.hA[(int64_t)pr * derived_block<NA, KA>() + n * KA + k];
   }
   for (int e = threadIdx.x; e < m.T * m.T * P::kRad; e += kBlock) {
     const int pr = e / P::kRad;
@@ -168,23 +167,22 @@ __device__ __forceinline__ const float* ang_tab(const PairTab<S, true>& t, int t
   return t.ang + (tc * kMaxTypes + tk) * PairTab<S, true>::kAng;
 }
 
-// The channel sums C_n (and with DERIV D_n) from a species pair's table.
+// The channel sums C_n (and with DERIV D_n = sum_k h_nk T_k', T_k' = k U_{k-1}) from a
+// species pair's table.
 template <class S, bool DERIV>
 __device__ __forceinline__ void radial_cd_tab(float x, const float* tab, float* C, float* D) {
-  constexpr int NA = S::NA, KA = S::KA, kTerm = PairTab<S, true>::kTerm;
+  constexpr int NA = S::NA, KA = S::KA, kLast = PairTab<S, true>::kLast;
   const float x2 = x + x;
   float Tm = 0.f, T = 1.f;  // T_{k-1}, T_k
   float Um = 0.f, U = 0.f;  // U_{k-2}, U_{k-1}
 #pragma unroll
   for (int k = 0; k < KA; ++k) {
+    const float dT = (float)k * U;
 #pragma unroll
-    for (int n = 0; n < NA; ++n) C[n] = k == 0 ? tab[n] : fmaf(tab[k * kTerm + n], T, C[n]);
-    if (DERIV && k > 0) {
-#pragma unroll
-      for (int n = 0; n < NA; ++n) {
-        const float d = tab[k * kTerm + NA + n];
-        D[n] = k == 1 ? d : fmaf(d, U, D[n]);
-      }
+    for (int n = 0; n < NA; ++n) {
+      const float h = tab[n < 4 ? 4 * k + n : kLast + k];
+      C[n] = k == 0 ? h : fmaf(h, T, C[n]);
+      if (DERIV && k > 0) D[n] = k == 1 ? h : fmaf(h, dT, D[n]);
     }
     const float Tn = k == 0 ? x : fmaf(x2, T, -Tm);
     Tm = T;

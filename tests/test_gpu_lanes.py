@@ -1,6 +1,6 @@
 """Evaluation with several lanes to a center: system sizes on both sides of every change of
-the lane count (N L <= 131072, L = 16, 8, 4, 2, 1) and of the workgroup tiles, against the
-FP64 oracle.
+the lane counts (N L <= 131072, L = 16, 8, 4, 2, 1; four lanes in the force kernel up to
+49,152 and from 65,537 to 98,304 atoms) and of the workgroup tiles, against the FP64 oracle.
 
 Bars are the FP32 path's stated ones (per-atom energy 1e-6 eV, forces 1e-4 eV/A, virial
 1e-6 eV per atom and component); the deterministic form sums the same pair terms in another
@@ -31,7 +31,7 @@ def _box(n_atoms, species, seed):
     return at
 
 
-@pytest.mark.parametrize("n_atoms", [1, 17, 255, 4001, 8192, 8193, 16384, 16385, 32769, 65536, 65537])
+@pytest.mark.parametrize("n_atoms", [1, 17, 255, 4001, 8192, 8193, 16384, 16385, 32769, 49153, 65536, 65537, 98305])
 @pytest.mark.parametrize("species", [1, 2])
 def test_lane_counts_match_oracle(n_atoms, species):
     say(f"case: {n_atoms} atoms, {species} species, default and deterministic")
