@@ -122,11 +122,12 @@ struct nep_system {
   // NVT (nep_set_thermostat): Nose-Hoover chain length (0 = NVE), target and period
   int nvt_M = 0;
   double nvt_T = 0, nvt_tau = 0;
-  double* nhc = nullptr;  // device chain state {eta[kMaxChain], v_eta[kMaxChain], scale}
+  double* nhc = nullptr;  // device chain state (kNhcDoubles values)
+  bool nhc_ke = false;    // it holds the kinetic energy of the current velocities
   std::string err;
   // device buffers (inside the caller's workspace)
   double *x, *v, *x_alt, *v_alt, *x_build;
-  int32_t *type, *type_alt, *perm, *perm_alt, *cellid, *cell_sorted, *src, *key;
+  int32_t *type, *type_alt, *perm, *perm_alt, *cellid, *src, *key;
   int32_t *rank, *cell_count, *cell_start, *scan_tmp;
   int32_t *nbr, *cnt, *bp, *nactR, *nactA;
   uint16_t *nbrl, *selfl;
@@ -178,7 +179,6 @@ int64_t layout(nep_system* s, char* base, int64_t N, int capR, int capA, int max
   S.type_alt = c.take<int32_t>(N);
   S.perm = c.take<int32_t>(N);
   S.perm_alt = c.take<int32_t>(N);
-  S.cell_sorted = c.take<int32_t>(N);
   S.cell_count = c.take<int32_t>(max_ncell);
   S.cell_start = c.take<int32_t>(max_ncell + 1);
   S.scan_tmp = c.take<int32_t>(max_ncell / 1024 + 2);
@@ -450,8 +450,8 @@ int rebuild(nep_system* s, double skin, int scheduled, int reset, int nd2) {
   const ListOut lists{s->nbr, s->cnt, s->bp, s->nbrl, s->selfl};
   const RebuildRule rule{scheduled, reset, 0.25 * skin * skin, skin, s->be};
   HIPCHK(launch_rebuild(rule, s->partial, nd2, s->N, s->grid, s->capR, s->capA, s->x, s->v, s->type, s->perm,
-                        s->x_alt, s->v_alt, s->type_alt, s->perm_alt, s->x_build, s->cellid, s->cell_sorted, s->src,
-                        s->key, s->rank, s->cell_count, s->cell_start, s->scan_tmp, s->pos, lists, s->ht, s->lsc,
+                        s->x_alt, s->v_alt, s->type_alt, s->perm_alt, s->x_build, s->cellid, s->src, s->key,
+                        s->rank, s->cell_count, s->cell_start, s->scan_tmp, s->pos, lists, s->ht, s->lsc,
                         s->flags, s->st));
   return NEP_OK;
 }
@@ -734,6 +734,7 @@ int nep_set_state(nep_system* s, const double* x, const double* v, const int32_t
   s->have_state = true;
   s->have_list = false;
   s->force_valid[0] = s->force_valid[1] = false;
+  s->nhc_ke = false;
   s->step = 0;
   return NEP_OK;
 }
@@ -853,13 +854,19 @@ int thermo_row(nep_system* s, double* row, double err_rms, double err_max, int f
 
 // One velocity-Verlet step with model `slot`. The rebuild decision is taken on the device:
 // on the scheduled steps, and when an atom has moved more than skin/2 since the last build.
-int vv_step(nep_system* s, int slot, int prec, double dt, int rebuild_every, double skin) {
+// pending: the step before left its second half kick to this one; defer: this one leaves
+// its own to the next. nhc: the velocities are first scaled by the chain's factors; ke: the
+// second half kick also sums the kinetic energy (into the P_KE partials).
+struct StepLink {
+  bool pending = false, defer = false, nhc = false, ke = false;
+};
+int vv_step(nep_system* s, int slot, int prec, double dt, int rebuild_every, double skin, const StepLink& link) {
   const int64_t next = s->step + 1;
   const int scheduled = (rebuild_every > 0 && next % rebuild_every == 0) ? 1 : 0;
   hipEvent_t* ev = prof_take(s, 4);
   if (ev) HIPCHK(hipEventRecord(ev[0], s->st));
   HIPCHK(launch_kick_drift(s->N, dt, s->grid, s->F[slot], s->type, s->mt, s->x, s->v, s->pos, s->x_build,
-                           s->partial, s->st));
+                           link.pending, link.nhc ? s->nhc : nullptr, s->partial, s->st));
   if (ev) HIPCHK(hipEventRecord(ev[1], s->st));
   int st = rebuild(s, skin, scheduled, 0, kick_drift_blocks(s->N));
   if (st) return st;
@@ -869,24 +876,25 @@ int vv_step(nep_system* s, int slot, int prec, double dt, int rebuild_every, dou
     prof_pair(s, ev, 1, 2, 2);
   }
   if ((st = do_eval(s, slot, prec))) return st;
-  hipEvent_t* ev2 = prof_take(s, 2);
-  if (ev2) HIPCHK(hipEventRecord(ev2[0], s->st));
-  HIPCHK(launch_kick(s->N, dt, s->F[slot], s->type, s->mt, s->v, s->st));
-  if (ev2) {
-    HIPCHK(hipEventRecord(ev2[1], s->st));
-    prof_pair(s, ev2, 0, 1, 3);
+  if (!link.defer) {
+    hipEvent_t* ev2 = prof_take(s, 2);
+    if (ev2) HIPCHK(hipEventRecord(ev2[0], s->st));
+    HIPCHK(launch_kick(s->N, dt, s->F[slot], s->type, s->mt, s->v, link.ke ? s->partial : nullptr, s->st));
+    if (ev2) {
+      HIPCHK(hipEventRecord(ev2[1], s->st));
+      prof_pair(s, ev2, 0, 1, 3);
+    }
   }
   s->step = next;
   s->n_steps_total++;
   return NEP_OK;
 }
 
-// One Nose-Hoover chain half step (dt/2) on the current velocities.
-int nhc_half(nep_system* s, double dt) {
-  HIPCHK(launch_kinetic(s->N, s->v, s->type, s->mt, s->partial, s->st));
-  HIPCHK(launch_reduce_partials(s->partial, s->nblocks, P_KE, 1, s->res + 18, s->st));
-  HIPCHK(launch_nhc_half(s->N, s->res + 18, s->nhc, s->nvt_M, kBoltzmann * s->nvt_T, s->nvt_tau, 0.5 * dt, s->v,
-                         s->st));
+// Chain half steps (dt/2): the trailing one of a step and (or) the leading one of the next,
+// from the kinetic energy in the partials or (from_partials false) the one the chain left.
+int nhc_halves(nep_system* s, double dt, bool from_partials, bool trail, bool lead) {
+  HIPCHK(launch_nhc(s->N, from_partials ? s->partial : nullptr, s->nblocks, s->nhc, s->nvt_M, kBoltzmann * s->nvt_T,
+                    s->nvt_tau, 0.5 * dt, trail, lead, s->st));
   return NEP_OK;
 }
 
@@ -931,10 +939,34 @@ int nep_step(nep_system* s, int64_t n_steps, double dt_fs, int32_t rebuild_every
   if (mts_k == 0) {
     if (!s->force_valid[0] || s->force_prec[0] != precision)
       if ((st = do_eval(s, 0, precision))) return st;
+    // A step that the next one follows directly leaves its second half kick (NVE) or the
+    // chain's trailing half step and the scaling of the velocities (NVT) to that one's first
+    // kernel; before a check, a thermo row and the end of the run the step is completed.
+    const bool nvt = s->nvt_M > 0;
+    StepLink link;
+    link.nhc = link.ke = nvt;
+    bool led = false;  // the chain's leading half step of the coming step is taken already
     for (int64_t k = 0; k < n_steps; ++k) {
-      if (s->nvt_M > 0 && (st = nhc_half(s, dt_fs))) return st;
-      if ((st = vv_step(s, 0, precision, dt_fs, rebuild_every, skin))) return st;
-      if (s->nvt_M > 0 && (st = nhc_half(s, dt_fs))) return st;
+      const int64_t at = s->step + 1;
+      const bool last = k == n_steps - 1;
+      const bool scheduled = rebuild_every > 0 && at % rebuild_every == 0;
+      const bool row = thermo && rows < max_rows && (last || at % thermo_every == 0);
+      const bool stop = last || scheduled || row;
+      if (nvt && !led) {
+        if (!s->nhc_ke) HIPCHK(launch_kinetic(s->N, s->v, s->type, s->mt, s->partial, s->st));
+        if ((st = nhc_halves(s, dt_fs, !s->nhc_ke, false, true))) return st;
+      }
+      link.defer = !nvt && !stop;
+      if ((st = vv_step(s, 0, precision, dt_fs, rebuild_every, skin, link))) return st;
+      link.pending = link.defer;
+      if (nvt) {
+        if ((st = nhc_halves(s, dt_fs, true, true, !stop))) return st;
+        if (stop) HIPCHK(launch_scale_v(s->N, s->nhc, s->v, s->st));
+        led = !stop;
+        // the next leading half step takes the kinetic energy from the chain, except after a
+        // scheduled rebuild, where a run resumed from a checkpoint takes it from the velocities
+        s->nhc_ke = !scheduled;
+      }
       // a list that overflowed at a build (scheduled, or early since the last check)
       // stops the run here rather than after n_steps of truncated lists
       if (rebuild_every > 0 && s->step % rebuild_every == 0 && (st = check_flags(s))) return st;
@@ -961,12 +993,19 @@ int nep_step(nep_system* s, int64_t n_steps, double dt_fs, int32_t rebuild_every
       const double scale = s->judge_relative ? frms : 1.0;
       return rms > fallback_rms * scale || mx > fallback_max * scale;
     };
+    // the block's steps follow each other directly
+    auto inner = [&](int k) {
+      StepLink link;
+      link.pending = k > 0;
+      link.defer = k + 1 < mts_k;
+      return link;
+    };
     for (int64_t b = 0; b < nblk; ++b) {
       double rms = 0, mx = 0, frms = 0;
       if (!fallback) {
         HIPCHK(launch_kick_diff(s->N, 0.5 * big, s->F[0], s->F[1], s->type, s->mt, s->v, s->st));
         for (int k = 0; k < mts_k; ++k)
-          if ((st = vv_step(s, 1, precision, dt_fs, rebuild_every, skin))) return st;
+          if ((st = vv_step(s, 1, precision, dt_fs, rebuild_every, skin, inner(k)))) return st;
         if ((st = do_eval(s, 0, precision))) return st;
         if ((st = reduce_ew(s, 0))) return st;
         if ((st = force_error(s, &rms, &mx, &frms))) return st;
@@ -978,7 +1017,7 @@ int nep_step(nep_system* s, int64_t n_steps, double dt_fs, int32_t rebuild_every
         }
       } else {
         for (int k = 0; k < mts_k; ++k)
-          if ((st = vv_step(s, 0, precision, dt_fs, rebuild_every, skin))) return st;
+          if ((st = vv_step(s, 0, precision, dt_fs, rebuild_every, skin, inner(k)))) return st;
         if ((st = reduce_ew(s, 0))) return st;
         if ((st = do_eval(s, 1, precision))) return st;  // shadow surrogate evaluation
         if ((st = force_error(s, &rms, &mx, &frms))) return st;
@@ -1011,8 +1050,9 @@ int nep_set_thermostat(nep_system* s, double temperature, double tau_fs, int32_t
   s->nvt_M = chain_length;
   s->nvt_T = temperature;
   s->nvt_tau = tau_fs;
+  s->nhc_ke = false;
   double zero[kNhcDoubles] = {0};
-  zero[2 * kMaxChain] = 1.0;
+  zero[kNhcTrail] = zero[kNhcLead] = 1.0;
   HIPCHK(hipMemcpyAsync(s->nhc, zero, sizeof(zero), hipMemcpyHostToDevice, s->st));
   HIPCHK(hipStreamSynchronize(s->st));
   return NEP_OK;
@@ -1027,7 +1067,8 @@ int nep_set_thermostat_state(nep_system* s, const double* eta, const double* v_e
     h[k] = eta[k];
     h[kMaxChain + k] = v_eta[k];
   }
-  h[2 * kMaxChain] = 1.0;
+  h[kNhcTrail] = h[kNhcLead] = 1.0;
+  s->nhc_ke = false;
   HIPCHK(hipMemcpyAsync(s->nhc, h, sizeof(h), hipMemcpyHostToDevice, s->st));
   HIPCHK(hipStreamSynchronize(s->st));
   return NEP_OK;

@@ -232,7 +232,7 @@ struct RebuildRule {
 hipError_t launch_rebuild(const RebuildRule& rule, const double* d2, int nd2, int64_t N, const CellGrid& g, int capR,
                           int capA, double* x, double* v, int32_t* type, int32_t* perm, double* x_alt, double* v_alt,
                           int32_t* type_alt, int32_t* perm_alt, double* x_build, int32_t* cellid,
-                          int32_t* cell_sorted, int32_t* src, int32_t* key, int32_t* rank, int32_t* cell_count,
+                          int32_t* src, int32_t* key, int32_t* rank, int32_t* cell_count,
                           int32_t* cell_start, int32_t* scan_tmp, uint4* pos, const ListOut& lists, HaloTables ht,
                           ListScratch sc, int32_t* flags, hipStream_t st);
 // Rows of original ids [o_lo, o_hi), ascending, into rows[(o - o_lo) * cap + k].
@@ -291,11 +291,15 @@ hipError_t launch_max_partials(const double* partial, int nblocks, int slot, dou
 // Workgroups of k_kick_drift; each leaves the largest squared displacement since the build
 // of its atoms in d2 (1e300 for a non-finite one).
 int kick_drift_blocks(int64_t N);
+// pending: the second half kick of the step before, left out there, comes first. nhc (null:
+// none): the velocities are first scaled by the chain's two factors.
 hipError_t launch_kick_drift(int64_t N, double dt, CellGrid g, const float* F, const int32_t* type,
-                             MassTable mt, double* x, double* v, uint4* pos, const double* x_build, double* d2,
-                             hipStream_t st);
-hipError_t launch_kick(int64_t N, double dt, const float* F, const int32_t* type, MassTable mt,
-                       double* v, hipStream_t st);
+                             MassTable mt, double* x, double* v, uint4* pos, const double* x_build, bool pending,
+                             const double* nhc, double* d2, hipStream_t st);
+// Second half kick; ke_partial (nullable): the kinetic energy after it, per workgroup, in
+// the P_KE slots.
+hipError_t launch_kick(int64_t N, double dt, const float* F, const int32_t* type, MassTable mt, double* v,
+                       double* ke_partial, hipStream_t st);
 hipError_t launch_kick_diff(int64_t N, double dt, const float* Fa, const float* Fb,
                             const int32_t* type, MassTable mt, double* v, hipStream_t st);
 // FP64 parameters of one model (the packed FP64 vector on the device), for the
@@ -324,12 +328,18 @@ hipError_t launch_gather_vec64(int64_t N, const int32_t* perm, const double* aos
                                hipStream_t st);
 
 // Nose-Hoover chain: at most kMaxChain thermostats; the device state holds
-// {eta[kMaxChain], v_eta[kMaxChain], velocity scale}.
+// {eta[kMaxChain], v_eta[kMaxChain], velocity scales of a trailing and of a leading half
+// step, kinetic energy after them}.
 constexpr int kMaxChain = 16;
-constexpr int kNhcDoubles = 2 * kMaxChain + 1;
-// One chain half step of length h from the kinetic energy *ke, then v *= the scale.
-hipError_t launch_nhc_half(int64_t N, const double* ke, double* nhc, int M, double kT, double tau, double h,
-                           double* v, hipStream_t st);
+constexpr int kNhcTrail = 2 * kMaxChain, kNhcLead = kNhcTrail + 1, kNhcKe = kNhcTrail + 2;
+constexpr int kNhcDoubles = kNhcTrail + 3;
+// Chain half steps of length h, one after the other: the trailing one of a step and (or) the
+// leading one of the next. The kinetic energy is the sum of the nblocks P_KE partials, or
+// (partial null) the one the chain left. The scales of the half steps not taken are 1.
+hipError_t launch_nhc(int64_t N, const double* partial, int nblocks, double* nhc, int M, double kT, double tau,
+                      double h, bool trail, bool lead, hipStream_t st);
+// v *= the trailing scale.
+hipError_t launch_scale_v(int64_t N, const double* nhc, double* v, hipStream_t st);
 hipError_t launch_kinetic(int64_t N, const double* v, const int32_t* type, MassTable mt,
                           double* partial, hipStream_t st);
 hipError_t launch_force_error(int64_t N, const float* Fa, const float* Fb, double* partial,

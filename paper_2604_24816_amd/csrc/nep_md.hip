@@ -39,23 +39,31 @@ __device__ __forceinline__ double wrap_coord(double xv, double L) {
 }
 
 // v += dt/2 F/(m xi); x += dt v; wrap; the largest squared displacement since the build per
-// workgroup, for the rebuild decision. Strides over a capped grid (kIntegrateGrid
+// workgroup, for the rebuild decision. PENDING: the half kick that ends the step before comes
+// first (the same forces: one pass over v and F and one launch for both); NHC: before the
+// kicks v is scaled by the chain's trailing and leading factors. Strides over a capped grid (kIntegrateGrid
 // workgroups), so that these maxima are few.
 constexpr int kIntegrateGrid = 8192;
 
+template <bool PENDING, bool NHC>
 __global__ void k_kick_drift(int64_t N, double dt, CellGrid g, const float* __restrict__ F,
                              const int32_t* __restrict__ type, MassTable mt, double* __restrict__ x,
                              double* __restrict__ v, uint4* __restrict__ pos, const double* __restrict__ xb,
-                             double* __restrict__ d2_out) {
+                             const double* __restrict__ nhc, double* __restrict__ d2_out) {
   __shared__ double sh[kBlock / 64];
   double d2max = 0.0;
+  const double s0 = NHC ? nhc[kNhcTrail] : 1.0, s1 = NHC ? nhc[kNhcLead] : 1.0;
   for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < N; p += (int64_t)gridDim.x * blockDim.x) {
     const int32_t tp = type[p];
     const double inv = mt.inv_mxi[tp];
     double xn[3];
     double d2 = 0.0;
     for (int c = 0; c < 3; ++c) {
-      const double vv = v[c * N + p] + 0.5 * dt * (double)F[c * N + p] * inv;
+      const double a = (double)F[c * N + p];
+      double vv = v[c * N + p];
+      if (NHC) vv = vv * s0 * s1;
+      if (PENDING) vv = vv + 0.5 * dt * a * inv;
+      vv = vv + 0.5 * dt * a * inv;
       const double xx = wrap_coord(x[c * N + p] + dt * vv, g.box[c]);
       v[c * N + p] = vv;
       x[c * N + p] = xx;
@@ -72,14 +80,6 @@ __global__ void k_kick_drift(int64_t N, double dt, CellGrid g, const float* __re
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = d2max;
   __syncthreads();
   if (threadIdx.x == 0) d2_out[blockIdx.x] = fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
-}
-
-__global__ void k_kick(int64_t N, double dt, const float* __restrict__ F, const int32_t* __restrict__ type,
-                       MassTable mt, double* __restrict__ v) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= N) return;
-  const double inv = mt.inv_mxi[type[p]];
-  for (int c = 0; c < 3; ++c) v[c * N + p] += 0.5 * dt * (double)F[c * N + p] * inv;
 }
 
 // v += dt (Fa - Fb)/(m xi)
@@ -101,6 +101,25 @@ __device__ __forceinline__ void block_partial(double val, double* sh, double* ou
     __syncthreads();
   }
   if (threadIdx.x == 0) *out = sh[0];
+}
+
+template <bool KE>
+__global__ void k_kick(int64_t N, double dt, const float* __restrict__ F, const int32_t* __restrict__ type,
+                       MassTable mt, double* __restrict__ v, double* __restrict__ partial) {
+  __shared__ double sh[kBlock];
+  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  double ke = 0.0;
+  if (p < N) {
+    const int32_t t = type[p];
+    const double inv = mt.inv_mxi[t];
+    for (int c = 0; c < 3; ++c) {
+      const double vv = v[c * N + p] + 0.5 * dt * (double)F[c * N + p] * inv;
+      v[c * N + p] = vv;
+      ke += vv * vv;
+    }
+    ke *= 0.5 * mt.mass[t] * 103.642697;
+  }
+  if constexpr (KE) block_partial(ke, sh, partial + (int64_t)blockIdx.x * kPartialStride + P_KE);
 }
 
 __global__ void k_kinetic(int64_t N, const double* __restrict__ v, const int32_t* __restrict__ type,
@@ -144,18 +163,13 @@ __global__ void k_force_error(int64_t N, const float* __restrict__ Fa, const flo
 
 // One half step (h = dt/2) of a Nose-Hoover chain in the explicit reversible
 // Trotter form of Martyna, Tuckerman, Tobias and Klein (1996), FP64, one thread.
-// nhc = {eta[kMaxChain], v_eta[kMaxChain], scale}; ke = the current kinetic energy.
+// ke = the current kinetic energy, scaled on return; returns the velocity scale.
 // Chain masses Q_1 = Nf kT tau^2, Q_k = kT tau^2; forces G_1 = (2 KE - Nf kT)/Q_1,
 // G_k = (Q_{k-1} v_{k-1}^2 - kT)/Q_k. The outermost velocity takes a quarter-step kick,
 // the chain is swept inwards (each v_k damped by exp(-v_{k+1} h/4) around its kick),
 // the particle velocities are to be scaled by exp(-v_1 h), the positions advance by
 // v_k h, and the chain is swept outwards again with the forces recomputed.
-__global__ void k_nhc_half(const double* __restrict__ ke_in, double* __restrict__ nhc, int M, double kT,
-                           double Nf, double tau2, double h) {
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
-  double* eta = nhc;
-  double* ve = nhc + kMaxChain;
-  double ke = *ke_in;
+__device__ double nhc_half(double& ke, double* eta, double* ve, int M, double kT, double Nf, double tau2, double h) {
   const double Q1 = Nf * kT * tau2, Qk = kT * tau2;
   auto force = [&](int k) {
     return k == 0 ? (2.0 * ke - Nf * kT) / Q1 : ((k == 1 ? Q1 : Qk) * ve[k - 1] * ve[k - 1] - kT) / Qk;
@@ -174,7 +188,43 @@ __global__ void k_nhc_half(const double* __restrict__ ke_in, double* __restrict_
     ve[k] = (ve[k] * d + 0.5 * h * force(k)) * d;
   }
   ve[L] += 0.5 * h * force(L);
-  nhc[2 * kMaxChain] = sc;
+  return sc;
+}
+
+// The chain's half steps between two kicks (see launch_nhc): the sum of the kinetic energy's
+// partials and both half steps in one launch, where each half step took four (kinetic
+// energy, its sum, the chain, the scaling of v, which the next kick now does): 36 of the 240 us
+// of a 33,660-atom step.
+__global__ void __launch_bounds__(kRedBlock)
+k_nhc(const double* __restrict__ partial, int nblocks, double* __restrict__ nhc, int M, double kT, double Nf,
+      double tau2, double h, int trail, int lead) {
+  __shared__ double sh[kRedBlock / 64];
+  double ke = 0.0;
+  if (partial) {
+#pragma unroll 4
+    for (int b = threadIdx.x; b < nblocks; b += kRedBlock) ke += partial[(int64_t)b * kPartialStride + P_KE];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) ke += __shfl_xor(ke, o, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = ke;
+    __syncthreads();
+    ke = 0.0;
+    for (int k = 0; k < kRedBlock / 64; ++k) ke += sh[k];
+  } else {
+    ke = nhc[kNhcKe];
+  }
+  if (threadIdx.x != 0) return;
+  double eta[kMaxChain], ve[kMaxChain];
+  for (int k = 0; k < M; ++k) {
+    eta[k] = nhc[k];
+    ve[k] = nhc[kMaxChain + k];
+  }
+  nhc[kNhcTrail] = trail ? nhc_half(ke, eta, ve, M, kT, Nf, tau2, h) : 1.0;
+  nhc[kNhcLead] = lead ? nhc_half(ke, eta, ve, M, kT, Nf, tau2, h) : 1.0;
+  nhc[kNhcKe] = ke;
+  for (int k = 0; k < M; ++k) {
+    nhc[k] = eta[k];
+    nhc[kMaxChain + k] = ve[k];
+  }
 }
 
 // v *= scale (the chain's velocity scaling), all 3N components.
@@ -281,23 +331,33 @@ int kick_drift_blocks(int64_t N) {
 }
 
 hipError_t launch_kick_drift(int64_t N, double dt, CellGrid g, const float* F, const int32_t* type,
-                             MassTable mt, double* x, double* v, uint4* pos, const double* x_build, double* d2,
-                             hipStream_t st) {
-  hipLaunchKernelGGL(k_kick_drift, dim3(kick_drift_blocks(N)), dim3(kBlock), 0, st, N, dt, g, F, type, mt, x, v,
-                     pos, x_build, d2);
+                             MassTable mt, double* x, double* v, uint4* pos, const double* x_build, bool pending,
+                             const double* nhc, double* d2, hipStream_t st) {
+  auto kern = nhc ? (pending ? k_kick_drift<true, true> : k_kick_drift<false, true>)
+                  : (pending ? k_kick_drift<true, false> : k_kick_drift<false, false>);
+  hipLaunchKernelGGL(kern, dim3(kick_drift_blocks(N)), dim3(kBlock), 0, st, N, dt, g, F, type, mt, x, v, pos, x_build,
+                     nhc, d2);
   return hipGetLastError();
 }
 
-hipError_t launch_nhc_half(int64_t N, const double* ke, double* nhc, int M, double kT, double tau, double h,
-                           double* v, hipStream_t st) {
-  hipLaunchKernelGGL(k_nhc_half, dim3(1), dim3(64), 0, st, ke, nhc, M, kT, 3.0 * (double)N - 3.0, tau * tau, h);
-  hipLaunchKernelGGL(k_scale_v, dim3(grid_blocks(3 * N)), dim3(kBlock), 0, st, 3 * N, nhc + 2 * kMaxChain, v);
+hipError_t launch_nhc(int64_t N, const double* partial, int nblocks, double* nhc, int M, double kT, double tau,
+                      double h, bool trail, bool lead, hipStream_t st) {
+  hipLaunchKernelGGL(k_nhc, dim3(1), dim3(kRedBlock), 0, st, partial, nblocks, nhc, M, kT, 3.0 * (double)N - 3.0,
+                     tau * tau, h, trail ? 1 : 0, lead ? 1 : 0);
+  return hipGetLastError();
+}
+
+hipError_t launch_scale_v(int64_t N, const double* nhc, double* v, hipStream_t st) {
+  hipLaunchKernelGGL(k_scale_v, dim3(grid_blocks(3 * N)), dim3(kBlock), 0, st, 3 * N, nhc + kNhcTrail, v);
   return hipGetLastError();
 }
 
 hipError_t launch_kick(int64_t N, double dt, const float* F, const int32_t* type, MassTable mt, double* v,
-                       hipStream_t st) {
-  hipLaunchKernelGGL(k_kick, dim3(grid_blocks(N)), dim3(kBlock), 0, st, N, dt, F, type, mt, v);
+                       double* ke_partial, hipStream_t st) {
+  if (ke_partial)
+    hipLaunchKernelGGL(k_kick<true>, dim3(grid_blocks(N)), dim3(kBlock), 0, st, N, dt, F, type, mt, v, ke_partial);
+  else
+    hipLaunchKernelGGL(k_kick<false>, dim3(grid_blocks(N)), dim3(kBlock), 0, st, N, dt, F, type, mt, v, ke_partial);
   return hipGetLastError();
 }
 

@@ -26,6 +26,7 @@ __global__ void k_zero_i32(int32_t* p, int64_t n) {
 // step without a rebuild then dispatches a few thousand workgroups, not one per cell or per
 // 256 atoms.
 constexpr int kRebuildGrid = 8192;
+constexpr int kCopyGrid = 2048;  // workgroups that copy the sorted state back (a multiple of the dies)
 inline int rebuild_grid(int64_t nblocks) { return (int)(nblocks < kRebuildGrid ? nblocks : kRebuildGrid); }
 
 __device__ __forceinline__ int cell_coord(double xv, double L, int n) {
@@ -100,26 +101,30 @@ __device__ void select_bins(const RebuildRule& rule, double d2, int32_t* flags) 
   if (build) flags[FLAG_NBUILD] += 1;
 }
 
-// Largest of the n partial maxima over a workgroup of 1024 threads, valid in thread 0.
+// Whether the step rebuilds: from the largest of the n partial maxima (the same in every
+// workgroup that asks), with the flag words set when `write`. sh holds BLOCK / 64 doubles.
 constexpr int kSelBlock = 1024;
-__device__ __forceinline__ double block_max(const double* __restrict__ part, int n, double* sh) {
+template <int BLOCK>
+__device__ __forceinline__ bool decide(const RebuildRule& rule, const double* __restrict__ d2, int n, bool write,
+                                       int32_t* __restrict__ flags, double* sh) {
   double m = 0.0;
 #pragma unroll 4
-  for (int b = threadIdx.x; b < n; b += kSelBlock) m = fmax(m, part[b]);
+  for (int b = threadIdx.x; b < n; b += BLOCK) m = fmax(m, d2[b]);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
   __syncthreads();
-  if (threadIdx.x == 0)
-    for (int k = 1; k < kSelBlock / 64; ++k) m = fmax(m, sh[k]);
-  return m;
+  m = sh[0];
+#pragma unroll
+  for (int k = 1; k < BLOCK / 64; ++k) m = fmax(m, sh[k]);
+  if (write && threadIdx.x == 0) select_bins(rule, m, flags);
+  return rule.scheduled || m > rule.half_skin2;
 }
 
 __global__ void __launch_bounds__(kSelBlock)
 k_select(RebuildRule rule, const double* __restrict__ d2, int nd2, int32_t* __restrict__ flags) {
   __shared__ double sh[kSelBlock / 64];
-  const double m = block_max(d2, nd2, sh);
-  if (threadIdx.x == 0) select_bins(rule, m, flags);
+  decide<kSelBlock>(rule, d2, nd2, true, flags, sh);
 }
 
 // Systems of up to kSortAtoms atoms in kSortCells cells: the decision, the binning, the
@@ -132,16 +137,11 @@ k_select_sort(RebuildRule rule, const double* __restrict__ d2, int nd2, int64_t 
               const double* __restrict__ x, const int32_t* __restrict__ perm, int32_t* __restrict__ start,
               int32_t* __restrict__ src, int32_t* __restrict__ key, int32_t* __restrict__ flags) {
   __shared__ double shd[kSelBlock / 64];
-  __shared__ int count[kSortCells], sh[kSelBlock / 64], build;
+  __shared__ int count[kSortCells], sh[kSelBlock / 64];
   const int t = threadIdx.x;
-  const double m = block_max(d2, nd2, shd);
-  if (t == 0) {
-    select_bins(rule, m, flags);
-    build = rule.scheduled || m > rule.half_skin2;
-  }
+  if (!decide<kSelBlock>(rule, d2, nd2, true, flags, shd)) return;
   for (int c = t; c < kSortCells; c += kSelBlock) count[c] = 0;
   __syncthreads();
-  if (!build) return;
   constexpr int PER = kSortAtoms / kSelBlock;
   int cr[PER];  // cell | rank in the cell << 16
 #pragma unroll
@@ -183,10 +183,21 @@ k_select_sort(RebuildRule rule, const double* __restrict__ d2, int nd2, int64_t 
 }
 
 // Cell of every atom and its rank among the cell's atoms in arrival order. count is zero
-// on entry (k_sort_permute clears it for the next build).
-__global__ void k_bin(int64_t N, CellGrid g, const double* __restrict__ x, int32_t* __restrict__ cellid,
-                      int32_t* __restrict__ rank, int32_t* __restrict__ count, const int32_t* __restrict__ flags) {
-  if (flags[FLAG_REBUILD] == 0) return;
+// on entry (k_sort_halo clears it for the next build). DECIDE: the rebuild decision is taken
+// here, by every workgroup for itself from at most kDecideMax partial maxima, which saves
+// the launch of k_select; with more of them their re-reading would cost more.
+constexpr int kDecideMax = 1024;
+template <bool DECIDE>
+__global__ void __launch_bounds__(kBlock)
+k_bin(RebuildRule rule, const double* __restrict__ d2, int nd2, int64_t N, CellGrid g, const double* __restrict__ x,
+      int32_t* __restrict__ cellid, int32_t* __restrict__ rank, int32_t* __restrict__ count,
+      int32_t* __restrict__ flags) {
+  __shared__ double sh[kBlock / 64];
+  if constexpr (DECIDE) {
+    if (!decide<kBlock>(rule, d2, nd2, blockIdx.x == 0, flags, sh)) return;
+  } else if (flags[FLAG_REBUILD] == 0) {
+    return;
+  }
   for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < N; p += (int64_t)gridDim.x * blockDim.x) {
     const int c = cell_of(g, x, N, p);
     cellid[p] = c;
@@ -243,6 +254,40 @@ __global__ void k_scatter(int64_t N, const int32_t* __restrict__ cellid, const i
   }
 }
 
+// Up to kScanCells cells: every workgroup scans all the counts itself, in LDS, and scatters
+// its atoms (the first also stores the starts): one launch instead of three.
+constexpr int kScanCells = 8192;
+__global__ void __launch_bounds__(kBlock)
+k_scan_scatter(int64_t N, int ncell, const int32_t* __restrict__ count, const int32_t* __restrict__ cellid,
+               const int32_t* __restrict__ rank, const int32_t* __restrict__ perm, int32_t* __restrict__ start,
+               int32_t* __restrict__ src, int32_t* __restrict__ key, const int32_t* __restrict__ flags) {
+  if (flags[FLAG_REBUILD] == 0) return;
+  __shared__ int st[kScanCells];
+  __shared__ int sh[kBlock / 64];
+  for (int c = threadIdx.x; c < ncell; c += kBlock) st[c] = count[c];
+  __syncthreads();
+  const int per = (ncell + kBlock - 1) / kBlock;
+  const int c0 = threadIdx.x * per, c1 = c0 + per < ncell ? c0 + per : ncell;
+  int sum = 0, tot;
+  for (int c = c0; c < c1; ++c) sum += st[c];
+  int run = block_scan<kBlock / 64>(sum, sh, tot);
+  for (int c = c0; c < c1; ++c) {
+    const int v = st[c];
+    st[c] = run;
+    run += v;
+  }
+  __syncthreads();
+  if (blockIdx.x == 0) {
+    for (int c = threadIdx.x; c < ncell; c += kBlock) start[c] = st[c];
+    if (threadIdx.x == 0) start[ncell] = (int32_t)N;
+  }
+  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < N; p += (int64_t)gridDim.x * blockDim.x) {
+    const int pos = st[cellid[p]] + rank[p];
+    src[pos] = (int32_t)p;
+    key[pos] = perm[p];
+  }
+}
+
 // Within each cell, order atoms by original id and move their state there. One wavefront
 // per cell: each lane holds atoms of the cell, counts the cell's smaller keys (the keys are
 // distinct original ids) and moves its atom to that rank, so the result is the stable order
@@ -251,17 +296,21 @@ __global__ void k_scatter(int64_t N, const int32_t* __restrict__ cellid, const i
 constexpr int kSortMax = 256;
 constexpr int kSortWaves = kBlock / 64;
 
-__global__ void __launch_bounds__(kBlock)
-k_sort_permute(int64_t N, int ncell, const int32_t* __restrict__ start, int32_t* __restrict__ count,
-               int32_t* __restrict__ key, int32_t* __restrict__ src, const double* __restrict__ x,
-               const double* __restrict__ v, const int32_t* __restrict__ type, double* __restrict__ x2,
-               double* __restrict__ v2, int32_t* __restrict__ type2, int32_t* __restrict__ perm2,
-               double* __restrict__ xb, int32_t* __restrict__ cell_sorted, const int32_t* __restrict__ flags) {
-  if (flags[FLAG_REBUILD] == 0) return;
-  __shared__ int32_t kk[kSortWaves][kSortMax];
+// The sorted state of a build, in the alternate buffers until the positions that the build
+// still reads in the old order are free (k_build_cells copies it back); xb stays, as the
+// positions at the build.
+struct SortedState {
+  double *x2, *v2, *xb;
+  int32_t *type2, *perm2;
+};
+
+__device__ void sort_cells(int64_t N, int ncell, const int32_t* __restrict__ start, int32_t* __restrict__ count,
+                           int32_t* __restrict__ key, int32_t* __restrict__ src, const double* __restrict__ x,
+                           const double* __restrict__ v, const int32_t* __restrict__ type, const SortedState& o,
+                           int block, int nblocks, int32_t (*kk)[kSortMax]) {
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   constexpr int U = kSortMax / 64;
-  for (int c = blockIdx.x * kSortWaves + w; c < ncell; c += gridDim.x * kSortWaves) {  // wave-uniform
+  for (int c = block * kSortWaves + w; c < ncell; c += nblocks * kSortWaves) {  // wave-uniform
     const int a = start[c], n = start[c + 1] - a;
     if (lane == 0) count[c] = 0;
     if (n <= 0) continue;
@@ -269,13 +318,12 @@ k_sort_permute(int64_t N, int ncell, const int32_t* __restrict__ start, int32_t*
     auto move = [&](int64_t p, int64_t s, int32_t k) {
       for (int d = 0; d < 3; ++d) {
         const double xv = x[d * N + s];
-        x2[d * N + p] = xv;
-        xb[d * N + p] = xv;
-        v2[d * N + p] = v[d * N + s];
+        o.x2[d * N + p] = xv;
+        o.xb[d * N + p] = xv;
+        o.v2[d * N + p] = v[d * N + s];
       }
-      type2[p] = type[s];
-      perm2[p] = k;
-      cell_sorted[p] = c;
+      o.type2[p] = type[s];
+      o.perm2[p] = k;
     };
     if (n > kSortMax) {
       if (lane == 0) {
@@ -346,16 +394,25 @@ __device__ __forceinline__ int halo_cand(const CellGrid& g, const int32_t* __res
 }
 
 template <bool MAP>
-__device__ void halo_tile(int64_t N, const CellGrid& g, const int32_t* __restrict__ cell_sorted,
-                          const int32_t* __restrict__ cell_start, const HaloTables& ht, int tile) {
-  constexpr int kWords = MAP ? kMapCells / 32 : kCandMax;
-  __shared__ uint32_t buf[kWords];  // bitmap, or candidate ids to sort
-  __shared__ int scan[kBlock / 64];
-  __shared__ int cnt[kHaloCellsMax];
+struct HaloWork {
+  static constexpr int kWords = MAP ? kMapCells / 32 : kCandMax;
+  uint32_t buf[kWords];  // bitmap, or candidate ids to sort
+  int scan[kBlock / 64];
+  int cnt[kHaloCellsMax];
+};
+
+template <bool MAP>
+__device__ void halo_tile(int64_t N, const CellGrid& g, const double* __restrict__ x, const int32_t* __restrict__ src,
+                          const int32_t* __restrict__ cell_start, const HaloTables& ht, int tile, HaloWork<MAP>& hw) {
+  uint32_t* buf = hw.buf;
+  int* scan = hw.scan;
+  int* cnt = hw.cnt;
   const int64_t t0 = (int64_t)tile * kBlock;
   const int64_t t1 = t0 + kBlock < N ? t0 + kBlock : N;
   int32_t* info = ht.info + 4 * tile;
-  const int c_lo = cell_sorted[t0], c_hi = cell_sorted[t1 - 1];
+  // the cells of the tile's first and last atoms (src is ordered by cell; the order inside a
+  // cell does not matter)
+  const int c_lo = cell_of(g, x, N, src[t0]), c_hi = cell_of(g, x, N, src[t1 - 1]);
   const int ncr = c_hi - c_lo + 1;
   if (ncr > kTileCellsMax) return halo_none(info);
   int n_list = 64;  // words of buf in use
@@ -433,32 +490,26 @@ __device__ void halo_tile(int64_t N, const CellGrid& g, const int32_t* __restric
   }
 }
 
-// The tiles' halo tables; the sorted state, which k_sort_permute left in the alternate
-// buffers, goes back to the primary ones on the way.
+// The cell sort and the tiles' halo tables, which need each other's results no more than the
+// scatter's: workgroups [0, nsort) sort, the others build tables.
 template <bool MAP>
 __global__ void __launch_bounds__(kBlock)
-k_halo_tables(int64_t N, CellGrid g, const double* __restrict__ x2, const double* __restrict__ v2,
-              const int32_t* __restrict__ type2, const int32_t* __restrict__ perm2, double* __restrict__ x,
-              double* __restrict__ v, int32_t* __restrict__ type, int32_t* __restrict__ perm, uint4* __restrict__ pos,
-              const int32_t* __restrict__ cell_sorted, const int32_t* __restrict__ cell_start, HaloTables ht,
-              const int32_t* __restrict__ flags) {
+k_sort_halo(int64_t N, CellGrid g, int nsort, const int32_t* __restrict__ start, int32_t* __restrict__ count,
+            int32_t* __restrict__ key, int32_t* __restrict__ src, const double* __restrict__ x,
+            const double* __restrict__ v, const int32_t* __restrict__ type, SortedState o, HaloTables ht,
+            const int32_t* __restrict__ flags) {
   if (flags[FLAG_REBUILD] == 0) return;
+  __shared__ union {
+    int32_t kk[kSortWaves][kSortMax];
+    HaloWork<MAP> halo;
+  } sh;
+  if ((int)blockIdx.x < nsort) {
+    sort_cells(N, g.ncell, start, count, key, src, x, v, type, o, blockIdx.x, nsort, sh.kk);
+    return;
+  }
   const int ntiles = (int)((N + kBlock - 1) / kBlock);
-  for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const int64_t p = (int64_t)tile * kBlock + threadIdx.x;
-    if (p < N) {
-      double xn[3];
-      for (int c = 0; c < 3; ++c) {
-        xn[c] = x2[c * N + p];
-        x[c * N + p] = xn[c];
-        v[c * N + p] = v2[c * N + p];
-      }
-      const int32_t tp = type2[p];
-      pos_put(pos, p, xn[0], xn[1], xn[2], tp, g.box);
-      type[p] = tp;
-      perm[p] = perm2[p];
-    }
-    halo_tile<MAP>(N, g, cell_sorted, cell_start, ht, tile);
+  for (int tile = blockIdx.x - nsort; tile < ntiles; tile += gridDim.x - nsort) {
+    halo_tile<MAP>(N, g, x, src, start, ht, tile, sh.halo);
     __syncthreads();  // the LDS tables are reused by the next tile
   }
 }
@@ -753,15 +804,40 @@ __device__ void build_cell(int64_t N, const CellGrid& g, const double* __restric
                                    home, nc, shifted);
 }
 
+// Primary state from the sorted one (workgroups [0, ncopy)), and the cells' lists from the
+// positions at the build, which the copy does not touch (the others).
+struct PrimaryState {
+  double *x, *v;
+  int32_t *type, *perm;
+  uint4* pos;
+};
+__device__ void copy_back(int64_t N, const CellGrid& g, const SortedState& o, const PrimaryState& s, int block,
+                          int nblocks) {
+  for (int64_t p = (int64_t)block * kBlock + threadIdx.x; p < N; p += (int64_t)nblocks * kBlock) {
+    double xn[3];
+    for (int c = 0; c < 3; ++c) {
+      xn[c] = o.x2[c * N + p];
+      s.x[c * N + p] = xn[c];
+      s.v[c * N + p] = o.v2[c * N + p];
+    }
+    const int32_t tp = o.type2[p];
+    pos_put(s.pos, p, xn[0], xn[1], xn[2], tp, g.box);
+    s.type[p] = tp;
+    s.perm[p] = o.perm2[p];
+  }
+}
+
 template <int NE, bool MINIMG>
 __global__ void __launch_bounds__(kBlock)
-k_build_cells(int64_t N, CellGrid g, const double* __restrict__ x, const int32_t* __restrict__ start,
+k_build_cells(int64_t N, CellGrid g, SortedState o, PrimaryState prim, int ncopy, const int32_t* __restrict__ start,
               BinEdges be, int capR, ListOut lo_, HaloTables ht, ListScratch sc, int parts,
               int32_t* __restrict__ flags) {
   if (flags[FLAG_REBUILD] == 0) return;
   __shared__ CellStage S;
+  if ((int)blockIdx.x < ncopy) return copy_back(N, g, o, prim, blockIdx.x, ncopy);
+  const double* __restrict__ x = o.xb;
   const int n = g.ncell * parts;
-  for (int cb = blockIdx.x; cb < n; cb += gridDim.x) {
+  for (int cb = blockIdx.x - ncopy; cb < n; cb += gridDim.x - ncopy) {
     const int u = xcd_tile(cb, n);
     build_cell<NE, MINIMG>(N, g, x, start, be, capR, lo_, ht, sc, flags, u / parts, u % parts, parts, S);
     __syncthreads();  // the LDS staging is reused by the next cell
@@ -983,40 +1059,49 @@ hipError_t launch_zero_i32(int32_t* p, int64_t n, hipStream_t st) {
 hipError_t launch_rebuild(const RebuildRule& rule, const double* d2, int nd2, int64_t N, const CellGrid& g, int capR,
                           int capA, double* x, double* v, int32_t* type, int32_t* perm, double* x_alt, double* v_alt,
                           int32_t* type_alt, int32_t* perm_alt, double* x_build, int32_t* cellid,
-                          int32_t* cell_sorted, int32_t* src, int32_t* key, int32_t* rank, int32_t* cell_count,
+                          int32_t* src, int32_t* key, int32_t* rank, int32_t* cell_count,
                           int32_t* cell_start, int32_t* scan_tmp, uint4* pos, const ListOut& lout, HaloTables ht,
                           ListScratch sc, int32_t* flags, hipStream_t st) {
   const int nb = grid_blocks(N);
   const int ncell = g.ncell;
   const BinEdges& be = rule.be;
+  const dim3 gb(rebuild_grid(nb)), kb(kBlock);
   if (N <= kSortAtoms && ncell <= kSortCells) {
-    hipLaunchKernelGGL(k_select_sort, dim3(1), dim3(kSelBlock), 0, st, rule, d2, nd2, N, g, x, perm,
-                       cell_start, src, key, flags);
-  } else {
-    hipLaunchKernelGGL(k_select, dim3(1), dim3(kSelBlock), 0, st, rule, d2, nd2, flags);
-    hipLaunchKernelGGL(k_bin, dim3(rebuild_grid(nb)), dim3(kBlock), 0, st, N, g, x, cellid, rank, cell_count, flags);
-    const int ntiles = (ncell + kScanTile - 1) / kScanTile;
-    hipLaunchKernelGGL(k_scan_tiles, dim3(ntiles), dim3(kBlock), 0, st, cell_count, cell_start, ncell, scan_tmp,
-                       flags);
-    hipLaunchKernelGGL(k_scan_add, dim3(ntiles), dim3(kScanTile), 0, st, cell_start, ncell, N, scan_tmp, flags);
-    hipLaunchKernelGGL(k_scatter, dim3(rebuild_grid(nb)), dim3(kBlock), 0, st, N, cellid, rank, cell_start, perm, src,
+    hipLaunchKernelGGL(k_select_sort, dim3(1), dim3(kSelBlock), 0, st, rule, d2, nd2, N, g, x, perm, cell_start, src,
                        key, flags);
+  } else {
+    if (nd2 <= kDecideMax) {
+      hipLaunchKernelGGL(k_bin<true>, gb, kb, 0, st, rule, d2, nd2, N, g, x, cellid, rank, cell_count, flags);
+    } else {
+      hipLaunchKernelGGL(k_select, dim3(1), dim3(kSelBlock), 0, st, rule, d2, nd2, flags);
+      hipLaunchKernelGGL(k_bin<false>, gb, kb, 0, st, rule, d2, nd2, N, g, x, cellid, rank, cell_count, flags);
+    }
+    if (ncell <= kScanCells) {
+      hipLaunchKernelGGL(k_scan_scatter, gb, kb, 0, st, N, ncell, cell_count, cellid, rank, perm, cell_start, src,
+                         key, flags);
+    } else {
+      const int ntiles = (ncell + kScanTile - 1) / kScanTile;
+      hipLaunchKernelGGL(k_scan_tiles, dim3(ntiles), kb, 0, st, cell_count, cell_start, ncell, scan_tmp, flags);
+      hipLaunchKernelGGL(k_scan_add, dim3(ntiles), dim3(kScanTile), 0, st, cell_start, ncell, N, scan_tmp, flags);
+      hipLaunchKernelGGL(k_scatter, gb, kb, 0, st, N, cellid, rank, cell_start, perm, src, key, flags);
+    }
   }
-  hipLaunchKernelGGL(k_sort_permute, dim3(rebuild_grid(grid_blocks(ncell, kSortWaves))), dim3(kBlock), 0, st, N,
-                     ncell, cell_start, cell_count, key, src, x, v, type, x_alt, v_alt, type_alt, perm_alt, x_build,
-                     cell_sorted, flags);
-  auto halo = ncell <= kMapCells ? k_halo_tables<true> : k_halo_tables<false>;
-  hipLaunchKernelGGL(halo, dim3(rebuild_grid(nb)), dim3(kBlock), 0, st, N, g, x_alt, v_alt, type_alt, perm_alt, x, v,
-                     type, perm, pos, cell_sorted, cell_start, ht, flags);
+  const SortedState sorted{x_alt, v_alt, x_build, type_alt, perm_alt};
+  const PrimaryState prim{x, v, type, perm, pos};
+  const int nsort = rebuild_grid(grid_blocks(ncell, kSortWaves));
+  auto sort_halo = ncell <= kMapCells ? k_sort_halo<true> : k_sort_halo<false>;
+  hipLaunchKernelGGL(sort_halo, dim3(nsort + rebuild_grid(nb)), kb, 0, st, N, g, nsort, cell_start, cell_count, key,
+                     src, x, v, type, sorted, ht, flags);
   // the minimum-image rule inside the candidate loop only for boxes with fewer than
   // three cells along some dimension
   const bool small = g.nc[0] < 3 || g.nc[1] < 3 || g.nc[2] < 3;
   const bool one = be.nbins - 1 <= kEdgesOne;
   const int parts = build_parts(ncell);
+  const int ncopy = nb < kCopyGrid ? nb : kCopyGrid;
   auto cells = small ? (one ? k_build_cells<kEdgesOne, true> : k_build_cells<kEdgesTwo, true>)
                      : (one ? k_build_cells<kEdgesOne, false> : k_build_cells<kEdgesTwo, false>);
-  hipLaunchKernelGGL(cells, dim3(rebuild_grid((int64_t)ncell * parts)), dim3(kBlock), 0, st, N, g, x, cell_start, be,
-                     capR, lout, ht, sc, parts, flags);
+  hipLaunchKernelGGL(cells, dim3(ncopy + rebuild_grid((int64_t)ncell * parts)), kb, 0, st, N, g, sorted, prim, ncopy,
+                     cell_start, be, capR, lout, ht, sc, parts, flags);
   const int place_groups = grid_blocks(N, kPlaceAtoms);
   hipLaunchKernelGGL(k_place_lists, dim3(place_groups < kPlaceGrid ? place_groups : kPlaceGrid), dim3(64), 0, st,
                      N, be.nbins,
