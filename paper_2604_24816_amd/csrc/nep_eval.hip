@@ -578,40 +578,31 @@ __global__ void __launch_bounds__(kBlock, 2) k_desc_net(ModelDev m, EvalBuffers 
 // and one coalesced global atomic per halo atom and component flushes it at the end
 // (scattered global atomics resolve at the memory side one cache line each).
 struct HaloLds {
-  float F[3][kHaloMax];
+  alignas(16) float F[3][kHaloMax];
   int start[kHaloCellsMax];
   int off[kHaloCellsMax + 1];
-  int ncells, natoms, ok;
 };
 
-// Loads the tile's halo table and clears the LDS forces; returns whether the tile
-// uses the LDS halo (uniform over the workgroup).
-__device__ bool load_halo(const EvalBuffers& b, int tile, HaloLds& h) {
-  if (threadIdx.x == 0) {
-    h.ncells = b.hinfo[4 * tile + 0];
-    h.natoms = b.hinfo[4 * tile + 1];
-    h.ok = b.hinfo[4 * tile + 2];
-  }
-  __syncthreads();
-  if (!h.ok) return false;
-  const int nc = h.ncells, na = h.natoms;
+// Loads the tile's halo table of nc cells and clears the LDS forces of its na atoms (as
+// 16-byte words: the rows of F are padded to whole ones). A barrier must follow.
+__device__ __forceinline__ void load_halo(const EvalBuffers& b, int tile, int nc, int na, HaloLds& h) {
   for (int k = threadIdx.x; k < nc; k += kBlock) h.start[k] = b.hstart[(int64_t)tile * kHaloCellsMax + k];
   for (int k = threadIdx.x; k <= nc; k += kBlock) h.off[k] = b.hoff[(int64_t)tile * (kHaloCellsMax + 1) + k];
-  for (int t = threadIdx.x; t < na; t += kBlock) {
-    h.F[0][t] = 0.f;
-    h.F[1][t] = 0.f;
-    h.F[2][t] = 0.f;
+  static_assert(kHaloMax % 4 == 0, "whole words");
+  const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int t = threadIdx.x; 4 * t < na; t += kBlock) {
+    reinterpret_cast<float4*>(h.F[0])[t] = zero;
+    reinterpret_cast<float4*>(h.F[1])[t] = zero;
+    reinterpret_cast<float4*>(h.F[2])[t] = zero;
   }
-  __syncthreads();
-  return true;
 }
 
 // Adds the halo forces to F with one global atomic per halo atom and component that
 // received a force: 16 lanes to a halo cell, whose atoms are contiguous both in the halo
 // and in F.
-__device__ void flush_halo(const HaloLds& h, float* __restrict__ F, int64_t N) {
+__device__ void flush_halo(const HaloLds& h, int nc, float* __restrict__ F, int64_t N) {
   const int q = threadIdx.x >> 4, u = threadIdx.x & 15;
-  for (int c = q; c < h.ncells; c += kBlock / 16) {
+  for (int c = q; c < nc; c += kBlock / 16) {
     const int o = h.off[c], n = h.off[c + 1] - o;
     const int64_t g0 = h.start[c];
     for (int t = u; t < n; t += 16) {
@@ -713,17 +704,27 @@ __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, 
   const int64_t i = (int64_t)sub * (kBlock / L) + threadIdx.x / L;
   const int l = threadIdx.x % L;
   const bool valid = i < N;
-  bool lds = false;
-  int kR = 0, kA = 0;
-  if (valid) {
-    kR = radial_bound(b, i);
-    kA = angular_bound(b, i);
+  // the center's own loads first (clamped for the lanes past the system), so that they are
+  // in flight with the halo's
+  const int64_t ic = valid ? i : N - 1;
+  const int kR = radial_bound(b, ic), kA = angular_bound(b, ic);
+  const uint4* ri = b.rec + 4 * ic;
+  const uint4 r0 = ri[0], r1 = ri[1], r2w = ri[2];
+  const int ti = MULTI ? (int)ri[3].x : 0;
+  constexpr int KR = S::KR;
+  float G[NA * NC];
+  if constexpr (DET) {
+    load_g_row<S>(b.G + ic * g_row<S>(), G);
+  } else {
+#pragma unroll
+    for (int k = 0; k < NA * NC; ++k) G[k] = b.G[(int64_t)k * N + ic];
   }
-  if constexpr (MULTI) {
-    stage_pairs<S>(m, tab);
-    if (DET) __syncthreads();  // load_halo has barriers of its own
-  }
-  if constexpr (!DET) lds = load_halo(b, sub / L, halo);
+  const int tile = sub / L;
+  const int hcells = DET ? 0 : b.hinfo[4 * tile], hatoms = DET ? 0 : b.hinfo[4 * tile + 1];
+  const bool lds = !DET && b.hinfo[4 * tile + 2] != 0;
+  if constexpr (MULTI) stage_pairs<S>(m, tab);
+  if (lds) load_halo(b, tile, hcells, hatoms, halo);
+  if (MULTI || lds) __syncthreads();
   const double hx = box_quantum(b.box[0]), hy = box_quantum(b.box[1]), hz = box_quantum(b.box[2]);
   const CutConst cutR = cut_const(m.rcR);
   const float kXR = -0.25f * kPiF * cutR.rc_inv;  // X = kXR Z for the radial series
@@ -734,10 +735,7 @@ __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, 
 #pragma unroll
   for (int k = 0; k < 9; ++k) w[k] = 0.f;
   if (valid) {
-    const uint4* ri = b.rec + 4 * i;
-    const uint4 r0 = ri[0], r1 = ri[1], r2w = ri[2];
     const QPos qi{r0.x, r0.y, r0.z};
-    const int ti = MULTI ? (int)ri[3].x : 0;
     const uint4* plane = MULTI && ti ? b.rec1 : b.rec;  // the neighbours' coefficients towards this species
     // own radial coefficients (v = w_0 + sum_k w_k and w_1..w_8) towards each species
     const float wi[9] = {__uint_as_float(r0.w),  __uint_as_float(r1.x),  __uint_as_float(r1.y),
@@ -755,14 +753,6 @@ __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, 
           wi1[k] = rf[k];
         }
       }
-    }
-    constexpr int KR = S::KR;
-    float G[NA * NC];
-    if constexpr (DET) {
-      load_g_row<S>(b.G + i * g_row<S>(), G);
-    } else {
-#pragma unroll
-      for (int k = 0; k < NA * NC; ++k) G[k] = b.G[(int64_t)k * N + i];
     }
     const float rcR2 = (float)(m.rcR64 * m.rcR64), rcA2 = (float)(m.rcA64 * m.rcA64), zbl2 = (float)m.zbl_o2;
     int nz = 0;  // pairs inside the ZBL radius
@@ -893,7 +883,7 @@ __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, 
   if constexpr (!DET) {
     if (lds) {
       __syncthreads();
-      flush_halo(halo, b.F, N);
+      flush_halo(halo, hcells, b.F, N);
     }
   }
   // the tile's energy (the descriptor kernel's U_i, ZBL included) and virial in FP64

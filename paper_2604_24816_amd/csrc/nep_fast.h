@@ -319,7 +319,10 @@ __device__ __forceinline__ void for_each_rec_fast(const int32_t* __restrict__ nb
 // The loop of one of the L lanes that share a center (lane l visits entries l, l + L, ...
 // below k1): the record of entry p + L and the index of entry p + 2 L are in flight while
 // the body of entry p runs. Loads past the last visited entry read that entry again, so
-// every address stays inside the list however far L reaches ahead.
+// every address stays inside the list however far L reaches ahead. The body appears once
+// (the queue moves by register copies): a lane makes few turns, and a small system's
+// kernels run from a cold instruction cache, where code that runs once or twice costs more
+// than the copies.
 template <int W, int RS, int L, class Body>
 __device__ __forceinline__ void for_each_rec_lanes(const int32_t* __restrict__ nbr, const uint4* __restrict__ rec,
                                                    int64_t N, int64_t i, int l, int k1, Body&& body) {
@@ -327,22 +330,20 @@ __device__ __forceinline__ void for_each_rec_lanes(const int32_t* __restrict__ n
   auto index = [&](int p) { return nbr[(uint64_t)(uint32_t)(p < k1 ? p : k1 - 1) * (uint64_t)N + i]; };
   auto record = [&](int32_t j, int w) { return rec[(uint64_t)(uint32_t)j * RS + w]; };
   int32_t j0 = index(l), j1 = index(l + L);
-  uint4 rq[2][W];
+  uint4 r0[W];
 #pragma unroll
-  for (int w = 0; w < W; ++w) rq[0][w] = record(j0, w);
-  for (int p0 = l; p0 < k1; p0 += 2 * L) {
+  for (int w = 0; w < W; ++w) r0[w] = record(j0, w);
+#pragma unroll 1
+  for (int p = l; p < k1; p += L) {
+    const int32_t j2 = index(p + 2 * L);
+    uint4 r1[W];
 #pragma unroll
-    for (int ph = 0; ph < 2; ++ph) {
-      const int p = p0 + ph * L;
-      if (p < k1) {
-        const int32_t j2 = index(p + 2 * L);
+    for (int w = 0; w < W; ++w) r1[w] = record(j1, w);
+    body(p, j0, r0);
+    j0 = j1;
+    j1 = j2;
 #pragma unroll
-        for (int w = 0; w < W; ++w) rq[1 - ph][w] = record(j1, w);
-        body(p, j0, rq[ph]);
-        j0 = j1;
-        j1 = j2;
-      }
-    }
+    for (int w = 0; w < W; ++w) r0[w] = r1[w];
   }
 }
 
