@@ -805,19 +805,19 @@ int nep_compute_energy_forces_virial(nep_system* s, int32_t slot, int32_t precis
   } else if ((st = do_eval(s, slot, precision))) {
     return st;
   }
-  if ((st = reduce_ew(s, 0))) return st;
-  if (forces) {
-    double* dst = on_device ? forces : s->staging;
-    if (precision == NEP_FP64) HIPCHK(launch_state_out(N, s->perm, F64, dst, s->st));
-    else HIPCHK(launch_forces_out(N, s->perm, s->F[slot], dst, s->st));
-    if (!on_device) HIPCHK(hipMemcpyAsync(forces, s->staging, 3 * N * sizeof(double), hipMemcpyDeviceToHost, s->st));
-  }
-  if (per_atom_energy) {
-    double* dst = on_device ? per_atom_energy : s->staging;
-    if (precision == NEP_FP64) HIPCHK(launch_scalar_out64(N, s->perm, U64, dst, s->st));
-    else HIPCHK(launch_scalar_out(N, s->perm, s->U, dst, s->st));
-    if (!on_device)
-      HIPCHK(hipMemcpyAsync(per_atom_energy, s->staging, N * sizeof(double), hipMemcpyDeviceToHost, s->st));
+  // host outputs go through the staging buffer: forces with the sums, then the energies
+  double* fdst = forces && !on_device ? s->staging : forces;
+  double* udst = on_device ? per_atom_energy : nullptr;
+  auto results = [&](double* f, double* u) {
+    return precision == NEP_FP64 ? launch_results64(s->gpart, s->ew_rows, s->res, N, s->perm, F64, U64, f, u, s->st)
+                                 : launch_results(s->gpart, s->ew_rows, s->res, N, s->perm, s->F[slot], s->U, f, u, s->st);
+  };
+  HIPCHK(results(fdst, udst));
+  if (forces && !on_device)
+    HIPCHK(hipMemcpyAsync(forces, s->staging, 3 * N * sizeof(double), hipMemcpyDeviceToHost, s->st));
+  if (per_atom_energy && !on_device) {
+    HIPCHK(results(nullptr, s->staging));
+    HIPCHK(hipMemcpyAsync(per_atom_energy, s->staging, N * sizeof(double), hipMemcpyDeviceToHost, s->st));
   }
   double r[10];
   HIPCHK(hipMemcpyAsync(r, s->res, 10 * sizeof(double), hipMemcpyDeviceToHost, s->st));
@@ -1175,9 +1175,7 @@ int nep_train_forward(nep_system* s, int32_t slot, const float* theta, double* e
   HIPCHK(launch_train_forward(s->mdev[slot], theta, eval_buffers(s, slot), s->st));
   s->ew_rows = eval_rows(s->mdev[slot], s->N);
   s->force_valid[slot] = false;
-  int st;
-  if ((st = reduce_ew(s, 0))) return st;
-  if (forces) HIPCHK(launch_scatter_vec_f32(s->N, s->perm, s->F[slot], forces, s->st));
+  HIPCHK(launch_results_f32(s->gpart, s->ew_rows, s->res, s->N, s->perm, s->F[slot], forces, s->st));
   double r;
   HIPCHK(hipMemcpyAsync(&r, s->res, sizeof(double), hipMemcpyDeviceToHost, s->st));
   HIPCHK(hipStreamSynchronize(s->st));
@@ -1211,9 +1209,7 @@ int nep_train_forward_params(nep_system* s, int32_t slot, const float* params, d
   HIPCHK(launch_train_forward_params(s->mdev[slot], params, eval_buffers(s, slot), s->st));
   s->ew_rows = eval_rows(s->mdev[slot], s->N);
   s->force_valid[slot] = false;
-  int st;
-  if ((st = reduce_ew(s, 0))) return st;
-  if (forces) HIPCHK(launch_scatter_vec_f32(s->N, s->perm, s->F[slot], forces, s->st));
+  HIPCHK(launch_results_f32(s->gpart, s->ew_rows, s->res, s->N, s->perm, s->F[slot], forces, s->st));
   double r;
   HIPCHK(hipMemcpyAsync(&r, s->res, sizeof(double), hipMemcpyDeviceToHost, s->st));
   HIPCHK(hipStreamSynchronize(s->st));

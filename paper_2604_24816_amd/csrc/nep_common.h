@@ -151,8 +151,6 @@ struct ListScratch {
   uint4* q;
   uint4* l;
 };
-constexpr int kPlaceParts = 4;   // lanes per atom in the placement; part h starts at entry 32 h
-constexpr int kPartLen = 32;
 constexpr int64_t kMaxAtoms = (int64_t)1 << 28;  // list entries keep the bin in bits 28-31
 constexpr int kMaxCap = 4096;                     // per-atom list capacity (16-bit bin counters)
 
@@ -319,7 +317,6 @@ hipError_t launch_eval64(const ModelDev& m, const Model64& p, const EvalBuffers&
                          double* F64, hipStream_t st);
 // Rows of energy and virial partials it writes.
 int eval64_rows(int64_t N);
-hipError_t launch_scalar_out64(int64_t N, const int32_t* perm, const double* u, double* out, hipStream_t st);
 // FP64 gradient of gE E + sum gF . F with respect to the packed parameters (n_params
 // values, overwritten), gF_sorted [3][N] in sorted order or null.
 hipError_t launch_grad64(const ModelDev& m, const Model64& p, const EvalBuffers& b, const double* gF_sorted,
@@ -350,12 +347,15 @@ hipError_t launch_state_in(int64_t N, const double* x_aos, const double* v_aos,
                            int32_t* type, int32_t* perm, uint4* pos, int32_t* flags, hipStream_t st);
 hipError_t launch_state_out(int64_t N, const int32_t* perm, const double* soa, double* aos,
                             hipStream_t st);
-hipError_t launch_forces_out(int64_t N, const int32_t* perm, const float* F, double* aos,
-                             hipStream_t st);
-hipError_t launch_scalar_out(int64_t N, const int32_t* perm, const float* U, double* out,
-                             hipStream_t st);
-hipError_t launch_scatter_vec_f32(int64_t N, const int32_t* perm, const float* soa_sorted,
-                                  float* aos_orig, hipStream_t st);
+// Energy and virial sums (10 values into out) of an evaluation's ew_rows partials, and its
+// forces and per-atom energies (either may be null) in the caller's order; the FP64 and the
+// training forms.
+hipError_t launch_results(const double* ew, int ew_rows, double* out, int64_t N, const int32_t* perm, const float* F,
+                          const float* U, double* forces, double* energies, hipStream_t st);
+hipError_t launch_results64(const double* ew, int ew_rows, double* out, int64_t N, const int32_t* perm,
+                            const double* F, const double* U, double* forces, double* energies, hipStream_t st);
+hipError_t launch_results_f32(const double* ew, int ew_rows, double* out, int64_t N, const int32_t* perm,
+                              const float* F, float* forces, hipStream_t st);
 
 // Training (nep_train.hip)
 struct TrainBuffers {

@@ -977,21 +977,29 @@ hipError_t launch_shape(const ModelDev& m, int precision, const EvalBuffers& b, 
 }
 
 
-// Derived radial tables (nep_fast.h) of nblk coefficient blocks [nblk][N][K]: one thread
-// per (block, channel) writes h_n0 = (c_n0 + sum_k c_nk) / 2, h_nk = c_nk / 2 and
-// d_n(k-1) = k c_nk / 2 into that block's [N][2K - 1] table.
-__global__ void k_derive_coeffs(const float* __restrict__ c, int nblk, int N, int K, float* __restrict__ h) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= nblk * N) return;
-  const int blk = t / N, n = t % N;
-  const float* cn = c + ((int64_t)blk * N + n) * K;
-  float* hb = h + (int64_t)blk * N * (2 * K - 1);
-  float sum = 0.f;
-  for (int k = 0; k < K; ++k) sum += cn[k];
-  hb[n * K] = 0.5f * (cn[0] + sum);
-  for (int k = 1; k < K; ++k) {
-    hb[n * K + k] = 0.5f * cn[k];
-    hb[N * K + n * (K - 1) + k - 1] = (0.5f * (float)k) * cn[k];
+// Derived radial tables (nep_fast.h) of coefficient blocks [nblk][N][K]: one thread per
+// (block, channel) writes h_n0 = (c_n0 + sum_k c_nk) / 2, h_nk = c_nk / 2 and
+// d_n(k-1) = k c_nk / 2 into that block's [N][2K - 1] table. Workgroup 0 derives the radial
+// blocks, workgroup 1 the angular ones.
+struct DeriveArgs {
+  const float* c;
+  float* h;
+  int N, K;
+};
+__global__ void k_derive_coeffs(DeriveArgs r, DeriveArgs a, int nblk) {
+  const DeriveArgs d = blockIdx.x == 0 ? r : a;
+  const int N = d.N, K = d.K;
+  for (int t = threadIdx.x; t < nblk * N; t += blockDim.x) {
+    const int blk = t / N, n = t % N;
+    const float* cn = d.c + ((int64_t)blk * N + n) * K;
+    float* hb = d.h + (int64_t)blk * N * (2 * K - 1);
+    float sum = 0.f;
+    for (int k = 0; k < K; ++k) sum += cn[k];
+    hb[n * K] = 0.5f * (cn[0] + sum);
+    for (int k = 1; k < K; ++k) {
+      hb[n * K + k] = 0.5f * cn[k];
+      hb[N * K + n * (K - 1) + k - 1] = (0.5f * (float)k) * cn[k];
+    }
   }
 }
 
@@ -1003,8 +1011,8 @@ int64_t derived_coeff_floats(int T, int nR, int kR, int nA, int kA) {
 
 hipError_t launch_derive_coeffs(int T, int nR, int kR, int nA, int kA, const float* cR, const float* cA, float* hR,
                                 float* hA, hipStream_t st) {
-  hipLaunchKernelGGL(k_derive_coeffs, dim3(1), dim3(64), 0, st, cR, T * T, nR, kR, hR);
-  hipLaunchKernelGGL(k_derive_coeffs, dim3(1), dim3(64), 0, st, cA, T * T, nA, kA, hA);
+  hipLaunchKernelGGL(k_derive_coeffs, dim3(2), dim3(64), 0, st, DeriveArgs{cR, hR, nR, kR}, DeriveArgs{cA, hA, nA, kA},
+                     T * T);
   return hipGetLastError();
 }
 

@@ -755,12 +755,6 @@ __global__ void k_zero64(int64_t n, double* __restrict__ a) {
   if (k < n) a[k] = 0.0;
 }
 
-__global__ void k_scalar_out64(int64_t N, const int32_t* __restrict__ perm, const double* __restrict__ u,
-                               double* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < N) out[perm[i]] = u[i];
-}
-
 }  // namespace
 
 int eval64_rows(int64_t N) { return grid_blocks(N, kC64); }
@@ -813,11 +807,6 @@ hipError_t launch_grad64(const ModelDev& m, const Model64& p, const EvalBuffers&
 hipError_t launch_gather_vec64(int64_t N, const int32_t* perm, const double* aos_orig, double* soa_sorted,
                                hipStream_t st) {
   hipLaunchKernelGGL(k_gather_vec64, dim3(grid_blocks(N)), dim3(kBlock), 0, st, N, perm, aos_orig, soa_sorted);
-  return hipGetLastError();
-}
-
-hipError_t launch_scalar_out64(int64_t N, const int32_t* perm, const double* u, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_scalar_out64, dim3(grid_blocks(N)), dim3(kBlock), 0, st, N, perm, u, out);
   return hipGetLastError();
 }
 

@@ -8,14 +8,13 @@
 namespace nep {
 namespace {
 
-// Sums of slots first .. first + nvals - 1 over the rows of partials, one workgroup: 64
-// rows of 16 slots per pass (whole 128-byte rows, every slot at once), then the 64 row
-// groups of each slot in a fixed order.
+// Sums of slots first .. first + nvals - 1 over the rows of partials, one workgroup of
+// kRedBlock threads: 64 rows of 16 slots per pass (whole 128-byte rows, every slot at once),
+// then the 64 row groups of each slot in a fixed order. sh holds kRedBlock doubles.
 constexpr int kRedBlock = 1024;
 
-__global__ void __launch_bounds__(kRedBlock)
-k_reduce_partials(const double* __restrict__ partial, int nblocks, int first, int nvals, double* __restrict__ out) {
-  __shared__ double sh[kRedBlock];
+__device__ __forceinline__ void reduce_rows(const double* __restrict__ partial, int nblocks, int first, int nvals,
+                                            double* __restrict__ out, double* sh) {
   constexpr int kRows = kRedBlock / kPartialStride;
   const int slot = threadIdx.x % kPartialStride, row = threadIdx.x / kPartialStride;
   double s = 0.0;
@@ -30,6 +29,42 @@ k_reduce_partials(const double* __restrict__ partial, int nblocks, int first, in
     for (int r = 0; r < kRows; ++r) t += sh[r * kPartialStride + threadIdx.x];
     out[k] = t;
   }
+}
+
+__global__ void __launch_bounds__(kRedBlock)
+k_reduce_partials(const double* __restrict__ partial, int nblocks, int first, int nvals, double* __restrict__ out) {
+  __shared__ double sh[kRedBlock];
+  reduce_rows(partial, nblocks, first, nvals, out, sh);
+}
+
+// An evaluation's results in one launch: the first workgroup sums the energy and virial
+// partials, the others write forces [3 o + c] and (or) per-atom energies [o] in the
+// caller's order as FP64. R: the type the evaluation holds them in.
+template <class R>
+__global__ void __launch_bounds__(kRedBlock)
+k_results(const double* __restrict__ ew, int ew_rows, double* __restrict__ out, int64_t N,
+          const int32_t* __restrict__ perm, const R* __restrict__ F, const R* __restrict__ U,
+          double* __restrict__ forces, double* __restrict__ energies) {
+  __shared__ double sh[kRedBlock];
+  if (blockIdx.x == 0) return reduce_rows(ew, ew_rows, P_ENERGY, 10, out, sh);
+  const int64_t p = (int64_t)(blockIdx.x - 1) * kRedBlock + threadIdx.x;
+  if (p >= N) return;
+  const int64_t o = perm[p];
+  if (forces)
+    for (int c = 0; c < 3; ++c) forces[3 * o + c] = (double)F[c * N + p];
+  if (energies) energies[o] = (double)U[p];
+}
+
+// The same for the training forward: FP32 forces in the caller's order.
+__global__ void __launch_bounds__(kRedBlock)
+k_results_f32(const double* __restrict__ ew, int ew_rows, double* __restrict__ out, int64_t N,
+              const int32_t* __restrict__ perm, const float* __restrict__ F, float* __restrict__ forces) {
+  __shared__ double sh[kRedBlock];
+  if (blockIdx.x == 0) return reduce_rows(ew, ew_rows, P_ENERGY, 10, out, sh);
+  const int64_t p = (int64_t)(blockIdx.x - 1) * kRedBlock + threadIdx.x;
+  if (p >= N) return;
+  const int64_t o = perm[p];
+  for (int c = 0; c < 3; ++c) forces[3 * o + c] = F[c * N + p];
 }
 
 __device__ __forceinline__ double wrap_coord(double xv, double L) {
@@ -289,29 +324,6 @@ __global__ void k_state_out(int64_t N, const int32_t* __restrict__ perm, const d
   for (int c = 0; c < 3; ++c) aos[3 * o + c] = soa[c * N + p];
 }
 
-__global__ void k_forces_out(int64_t N, const int32_t* __restrict__ perm, const float* __restrict__ F,
-                             double* __restrict__ aos) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= N) return;
-  const int64_t o = perm[p];
-  for (int c = 0; c < 3; ++c) aos[3 * o + c] = (double)F[c * N + p];
-}
-
-__global__ void k_scalar_out(int64_t N, const int32_t* __restrict__ perm, const float* __restrict__ U,
-                             double* __restrict__ out) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= N) return;
-  out[perm[p]] = (double)U[p];
-}
-
-__global__ void k_scatter_vec_f32(int64_t N, const int32_t* __restrict__ perm, const float* __restrict__ s,
-                                  float* __restrict__ a) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= N) return;
-  const int64_t o = perm[p];
-  for (int c = 0; c < 3; ++c) a[3 * o + c] = s[c * N + p];
-}
-
 }  // namespace
 
 hipError_t launch_reduce_partials(const double* partial, int nblocks, int first, int nvals, double* out,
@@ -397,20 +409,26 @@ hipError_t launch_state_out(int64_t N, const int32_t* perm, const double* soa, d
   return hipGetLastError();
 }
 
-hipError_t launch_forces_out(int64_t N, const int32_t* perm, const float* F, double* aos, hipStream_t st) {
-  hipLaunchKernelGGL(k_forces_out, dim3(grid_blocks(N)), dim3(kBlock), 0, st, N, perm, F, aos);
+template <class R>
+static hipError_t results(const double* ew, int ew_rows, double* out, int64_t N, const int32_t* perm, const R* F,
+                          const R* U, double* forces, double* energies, hipStream_t st) {
+  const int nb = 1 + (forces || energies ? grid_blocks(N, kRedBlock) : 0);
+  hipLaunchKernelGGL(k_results<R>, dim3(nb), dim3(kRedBlock), 0, st, ew, ew_rows, out, N, perm, F, U, forces,
+                     energies);
   return hipGetLastError();
 }
-
-hipError_t launch_scalar_out(int64_t N, const int32_t* perm, const float* U, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_scalar_out, dim3(grid_blocks(N)), dim3(kBlock), 0, st, N, perm, U, out);
-  return hipGetLastError();
+hipError_t launch_results(const double* ew, int ew_rows, double* out, int64_t N, const int32_t* perm, const float* F,
+                          const float* U, double* forces, double* energies, hipStream_t st) {
+  return results(ew, ew_rows, out, N, perm, F, U, forces, energies, st);
 }
-
-hipError_t launch_scatter_vec_f32(int64_t N, const int32_t* perm, const float* soa_sorted, float* aos_orig,
-                                  hipStream_t st) {
-  hipLaunchKernelGGL(k_scatter_vec_f32, dim3(grid_blocks(N)), dim3(kBlock), 0, st, N, perm, soa_sorted,
-                     aos_orig);
+hipError_t launch_results64(const double* ew, int ew_rows, double* out, int64_t N, const int32_t* perm,
+                            const double* F, const double* U, double* forces, double* energies, hipStream_t st) {
+  return results(ew, ew_rows, out, N, perm, F, U, forces, energies, st);
+}
+hipError_t launch_results_f32(const double* ew, int ew_rows, double* out, int64_t N, const int32_t* perm,
+                              const float* F, float* forces, hipStream_t st) {
+  hipLaunchKernelGGL(k_results_f32, dim3(1 + (forces ? grid_blocks(N, kRedBlock) : 0)), dim3(kRedBlock), 0, st, ew,
+                     ew_rows, out, N, perm, F, forces);
   return hipGetLastError();
 }
 

@@ -514,10 +514,9 @@ k_sort_halo(int64_t N, CellGrid g, int nsort, const int32_t* __restrict__ start,
   }
 }
 
-// Halo-local index of sorted atom q in tile `tile` (q must lie in the halo).
-__device__ __forceinline__ int halo_index(const HaloTables& ht, int tile, int ncells, int q) {
-  const int32_t* hs = ht.start + (int64_t)tile * kHaloCellsMax;
-  const int32_t* ho = ht.off + (int64_t)tile * (kHaloCellsMax + 1);
+// Halo-local index of sorted atom q, which must lie in the halo of ncells cells with first
+// atoms hs and offsets ho.
+__device__ __forceinline__ int halo_search(const int32_t* hs, const int32_t* ho, int ncells, int q) {
   int lo = 0, hi = ncells - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
@@ -525,6 +524,10 @@ __device__ __forceinline__ int halo_index(const HaloTables& ht, int tile, int nc
     else hi = mid - 1;
   }
   return ho[lo] + (q - hs[lo]);
+}
+// The same in tile `tile`.
+__device__ __forceinline__ int halo_index(const HaloTables& ht, int tile, int ncells, int q) {
+  return halo_search(ht.start + (int64_t)tile * kHaloCellsMax, ht.off + (int64_t)tile * (kHaloCellsMax + 1), ncells, q);
 }
 
 // Distance bin of a pair inside the list cutoff: the number of interior edges <= r^2,
@@ -586,8 +589,13 @@ struct CellStage {
   uint8_t C[kCellCand];
   int cq0[27], cum[28];
   double shift[3][27];
-  uint32_t qk[kBlock / 64][kCellQueue];
-  double qr[kBlock / 64][kCellQueue];
+  union {
+    struct {
+      uint32_t qk[kBlock / 64][kCellQueue];
+      double qr[kBlock / 64][kCellQueue];
+    };
+    int32_t halo[2][2][kHaloCellsMax];  // first atoms and offsets of two tiles' halo cells, before the queues are used
+  };
   int loc0s[2][27];  // halo offset of each stencil cell for the cell's first two tiles
 };
 
@@ -744,6 +752,7 @@ __device__ void build_cell(int64_t N, const CellGrid& g, const double* __restric
   const int o0 = n0 == 3 ? 1 : 0, o1 = n1 == 3 ? 1 : 0, o2 = n2 == 3 ? 1 : 0;
   const int ns = n0 * n1 * n2;
   const int home = (o2 * n1 + o1) * n0 + o0;
+  int n_s = 0;
   if (t < ns) {
     const int r3[3] = {cx + t % n0 - o0, cy + (t / n0) % n1 - o1, cz + t / (n0 * n1) - o2};
     int w3[3];
@@ -753,30 +762,37 @@ __device__ void build_cell(int64_t N, const CellGrid& g, const double* __restric
       S.shift[d][t] = r3[d] < 0 ? -g.box[d] : (r3[d] >= g.nc[d] ? g.box[d] : 0.0);
     }
     const int cc = cell_lin(g, w3[0], w3[1], w3[2]);
-    S.cq0[t] = start[cc];
-    S.cum[t] = start[cc + 1] - start[cc];
+    const int q0 = start[cc];
+    n_s = start[cc + 1] - q0;
+    S.cq0[t] = q0;
   }
-  __syncthreads();
-  if (t == 0) {
-    int acc = 0;
-    for (int k = 0; k < ns; ++k) {
-      const int v = S.cum[k];
-      S.cum[k] = acc;
-      acc += v;
+  // the halo tables of the tile of the cell's first atom and of the next tile if it holds
+  // atoms of the cell (other tiles, for cells of more than 256 atoms, are searched in global
+  // memory when reached)
+  int hn[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int tl = tile0 + u;
+    hn[u] = tl * kBlock < s1 && ht.info[4 * tl + 2] != 0 ? ht.info[4 * tl] : 0;
+    for (int k = t; k < hn[u]; k += kBlock) {
+      S.halo[u][0][k] = ht.start[(int64_t)tl * kHaloCellsMax + k];
+      S.halo[u][1][k] = ht.off[(int64_t)tl * (kHaloCellsMax + 1) + k];
     }
-    S.cum[ns] = acc;
+  }
+  if (w == 0) {  // exclusive prefix of the stencil cells' counts
+    const int incl = wave_scan(n_s);
+    if (t < ns) S.cum[t] = incl - n_s;
+    if (t == ns - 1) S.cum[ns] = incl;
   }
   __syncthreads();
   const int nc = S.cum[ns];
-  // halo-local offsets for the tile of the cell's first atom and the next tile if it
-  // holds atoms of the cell (other tiles, for cells of more than 256 atoms, are
-  // looked up when reached); computed while the positions load
+  // halo-local offset of each stencil cell in the two tiles
   if (t >= 64 && t < 64 + 2 * ns) {
-    const int u = t - 64, tl = tile0 + u / ns, sc0 = u % ns;
+    const int u = (t - 64) / ns, sc0 = (t - 64) % ns;
     int v = 0;
-    if (tl * kBlock < s1 && ht.info[4 * tl + 2] != 0 && S.cum[sc0 + 1] > S.cum[sc0])
-      v = halo_index(ht, tl, ht.info[4 * tl + 0], S.cq0[sc0]) - S.cq0[sc0];
-    S.loc0s[u / ns][sc0] = v;
+    if (hn[u] > 0 && S.cum[sc0 + 1] > S.cum[sc0])
+      v = halo_search(S.halo[u][0], S.halo[u][1], hn[u], S.cq0[sc0]) - S.cq0[sc0];
+    S.loc0s[u][sc0] = v;
   }
   const bool staged = nc <= kCellCand;
   if (staged) {
@@ -844,34 +860,38 @@ k_build_cells(int64_t N, CellGrid g, SortedState o, PrimaryState prim, int ncopy
   }
 }
 
-// Workgroups to a cell: as many as give the chip's 256 compute units eight workgroups each,
-// up to one atom per wavefront of a 32-atom cell. Every workgroup of a cell stages the whole
-// stencil, so more of them only pay while compute units are idle: 4,000 atoms (125 cells)
-// took 52 us with one and take 30 with eight.
+// Workgroups to a cell: as many as fill the chip's 256 compute units once, four to a unit
+// (what the staging's LDS allows), up to one atom per wavefront of a 32-atom cell; every
+// workgroup of a cell stages the whole stencil. us with 1 / 2 / 4 / 8 of them:
+//   8 cells (256 atoms)     28 18 14 13      512 (16,384)   56 41 48 57
+//   216 (4,000)             51 31 25 27    1,000 (32,000)   66 70 80 99
 inline int build_parts(int ncell) {
-  const int p = 2048 / ncell;
+  const int p = 1024 / ncell;
   return p < 1 ? 1 : (p > 8 ? 8 : p);
 }
 
-// One wavefront per 16 atoms, four lanes per atom: counts each atom's scratch
+// One wavefront per 64 / PARTS atoms, PARTS lanes per atom: counts each atom's scratch
 // entries per bin, writes the bin breakpoints, and orders the entries by bin (stable
-// inside a bin), writing the list and its halo-local indices row by row, 16
-// consecutive atoms (64 bytes) per store, through LDS tiles of kPlaceRows rows;
-// longer lists take further rounds. Lane h counts and places entries [32 h, 32 (h + 1))
+// inside a bin), writing the list and its halo-local indices row by row, 64 / PARTS
+// consecutive atoms (64 or 16 bytes) per store, through LDS tiles of kPlaceRows rows;
+// longer lists take further rounds. Lane h counts and places entries [PLEN h, PLEN (h + 1))
 // (the last lane the rest), starting each bin after the entries of earlier parts.
-// Entries outside the current round go to a spare row.
+// Entries outside the current round go to a spare row. Four lanes with 32 entries each write
+// whole 64-byte rows; where the chip is not full (place_parts) 16 lanes with 16 entries each
+// shorten the serial chain of counts and positions.
 constexpr int kPlaceRows = 159;  // one round for lists up to 159 entries (FCC metals at 7 A: ~135-150)
-constexpr int kPlaceAtoms = 64 / kPlaceParts;
 constexpr int kPlaceGrid = 16384;  // workgroups of the placement (grid-stride over atom groups)
 
+template <int PARTS>
 __global__ void __launch_bounds__(64)
 k_place_lists(int64_t N, int nbins, int binA, int capR, int capA, ListOut lo_, ListScratch sc,
               int32_t* __restrict__ flags) {
   if (flags[FLAG_REBUILD] == 0) return;
+  constexpr int kPlaceAtoms = 64 / PARTS, PLEN = PARTS == 4 ? 32 : 16;
   __shared__ uint32_t tile[(kPlaceRows + 1) * kPlaceAtoms];
   __shared__ uint16_t ltile[(kPlaceRows + 1) * kPlaceAtoms];
   __shared__ uint16_t off[kMaxBins * 64];  // next position of each bin, per lane
-  __shared__ uint64_t parts[kPlaceParts][BinCounts::kWords][kPlaceAtoms];  // per-bin counts of each part
+  __shared__ uint64_t parts[PARTS][BinCounts::kWords][kPlaceAtoms];  // per-bin counts of each part
   const int lane = threadIdx.x;
   const int a = lane % kPlaceAtoms;  // atom of the wavefront
   const int h = lane / kPlaceAtoms;  // which part of its column
@@ -888,8 +908,8 @@ k_place_lists(int64_t N, int nbins, int binA, int capR, int capA, ListOut lo_, L
       const int64_t pn = (grp + gridDim.x) * kPlaceAtoms + a;
       cnt_next = grp + gridDim.x < ngroups && pn < N ? lo_.cnt[pn] : 0;
     }
-    const int g_lo = h * kPartLen;
-    const int g_hi = h == kPlaceParts - 1 ? cnt : (g_lo + kPartLen < cnt ? g_lo + kPartLen : cnt);
+    const int g_lo = h * PLEN;
+    const int g_hi = h == PARTS - 1 ? cnt : (g_lo + PLEN < cnt ? g_lo + PLEN : cnt);
     const bool work = valid && g_lo < cnt;
     // longest list of the wavefront (uniform loop bounds for the row writes)
     int rows_max = cnt;
@@ -925,7 +945,7 @@ k_place_lists(int64_t N, int nbins, int binA, int capR, int capA, ListOut lo_, L
     };
     uint32_t c0[kStage], c1[kStage];
     uint4 l0[kStage / 8], l1[kStage / 8];  // their halo indices, loaded with them
-    const bool two = work && g_lo + kStage < g_hi;
+    const bool two = PLEN > kStage && work && g_lo + kStage < g_hi;
     if (work) {
       load_q(g_lo, c0);
       load_l(g_lo, l0);
@@ -935,7 +955,7 @@ k_place_lists(int64_t N, int nbins, int binA, int capR, int capA, ListOut lo_, L
       }
       count_chunk(g_lo, c0);
       if (two) count_chunk(g_lo + kStage, c1);
-      for (int g = g_lo + 2 * kStage; g < g_hi; g += kStage) {
+      for (int g = g_lo + PLEN; g < g_hi; g += kStage) {
         uint32_t t[kStage];
         load_q(g, t);
         count_chunk(g, t);
@@ -946,7 +966,7 @@ k_place_lists(int64_t N, int nbins, int binA, int capR, int capA, ListOut lo_, L
     __syncthreads();
     BinCounts before, total;
   #pragma unroll
-    for (int q = 0; q < kPlaceParts; ++q)
+    for (int q = 0; q < PARTS; ++q)
   #pragma unroll
       for (int k = 0; k < BinCounts::kWords; ++k) {
         const uint64_t c = parts[q][k][a];
@@ -999,7 +1019,7 @@ k_place_lists(int64_t N, int nbins, int binA, int capR, int capA, ListOut lo_, L
         };
         place_chunk(g_lo, c0, l0);
         if (two) place_chunk(g_lo + kStage, c1, l1);
-        for (int g = g_lo + 2 * kStage; g < g_hi; g += kStage) {
+        for (int g = g_lo + PLEN; g < g_hi; g += kStage) {
           uint32_t t[kStage];
           uint4 lt[kStage / 8];
           load_q(g, t);
@@ -1008,9 +1028,9 @@ k_place_lists(int64_t N, int nbins, int binA, int capR, int capA, ListOut lo_, L
         }
       }
       __syncthreads();
-      // the kPlaceParts lane groups write interleaved rows
+      // the PARTS lane groups write interleaved rows
       const int nrow = rows_max - r0 < rows ? rows_max - r0 : rows;
-      for (int r = h; r < nrow; r += kPlaceParts) {
+      for (int r = h; r < nrow; r += PARTS) {
         if (valid && r0 + r < cnt) {
           lo_.nbr[(int64_t)(r0 + r) * N + p] = (int32_t)tile[r * kPlaceAtoms + a];
           lo_.nbrl[(int64_t)(r0 + r) * N + p] = ltile[r * kPlaceAtoms + a];
@@ -1051,6 +1071,10 @@ hipError_t launch_zero_i32(int32_t* p, int64_t n, hipStream_t st) {
   hipLaunchKernelGGL(k_zero_i32, dim3(grid_blocks(n)), dim3(kBlock), 0, st, p, n);
   return hipGetLastError();
 }
+
+// Lanes per atom in the placement; us with 4 / 16: 256 atoms 15 / 9, 4,000 16 / 13,
+// 16,384 21 / 27, 32,000 23 / 47.
+inline int place_parts(int64_t N) { return N <= 8192 ? 16 : 4; }
 
 // The rebuild decision (see RebuildRule) from nd2 partial displacement maxima, then the
 // rebuild: every kernel after the decision returns at once when flags[FLAG_REBUILD] == 0,
@@ -1102,9 +1126,10 @@ hipError_t launch_rebuild(const RebuildRule& rule, const double* d2, int nd2, in
                      : (one ? k_build_cells<kEdgesOne, false> : k_build_cells<kEdgesTwo, false>);
   hipLaunchKernelGGL(cells, dim3(ncopy + rebuild_grid((int64_t)ncell * parts)), kb, 0, st, N, g, sorted, prim, ncopy,
                      cell_start, be, capR, lout, ht, sc, parts, flags);
-  const int place_groups = grid_blocks(N, kPlaceAtoms);
-  hipLaunchKernelGGL(k_place_lists, dim3(place_groups < kPlaceGrid ? place_groups : kPlaceGrid), dim3(64), 0, st,
-                     N, be.nbins,
+  const int pp = place_parts(N);
+  const int place_groups = grid_blocks(N, 64 / pp);
+  hipLaunchKernelGGL(pp == 16 ? k_place_lists<16> : k_place_lists<4>,
+                     dim3(place_groups < kPlaceGrid ? place_groups : kPlaceGrid), dim3(64), 0, st, N, be.nbins,
                      be.idxA[0][kFracs - 1], capR, capA, lout, sc, flags);
   return hipGetLastError();
 }
