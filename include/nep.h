@@ -21,7 +21,9 @@
  *     (allocated by the caller, e.g. as a torch tensor). The library never
  *     allocates device memory; it only carves the workspace. Pointers are
  *     borrowed for the duration of the call. The system object itself is a
- *     small host allocation freed by nep_system_destroy.
+ *     small host allocation freed by nep_system_destroy. Error words and
+ *     scalar results come back through a block of pinned host memory (80 KB for
+ *     the process, allocated with the first system).
  *   - Ordering: all device work of a system runs in order on the HIP stream
  *     given at creation. Calls that return host values synchronise that
  *     stream before returning; calls whose outputs are device pointers

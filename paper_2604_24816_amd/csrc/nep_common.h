@@ -142,6 +142,7 @@ struct ListOut {
   int32_t* bp;      // [kMaxBins][N] cumulative bin breakpoints
   uint16_t* nbrl;   // [capR][N] halo-local index of each entry
   uint16_t* selfl;  // [N] halo-local index of the atom itself
+  int32_t* alarm;   // host words at the FLAG_OVF_ indices, set to 1 when a list overflows (nullable)
 };
 
 // Per-build scratch: each atom's candidates in stencil order, sixteen per segment
@@ -218,7 +219,8 @@ inline int grid_blocks(int64_t n, int block = kBlock) {
 
 // ---------------------------------------------------------------- launchers
 // Neighbour lists (nep_neighbors.hip)
-hipError_t launch_zero_i32(int32_t* p, int64_t n, hipStream_t st);
+// Clears the words that a new system's first calls read: flags, cell counters, lists.
+hipError_t launch_clear(int32_t* flags, int32_t* cells, int ncell, int32_t* nbr, int64_t n, hipStream_t st);
 // What a step's rebuild decision needs: lists are rebuilt on a scheduled step, or when the
 // largest squared displacement since the build exceeds half_skin2 = (skin / 2)^2; reset
 // clears the flag words first (a build requested by the caller).
@@ -344,16 +346,18 @@ hipError_t launch_force_error(int64_t N, const float* Fa, const float* Fb, doubl
 hipError_t launch_sum_i32(int64_t N, const int32_t* a, double* partial, int slot, hipStream_t st);
 hipError_t launch_state_in(int64_t N, const double* x_aos, const double* v_aos,
                            const int32_t* type_in, int n_types, CellGrid g, double* x, double* v,
-                           int32_t* type, int32_t* perm, uint4* pos, int32_t* flags, hipStream_t st);
+                           int32_t* type, int32_t* perm, uint4* pos, int32_t* flags, int32_t* err, hipStream_t st);
 hipError_t launch_state_out(int64_t N, const int32_t* perm, const double* soa, double* aos,
                             hipStream_t st);
 // Energy and virial sums (10 values into out) of an evaluation's ew_rows partials, and its
 // forces and per-atom energies (either may be null) in the caller's order; the FP64 and the
-// training forms.
+// training forms. gate (nullable): flag words; with an error in them nothing but the sums is
+// written.
 hipError_t launch_results(const double* ew, int ew_rows, double* out, int64_t N, const int32_t* perm, const float* F,
-                          const float* U, double* forces, double* energies, hipStream_t st);
+                          const float* U, double* forces, double* energies, const int32_t* gate, hipStream_t st);
 hipError_t launch_results64(const double* ew, int ew_rows, double* out, int64_t N, const int32_t* perm,
-                            const double* F, const double* U, double* forces, double* energies, hipStream_t st);
+                            const double* F, const double* U, double* forces, double* energies, const int32_t* gate,
+                            hipStream_t st);
 hipError_t launch_results_f32(const double* ew, int ew_rows, double* out, int64_t N, const int32_t* perm,
                               const float* F, float* forces, hipStream_t st);
 

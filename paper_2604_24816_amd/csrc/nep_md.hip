@@ -39,16 +39,19 @@ k_reduce_partials(const double* __restrict__ partial, int nblocks, int first, in
 
 // An evaluation's results in one launch: the first workgroup sums the energy and virial
 // partials, the others write forces [3 o + c] and (or) per-atom energies [o] in the
-// caller's order as FP64. R: the type the evaluation holds them in.
+// caller's order as FP64. R: the type the evaluation holds them in. gate: the flag words, where
+// the state and the lists are not checked on the host yet; an error there leaves the caller's
+// arrays as they are.
 template <class R>
 __global__ void __launch_bounds__(kRedBlock)
 k_results(const double* __restrict__ ew, int ew_rows, double* __restrict__ out, int64_t N,
           const int32_t* __restrict__ perm, const R* __restrict__ F, const R* __restrict__ U,
-          double* __restrict__ forces, double* __restrict__ energies) {
+          double* __restrict__ forces, double* __restrict__ energies, const int32_t* __restrict__ gate) {
   __shared__ double sh[kRedBlock];
   if (blockIdx.x == 0) return reduce_rows(ew, ew_rows, P_ENERGY, 10, out, sh);
   const int64_t p = (int64_t)(blockIdx.x - 1) * kRedBlock + threadIdx.x;
   if (p >= N) return;
+  if (gate && (gate[FLAG_OVF_R] | gate[FLAG_OVF_A] | gate[FLAG_TYPE] | gate[FLAG_NONFINITE])) return;
   const int64_t o = perm[p];
   if (forces)
     for (int c = 0; c < 3; ++c) forces[3 * o + c] = (double)F[c * N + p];
@@ -288,29 +291,34 @@ __global__ void k_sum_i32(int64_t N, const int32_t* __restrict__ a, double* __re
   block_partial(p < N ? (double)a[p] : 0.0, sh, partial + (int64_t)blockIdx.x * kPartialStride + slot);
 }
 
+// err: the words that report a bad species or value, the flags themselves or host words at the
+// same indices (then the flags start from zero here).
 __global__ void k_state_in(int64_t N, const double* __restrict__ xa, const double* __restrict__ va,
                            const int32_t* __restrict__ tin, int n_types, CellGrid g, double* __restrict__ x,
                            double* __restrict__ v, int32_t* __restrict__ type, int32_t* __restrict__ perm,
-                           uint4* __restrict__ pos, int32_t* __restrict__ flags) {
+                           uint4* __restrict__ pos, int32_t* flags, int32_t* err) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p < FLAG_COUNT && err != flags) flags[p] = 0;
   if (p >= N) return;
   double xn[3];
   for (int c = 0; c < 3; ++c) {
     double xv = xa[3 * p + c];
-    if (!isfinite(xv)) flags[FLAG_NONFINITE] = 1;
-    else if (xv < 0.0 || xv >= g.box[c]) {
+    if (!isfinite(xv)) {
+      err[FLAG_NONFINITE] = 1;
+      xv = 0.0;  // keeps what is launched before the check in bounds
+    } else if (xv < 0.0 || xv >= g.box[c]) {
       xv = xv - g.box[c] * floor(xv / g.box[c]);
       if (xv >= g.box[c]) xv -= g.box[c];
     }
     x[c * N + p] = xv;
     xn[c] = xv;
     const double vv = va ? va[3 * p + c] : 0.0;
-    if (!isfinite(vv)) flags[FLAG_NONFINITE] = 1;
+    if (!isfinite(vv)) err[FLAG_NONFINITE] = 1;
     v[c * N + p] = vv;
   }
   const int t = tin[p];
   const bool bad = t < 0 || t >= n_types;
-  if (bad) flags[FLAG_TYPE] = 1;
+  if (bad) err[FLAG_TYPE] = 1;
   pos_put(pos, p, xn[0], xn[1], xn[2], bad ? 0 : t, g.box);
   type[p] = bad ? 0 : t;
   perm[p] = (int32_t)p;
@@ -398,9 +406,9 @@ hipError_t launch_sum_i32(int64_t N, const int32_t* a, double* partial, int slot
 
 hipError_t launch_state_in(int64_t N, const double* x_aos, const double* v_aos, const int32_t* type_in,
                            int n_types, CellGrid g, double* x, double* v, int32_t* type, int32_t* perm,
-                           uint4* pos, int32_t* flags, hipStream_t st) {
+                           uint4* pos, int32_t* flags, int32_t* err, hipStream_t st) {
   hipLaunchKernelGGL(k_state_in, dim3(grid_blocks(N)), dim3(kBlock), 0, st, N, x_aos, v_aos, type_in,
-                     n_types, g, x, v, type, perm, pos, flags);
+                     n_types, g, x, v, type, perm, pos, flags, err);
   return hipGetLastError();
 }
 
@@ -411,19 +419,20 @@ hipError_t launch_state_out(int64_t N, const int32_t* perm, const double* soa, d
 
 template <class R>
 static hipError_t results(const double* ew, int ew_rows, double* out, int64_t N, const int32_t* perm, const R* F,
-                          const R* U, double* forces, double* energies, hipStream_t st) {
+                          const R* U, double* forces, double* energies, const int32_t* gate, hipStream_t st) {
   const int nb = 1 + (forces || energies ? grid_blocks(N, kRedBlock) : 0);
   hipLaunchKernelGGL(k_results<R>, dim3(nb), dim3(kRedBlock), 0, st, ew, ew_rows, out, N, perm, F, U, forces,
-                     energies);
+                     energies, gate);
   return hipGetLastError();
 }
 hipError_t launch_results(const double* ew, int ew_rows, double* out, int64_t N, const int32_t* perm, const float* F,
-                          const float* U, double* forces, double* energies, hipStream_t st) {
-  return results(ew, ew_rows, out, N, perm, F, U, forces, energies, st);
+                          const float* U, double* forces, double* energies, const int32_t* gate, hipStream_t st) {
+  return results(ew, ew_rows, out, N, perm, F, U, forces, energies, gate, st);
 }
 hipError_t launch_results64(const double* ew, int ew_rows, double* out, int64_t N, const int32_t* perm,
-                            const double* F, const double* U, double* forces, double* energies, hipStream_t st) {
-  return results(ew, ew_rows, out, N, perm, F, U, forces, energies, st);
+                            const double* F, const double* U, double* forces, double* energies, const int32_t* gate,
+                            hipStream_t st) {
+  return results(ew, ew_rows, out, N, perm, F, U, forces, energies, gate, st);
 }
 hipError_t launch_results_f32(const double* ew, int ew_rows, double* out, int64_t N, const int32_t* perm,
                               const float* F, float* forces, hipStream_t st) {

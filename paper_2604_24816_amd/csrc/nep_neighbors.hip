@@ -14,9 +14,11 @@
 namespace nep {
 namespace {
 
-__global__ void k_zero_i32(int32_t* p, int64_t n) {
+__global__ void k_clear(int32_t* flags, int32_t* cells, int ncell, int32_t* nbr, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
+  if (i < n) nbr[i] = 0;
+  if (i < FLAG_COUNT) flags[i] = 0;
+  for (int64_t c = i; c < ncell; c += (int64_t)gridDim.x * blockDim.x) cells[c] = 0;
 }
 
 // Workgroups of the rebuild kernels. Every rebuild kernel is enqueued each step and
@@ -728,7 +730,10 @@ __device__ void build_atoms(int64_t N, const CellGrid& g, const double* __restri
     drain();
     if (lane == 0) {
       lo_.cnt[p] = nw < capR ? nw : capR;
-      if (nw > capR) atomicMax(&flags[FLAG_OVF_R], nw);
+      if (nw > capR) {
+        atomicMax(&flags[FLAG_OVF_R], nw);
+        if (lo_.alarm) lo_.alarm[FLAG_OVF_R] = 1;
+      }
     }
   }
 }
@@ -982,7 +987,10 @@ k_place_lists(int64_t N, int nbins, int binA, int capR, int capA, ListOut lo_, L
         bstart[k] = t;
         t += k < nbins ? total.get(k) : 0;
         if (valid && h == 0 && k < nbins) lo_.bp[(int64_t)k * N + p] = t < capR ? t : capR;
-        if (valid && h == 0 && k == binA && t > capA) atomicMax(&flags[FLAG_OVF_A], t);
+        if (valid && h == 0 && k == binA && t > capA) {
+          atomicMax(&flags[FLAG_OVF_A], t);
+          if (lo_.alarm) lo_.alarm[FLAG_OVF_A] = 1;
+        }
       }
     }
     constexpr int rows = kPlaceRows;  // row `rows` of the tiles is the spare row
@@ -1066,9 +1074,8 @@ __global__ void k_export(int64_t N, const int32_t* __restrict__ perm, const int3
 
 }  // namespace
 
-hipError_t launch_zero_i32(int32_t* p, int64_t n, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_zero_i32, dim3(grid_blocks(n)), dim3(kBlock), 0, st, p, n);
+hipError_t launch_clear(int32_t* flags, int32_t* cells, int ncell, int32_t* nbr, int64_t n, hipStream_t st) {
+  hipLaunchKernelGGL(k_clear, dim3(grid_blocks(n > 0 ? n : 1)), dim3(kBlock), 0, st, flags, cells, ncell, nbr, n);
   return hipGetLastError();
 }
 
