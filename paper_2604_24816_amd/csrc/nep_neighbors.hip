@@ -572,23 +572,41 @@ constexpr int kStage = 16;  // entries of a scratch segment
 // (27 cells; along a dimension of one or two cells, each cell once) are staged in LDS once,
 // in stencil order and by sorted index inside a cell, and each wavefront takes the
 // workgroup's atoms in turn, its 64 lanes testing two chunks of 64 candidates at a time
-// (their staged positions read together, for the latency). The accepted candidates are
+// (read together and without a branch, for the latency; cells away from the periodic
+// boundary have a loop without the shifts). The accepted candidates are
 // compacted (ballot and prefix count) into a per-wavefront LDS queue in candidate
 // order; only those are binned and written, 64 entries per pass, to the atom's
-// scratch column as q | bin << 28 with its halo-local index. Stencils of more than kCellCand
-// atoms (compressed boxes and dense clusters) are not staged: their candidates are read from
+// scratch column as q | bin << 28 with its halo-local index. Larger stencils
+// (compressed boxes and dense clusters) are not staged: their candidates are read from
 // global memory, in the same order. Candidate vectors are x_q - x_p in FP64 plus the
 // periodic shift of the stencil cell (-L, 0 or +L: what the minimum-image rule gives every
 // pair that can lie within the cutoff when the dimension holds at least three cells), or the
 // minimum-image rule itself in a dimension of fewer cells; r^2 = (dx*dx + dy*dy) + dz*dz
 // without FMA.
-constexpr int kCellCand = 1024;  // stencil atoms a workgroup stages in LDS
+//
+// The staging holds kCellCand atoms, or as many as the stencil of a uniform box of this size
+// with a margin of 15%, up to kCellCandMax: a cell edge is 7.0 to 7.6 A in large boxes, 750 to
+// 1,000 stencil atoms at metallic densities, but up to 9.3 A where a side holds three cells.
+// us for the kernel with that stencil staged / read from global memory: 1,372 atoms (8.4 A)
+// 19 / 37, 5,324 (8.0 A) 30 / 72, 13,500 (7.7 A) 67 / 127, 27,436 (7.6 A) 93 / 215. With 2,048
+// atoms staged whatever the box, two workgroups instead of four fit a compute unit (4,000
+// atoms 34 us, 24 with 1,024).
+constexpr int kCellCand = 1024, kCellCandMax = 2048;
+inline int cell_cand(int64_t N, const CellGrid& g) {
+  double part = 1.0;  // of the box that a stencil covers
+  for (int d = 0; d < 3; ++d) part *= g.nc[d] < 3 ? 1.0 : 3.0 / g.nc[d];
+  const double want = 1.15 * part * (double)N;
+  return want <= kCellCand ? kCellCand : (want >= kCellCandMax ? kCellCandMax : ((int)want + 63) & ~63);
+}
+// The staged candidates, one array after the other in the launch's LDS.
+struct Cands {
+  double *X, *Y, *Z;
+  uint8_t* C;  // stencil cells
+};
+inline int cand_bytes(int cand) { return cand * (int)(3 * sizeof(double) + 1); }
 constexpr int kCellQueue = 192;  // accepted candidates queued per wavefront (two chunks past a drain)
 
 struct CellStage {
-  double X[kCellCand], Y[kCellCand], Z[kCellCand];
-  int32_t Q[kCellCand];
-  uint8_t C[kCellCand];
   int cq0[27], cum[28];
   double shift[3][27];
   union {
@@ -603,19 +621,19 @@ struct CellStage {
 
 // Atoms s0 + first, s0 + first + step, ... of the cell [s0, s1), whose own stencil cell is
 // `home`; nc candidates.
-template <int NE, bool STAGED, bool MINIMG>
+template <int NE, bool STAGED, bool SHIFT, bool MINIMG>
 __device__ void build_atoms(int64_t N, const CellGrid& g, const double* __restrict__ x, const BinEdges& be, int capR,
                             const ListOut& lo_, const HaloTables& ht, const ListScratch& sc,
-                            int32_t* __restrict__ flags, CellStage& S, int s0, int s1, int first, int step, int ns,
-                            int home, int nc, bool shifted) {
+                            int32_t* __restrict__ flags, CellStage& S, const Cands& P, int s0, int s1, int first, int step, int ns,
+                            int home, int nc) {
 #pragma clang fp contract(off)
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int tile0 = s0 / kBlock;
   const double cut2 = be.e2[be.nbins - 1];
   uint32_t* scq = reinterpret_cast<uint32_t*>(sc.q);
   uint16_t* scl = reinterpret_cast<uint16_t*>(sc.l);
   auto cell_slot = [&](int k) {  // stencil cell of candidate k
-    if constexpr (STAGED) return (int)S.C[k];
+    if constexpr (STAGED) return (int)P.C[k];
     int c = 0;
     for (int m = 1; m < ns; ++m) c += k >= S.cum[m] ? 1 : 0;
     return c;
@@ -639,9 +657,9 @@ __device__ void build_atoms(int64_t N, const CellGrid& g, const double* __restri
     const int ks = S.cum[home] + (p - s0);  // the atom's own slot
     double xi, yi, zi;
     if constexpr (STAGED) {
-      xi = S.X[ks];
-      yi = S.Y[ks];
-      zi = S.Z[ks];
+      xi = P.X[ks];
+      yi = P.Y[ks];
+      zi = P.Z[ks];
     } else {
       xi = x[p];
       yi = x[N + p];
@@ -658,7 +676,7 @@ __device__ void build_atoms(int64_t N, const CellGrid& g, const double* __restri
         const int lc = __shfl(loc0, sidx);
         const int e = nw + j;
         if (v && e < capR) {
-          const int q = STAGED ? S.Q[k] : S.cq0[sidx] + (k - S.cum[sidx]);
+          const int q = S.cq0[sidx] + (k - S.cum[sidx]);
           const int64_t o = ((int64_t)(e / kStage) * N + p) * kStage + e % kStage;
           scq[o] = (uint32_t)q | ((uint32_t)bin_of<NE>(S.qr[w][j], be) << 28);
           scl[o] = hok ? (uint16_t)(lc + q) : kNoLocal;
@@ -672,9 +690,9 @@ __device__ void build_atoms(int64_t N, const CellGrid& g, const double* __restri
       double dx, dy, dz;
       int sidx = 0;
       if constexpr (STAGED) {
-        dx = S.X[k] - xi;
-        dy = S.Y[k] - yi;
-        dz = S.Z[k] - zi;
+        dx = P.X[k] - xi;
+        dy = P.Y[k] - yi;
+        dz = P.Z[k] - zi;
       } else {
         sidx = cell_slot(k);
         const int64_t q = S.cq0[sidx] + (k - S.cum[sidx]);
@@ -682,8 +700,8 @@ __device__ void build_atoms(int64_t N, const CellGrid& g, const double* __restri
         dy = x[N + q] - yi;
         dz = x[2 * N + q] - zi;
       }
-      if (MINIMG || shifted) {
-        if constexpr (STAGED) sidx = S.C[k];
+      if constexpr (SHIFT) {
+        if constexpr (STAGED) sidx = P.C[k];
         if constexpr (MINIMG) {
           dx = g.nc[0] < 3 ? min_image(dx, g.box[0]) : dx + S.shift[0][sidx];
           dy = g.nc[1] < 3 ? min_image(dy, g.box[1]) : dy + S.shift[1][sidx];
@@ -713,18 +731,9 @@ __device__ void build_atoms(int64_t N, const CellGrid& g, const double* __restri
     // two chunks per pass, their staged positions read together
     for (int k0 = 0; k0 < nc; k0 += 128) {
       const int ka = k0 + lane, kb = k0 + 64 + lane;
-      bool acc_a = false, acc_b = false;
-      double ra = 0.0, rb = 0.0;
-      if (ka < nc && ka != ks) {
-        ra = dist2(ka);
-        acc_a = ra < cut2;
-      }
-      if (kb < nc && kb != ks) {
-        rb = dist2(kb);
-        acc_b = rb < cut2;
-      }
-      enqueue(ka, acc_a, ra);
-      enqueue(kb, acc_b, rb);
+      const double ra = dist2(ka < nc ? ka : ks), rb = dist2(kb < nc ? kb : ks);
+      enqueue(ka, ra < cut2 && ka < nc && ka != ks, ra);
+      enqueue(kb, rb < cut2 && kb < nc && kb != ks, rb);
       if (nq > kCellQueue - 128) drain();
     }
     drain();
@@ -742,13 +751,13 @@ template <int NE, bool MINIMG>
 __device__ void build_cell(int64_t N, const CellGrid& g, const double* __restrict__ x,
                            const int32_t* __restrict__ start, const BinEdges& be, int capR, const ListOut& lo_,
                            const HaloTables& ht, const ListScratch& sc, int32_t* __restrict__ flags, int c, int part,
-                           int parts, CellStage& S) {
+                           int parts, CellStage& S, const Cands& P, int cand) {
   const int s0 = start[c], s1 = start[c + 1];
   constexpr int W = kBlock / 64;
   if (s0 + part * W >= s1) return;  // empty cell, brick slot outside the grid, or no atom left for this part
   int cx, cy, cz;
   cell_coords(g, c, cx, cy, cz);
-  const int t = threadIdx.x, w = t >> 6;
+  const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int tile0 = s0 / kBlock;
   // stencil cells t = (a n1 + b) n0 + e: along a dimension of at least three cells the
   // offsets -1, 0, 1, otherwise every cell once, starting with the cell's own
@@ -799,30 +808,30 @@ __device__ void build_cell(int64_t N, const CellGrid& g, const double* __restric
       v = halo_search(S.halo[u][0], S.halo[u][1], hn[u], S.cq0[sc0]) - S.cq0[sc0];
     S.loc0s[u][sc0] = v;
   }
-  const bool staged = nc <= kCellCand;
+  const bool staged = nc <= cand;
   if (staged) {
     for (int k = t; k < nc; k += kBlock) {
       int sidx = 0;
 #pragma unroll
       for (int m = 1; m < 27; ++m) sidx += m < ns && k >= S.cum[m] ? 1 : 0;
       const int q = S.cq0[sidx] + (k - S.cum[sidx]);
-      S.X[k] = x[q];
-      S.Y[k] = x[N + q];
-      S.Z[k] = x[2 * N + q];
-      S.Q[k] = q;
-      S.C[k] = (uint8_t)sidx;
+      P.X[k] = x[q];
+      P.Y[k] = x[N + q];
+      P.Z[k] = x[2 * N + q];
+      P.C[k] = (uint8_t)sidx;
     }
   }
   __syncthreads();
   // a cell away from the periodic boundary has no image shifts
   const bool shifted = cx == 0 || cy == 0 || cz == 0 || cx == g.nc[0] - 1 || cy == g.nc[1] - 1 ||
                        cz == g.nc[2] - 1;
-  if (staged)
-    build_atoms<NE, true, MINIMG>(N, g, x, be, capR, lo_, ht, sc, flags, S, s0, s1, part * W + w, parts * W, ns, home,
-                                  nc, shifted);
+  const int first = part * W + w, step = parts * W;
+  if (!staged)
+    build_atoms<NE, false, true, MINIMG>(N, g, x, be, capR, lo_, ht, sc, flags, S, P, s0, s1, first, step, ns, home, nc);
+  else if (MINIMG || shifted)
+    build_atoms<NE, true, true, MINIMG>(N, g, x, be, capR, lo_, ht, sc, flags, S, P, s0, s1, first, step, ns, home, nc);
   else
-    build_atoms<NE, false, MINIMG>(N, g, x, be, capR, lo_, ht, sc, flags, S, s0, s1, part * W + w, parts * W, ns,
-                                   home, nc, shifted);
+    build_atoms<NE, true, false, MINIMG>(N, g, x, be, capR, lo_, ht, sc, flags, S, P, s0, s1, first, step, ns, home, nc);
 }
 
 // Primary state from the sorted one (workgroups [0, ncopy)), and the cells' lists from the
@@ -851,16 +860,18 @@ __device__ void copy_back(int64_t N, const CellGrid& g, const SortedState& o, co
 template <int NE, bool MINIMG>
 __global__ void __launch_bounds__(kBlock)
 k_build_cells(int64_t N, CellGrid g, SortedState o, PrimaryState prim, int ncopy, const int32_t* __restrict__ start,
-              BinEdges be, int capR, ListOut lo_, HaloTables ht, ListScratch sc, int parts,
+              BinEdges be, int capR, ListOut lo_, HaloTables ht, ListScratch sc, int parts, int cand,
               int32_t* __restrict__ flags) {
   if (flags[FLAG_REBUILD] == 0) return;
   __shared__ CellStage S;
+  extern __shared__ double cands[];
+  const Cands P{cands, cands + cand, cands + 2 * cand, reinterpret_cast<uint8_t*>(cands + 3 * cand)};
   if ((int)blockIdx.x < ncopy) return copy_back(N, g, o, prim, blockIdx.x, ncopy);
   const double* __restrict__ x = o.xb;
   const int n = g.ncell * parts;
   for (int cb = blockIdx.x - ncopy; cb < n; cb += gridDim.x - ncopy) {
     const int u = xcd_tile(cb, n);
-    build_cell<NE, MINIMG>(N, g, x, start, be, capR, lo_, ht, sc, flags, u / parts, u % parts, parts, S);
+    build_cell<NE, MINIMG>(N, g, x, start, be, capR, lo_, ht, sc, flags, u / parts, u % parts, parts, S, P, cand);
     __syncthreads();  // the LDS staging is reused by the next cell
   }
 }
@@ -1131,8 +1142,9 @@ hipError_t launch_rebuild(const RebuildRule& rule, const double* d2, int nd2, in
   const int ncopy = nb < kCopyGrid ? nb : kCopyGrid;
   auto cells = small ? (one ? k_build_cells<kEdgesOne, true> : k_build_cells<kEdgesTwo, true>)
                      : (one ? k_build_cells<kEdgesOne, false> : k_build_cells<kEdgesTwo, false>);
-  hipLaunchKernelGGL(cells, dim3(ncopy + rebuild_grid((int64_t)ncell * parts)), kb, 0, st, N, g, sorted, prim, ncopy,
-                     cell_start, be, capR, lout, ht, sc, parts, flags);
+  const int cand = cell_cand(N, g);
+  hipLaunchKernelGGL(cells, dim3(ncopy + rebuild_grid((int64_t)ncell * parts)), kb, cand_bytes(cand), st, N, g, sorted,
+                     prim, ncopy, cell_start, be, capR, lout, ht, sc, parts, cand, flags);
   const int pp = place_parts(N);
   const int place_groups = grid_blocks(N, 64 / pp);
   hipLaunchKernelGGL(pp == 16 ? k_place_lists<16> : k_place_lists<4>,

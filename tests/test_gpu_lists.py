@@ -31,6 +31,8 @@ CASES = {
     "three cells, 8 workgroups each": dict(nx=6, ny=6, nz=6, drop=0),
     "largest one-workgroup sort": dict(nx=16, ny=16, nz=16, drop=0),
     "first general sort by atoms": dict(nx=16, ny=16, nz=17, drop=1023),
+    "stencils of every atom, larger staging": dict(nx=7, ny=7, nz=7, drop=0),
+    "cells of 8.0 A": dict(nx=11, ny=11, nz=11, drop=5),
     "general sort by cells": dict(nx=8, ny=8, nz=8, drop=0, box=(100.0, 101.0, 99.0)),
     "sorted halo candidates": dict(nx=10, ny=10, nz=10, drop=17, box=(470.0, 465.0, 460.0)),
 }
@@ -53,6 +55,24 @@ def test_lists_and_forces(name):
     # every build starts from the cell counts the last one left at zero
     s.build_neighbors(1.0)
     assert s.compute()[0] == E
+
+
+@pytest.mark.parametrize("n_atoms", [2300, 4400, 4900, 6000])
+def test_staged_and_unstaged_stencils(n_atoms):
+    """Random atoms in a 30 A box (cells of 7.5 A, stencils of 0.42 n): staged in the smallest
+    size, in the largest, in some cells only, and in none."""
+    hp, params = I.FULL_HPARAMS, I.random_model(I.FULL_HPARAMS, 0)
+    rng = np.random.default_rng(n_atoms)
+    box = np.array([30.0, 30.5, 29.9])
+    at = I.Atoms(x=rng.uniform(0.0, 1.0, (n_atoms, 3)) * box, types=np.zeros(n_atoms, np.int32), box=box,
+                 masses=np.array([I.CU_MASS_AMU]))
+    say(f"case: {n_atoms} random atoms, lists only")
+    s = make_system(at, hp, params, cap_radial=512, cap_angular=512)
+    for which, cut in [(0, 7.0), (1, 6.0)]:
+        off, idx = s.export_neighbors(which)
+        cnt, oidx = oracle.neighbors(at.x, at.box, cut, cap=512)
+        ok, msg = lists_equal(off, idx, cnt, oidx)
+        assert ok, (which, msg)
 
 
 def test_rebuild_on_displacement_and_schedule():
