@@ -937,9 +937,24 @@ int desc_lanes(int64_t N) {
 //   62,500      115 135 220   92 106 169   100 115 161
 //   80,000      155 192 341  146 198 250   146 166 205
 //   120,000     154 192 354  167 197 312   185 215 298
+// Two species share the LDS pipe between tables and force sums, so that two lanes cost as much
+// per center as one, and the deterministic form gains at every size. They are taken where a
+// round of 65,536 centers in place of one of 131,072 ends the launch earlier, and from five
+// such rounds on; with one species only just above 131,072 centers. l <= 2: with two species,
+// within its first round of 196,608 centers. us, default / deterministic:
+//   N, full            L = 1       2        N, l <= 2, default    L = 1    2
+//   one      135,036   226 512   209 394    two        95,760     55    45
+//            186,624   223 539   225 461               149,355    76    71
+//   two      177,293   360 522   283 439               243,200   104   103
+//            243,200   369  -    376  -     one        100,800    45    58
+//            411,316   744 1197  659 982
+//            820,800  1292 2290 1230 1959
 // Both modes take the same lanes, since the virial's partial sums follow them.
 int force_lanes(const ModelDev& m, int64_t N) {
-  if (m.L3 > 2 && ((N > 32768 && N <= 49152) || (N > 65536 && N <= 98304))) return 4;
+  const int64_t half = (N + 65535) / 65536;  // rounds of 65,536 centers
+  if (m.L3 <= 2) return m.T > 1 && N > 65536 && N <= 196608 ? 2 : desc_lanes(N);
+  if ((N > 32768 && N <= 49152) || (N > 65536 && N <= 98304)) return 4;
+  if (N > 131072 && (m.T > 1 ? half % 2 == 1 || half > 4 : N <= 163840)) return 2;
   return desc_lanes(N);
 }
 

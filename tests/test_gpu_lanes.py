@@ -7,6 +7,8 @@ Bars are the FP32 path's stated ones (per-atom energy 1e-6 eV, forces 1e-4 eV/A,
 order, so its forces may differ by FP32 roundings of a few eV/A-sized partial sums (1e-6 eV/A)
 and its energy and virial not at all.
 """
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -44,6 +46,27 @@ def test_lane_counts_match_oracle(n_atoms, species):
     Ed, Wd, Fd, Ud = s.compute(per_atom=True)
     m = oracle.Model.from_hparams(hp, params)
     Eo, Wo, Uo, Fo = oracle.evaluate(m, at.x, at.types, at.box)
+    assert np.abs(U - Uo).max() < 1e-6 and abs(E - Eo) / at.n < 1e-6
+    assert np.abs(F - Fo).max() < 1e-4 and np.abs(W - Wo).max() / at.n < 1e-6
+    assert Ed == E and np.array_equal(Wd, W) and np.array_equal(Ud, U)
+    assert np.abs(Fd - F).max() < 1e-6
+
+
+@pytest.mark.parametrize("n_atoms, species, surrogate", [(131072, 2, False), (131073, 1, False), (131073, 2, False),
+                                                        (65537, 2, True)])
+def test_two_lanes_in_large_systems(n_atoms, species, surrogate):
+    """The force kernel's two lanes beside one lane in the descriptor kernel, and the largest
+    size that keeps one."""
+    say(f"case: {n_atoms} atoms, {species} species, surrogate {surrogate}")
+    hp = I.SURROGATE_SHORTER_HPARAMS if surrogate else I.FULL_HPARAMS
+    hp = dataclasses.replace(hp, n_types=species, zbl_z=(29.0,) * species)
+    params = I.random_model(hp, 3 + species)
+    at = _box(n_atoms, species, 71)
+    s = make_system(at, hp, params)
+    E, W, F, U = s.compute(per_atom=True)
+    s.set_deterministic(True)
+    Ed, Wd, Fd, Ud = s.compute(per_atom=True)
+    Eo, Wo, Uo, Fo = oracle.evaluate(oracle.Model.from_hparams(hp, params), at.x, at.types, at.box)
     assert np.abs(U - Uo).max() < 1e-6 and abs(E - Eo) / at.n < 1e-6
     assert np.abs(F - Fo).max() < 1e-4 and np.abs(W - Wo).max() / at.n < 1e-6
     assert Ed == E and np.array_equal(Wd, W) and np.array_equal(Ud, U)
