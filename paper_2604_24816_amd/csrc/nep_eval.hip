@@ -191,12 +191,15 @@ __device__ __forceinline__ float network_wave(const ModelDev& m, const float* qs
 // afterwards (zbl_center).
 // With L > 1 this lane (l of the L that share the center) visits entries l, l + L, ... and
 // the sums over the lanes are formed at the end, in every lane.
-template <class S, bool MULTI, int L>
+template <class S, int PREC, bool MULTI, int L>
 __device__ __forceinline__ void desc_pass(const ModelDev& m, const EvalBuffers& b, const PairTab<S, MULTI>& tab,
                                           int64_t i, int l, int ti, QPos qi, float* q, float* s, int& nz, int& nr,
                                           int& na) {
   constexpr int NR = S::NR, NA = S::NA, NC = S::NC, KR = S::KR, KA = S::KA, TT = MULTI ? kMaxTypes : 1;
+  // the bfloat16 network with several species: a pair's g_n from its coefficients, added to q_n
+  constexpr bool PAIRWISE = PREC == 1 && MULTI;
   const int64_t N = b.N;
+  const float rcR_inv = 1.f / m.rcR, rcA_inv = 1.f / m.rcA;
   const CutConst cutR = cut_const(m.rcR), cutA = cut_const(m.rcA);
   const float rcR2 = (float)(m.rcR64 * m.rcR64), rcA2 = (float)(m.rcA64 * m.rcA64), zbl2 = (float)m.zbl_o2;
   const bool zbl_on = m.zbl_o2 > 0.0;
@@ -221,7 +224,12 @@ __device__ __forceinline__ void desc_pass(const ModelDev& m, const EvalBuffers& 
     const int tj = MULTI ? (int)w[0].w : 0;
     ++nr;
     nz += (zbl_on && r2 < zbl2) ? 1 : 0;
-    {
+    if constexpr (PAIRWISE) {
+      float g[NR];
+      radial_g<NR, KR>(r, rcR_inv, tab.rad + (ti * kMaxTypes + tj) * (NR * KR), g);
+#pragma unroll
+      for (int n = 0; n < NR; ++n) q[n] += g[n];
+    } else {
       // T_k by the recurrence T_{k+1} = 2x T_k - T_{k-1}
       const RadialGeo ra = radial_geo<false>(r, cutR);
       float ft[TT];  // f_c for the neighbour's species, 0 for the others
@@ -245,7 +253,9 @@ __device__ __forceinline__ void desc_pass(const ModelDev& m, const EvalBuffers& 
       ++na;
       float g[NA];
       const RadialGeo ra = radial_geo<false>(r, cutA);
-      if constexpr (MULTI) {
+      if constexpr (PAIRWISE) {
+        radial_g<NA, KA>(r, rcA_inv, ang_tab(tab, ti, tj), g);
+      } else if constexpr (MULTI) {
         radial_cd_tab<S, false>(ra.x, ang_tab(tab, ti, tj), g, nullptr);
 #pragma unroll
         for (int n = 0; n < NA; ++n) g[n] *= ra.fc;
@@ -276,6 +286,7 @@ __device__ __forceinline__ void desc_pass(const ModelDev& m, const EvalBuffers& 
 #pragma unroll
     for (int k = 0; k < NA * NC; ++k) s[k] = lanes_sum<L>(s[k]);
   }
+  if constexpr (PAIRWISE) return;
 #pragma unroll
   for (int t = 0; t < TT; ++t) {
     float Qb[KR];
@@ -318,10 +329,10 @@ __device__ __forceinline__ void load_g_row(const float* row, float* g) {
 
 // The part of the descriptor kernel after the pair loop when L lanes share a center: q[0..NR)
 // and s hold the center's sums in every lane. lds: this wavefront's operand tile.
-template <class S, int PREC, bool MULTI, int L>
+template <class S, bool MULTI, int L>
 __device__ __forceinline__ void finish_lanes(const ModelDev& m, const EvalBuffers& b, int64_t i, int l, bool valid,
                                              int ti, const float* q, const float* s, int nz, float* lds,
-                                             const NetLds<PREC>& net, const PairTab<S, MULTI>& tab) {
+                                             const NetLds& net, const PairTab<S, MULTI>& tab) {
   constexpr int NR = S::NR, NA = S::NA, NC = S::NC, D = S::D, L3 = S::L3;
   constexpr int RT = 64 / L >= 16 ? 64 / L / 16 : 1;
   constexpr int ROUNDS = (NA + L - 1) / L;  // angular channels of a lane
@@ -357,7 +368,7 @@ __device__ __forceinline__ void finish_lanes(const ModelDev& m, const EvalBuffer
       if constexpr (S::FB) row[NR + L3 * NA + n] = fourbody_q(sl[r]) * net.sigma[NR + L3 * NA + n];
     }
   }
-  net_product<PREC, RT, true>(lds, lds, net);
+  net_product<RT, true>(lds, lds, net);
   float U = 0.f;
 #pragma unroll
   for (int mu0 = 0; mu0 < 32; mu0 += L) {
@@ -367,7 +378,7 @@ __device__ __forceinline__ void finish_lanes(const ModelDev& m, const EvalBuffer
     row[mu] = w * (1.f - t * t);
   }
   U = lanes_sum<L>(U) - m.b1[0];
-  net_product<PREC, RT, false>(lds, lds, net);
+  net_product<RT, false>(lds, lds, net);
   if (!valid) return;
   auto fp = [&](int v) { return row[v] * net.sigma[v]; };  // dU/dq_v
   // the 64-byte records: position (words 0..2), radial coefficients (3..11), species, zeros
@@ -452,11 +463,11 @@ __global__ void __launch_bounds__(kBlock, 2) k_desc_net(ModelDev m, EvalBuffers 
   const bool valid = i < N;
   __shared__ PairTab<S, MULTI> tab;
   if constexpr (MULTI) {
-    stage_pairs<S>(m, tab);
+    stage_pairs<S, PREC == 1>(m, tab);
     __syncthreads();
   }
   if constexpr (L > 1) {
-    __shared__ NetLds<PREC> net;
+    __shared__ NetLds net;
     stage_network<S>(m, net);
     float q[NR], s[NA * NC];
 #pragma unroll
@@ -468,14 +479,14 @@ __global__ void __launch_bounds__(kBlock, 2) k_desc_net(ModelDev m, EvalBuffers 
     if (valid) {
       const uint4 w0 = b.pos[i];
       int nr = 0, na = 0;
-      desc_pass<S, MULTI, L>(m, b, tab, i, l, ti, QPos{w0.x, w0.y, w0.z}, q, s, nz, nr, na);
+      desc_pass<S, PREC, MULTI, L>(m, b, tab, i, l, ti, QPos{w0.x, w0.y, w0.z}, q, s, nz, nr, na);
       if (l == 0) {
         b.nactR[i] = nr;
         b.nactA[i] = na;
       }
     }
     __syncthreads();  // the staged weights
-    finish_lanes<S, PREC, MULTI, L>(m, b, i, l, valid, ti, q, s, nz, lds[threadIdx.x >> 6], net, tab);
+    finish_lanes<S, MULTI, L>(m, b, i, l, valid, ti, q, s, nz, lds[threadIdx.x >> 6], net, tab);
     return;
   }
 
@@ -491,7 +502,7 @@ __global__ void __launch_bounds__(kBlock, 2) k_desc_net(ModelDev m, EvalBuffers 
   if (valid) {
     const uint4 w0 = b.pos[i];
     int nr = 0, na = 0;
-    desc_pass<S, MULTI, 1>(m, b, tab, i, 0, ti, QPos{w0.x, w0.y, w0.z}, q, s, nz, nr, na);
+    desc_pass<S, PREC, MULTI, 1>(m, b, tab, i, 0, ti, QPos{w0.x, w0.y, w0.z}, q, s, nz, nr, na);
     b.nactR[i] = nr;
     b.nactA[i] = na;
     desc_finish<S>(s, q);
@@ -922,6 +933,9 @@ void launch_force(const ModelDev& m, const EvalBuffers& b, hipStream_t st) {
 //   108,000     224  249  259  316  470
 // More lanes cost per wavefront (the sums over lanes, a halo to clear and flush per 256 / L
 // centers), fewer leave SIMDs idle.
+// The bfloat16 network keeps one lane and its own pair sums (desc_pass): it rounds the
+// descriptors to eight bits, so that a sum in another order moves about one in a thousand of
+// them by a whole step (outputs then differ by 1e-4 of their norm, with the same error).
 constexpr int64_t kFillLanes = 131072;
 constexpr int kMaxLanes = 16;
 int desc_lanes(int64_t N) {
@@ -963,12 +977,16 @@ int force_lanes(const ModelDev& m, int64_t N) {
 template <class S, int PREC, bool MULTI>
 hipError_t launch_pair(const ModelDev& m, const EvalBuffers& b, hipStream_t st, hipEvent_t* ev) {
   if (ev) (void)hipEventRecord(ev[0], st);
-  switch (desc_lanes(b.N)) {
-    case 16: launch_desc<S, PREC, MULTI, 16>(m, b, st); break;
-    case 8: launch_desc<S, PREC, MULTI, 8>(m, b, st); break;
-    case 4: launch_desc<S, PREC, MULTI, 4>(m, b, st); break;
-    case 2: launch_desc<S, PREC, MULTI, 2>(m, b, st); break;
-    default: launch_desc<S, PREC, MULTI, 1>(m, b, st); break;
+  if constexpr (PREC == 1) {
+    launch_desc<S, 1, MULTI, 1>(m, b, st);
+  } else {
+    switch (desc_lanes(b.N)) {
+      case 16: launch_desc<S, 0, MULTI, 16>(m, b, st); break;
+      case 8: launch_desc<S, 0, MULTI, 8>(m, b, st); break;
+      case 4: launch_desc<S, 0, MULTI, 4>(m, b, st); break;
+      case 2: launch_desc<S, 0, MULTI, 2>(m, b, st); break;
+      default: launch_desc<S, 0, MULTI, 1>(m, b, st); break;
+    }
   }
   if (ev) (void)hipEventRecord(ev[1], st);
   switch (force_lanes(m, b.N)) {

@@ -147,15 +147,17 @@ struct PairTab {
   alignas(16) float ang[kPairs * kAng + 4];
   float rad[kPairs * kRad + 4];
 };
-// Filled by the whole workgroup; a barrier must follow.
-template <class S>
+// Filled by the whole workgroup; a barrier must follow. RAW: ang holds the angular
+// coefficients c_nk themselves, [n][k].
+template <class S, bool RAW = false>
 __device__ __forceinline__ void stage_pairs(const ModelDev& m, PairTab<S, true>& t) {
   using P = PairTab<S, true>;
   constexpr int NA = S::NA, KA = S::KA;
   for (int e = threadIdx.x; e < m.T * m.T * NA * KA; e += kBlock) {
     const int pr = e / (NA * KA), n = e / KA % NA, k = e % KA;
-    t.ang[(pr / m.T * kMaxTypes + pr % m.T) * P::kAng + (n < 4 ? 4 * k + n : P::kLast + k)] =
-        m.hA[(int64_t)pr * derived_block<NA, KA>() + n * KA + k];
+    float* a = t.ang + (pr / m.T * kMaxTypes + pr % m.T) * P::kAng;
+    if constexpr (RAW) a[n * KA + k] = m.cA[e];
+    else a[n < 4 ? 4 * k + n : P::kLast + k] = m.hA[(int64_t)pr * derived_block<NA, KA>() + n * KA + k];
   }
   for (int e = threadIdx.x; e < m.T * m.T * P::kRad; e += kBlock) {
     const int pr = e / P::kRad;
@@ -392,7 +394,6 @@ __device__ __forceinline__ int lanes_sum(int v) {
 // odd) and the MFMA operand and result patterns (lane (lr, lk) at 37 lr + lk and
 // 148 lk + lr) within two passes of the 64 LDS banks.
 constexpr int kNetStride = 37;
-constexpr int kBfStride = 40;  // bfloat16 weights staged in LDS: 16-byte aligned rows
 
 // With L > 1 lanes to a center the part after the pair loop (descriptors from the sums,
 // network, dU/ds, record) would be repeated by every lane; it is spread over them instead:
@@ -402,20 +403,17 @@ constexpr int kBfStride = 40;  // bfloat16 weights staged in LDS: 16-byte aligne
 // load sits in this part. Both matter because a small system runs one short wavefront per
 // SIMD: 4,000 atoms at 16 lanes took 24 us with everything repeated and the weights
 // gathered from global memory.
-template <int PREC>
 struct NetLds {
-  float w[PREC == 0 ? 32 * 33 : 1];                      // W0 [hidden][descriptor], zero padded
-  alignas(16) uint16_t wb[PREC == 1 ? 32 * kBfStride : 8];  // the same as bfloat16
+  float w[32 * 33];  // W0 [hidden][descriptor], zero padded
   float b0[32], w1[32], sigma[32];
 };
 
-template <class S, int PREC>
-__device__ __forceinline__ void stage_network(const ModelDev& m, NetLds<PREC>& n) {
+template <class S>
+__device__ __forceinline__ void stage_network(const ModelDev& m, NetLds& n) {
   for (int t = threadIdx.x; t < 32 * 32; t += kBlock) {
     const int hid = t >> 5, d = t & 31;
     const bool in = hid < S::H && d < S::D;
-    if constexpr (PREC == 0) n.w[hid * 33 + d] = in ? m.W0[hid * S::D + d] : 0.f;
-    else n.wb[hid * kBfStride + d] = in ? m.W0bf[hid * S::D + d] : (uint16_t)0;
+    n.w[hid * 33 + d] = in ? m.W0[hid * S::D + d] : 0.f;
   }
   if (threadIdx.x < 32) {
     const int t = threadIdx.x;
@@ -428,8 +426,8 @@ __device__ __forceinline__ void stage_network(const ModelDev& m, NetLds<PREC>& n
 // rows x 32 times W0^T (FORWARD: descriptors to hidden units) or W0 (hidden units to
 // descriptors) of a wavefront's operand tile of RT 16-row MFMA tiles, into dst (which may be
 // the same tile). Rows that belong to no center hold whatever the LDS held and are never read back.
-template <int PREC, int RT, bool FORWARD>
-__device__ __forceinline__ void net_product(const float* src, float* dst, const NetLds<PREC>& n) {
+template <int RT, bool FORWARD>
+__device__ __forceinline__ void net_product(const float* src, float* dst, const NetLds& n) {
   const int lane = threadIdx.x & 63;
   const int lr = lane & 15, lk = lane >> 4;
   wave_lds_sync();
@@ -438,38 +436,18 @@ __device__ __forceinline__ void net_product(const float* src, float* dst, const 
   for (int R = 0; R < RT; ++R)
 #pragma unroll
     for (int C = 0; C < 2; ++C) acc[R][C] = floatx4{0.f, 0.f, 0.f, 0.f};
-  if constexpr (PREC == 0) {
 #pragma unroll
-    for (int kb = 0; kb < 8; ++kb) {
-      const int k = 4 * kb + lk;
-      float bop[2];
+  for (int kb = 0; kb < 8; ++kb) {
+    const int k = 4 * kb + lk;
+    float bop[2];
 #pragma unroll
-      for (int C = 0; C < 2; ++C) bop[C] = FORWARD ? n.w[(16 * C + lr) * 33 + k] : n.w[k * 33 + 16 * C + lr];
-#pragma unroll
-      for (int R = 0; R < RT; ++R) {
-        const float aop = src[(16 * R + lr) * kNetStride + k];
-#pragma unroll
-        for (int C = 0; C < 2; ++C)
-          acc[R][C] = __builtin_amdgcn_mfma_f32_16x16x4f32(aop, bop[C], acc[R][C], 0, 0, 0);
-      }
-    }
-  } else {
-    bf16x8 bop[2];
-#pragma unroll
-    for (int C = 0; C < 2; ++C)
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        bop[C][e] = bits_to_bf16(FORWARD ? n.wb[(16 * C + lr) * kBfStride + 8 * lk + e]
-                                         : n.wb[(8 * lk + e) * kBfStride + 16 * C + lr]);
+    for (int C = 0; C < 2; ++C) bop[C] = FORWARD ? n.w[(16 * C + lr) * 33 + k] : n.w[k * 33 + 16 * C + lr];
 #pragma unroll
     for (int R = 0; R < RT; ++R) {
-      bf16x8 aop;
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        aop[e] = bits_to_bf16(f32_to_bf16_bits(src[(16 * R + lr) * kNetStride + 8 * lk + e]));
+      const float aop = src[(16 * R + lr) * kNetStride + k];
 #pragma unroll
       for (int C = 0; C < 2; ++C)
-        acc[R][C] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aop, bop[C], acc[R][C], 0, 0, 0);
+        acc[R][C] = __builtin_amdgcn_mfma_f32_16x16x4f32(aop, bop[C], acc[R][C], 0, 0, 0);
     }
   }
   wave_lds_sync();

@@ -30,6 +30,36 @@ __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
 
 __device__ __forceinline__ __bf16 bits_to_bf16(uint16_t b) { return __builtin_bit_cast(__bf16, b); }
 
+// Chebyshev-based radial basis f_k(r) = (T_k(x) + 1) f_c(r) / 2 with
+// x = 2 (r/rc - 1)^2 - 1 and f_c = (1 + cos(pi r / rc)) / 2 (published NEP form).
+// Returns g_n = sum_k c_nk f_k.
+template <int N, int K, class CP>
+__device__ __forceinline__ void radial_g(float r, float rc_inv, CP c, float* g) {
+  float sn, cs;
+  sincospif(r * rc_inv, &sn, &cs);
+  const float fc = 0.5f * (1.f + cs);
+  const float y = r * rc_inv - 1.f;
+  const float x = 2.f * y * y - 1.f;
+  float Tm1 = 1.f, T = x;
+  float fk[K];
+  fk[0] = 1.f;
+  fk[1] = 0.5f * (x + 1.f);
+#pragma unroll
+  for (int k = 2; k < K; ++k) {
+    const float Tn = 2.f * x * T - Tm1;
+    Tm1 = T;
+    T = Tn;
+    fk[k] = 0.5f * (Tn + 1.f);
+  }
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+    float a = 0.f;
+#pragma unroll
+    for (int k = 0; k < K; ++k) a = fmaf(c[n * K + k], fk[k], a);
+    g[n] = a * fc;
+  }
+}
+
 // Deterministic FP64 sums of K values over a 256-thread workgroup: a butterfly over the
 // 64 lanes of each wavefront (cross-lane moves, no barrier), then the four wavefront
 // partials in a fixed order, with one barrier for all K. The result is valid in thread 0.

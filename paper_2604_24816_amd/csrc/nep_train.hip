@@ -100,7 +100,7 @@ k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, 
   constexpr int kNet = 32 * 32 + 2 * 32;          // a wavefront's network sums
   static_assert(H * D + 2 * H + NCOEF <= kGradStride, "row too short");
   static_assert(5 * TILE >= kNet, "the tiles hold a wavefront's network sums");
-  __shared__ NetLds<0> net;
+  __shared__ NetLds net;
   __shared__ PairTab<S, MULTI> tab;
   __shared__ float tiles[kBlock / 64][5 * TILE];  // q~, v~, h (alpha), z (beta), gE t - z d
   __shared__ float red[kBlock / 64][COEF ? NCOEF : 1];
@@ -268,8 +268,8 @@ k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, 
       tq[row + k] = k < D ? q[k < D ? k : 0] * net.sigma[k] : 0.f;
       tv[row + k] = k < D ? v[k < D ? k : 0] * net.sigma[k] : 0.f;
     }
-  net_product<0, RT, true>(tq, ta, net);
-  net_product<0, RT, true>(tv, tb, net);
+  net_product<RT, true>(tq, ta, net);
+  net_product<RT, true>(tv, tb, net);
   const float gEf = (float)gE;
 #pragma unroll
   for (int mu0 = 0; mu0 < 32; mu0 += L) {
@@ -325,8 +325,8 @@ k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, 
         total(x, e);
       }
     };
-    net_product<0, RT, false>(ta, ta, net);
-    net_product<0, RT, false>(tb, tb, net);
+    net_product<RT, false>(ta, ta, net);
+    net_product<RT, false>(tb, tb, net);
     // dL/dq and dU/dq of the lane's center (zero where there is none)
     float rho[D], fp[D];
 #pragma unroll

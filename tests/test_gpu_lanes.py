@@ -85,17 +85,3 @@ def test_surrogate_lane_counts(n_atoms):
     E, W, F, U = s.compute(slot=1, per_atom=True)
     Eo, Wo, Uo, Fo = oracle.evaluate(oracle.Model.from_hparams(shp, sp), at.x, at.types, at.box)
     assert np.abs(U - Uo).max() < 1e-6 and np.abs(F - Fo).max() < 1e-4 and np.abs(W - Wo).max() / at.n < 1e-6
-
-
-@pytest.mark.parametrize("cells", [4, 13, 19, 25])
-def test_bf16_lane_counts(cells):
-    """The bfloat16 operand tiles at 16, 8, 4 and 2 lanes, on the near-lattice boxes for which
-    the bars of the bfloat16 path are stated (both sides round the same quantities, and a value
-    within FP32 error of a rounding boundary may round the other way)."""
-    at = I.fcc_box(cells, 0.05, 92)
-    say(f"case: {at.n} atoms, BF16 network")
-    hp, params = I.FULL_HPARAMS, I.random_model(I.FULL_HPARAMS, 0)
-    s = make_system(at, hp, params)
-    E, W, F, U = s.compute(precision="bf16", per_atom=True)
-    Eb, Wb, Ub, Fb = oracle.evaluate(oracle.Model.from_hparams(hp, params), at.x, at.types, at.box, bf16=True)
-    assert np.abs(U - Ub).mean() < 2e-6 and np.abs(U - Ub).max() < 5e-4 and np.abs(F - Fb).max() < 5e-3
