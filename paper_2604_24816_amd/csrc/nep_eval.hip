@@ -926,11 +926,12 @@ void launch_force(const ModelDev& m, const EvalBuffers& b, hipStream_t st) {
 // to 32,000 atoms), so L lanes share a center, as many as keep N L <= 131072. On both sides
 // of that line, us of k_desc_net + k_force, one species:
 //   N         L = 1    2    4    8   16
-//   4,000       156  101   65   47   41
-//   13,500      160  102   67   61   85
-//   32,000      162  109   88  111  157
-//   62,500      176  143  158  198  284
-//   108,000     224  249  259  316  470
+//   256         140   89   56   39   32
+//   4,000       150   92   59   44   38
+//   13,500      160   97   62   58   78
+//   32,000      154  104   84  107  146
+//   62,500      166  134  150  192  263
+//   108,000     217  242  251  307  432
 // More lanes cost per wavefront (the sums over lanes, a halo to clear and flush per 256 / L
 // centers), fewer leave SIMDs idle.
 // The bfloat16 network keeps one lane and its own pair sums (desc_pass): it rounds the
