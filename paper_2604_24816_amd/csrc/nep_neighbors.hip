@@ -879,8 +879,8 @@ k_build_cells(int64_t N, CellGrid g, SortedState o, PrimaryState prim, int ncopy
 // Workgroups to a cell: as many as fill the chip's 256 compute units once, four to a unit
 // (what the staging's LDS allows), up to one atom per wavefront of a 32-atom cell; every
 // workgroup of a cell stages the whole stencil. us with 1 / 2 / 4 / 8 of them:
-//   8 cells (256 atoms)     28 18 14 13      512 (16,384)   56 41 48 57
-//   216 (4,000)             51 31 25 27    1,000 (32,000)   66 70 80 99
+//   8 cells (256 atoms)     28 19 14 12      512 (16,384)   48 38 45 55
+//   216 (4,000)             43 27 23 26    1,000 (32,000)   62 65 76 95
 inline int build_parts(int ncell) {
   const int p = 1024 / ncell;
   return p < 1 ? 1 : (p > 8 ? 8 : p);
