@@ -133,7 +133,10 @@ int nep_system_set_params(nep_system* s, int32_t slot, const double* params, int
 
 /* Set positions x [N][3] (inside [0, L) per axis), velocities v [N][3] (NULL = zero),
  * types [N] and masses per type [n_types] (amu, host). on_device = 1: x, v,
- * types are device pointers. Invalidates the neighbour lists. */
+ * types are device pointers. Invalidates the neighbour lists. A refused species
+ * (NEP_ERR_TYPE) or value (NEP_ERR_NONFINITE) leaves the system without a state until
+ * the next accepted one; a bad argument (NEP_ERR_ARG, masses included) leaves it as it
+ * was. */
 int nep_set_state(nep_system* s, const double* x, const double* v, const int32_t* types,
                   const double* masses, int32_t on_device);
 

@@ -798,8 +798,13 @@ int nep_system_set_params(nep_system* s, int32_t slot, const double* params, int
 int nep_set_state(nep_system* s, const double* x, const double* v, const int32_t* types, const double* masses,
                   int32_t on_device) {
   if (!s || !x || !types || !masses) return fail(s, NEP_ERR_ARG, "null argument");
-  for (int t = 0; t < s->n_types; ++t) {
+  for (int t = 0; t < s->n_types; ++t)
     if (!(masses[t] > 0) || !std::isfinite(masses[t])) return fail(s, NEP_ERR_ARG, "masses must be positive");
+  // from here on the earlier state is overwritten: unless the new one is accepted there is none
+  s->have_state = s->have_list = false;
+  s->force_valid[0] = s->force_valid[1] = false;
+  s->nhc_ke = false;
+  for (int t = 0; t < s->n_types; ++t) {
     s->mt.mass[t] = masses[t];
     s->mt.inv_mxi[t] = 1.0 / (masses[t] * kXi);
   }
@@ -833,9 +838,6 @@ int nep_set_state(nep_system* s, const double* x, const double* v, const int32_t
   if (f[FLAG_TYPE]) return fail(s, NEP_ERR_TYPE, "atom type out of range");
   if (f[FLAG_NONFINITE]) return fail(s, NEP_ERR_NONFINITE, "non-finite position or velocity");
   s->have_state = true;
-  s->have_list = false;
-  s->force_valid[0] = s->force_valid[1] = false;
-  s->nhc_ke = false;
   s->step = 0;
   return NEP_OK;
 }
