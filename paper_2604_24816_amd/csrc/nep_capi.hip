@@ -865,23 +865,19 @@ int nep_export_neighbors(nep_system* s, int32_t which, int64_t* offsets, int32_t
   if (!s || !offsets || !idx || which < 0 || which > 1) return fail(s, NEP_ERR_ARG, "bad argument");
   if (!s->have_list) return fail(s, NEP_ERR_STALE_LIST, "no list built");
   const int64_t N = s->N;
-  const int cap = which == 0 ? s->capR : s->capA;
-  // rows of original ids are produced in chunks that fit the staging buffer (3N doubles)
-  const int64_t chunk = std::max<int64_t>(1, (3 * N * (int64_t)sizeof(double)) / ((int64_t)cap * 4 + 4));
-  int32_t* rows = reinterpret_cast<int32_t*>(s->staging);
-  int32_t* rcnt = rows + chunk * cap;
+  // no row is longer than the radial capacity; the rows lie in the list scratch (16
+  // ceil(capR / 16) words per atom, free between builds), their lengths in the staging buffer
+  const int cap = which == 0 ? s->capR : std::min(s->capA, s->capR);
+  int32_t* rows = reinterpret_cast<int32_t*>(s->lsc.q);
+  int32_t* rcnt = reinterpret_cast<int32_t*>(s->staging);
   std::vector<int32_t> cnt(N);
   std::vector<int32_t> all((size_t)N * cap);
-  for (int64_t o0 = 0; o0 < N; o0 += chunk) {
-    const int64_t o1 = std::min(N, o0 + chunk);
-    // the angular list with skin is the prefix of bins up to rc_angular + skin
-    const int32_t* cnt_src = which == 0 ? s->cnt : s->bp + (int64_t)s->be.idxA[0][kFracs - 1] * N;
-    HIPCHK(launch_export(N, s->perm, s->nbr, cnt_src, cap, o0, o1, rows, rcnt, s->st));
-    HIPCHK(hipMemcpyAsync(cnt.data() + o0, rcnt, (o1 - o0) * sizeof(int32_t), hipMemcpyDeviceToHost, s->st));
-    HIPCHK(hipMemcpyAsync(all.data() + o0 * cap, rows, (size_t)(o1 - o0) * cap * sizeof(int32_t),
-                          hipMemcpyDeviceToHost, s->st));
-    HIPCHK(hipStreamSynchronize(s->st));
-  }
+  // the angular list with skin is the prefix of bins up to rc_angular + skin
+  const int32_t* cnt_src = which == 0 ? s->cnt : s->bp + (int64_t)s->be.idxA[0][kFracs - 1] * N;
+  HIPCHK(launch_export(N, s->perm, s->nbr, cnt_src, cap, rows, rcnt, s->st));
+  HIPCHK(hipMemcpyAsync(cnt.data(), rcnt, N * sizeof(int32_t), hipMemcpyDeviceToHost, s->st));
+  HIPCHK(hipMemcpyAsync(all.data(), rows, all.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s->st));
+  HIPCHK(hipStreamSynchronize(s->st));
   offsets[0] = 0;
   for (int64_t o = 0; o < N; ++o) offsets[o + 1] = offsets[o] + cnt[o];
   if (offsets[N] > cap_total) return fail(s, NEP_ERR_ARG, "cap_total too small");

@@ -235,10 +235,9 @@ hipError_t launch_rebuild(const RebuildRule& rule, const double* d2, int nd2, in
                           int32_t* src, int32_t* key, int32_t* rank, int32_t* cell_count,
                           int32_t* cell_start, int32_t* scan_tmp, uint4* pos, const ListOut& lists, HaloTables ht,
                           ListScratch sc, int32_t* flags, hipStream_t st);
-// Rows of original ids [o_lo, o_hi), ascending, into rows[(o - o_lo) * cap + k].
+// Rows of original ids, ascending, into rows[o * cap + k], their lengths into row_cnt[o].
 hipError_t launch_export(int64_t N, const int32_t* perm, const int32_t* nbr, const int32_t* cnt,
-                         int cap, int64_t o_lo, int64_t o_hi, int32_t* rows, int32_t* row_cnt,
-                         hipStream_t st);
+                         int cap, int32_t* rows, int32_t* row_cnt, hipStream_t st);
 
 // Evaluation (nep_eval.hip)
 struct EvalBuffers {

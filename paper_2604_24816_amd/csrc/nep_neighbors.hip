@@ -1061,16 +1061,15 @@ k_place_lists(int64_t N, int nbins, int binA, int capR, int capA, ListOut lo_, L
   }
 }
 
-// Lists in original ids, one row per original atom in [o_lo, o_hi), ascending.
+// Lists in original ids, one row per original atom, ascending.
 __global__ void k_export(int64_t N, const int32_t* __restrict__ perm, const int32_t* __restrict__ nbr,
-                         const int32_t* __restrict__ cnt, int cap, int64_t o_lo, int64_t o_hi,
-                         int32_t* __restrict__ rows, int32_t* __restrict__ row_cnt) {
+                         const int32_t* __restrict__ cnt, int cap, int32_t* __restrict__ rows,
+                         int32_t* __restrict__ row_cnt) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= N) return;
   const int64_t o = perm[p];
-  if (o < o_lo || o >= o_hi) return;
   const int n = cnt[p] < cap ? cnt[p] : cap;
-  int32_t* row = rows + (o - o_lo) * cap;
+  int32_t* row = rows + o * cap;
   for (int k = 0; k < n; ++k) {
     const int32_t val = perm[nbr[(int64_t)k * N + p]];
     int j = k - 1;
@@ -1080,7 +1079,7 @@ __global__ void k_export(int64_t N, const int32_t* __restrict__ perm, const int3
     }
     row[j + 1] = val;
   }
-  row_cnt[o - o_lo] = n;
+  row_cnt[o] = n;
 }
 
 }  // namespace
@@ -1154,10 +1153,8 @@ hipError_t launch_rebuild(const RebuildRule& rule, const double* d2, int nd2, in
 }
 
 hipError_t launch_export(int64_t N, const int32_t* perm, const int32_t* nbr, const int32_t* cnt,
-                         int cap, int64_t o_lo, int64_t o_hi, int32_t* rows, int32_t* row_cnt,
-                         hipStream_t st) {
-  hipLaunchKernelGGL(k_export, dim3(grid_blocks(N)), dim3(kBlock), 0, st, N, perm, nbr, cnt, cap, o_lo,
-                     o_hi, rows, row_cnt);
+                         int cap, int32_t* rows, int32_t* row_cnt, hipStream_t st) {
+  hipLaunchKernelGGL(k_export, dim3(grid_blocks(N)), dim3(kBlock), 0, st, N, perm, nbr, cnt, cap, rows, row_cnt);
   return hipGetLastError();
 }
 
