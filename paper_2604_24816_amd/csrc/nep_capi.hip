@@ -1476,8 +1476,8 @@ int nep_compute_energy_forces_virial_noalloc(const nep_model* model, int64_t n_a
   s.st = (hipStream_t)hip_stream;
   // Everything is queued and the host waits once: the checks that come between the calls
   // this one stands for are made on the flags at the end, and until then an error only keeps
-  // the results from the caller's arrays (a bad species or value counts as 0 and an
-  // overflowing list is cut, as on a step of dynamics). 256 atoms 181 us with a wait after
+  // the results from the caller's arrays (a bad species counts as 0, a bad value as a place in
+  // the box and an overflowing list is cut, as on a step of dynamics). 256 atoms 181 us with a wait after
   // each part, 142 with one.
   ModelImage image;
   struct Wait {

@@ -291,6 +291,17 @@ __global__ void k_sum_i32(int64_t N, const int32_t* __restrict__ a, double* __re
   block_partial(p < N ? (double)a[p] : 0.0, sh, partial + (int64_t)blockIdx.x * kPartialStride + slot);
 }
 
+// A place in the box for a coordinate that is no number, which keeps what is queued before the
+// host has seen the error in bounds and at its ordinary cost: fractional parts of multiples of
+// the golden ratio and of two more irrationals fill the box evenly. One place for all of them
+// would make one cell of a whole bad configuration, whose 20,000 atoms the list build would sort
+// and pair in seconds.
+__device__ __forceinline__ double stand_in(int64_t p, int c, double L) {
+  const double a = c == 0 ? 0.6180339887498949 : (c == 1 ? 0.7548776662466927 : 0.8191725133961645);
+  const double t = a * (double)(p + 1);
+  return L * (t - floor(t));
+}
+
 // err: the words that report a bad species or value, the flags themselves or host words at the
 // same indices (then the flags start from zero here).
 __global__ void k_state_in(int64_t N, const double* __restrict__ xa, const double* __restrict__ va,
@@ -305,8 +316,9 @@ __global__ void k_state_in(int64_t N, const double* __restrict__ xa, const doubl
     double xv = xa[3 * p + c];
     if (!isfinite(xv)) {
       err[FLAG_NONFINITE] = 1;
-      xv = 0.0;  // keeps what is launched before the check in bounds
-    } else if (xv < 0.0 || xv >= g.box[c]) {
+      xv = stand_in(p, c, g.box[c]);
+    }
+    if (xv < 0.0 || xv >= g.box[c]) {
       xv = xv - g.box[c] * floor(xv / g.box[c]);
       if (xv >= g.box[c]) xv -= g.box[c];
     }
