@@ -293,8 +293,11 @@ k_scan_scatter(int64_t N, int ncell, const int32_t* __restrict__ count, const in
 // Within each cell, order atoms by original id and move their state there. One wavefront
 // per cell: each lane holds atoms of the cell, counts the cell's smaller keys (the keys are
 // distinct original ids) and moves its atom to that rank, so the result is the stable order
-// whatever order the scatter's atomics left. Cells of more than kSortMax atoms (none at
-// metallic densities) are sorted by one lane by insertion.
+// whatever order the scatter's atomics left. The keys are read through LDS kSortMax at a
+// time: once for a cell of up to that many atoms (all cells at metallic densities), n / 256
+// times for each 256 of a larger one's n. By one lane, with an insertion sort, those cost n^2
+// dependent accesses: the list build of 4,000 atoms in one cell took 53 ms (26 so), of 1,200
+// in a 10 A cube 5.3 (1.8).
 constexpr int kSortMax = 256;
 constexpr int kSortWaves = kBlock / 64;
 
@@ -307,64 +310,54 @@ struct SortedState {
 };
 
 __device__ void sort_cells(int64_t N, int ncell, const int32_t* __restrict__ start, int32_t* __restrict__ count,
-                           int32_t* __restrict__ key, int32_t* __restrict__ src, const double* __restrict__ x,
-                           const double* __restrict__ v, const int32_t* __restrict__ type, const SortedState& o,
-                           int block, int nblocks, int32_t (*kk)[kSortMax]) {
+                           const int32_t* __restrict__ key, const int32_t* __restrict__ src,
+                           const double* __restrict__ x, const double* __restrict__ v,
+                           const int32_t* __restrict__ type, const SortedState& o, int block, int nblocks,
+                           int32_t (*kk)[kSortMax]) {
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   constexpr int U = kSortMax / 64;
   for (int c = block * kSortWaves + w; c < ncell; c += nblocks * kSortWaves) {  // wave-uniform
     const int a = start[c], n = start[c + 1] - a;
     if (lane == 0) count[c] = 0;
-    if (n <= 0) continue;
-    // sorted atom p of the cell from atom s, original id k
-    auto move = [&](int64_t p, int64_t s, int32_t k) {
-      for (int d = 0; d < 3; ++d) {
-        const double xv = x[d * N + s];
-        o.x2[d * N + p] = xv;
-        o.xb[d * N + p] = xv;
-        o.v2[d * N + p] = v[d * N + s];
+    for (int b0 = 0; b0 < n; b0 += kSortMax) {
+      int32_t mk[U], ms[U];
+      int rank[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int l = b0 + lane + 64 * u;
+        mk[u] = l < n ? key[a + l] : 0;
+        ms[u] = l < n ? src[a + l] : 0;
+        rank[u] = 0;
       }
-      o.type2[p] = type[s];
-      o.perm2[p] = k;
-    };
-    if (n > kSortMax) {
-      if (lane == 0) {
-        for (int i = a + 1; i < a + n; ++i) {
-          const int32_t k = key[i], s0 = src[i];
-          int j = i - 1;
-          while (j >= a && key[j] > k) {
-            key[j + 1] = key[j];
-            src[j + 1] = src[j];
-            --j;
-          }
-          key[j + 1] = k;
-          src[j + 1] = s0;
+      for (int c0 = 0; c0 < n; c0 += kSortMax) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int l = lane + 64 * u;
+          if (c0 + l < n) kk[w][l] = c0 == b0 ? mk[u] : key[a + c0 + l];
         }
-        for (int i = a; i < a + n; ++i) move(i, src[i], key[i]);
+        wave_lds_sync();
+        const int nk = n - c0 < kSortMax ? n - c0 : kSortMax;
+        for (int m = 0; m < nk; ++m) {
+          const int32_t km = kk[w][m];
+#pragma unroll
+          for (int u = 0; u < U; ++u) rank[u] += km < mk[u] ? 1 : 0;
+        }
+        wave_lds_sync();
       }
-      continue;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (b0 + lane + 64 * u >= n) continue;
+        const int64_t p = a + rank[u], s = ms[u];
+        for (int d = 0; d < 3; ++d) {
+          const double xv = x[d * N + s];
+          o.x2[d * N + p] = xv;
+          o.xb[d * N + p] = xv;
+          o.v2[d * N + p] = v[d * N + s];
+        }
+        o.type2[p] = type[s];
+        o.perm2[p] = mk[u];
+      }
     }
-    int32_t mk[U], ms[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int l = lane + 64 * u;
-      mk[u] = l < n ? key[a + l] : 0;
-      ms[u] = l < n ? src[a + l] : 0;
-      if (l < n) kk[w][l] = mk[u];
-    }
-    wave_lds_sync();
-    int rank[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) rank[u] = 0;
-    for (int m = 0; m < n; ++m) {
-      const int32_t km = kk[w][m];
-#pragma unroll
-      for (int u = 0; u < U; ++u) rank[u] += km < mk[u] ? 1 : 0;
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (lane + 64 * u < n) move(a + rank[u], ms[u], mk[u]);
-    wave_lds_sync();
   }
 }
 
@@ -497,7 +490,7 @@ __device__ void halo_tile(int64_t N, const CellGrid& g, const double* __restrict
 template <bool MAP>
 __global__ void __launch_bounds__(kBlock)
 k_sort_halo(int64_t N, CellGrid g, int nsort, const int32_t* __restrict__ start, int32_t* __restrict__ count,
-            int32_t* __restrict__ key, int32_t* __restrict__ src, const double* __restrict__ x,
+            const int32_t* __restrict__ key, const int32_t* __restrict__ src, const double* __restrict__ x,
             const double* __restrict__ v, const int32_t* __restrict__ type, SortedState o, HaloTables ht,
             const int32_t* __restrict__ flags) {
   if (flags[FLAG_REBUILD] == 0) return;
