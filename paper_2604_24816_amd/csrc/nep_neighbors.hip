@@ -569,13 +569,13 @@ constexpr int kStage = 16;  // entries of a scratch segment
 // boundary have a loop without the shifts). The accepted candidates are
 // compacted (ballot and prefix count) into a per-wavefront LDS queue in candidate
 // order; only those are binned and written, 64 entries per pass, to the atom's
-// scratch column as q | bin << 28 with its halo-local index. Larger stencils
-// (compressed boxes and dense clusters) are not staged: their candidates are read from
-// global memory, in the same order. Candidate vectors are x_q - x_p in FP64 plus the
-// periodic shift of the stencil cell (-L, 0 or +L: what the minimum-image rule gives every
-// pair that can lie within the cutoff when the dimension holds at least three cells), or the
-// minimum-image rule itself in a dimension of fewer cells; r^2 = (dx*dx + dy*dy) + dz*dz
-// without FMA.
+// scratch column as q | bin << 28 with its halo-local index. Stencils larger than the staging
+// (compressed boxes and dense clusters) are staged and tested part by part, in the same
+// order, the length of each atom's column kept in cnt between the parts. Candidate vectors
+// are x_q - x_p in FP64 plus the periodic shift of the stencil cell (-L, 0 or +L: what the
+// minimum-image rule gives every pair that can lie within the cutoff when the dimension
+// holds at least three cells), or the minimum-image rule itself in a dimension of fewer
+// cells; r^2 = (dx*dx + dy*dy) + dz*dz without FMA.
 //
 // The staging holds kCellCand atoms, or as many as the stencil of a uniform box of this size
 // with a margin of 15%, up to kCellCandMax: a cell edge is 7.0 to 7.6 A in large boxes, 750 to
@@ -583,7 +583,9 @@ constexpr int kStage = 16;  // entries of a scratch segment
 // us for the kernel with that stencil staged / read from global memory: 1,372 atoms (8.4 A)
 // 19 / 37, 5,324 (8.0 A) 30 / 72, 13,500 (7.7 A) 67 / 127, 27,436 (7.6 A) 93 / 215. With 2,048
 // atoms staged whatever the box, two workgroups instead of four fit a compute unit (4,000
-// atoms 34 us, 24 with 1,024).
+// atoms 34 us, 24 with 1,024). Past that, whole list builds in parts / with the stencil read
+// from global memory: 30,000 random atoms at 0.24 A^-3 482 / 738, 122,880 1,654 / 2,663,
+// 204,800 at 0.4 A^-3 4,923 / 7,676.
 constexpr int kCellCand = 1024, kCellCandMax = 2048;
 inline int cell_cand(int64_t N, const CellGrid& g) {
   double part = 1.0;  // of the box that a stencil covers
@@ -613,24 +615,19 @@ struct CellStage {
 };
 
 // Atoms s0 + first, s0 + first + step, ... of the cell [s0, s1), whose own stencil cell is
-// `home`; nc candidates.
-template <int NE, bool STAGED, bool SHIFT, bool MINIMG>
+// `home`, against the staged candidates c0 .. c0 + nc - 1: all of the stencil, or (PART) a part
+// of it, the last one or not.
+template <int NE, bool PART, bool SHIFT, bool MINIMG>
 __device__ void build_atoms(int64_t N, const CellGrid& g, const double* __restrict__ x, const BinEdges& be, int capR,
                             const ListOut& lo_, const HaloTables& ht, const ListScratch& sc,
                             int32_t* __restrict__ flags, CellStage& S, const Cands& P, int s0, int s1, int first, int step, int ns,
-                            int home, int nc) {
+                            int home, int nc, int c0 = 0, bool last = true) {
 #pragma clang fp contract(off)
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int tile0 = s0 / kBlock;
   const double cut2 = be.e2[be.nbins - 1];
   uint32_t* scq = reinterpret_cast<uint32_t*>(sc.q);
   uint16_t* scl = reinterpret_cast<uint16_t*>(sc.l);
-  auto cell_slot = [&](int k) {  // stencil cell of candidate k
-    if constexpr (STAGED) return (int)P.C[k];
-    int c = 0;
-    for (int m = 1; m < ns; ++m) c += k >= S.cum[m] ? 1 : 0;
-    return c;
-  };
   int cached_tile = -1, hok = 0, hcells = 0, loc0 = 0;  // loc0: of stencil cell `lane`, for the atom's tile
   for (int p = s0 + first; p < s1; p += step) {  // wave-uniform
     const int tile = p / kBlock;
@@ -647,29 +644,29 @@ __device__ void build_atoms(int64_t N, const CellGrid& g, const double* __restri
     }
     const int self_off = __shfl(loc0, home);
     if (lane == 0) lo_.selfl[p] = hok ? (uint16_t)(self_off + p) : kNoLocal;
-    const int ks = S.cum[home] + (p - s0);  // the atom's own slot
+    const int ks = S.cum[home] + (p - s0) - c0;  // the atom's own slot
     double xi, yi, zi;
-    if constexpr (STAGED) {
-      xi = P.X[ks];
-      yi = P.Y[ks];
-      zi = P.Z[ks];
-    } else {
+    if constexpr (PART) {
       xi = x[p];
       yi = x[N + p];
       zi = x[2 * N + p];
+    } else {
+      xi = P.X[ks];
+      yi = P.Y[ks];
+      zi = P.Z[ks];
     }
-    int nw = 0, nq = 0;  // entries written, entries queued (wave-uniform)
+    int nw = PART && c0 > 0 ? lo_.cnt[p] : 0, nq = 0;  // entries written, entries queued (wave-uniform)
     auto drain = [&]() {
       wave_lds_sync();
       for (int j0 = 0; j0 < nq; j0 += 64) {
         const int j = j0 + lane;
         const bool v = j < nq;
         const int k = v ? (int)S.qk[w][j] : 0;
-        const int sidx = cell_slot(k);
+        const int sidx = P.C[k];
         const int lc = __shfl(loc0, sidx);
         const int e = nw + j;
         if (v && e < capR) {
-          const int q = S.cq0[sidx] + (k - S.cum[sidx]);
+          const int q = S.cq0[sidx] + (c0 + k - S.cum[sidx]);
           const int64_t o = ((int64_t)(e / kStage) * N + p) * kStage + e % kStage;
           scq[o] = (uint32_t)q | ((uint32_t)bin_of<NE>(S.qr[w][j], be) << 28);
           scl[o] = hok ? (uint16_t)(lc + q) : kNoLocal;
@@ -680,21 +677,9 @@ __device__ void build_atoms(int64_t N, const CellGrid& g, const double* __restri
       wave_lds_sync();
     };
     auto dist2 = [&](int k) {
-      double dx, dy, dz;
-      int sidx = 0;
-      if constexpr (STAGED) {
-        dx = P.X[k] - xi;
-        dy = P.Y[k] - yi;
-        dz = P.Z[k] - zi;
-      } else {
-        sidx = cell_slot(k);
-        const int64_t q = S.cq0[sidx] + (k - S.cum[sidx]);
-        dx = x[q] - xi;
-        dy = x[N + q] - yi;
-        dz = x[2 * N + q] - zi;
-      }
+      double dx = P.X[k] - xi, dy = P.Y[k] - yi, dz = P.Z[k] - zi;
       if constexpr (SHIFT) {
-        if constexpr (STAGED) sidx = P.C[k];
+        const int sidx = P.C[k];
         if constexpr (MINIMG) {
           dx = g.nc[0] < 3 ? min_image(dx, g.box[0]) : dx + S.shift[0][sidx];
           dy = g.nc[1] < 3 ? min_image(dy, g.box[1]) : dy + S.shift[1][sidx];
@@ -724,15 +709,16 @@ __device__ void build_atoms(int64_t N, const CellGrid& g, const double* __restri
     // two chunks per pass, their staged positions read together
     for (int k0 = 0; k0 < nc; k0 += 128) {
       const int ka = k0 + lane, kb = k0 + 64 + lane;
-      const double ra = dist2(ka < nc ? ka : ks), rb = dist2(kb < nc ? kb : ks);
+      const int kn = PART ? 0 : ks;  // a slot for the lanes past the last one
+      const double ra = dist2(ka < nc ? ka : kn), rb = dist2(kb < nc ? kb : kn);
       enqueue(ka, ra < cut2 && ka < nc && ka != ks, ra);
       enqueue(kb, rb < cut2 && kb < nc && kb != ks, rb);
       if (nq > kCellQueue - 128) drain();
     }
     drain();
     if (lane == 0) {
-      lo_.cnt[p] = nw < capR ? nw : capR;
-      if (nw > capR) {
+      lo_.cnt[p] = !last || nw < capR ? nw : capR;
+      if (last && nw > capR) {
         atomicMax(&flags[FLAG_OVF_R], nw);
         if (lo_.alarm) lo_.alarm[FLAG_OVF_R] = 1;
       }
@@ -801,30 +787,38 @@ __device__ void build_cell(int64_t N, const CellGrid& g, const double* __restric
       v = halo_search(S.halo[u][0], S.halo[u][1], hn[u], S.cq0[sc0]) - S.cq0[sc0];
     S.loc0s[u][sc0] = v;
   }
-  const bool staged = nc <= cand;
-  if (staged) {
-    for (int k = t; k < nc; k += kBlock) {
+  // a cell away from the periodic boundary has no image shifts
+  const bool shifted = cx == 0 || cy == 0 || cz == 0 || cx == g.nc[0] - 1 || cy == g.nc[1] - 1 ||
+                       cz == g.nc[2] - 1;
+  const int first = part * W + w, step = parts * W;
+  auto stage = [&](int c0, int n) {
+    for (int k = t; k < n; k += kBlock) {
       int sidx = 0;
 #pragma unroll
-      for (int m = 1; m < 27; ++m) sidx += m < ns && k >= S.cum[m] ? 1 : 0;
-      const int q = S.cq0[sidx] + (k - S.cum[sidx]);
+      for (int m = 1; m < 27; ++m) sidx += m < ns && c0 + k >= S.cum[m] ? 1 : 0;
+      const int q = S.cq0[sidx] + (c0 + k - S.cum[sidx]);
       P.X[k] = x[q];
       P.Y[k] = x[N + q];
       P.Z[k] = x[2 * N + q];
       P.C[k] = (uint8_t)sidx;
     }
+    __syncthreads();
+  };
+  if (nc <= cand) {
+    stage(0, nc);
+    if (MINIMG || shifted)
+      build_atoms<NE, false, true, MINIMG>(N, g, x, be, capR, lo_, ht, sc, flags, S, P, s0, s1, first, step, ns, home, nc);
+    else
+      build_atoms<NE, false, false, MINIMG>(N, g, x, be, capR, lo_, ht, sc, flags, S, P, s0, s1, first, step, ns, home, nc);
+    return;
   }
-  __syncthreads();
-  // a cell away from the periodic boundary has no image shifts
-  const bool shifted = cx == 0 || cy == 0 || cz == 0 || cx == g.nc[0] - 1 || cy == g.nc[1] - 1 ||
-                       cz == g.nc[2] - 1;
-  const int first = part * W + w, step = parts * W;
-  if (!staged)
-    build_atoms<NE, false, true, MINIMG>(N, g, x, be, capR, lo_, ht, sc, flags, S, P, s0, s1, first, step, ns, home, nc);
-  else if (MINIMG || shifted)
-    build_atoms<NE, true, true, MINIMG>(N, g, x, be, capR, lo_, ht, sc, flags, S, P, s0, s1, first, step, ns, home, nc);
-  else
-    build_atoms<NE, true, false, MINIMG>(N, g, x, be, capR, lo_, ht, sc, flags, S, P, s0, s1, first, step, ns, home, nc);
+  for (int c0 = 0; c0 < nc; c0 += cand) {
+    const int n = nc - c0 < cand ? nc - c0 : cand;
+    if (c0 > 0) __syncthreads();  // the part before is read no more
+    stage(c0, n);
+    build_atoms<NE, true, true, MINIMG>(N, g, x, be, capR, lo_, ht, sc, flags, S, P, s0, s1, first, step, ns, home, n, c0,
+                                        c0 + n == nc);
+  }
 }
 
 // Primary state from the sorted one (workgroups [0, ncopy)), and the cells' lists from the

@@ -41,3 +41,20 @@ def test_lists_and_state_of_a_dense_cell(n):
     for a, b in zip(*out):
         assert np.array_equal(a, b)
 
+
+
+@pytest.mark.parametrize("n_atoms,shape", [(2049, (2, 2, 2)), (4097, (2, 3, 4)), (9000, (3, 3, 3)), (20000, (4, 4, 4)),
+                                           (33000, (5, 4, 4))])
+def test_stencils_in_parts(n_atoms, shape):
+    """Stencils of 2,049 to about 10,000 atoms, staged in two to six parts (shape: cells a side)."""
+    say(f"case: {n_atoms} random atoms in {shape} cells")
+    rng = np.random.default_rng(n_atoms)
+    box = 7.1 * np.array(shape, float) + np.array([0.2, 0.3, 0.25])
+    at = I.Atoms(x=rng.random((n_atoms, 3)) * box, types=np.zeros(n_atoms, np.int32), box=box,
+                 masses=np.array([I.CU_MASS_AMU]))
+    s = make_system(at, I.FULL_HPARAMS, I.random_model(I.FULL_HPARAMS, 0), cap_radial=3072, cap_angular=3072)
+    for which, cut in [(0, 7.0), (1, 6.0)]:
+        off, idx = s.export_neighbors(which)
+        cnt, oidx = oracle.neighbors(at.x, at.box, cut, cap=3072)
+        ok, msg = lists_equal(off, idx, cnt, oidx)
+        assert ok, (which, msg)
