@@ -319,9 +319,10 @@ __device__ void sort_cells(int64_t N, int ncell, const int32_t* __restrict__ sta
   for (int c = block * kSortWaves + w; c < ncell; c += nblocks * kSortWaves) {  // wave-uniform
     const int a = start[c], n = start[c + 1] - a;
     if (lane == 0) count[c] = 0;
-    for (int b0 = 0; b0 < n; b0 += kSortMax) {
-      int32_t mk[U], ms[U];
-      int rank[U];
+    if (n <= 0) continue;
+    int32_t mk[U], ms[U];
+    int rank[U];
+    auto load = [&](int b0) {  // the lane's atoms of those from b0 on
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int l = b0 + lane + 64 * u;
@@ -329,21 +330,17 @@ __device__ void sort_cells(int64_t N, int ncell, const int32_t* __restrict__ sta
         ms[u] = l < n ? src[a + l] : 0;
         rank[u] = 0;
       }
-      for (int c0 = 0; c0 < n; c0 += kSortMax) {
+    };
+    auto count_smaller = [&](int nk) {  // among the nk keys in LDS
+      wave_lds_sync();
+      for (int m = 0; m < nk; ++m) {
+        const int32_t km = kk[w][m];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int l = lane + 64 * u;
-          if (c0 + l < n) kk[w][l] = c0 == b0 ? mk[u] : key[a + c0 + l];
-        }
-        wave_lds_sync();
-        const int nk = n - c0 < kSortMax ? n - c0 : kSortMax;
-        for (int m = 0; m < nk; ++m) {
-          const int32_t km = kk[w][m];
-#pragma unroll
-          for (int u = 0; u < U; ++u) rank[u] += km < mk[u] ? 1 : 0;
-        }
-        wave_lds_sync();
+        for (int u = 0; u < U; ++u) rank[u] += km < mk[u] ? 1 : 0;
       }
+      wave_lds_sync();
+    };
+    auto move = [&](int b0) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         if (b0 + lane + 64 * u >= n) continue;
@@ -357,6 +354,24 @@ __device__ void sort_cells(int64_t N, int ncell, const int32_t* __restrict__ sta
         o.type2[p] = type[s];
         o.perm2[p] = mk[u];
       }
+    };
+    if (n <= kSortMax) {
+      load(0);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (lane + 64 * u < n) kk[w][lane + 64 * u] = mk[u];
+      count_smaller(n);
+      move(0);
+      continue;
+    }
+    for (int b0 = 0; b0 < n; b0 += kSortMax) {
+      load(b0);
+      for (int c0 = 0; c0 < n; c0 += kSortMax) {
+        const int nk = n - c0 < kSortMax ? n - c0 : kSortMax;
+        for (int l = lane; l < nk; l += 64) kk[w][l] = key[a + c0 + l];
+        count_smaller(nk);
+      }
+      move(b0);
     }
   }
 }
