@@ -411,6 +411,7 @@ EvalBuffers eval_buffers(nep_system* s, int slot) {
   b.rec1 = s->lsc.q;  // at least 64 bytes per atom
   b.G = s->G;
   b.F = s->F[slot];
+  b.late = s->x_alt;  // free between list builds
   b.ew = s->gpart;  // the gradient partials' buffer, free during an evaluation (256 doubles per tile are enough)
   b.flags = s->flags;
   b.flag_r = slot == 0 ? FLAG_BIN_R : FLAG_BIN_R1;

@@ -260,6 +260,7 @@ struct EvalBuffers {
   uint4* rec1;           // [N][4] the records' second plane (two species)
   float* G;              // [nA * ncomp][N] dU/ds for the angular accumulators
   float* F;              // [3][N] forces (FP32 accumulation)
+  double* late;          // [3][N] ZBL forces that are added after all others
   double* ew;            // [eval_rows()][kPartialStride] energy and virial partials
   int32_t* flags;
   int flag_r, flag_a;    // flag words holding this model's last radial / angular bin

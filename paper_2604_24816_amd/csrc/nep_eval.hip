@@ -692,6 +692,20 @@ __device__ __forceinline__ void angular_pair_force(const ModelDev& m, const AngC
   n2 = fmaf(-uz, sc, -(vz * vscale));
 }
 
+// Whether the ZBL forces are added after all others, by a launch of their own. Every atomic
+// addition to an atom's force rounds to the force's size, and a ZBL force may be many
+// times the others'; with L > 4 some twenty workgroups add to each atom. Error of the forces
+// against FP64 (norm, relative) for FCC boxes of 4,000 atoms with neighbours inside the ZBL
+// radius: one thread per center 6.9e-8, 4 lanes 6.5e-8, 16 lanes 7.8e-8 and with this launch
+// 3.5e-8 (9.5e-8 with the ZBL force of each lane summed in FP32). It costs 2 to 4 us; four
+// lanes in place of sixteen would cost 16 to 22 of the 150 us of such a box's evaluation.
+template <bool DET, int L>
+constexpr bool late_zbl() { return !DET && L > 4; }
+__global__ void k_add_late(int64_t n, const double* __restrict__ late, float* __restrict__ F) {
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k < n) F[k] = (float)((double)F[k] + late[k]);
+}
+
 // DET: the deterministic form. Nothing is scattered: each atom adds, after its own pair
 // terms, the angular forces of the centers that have it as an angular neighbour, each
 // recomputed from that center's dU/ds (atom-major rows) in list order, and stores its
@@ -840,14 +854,7 @@ __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, 
       for_each_rec_lanes<W, 4, L>(b.nbr, plane, N, i, l, kR, pair_both);
     else
       for_each_rec_fast<W, 1, 4>(b.nbr, plane, N, i, 0, kR, pair_both);
-    if constexpr (L > 1) nz = lanes_sum<L>(nz);
-    if (nz) {
-      float f[3] = {fx, fy, fz};
-      zbl_center<MULTI>(m, b, i, ti, b.x[i], b.x[N + i], b.x[2 * N + i], nullptr, f, w, l, L);
-      fx = f[0];
-      fy = f[1];
-      fz = f[2];
-    }
+    nz = lanes_sum<L>(nz);
     if constexpr (DET) {
       // the neighbours' angular terms on this atom, in list order
       const uint64_t n64 = (uint64_t)N;
@@ -874,6 +881,22 @@ __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, 
     fx = lanes_sum<L>(fx);
     fy = lanes_sum<L>(fy);
     fz = lanes_sum<L>(fz);
+    // the ZBL force, rounded once with the sum of the others or left to k_add_late
+    double f[3] = {0.0, 0.0, 0.0};
+    if (nz) {
+      zbl_center<MULTI>(m, b, i, ti, b.x[i], b.x[N + i], b.x[2 * N + i], nullptr, f, w, l, L);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) f[c] = lanes_sum<L>(f[c]);
+    }
+    if (late_zbl<DET, L>() && zbl_on) {
+      if (l == 0)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) b.late[c * N + i] = f[c];
+    } else if (nz) {
+      fx = (float)((double)fx + f[0]);
+      fy = (float)((double)fy + f[1]);
+      fz = (float)((double)fz + f[2]);
+    }
     if (l == 0) {
       if constexpr (DET) {
         b.F[i] = fx;
@@ -917,8 +940,13 @@ void launch_desc(const ModelDev& m, const EvalBuffers& b, hipStream_t st) {
 template <class S, bool MULTI, int L>
 void launch_force(const ModelDev& m, const EvalBuffers& b, hipStream_t st) {
   const dim3 nb(grid_blocks(b.N, kBlock / L));
-  if (b.deterministic) hipLaunchKernelGGL((k_force<S, MULTI, true, L>), nb, dim3(kBlock), 0, st, m, b);
-  else hipLaunchKernelGGL((k_force<S, MULTI, false, L>), nb, dim3(kBlock), 0, st, m, b);
+  if (b.deterministic) {
+    hipLaunchKernelGGL((k_force<S, MULTI, true, L>), nb, dim3(kBlock), 0, st, m, b);
+    return;
+  }
+  hipLaunchKernelGGL((k_force<S, MULTI, false, L>), nb, dim3(kBlock), 0, st, m, b);
+  if (late_zbl<false, L>() && m.zbl_o2 > 0)
+    hipLaunchKernelGGL(k_add_late, dim3(grid_blocks(3 * b.N)), dim3(kBlock), 0, st, 3 * b.N, b.late, b.F);
 }
 
 // One thread per center fills the chip (1,024 SIMDs, two wavefronts each) from about 131,072

@@ -27,17 +27,8 @@ constexpr double kPi64 = 3.14159265358979323846;
 constexpr int kL64 = 16;              // lanes of a center
 constexpr int kC64 = kBlock / kL64;   // centers of a workgroup
 
-// Sum over the 16 lanes of a center, in every one of them (the moves of lanes_sum).
-template <int CTRL>
-__device__ __forceinline__ double dpp_add64(double v) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
-  return v + __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
-}
-__device__ __forceinline__ double lanes_sum64(double v) {
-  return dpp_add64<0x140>(dpp_add64<0x141>(dpp_add64<0x4e>(dpp_add64<0xb1>(v))));
-}
+// Sum over the 16 lanes of a center, in every one of them.
+__device__ __forceinline__ double lanes_sum64(double v) { return lanes_sum<kL64>(v); }
 
 // f_k(r) = f_c(r) (T_k(x) + 1) / 2 and df_k/dr for k < K, with x = 2 (r/rc - 1)^2 - 1
 // and f_c = (1 + cos(pi r / rc)) / 2.

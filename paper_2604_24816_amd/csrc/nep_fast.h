@@ -372,6 +372,13 @@ template <int CTRL>
 __device__ __forceinline__ int dpp_add(int v) {
   return v + __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
 }
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+  return v + __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
 // Sum over the whole wavefront, valid in lane 63: the row sums, then rows 0 -> 1 and 2 -> 3
 // and rows 0-1 -> 2-3 by row broadcasts. All 64 lanes must be active.
 __device__ __forceinline__ float wave_sum_last(float v) {
@@ -382,6 +389,14 @@ __device__ __forceinline__ float wave_sum_last(float v) {
 }
 template <int L>
 __device__ __forceinline__ int lanes_sum(int v) {
+  if constexpr (L >= 2) v = dpp_add<0xb1>(v);
+  if constexpr (L >= 4) v = dpp_add<0x4e>(v);
+  if constexpr (L >= 8) v = dpp_add<0x141>(v);
+  if constexpr (L >= 16) v = dpp_add<0x140>(v);
+  return v;
+}
+template <int L>
+__device__ __forceinline__ double lanes_sum(double v) {
   if constexpr (L >= 2) v = dpp_add<0xb1>(v);
   if constexpr (L >= 4) v = dpp_add<0x4e>(v);
   if constexpr (L >= 8) v = dpp_add<0x141>(v);

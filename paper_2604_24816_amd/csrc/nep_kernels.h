@@ -184,11 +184,14 @@ __device__ __forceinline__ double pair_r2_64(double xj, double yj, double zj, do
 // into uz, and, when f is given, the force on i (the whole pair derivative, both
 // atoms' halves, along u) into f[3] and the virial of dU_i/dr_ij into w[9]. Called
 // only for centers that have such pairs, after the main loop: it visits the radial list.
+// f is summed in FP64: the pairs' terms are many times their sum and the other forces, so
+// that FP32 partial sums, of several lanes above all, would cost the force several
+// roundings of its largest terms.
 // (q0, qs): the first position and the stride of a lane that shares the center with others
 // (which then adds its part only).
 template <bool MULTI>
 __device__ __forceinline__ void zbl_center(const ModelDev& m, const EvalBuffers& b, int64_t i, int ti, double xi,
-                                        double yi, double zi, float* uz, float* f, float* w, int q0 = 0,
+                                        double yi, double zi, float* uz, double* f, float* w, int q0 = 0,
                                         int qs = 1) {
   const int64_t N = b.N;
   const double Lx = b.box[0], Ly = b.box[1], Lz = b.box[2];
@@ -210,7 +213,7 @@ __device__ __forceinline__ void zbl_center(const ModelDev& m, const EvalBuffers&
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
         const double fa = de * d[a] / r;  // both halves of the pair derivative along u
-        f[a] += (float)fa;
+        f[a] += fa;
 #pragma unroll
         for (int c = 0; c < 3; ++c) w[a * 3 + c] += (float)(-d[a] * 0.5 * de * d[c] / r);
       }
