@@ -294,8 +294,8 @@ k_scan_scatter(int64_t N, int ncell, const int32_t* __restrict__ count, const in
 // per cell: each lane holds atoms of the cell, counts the cell's smaller keys (the keys are
 // distinct original ids) and moves its atom to that rank, so the result is the stable order
 // whatever order the scatter's atomics left. The keys are read through LDS kSortMax at a
-// time: once for a cell of up to that many atoms (all cells at metallic densities), n / 256
-// times for each 256 of a larger one's n. By one lane, with an insertion sort, those cost n^2
+// time: once for a cell of up to that many atoms (all cells at metallic densities), once for
+// each 64 atoms of a larger one. By one lane, with an insertion sort, those cost n^2
 // dependent accesses: the list build of 4,000 atoms in one cell took 53 ms (26 so), of 1,200
 // in a 10 A cube 5.3 (1.8).
 constexpr int kSortMax = 256;
@@ -310,69 +310,63 @@ struct SortedState {
 };
 
 __device__ void sort_cells(int64_t N, int ncell, const int32_t* __restrict__ start, int32_t* __restrict__ count,
-                           const int32_t* __restrict__ key, const int32_t* __restrict__ src,
-                           const double* __restrict__ x, const double* __restrict__ v,
-                           const int32_t* __restrict__ type, const SortedState& o, int block, int nblocks,
-                           int32_t (*kk)[kSortMax]) {
+                           int32_t* __restrict__ key, int32_t* __restrict__ src, const double* __restrict__ x,
+                           const double* __restrict__ v, const int32_t* __restrict__ type, const SortedState& o,
+                           int block, int nblocks, int32_t (*kk)[kSortMax]) {
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   constexpr int U = kSortMax / 64;
   for (int c = block * kSortWaves + w; c < ncell; c += nblocks * kSortWaves) {  // wave-uniform
     const int a = start[c], n = start[c + 1] - a;
     if (lane == 0) count[c] = 0;
     if (n <= 0) continue;
-    int32_t mk[U], ms[U];
-    int rank[U];
-    auto load = [&](int b0) {  // the lane's atoms of those from b0 on
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int l = b0 + lane + 64 * u;
-        mk[u] = l < n ? key[a + l] : 0;
-        ms[u] = l < n ? src[a + l] : 0;
-        rank[u] = 0;
+    // sorted atom p of the cell from atom s, original id k
+    auto move = [&](int64_t p, int64_t s, int32_t k) {
+      for (int d = 0; d < 3; ++d) {
+        const double xv = x[d * N + s];
+        o.x2[d * N + p] = xv;
+        o.xb[d * N + p] = xv;
+        o.v2[d * N + p] = v[d * N + s];
       }
+      o.type2[p] = type[s];
+      o.perm2[p] = k;
     };
-    auto count_smaller = [&](int nk) {  // among the nk keys in LDS
-      wave_lds_sync();
-      for (int m = 0; m < nk; ++m) {
-        const int32_t km = kk[w][m];
-#pragma unroll
-        for (int u = 0; u < U; ++u) rank[u] += km < mk[u] ? 1 : 0;
-      }
-      wave_lds_sync();
-    };
-    auto move = [&](int b0) {
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (b0 + lane + 64 * u >= n) continue;
-        const int64_t p = a + rank[u], s = ms[u];
-        for (int d = 0; d < 3; ++d) {
-          const double xv = x[d * N + s];
-          o.x2[d * N + p] = xv;
-          o.xb[d * N + p] = xv;
-          o.v2[d * N + p] = v[d * N + s];
+    if (__builtin_expect(n > kSortMax, 0)) {
+      for (int l0 = 0; l0 < n; l0 += 64) {  // 64 atoms, one to a lane
+        const bool on = l0 + lane < n;
+        const int32_t k = on ? key[a + l0 + lane] : 0;
+        int rank = 0;
+        for (int c0 = 0; c0 < n; c0 += kSortMax) {
+          const int nk = n - c0 < kSortMax ? n - c0 : kSortMax;
+          for (int l = lane; l < nk; l += 64) kk[w][l] = key[a + c0 + l];
+          wave_lds_sync();
+          for (int m = 0; m < nk; ++m) rank += kk[w][m] < k ? 1 : 0;
+          wave_lds_sync();
         }
-        o.type2[p] = type[s];
-        o.perm2[p] = mk[u];
+        if (on) move(a + rank, src[a + l0 + lane], k);
       }
-    };
-    if (n <= kSortMax) {
-      load(0);
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (lane + 64 * u < n) kk[w][lane + 64 * u] = mk[u];
-      count_smaller(n);
-      move(0);
       continue;
     }
-    for (int b0 = 0; b0 < n; b0 += kSortMax) {
-      load(b0);
-      for (int c0 = 0; c0 < n; c0 += kSortMax) {
-        const int nk = n - c0 < kSortMax ? n - c0 : kSortMax;
-        for (int l = lane; l < nk; l += 64) kk[w][l] = key[a + c0 + l];
-        count_smaller(nk);
-      }
-      move(b0);
+    int32_t mk[U], ms[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int l = lane + 64 * u;
+      mk[u] = l < n ? key[a + l] : 0;
+      ms[u] = l < n ? src[a + l] : 0;
+      if (l < n) kk[w][l] = mk[u];
     }
+    wave_lds_sync();
+    int rank[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) rank[u] = 0;
+    for (int m = 0; m < n; ++m) {
+      const int32_t km = kk[w][m];
+#pragma unroll
+      for (int u = 0; u < U; ++u) rank[u] += km < mk[u] ? 1 : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (lane + 64 * u < n) move(a + rank[u], ms[u], mk[u]);
+    wave_lds_sync();
   }
 }
 
@@ -505,7 +499,7 @@ __device__ void halo_tile(int64_t N, const CellGrid& g, const double* __restrict
 template <bool MAP>
 __global__ void __launch_bounds__(kBlock)
 k_sort_halo(int64_t N, CellGrid g, int nsort, const int32_t* __restrict__ start, int32_t* __restrict__ count,
-            const int32_t* __restrict__ key, const int32_t* __restrict__ src, const double* __restrict__ x,
+            int32_t* __restrict__ key, int32_t* __restrict__ src, const double* __restrict__ x,
             const double* __restrict__ v, const int32_t* __restrict__ type, SortedState o, HaloTables ht,
             const int32_t* __restrict__ flags) {
   if (flags[FLAG_REBUILD] == 0) return;
