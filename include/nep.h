@@ -263,7 +263,8 @@ int nep_halo_stats(nep_system* s, int64_t* stats4);
  * for L = gE * E + sum_i gF_i . F_i, with gF [N][3] device FP32 in original order
  * (NULL = no force term); accumulate = 1 adds to grad instead of overwriting it.
  * It must follow nep_train_forward (or an evaluation) of the same slot at the
- * same positions, whose pair lists it reuses. Does not synchronise. */
+ * same positions, whose pair lists it reuses. The sums over atoms have a fixed
+ * order: the same inputs give bitwise the same gradient. Does not synchronise. */
 int nep_train_forward(nep_system* s, int32_t slot, const float* theta, double* energy,
                       float* forces);
 int nep_train_backward(nep_system* s, int32_t slot, const float* theta, double gE,
@@ -277,7 +278,7 @@ int nep_train_backward(nep_system* s, int32_t slot, const float* theta, double g
  * writes (or, with accumulate = 1, adds) dL/dparams, including dL/dc and the
  * gradient with respect to the descriptor scaler sigma (a caller that keeps
  * sigma fixed ignores that block). The gradient kernels use the system's
- * partial-sum buffer, so calls on one system must not overlap. The same
+ * evaluation buffers, so calls on one system must not overlap. The same
  * ordering rules as nep_train_backward apply. Does not synchronise. */
 int nep_train_forward_params(nep_system* s, int32_t slot, const float* params, double* energy,
                              float* forces);

@@ -210,7 +210,7 @@ struct nep_system {
 
 namespace {
 
-constexpr int kGradMax = 1408;                  // equals train_grad_stride()
+constexpr int kGradMax = 1408;                  // doubles of gradient sums per tile of 256 atoms
 constexpr int kDerivedMax = 10;                 // channels and basis functions the derived tables hold
 
 // Lays out every buffer; with base == nullptr it only measures.
@@ -1314,20 +1314,28 @@ int nep_train_forward(nep_system* s, int32_t slot, const float* theta, double* e
   return NEP_OK;
 }
 
-int nep_train_backward(nep_system* s, int32_t slot, const float* theta, double gE, const float* gF, float* grad,
-                       int32_t accumulate) {
-  if (!s || !theta || !grad || slot < 0 || slot > 1 || !s->has_model[slot]) return fail(s, NEP_ERR_ARG, "bad argument");
-  if (!s->have_list) return fail(s, NEP_ERR_STALE_LIST, "build the neighbour lists first");
+static TrainBuffers train_buffers(nep_system* s, int slot, const float* params, double gE, const float* gF,
+                                  float* grad, int32_t accumulate) {
   TrainBuffers t;
   t.e = eval_buffers(s, slot);
-  t.theta = theta;
+  t.theta = params;
   t.gE = gE;
   t.perm = s->perm;
   t.gF = gF;
   t.w = s->gF;
   t.gpart = s->gpart;
+  t.gpart_size = (int64_t)s->nblocks * kGradMax;
+  t.rec1_size = (int64_t)((s->capR + 15) / 16) * s->N * 8;
   t.grad = grad;
   t.accumulate = accumulate ? 1 : 0;
+  return t;
+}
+
+int nep_train_backward(nep_system* s, int32_t slot, const float* theta, double gE, const float* gF, float* grad,
+                       int32_t accumulate) {
+  if (!s || !theta || !grad || slot < 0 || slot > 1 || !s->has_model[slot]) return fail(s, NEP_ERR_ARG, "bad argument");
+  if (!s->have_list) return fail(s, NEP_ERR_STALE_LIST, "build the neighbour lists first");
+  const TrainBuffers t = train_buffers(s, slot, theta, gE, gF, grad, accumulate);
   HIPCHK(launch_train_backward(s->mdev[slot], t, s->st));
   s->force_valid[slot] = false;
   return NEP_OK;
@@ -1351,16 +1359,7 @@ int nep_train_backward_params(nep_system* s, int32_t slot, const float* params, 
                               float* grad, int32_t accumulate) {
   if (!s || !params || !grad || slot < 0 || slot > 1 || !s->has_model[slot]) return fail(s, NEP_ERR_ARG, "bad argument");
   if (!s->have_list) return fail(s, NEP_ERR_STALE_LIST, "build the neighbour lists first");
-  TrainBuffers t;
-  t.e = eval_buffers(s, slot);
-  t.theta = params;
-  t.gE = gE;
-  t.perm = s->perm;
-  t.gF = gF;
-  t.w = s->gF;
-  t.gpart = s->gpart;
-  t.grad = grad;
-  t.accumulate = accumulate ? 1 : 0;
+  const TrainBuffers t = train_buffers(s, slot, params, gE, gF, grad, accumulate);
   HIPCHK(launch_train_backward_params(s->mdev[slot], t, s->st));
   s->force_valid[slot] = false;
   return NEP_OK;

@@ -369,7 +369,9 @@ struct TrainBuffers {
   const float* gF;       // [N][3] original order, may be null
   float* w;              // [N][3] scratch: gF in sorted order
   double gE;
-  double* gpart;         // [tiles of 256 atoms][train_grad_stride()] FP64 gradient sums
+  // FP64 gradient sums, a row to a workgroup, go to gpart, e.G, e.rec and e.rec1
+  double* gpart;
+  int64_t gpart_size, rec1_size;  // in doubles
   float* grad;           // [G] output
   int accumulate;        // 1: grad += result
 };
@@ -381,7 +383,6 @@ hipError_t launch_train_backward(const ModelDev& m, const TrainBuffers& t, hipSt
 hipError_t launch_train_forward_params(const ModelDev& m, const float* params, const EvalBuffers& b,
                                        hipStream_t st);
 hipError_t launch_train_backward_params(const ModelDev& m, const TrainBuffers& t, hipStream_t st);
-int train_grad_stride();
 hipError_t launch_adam(float* theta, const float* g, float* m1, float* m2, int64_t n, int64_t t,
                        double lr, double b1, double b2, double eps, hipStream_t st);
 

@@ -28,19 +28,50 @@ namespace {
 using namespace kern;
 
 // A row of gradient sums: [W0 sums (hidden-major) | alpha | gE t - z d | cR | cA | sigma].
-constexpr int kGradStride = 1408;
-constexpr int kGradRows = 64;   // rows that the workgroups share
-inline int grad_rows(int64_t N) {
-  const int nb = grid_blocks(N);
-  return nb < kGradRows ? nb : kGradRows;
+// Every workgroup of the gradient kernel stores a row of its own and the rows are summed in
+// a fixed order, so that equal inputs give equal bits. The rows lie in the buffers that only
+// an evaluation or a list build uses, one after the other: a workgroup has 16 centers or
+// more, for which these hold 1,176 doubles and the list scratch 128 for every 16 entries
+// of the radial capacity; a row takes 1,350 at most (two species), fewer where the lanes
+// would not fit (train_lanes).
+constexpr int kGradSegs = 4;
+struct GradRows {
+  double* base[kGradSegs];
+  int end[kGradSegs];  // rows in the segments up to this one
+  int len;             // doubles of a row
+  __device__ __forceinline__ double* row(int r) const {
+    double* p = base[0];
+    int first = 0;
+#pragma unroll
+    for (int k = 1; k < kGradSegs; ++k)
+      if (r >= end[k - 1]) {
+        p = base[k];
+        first = end[k - 1];
+      }
+    return p + (int64_t)(r - first) * len;
+  }
+};
+GradRows grad_rows(const TrainBuffers& t, int len) {
+  const int64_t N = t.e.N;
+  double* const base[kGradSegs] = {t.gpart, reinterpret_cast<double*>(t.e.G), reinterpret_cast<double*>(t.e.rec),
+                                   reinterpret_cast<double*>(t.e.rec1)};
+  const int64_t size[kGradSegs] = {t.gpart_size, 60 * N, 8 * N, t.rec1_size};
+  GradRows g;
+  g.len = len;
+  int rows = 0;
+  for (int k = 0; k < kGradSegs; ++k) {
+    rows += (int)(size[k] / len);
+    g.base[k] = base[k];
+    g.end[k] = rows;
+  }
+  return g;
 }
 
-// The force weights in sorted order, [N][3], and the rows cleared.
+// The force weights in sorted order, [N][3].
 __global__ void k_train_prep(int64_t N, const int32_t* __restrict__ perm, const float* __restrict__ gF,
-                             float* __restrict__ w, double* __restrict__ rows, int64_t nrow) {
+                             float* __restrict__ w) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  for (int64_t k = p; k < nrow; k += (int64_t)gridDim.x * blockDim.x) rows[k] = 0.0;
-  if (!gF || p >= N) return;
+  if (p >= N) return;
   const int64_t o = perm[p];
   for (int c = 0; c < 3; ++c) w[3 * p + c] = gF[3 * o + c];
 }
@@ -78,7 +109,7 @@ __device__ __forceinline__ void for_each_train(const EvalBuffers& b, const float
 }
 
 // Gradients of the network parameters and, with COEF, of the coefficients and the scaler,
-// summed over centers into `rows`. L lanes share a center: one pass over its list gives the
+// each workgroup's sum over its centers into its row. L lanes share a center: one pass over its list gives the
 // basis sums, the accumulators s and their JVP sd together (two accumulators per harmonic
 // and channel: one wavefront per SIMD); the network runs on MFMA with the wavefront's
 // centers as rows, as does the sum of the outer products over them; the angular
@@ -90,7 +121,7 @@ __device__ __forceinline__ void for_each_train(const EvalBuffers& b, const float
 // shape); with sincospi and coefficient gathers per pair in place of the tables.
 template <class S, bool MULTI, bool COEF, int L>
 __global__ void __launch_bounds__(kBlock, 1)
-k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, double* __restrict__ rows, int nrows) {
+k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, GradRows rows) {
   constexpr int NR = S::NR, NA = S::NA, NC = S::NC, D = S::D, H = S::H, KR = S::KR, KA = S::KA;
   constexpr int TT = MULTI ? kMaxTypes : 1;
   constexpr int CW = 64 / L;                      // centers of a wavefront
@@ -98,7 +129,6 @@ k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, 
   constexpr int TILE = 16 * RT * kNetStride;
   constexpr int NCOEF = TT * TT * (NR * KR + NA * KA) + D;
   constexpr int kNet = 32 * 32 + 2 * 32;          // a wavefront's network sums
-  static_assert(H * D + 2 * H + NCOEF <= kGradStride, "row too short");
   static_assert(5 * TILE >= kNet, "the tiles hold a wavefront's network sums");
   __shared__ NetLds net;
   __shared__ PairTab<S, MULTI> tab;
@@ -439,40 +469,68 @@ k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, 
     tq[32 * 32 + 32 + lane] = cb;
   }
   __syncthreads();
-  double* out = rows + (int64_t)(blockIdx.x % nrows) * kGradStride;
-  auto add = [&](int e, float a0, float a1, float a2, float a3) {
-    unsafeAtomicAdd(out + e, ((double)a0 + (double)a1) + ((double)a2 + (double)a3));
+  double* out = rows.row(blockIdx.x);
+  auto put = [&](int e, float a0, float a1, float a2, float a3) {
+    out[e] = ((double)a0 + (double)a1) + ((double)a2 + (double)a3);
   };
   for (int e = threadIdx.x; e < H * D + 2 * H; e += kBlock) {
     const int u = e - H * D;
     const int src = u < 0 ? (e / D) * 32 + e % D : (u < H ? 32 * 32 + u : 32 * 32 + 32 + u - H);
-    add(e, tiles[0][src], tiles[1][src], tiles[2][src], tiles[3][src]);
+    put(e, tiles[0][src], tiles[1][src], tiles[2][src], tiles[3][src]);
   }
   if constexpr (COEF)
     for (int e = threadIdx.x; e < NCOEF; e += kBlock)
-      add(H * D + 2 * H + e, red[0][e], red[1][e], red[2][e], red[3][e]);
+      put(H * D + 2 * H + e, red[0][e], red[1][e], red[2][e], red[3][e]);
 }
 
-// The gradient from the rows, in packed order: [cR | cA | sigma] first when ncoef > 0, then
-// [W0 | b0 | w1 | b1]. Four threads to an entry, each a quarter of the rows.
-__global__ void __launch_bounds__(kBlock)
-k_grad_finish(const double* __restrict__ rows, int nrows, int H, int D, int ncoef, double gE, int64_t N,
-              float* __restrict__ grad, int accumulate) {
+// More than kGradGroups rows are first summed in that many groups of `per` rows, each into
+// its first one. Four threads to an entry, each a quarter of the rows in order.
+constexpr int kGradGroups = 256;
+__global__ void __launch_bounds__(kBlock) k_grad_groups(GradRows rows, int nrows, int per) {
   __shared__ double sh[kBlock];
-  const int e = blockIdx.x * (kBlock / 4) + threadIdx.x % (kBlock / 4), part = threadIdx.x / (kBlock / 4);
-  const int G = H * D + 2 * H + 1;
-  const int u = e - ncoef;  // entry of the network block
-  const int src = u < 0 ? G - 1 + e : u;
+  constexpr int E = kBlock / 4;
+  const int e = blockIdx.x * E + threadIdx.x % E, part = threadIdx.x / E;
+  const int first = blockIdx.y * per, end = first + per < nrows ? first + per : nrows;
   double sum = 0.0;
-  if (e < ncoef + G - 1) {
+  if (e < rows.len) {
 #pragma unroll 4
-    for (int r = part; r < nrows; r += 4) sum += rows[(int64_t)r * kGradStride + src];
+    for (int r = first + part; r < end; r += 4) sum += rows.row(r)[e];
   }
   sh[threadIdx.x] = sum;
   __syncthreads();
-  if (part != 0 || e >= ncoef + G) return;
   const int t = threadIdx.x;
-  double out = (sh[t] + sh[t + kBlock / 4]) + (sh[t + kBlock / 2] + sh[t + 3 * (kBlock / 4)]);
+  if (part == 0 && e < rows.len && first < end) rows.row(first)[e] = (sh[t] + sh[t + E]) + (sh[t + 2 * E] + sh[t + 3 * E]);
+}
+
+// The gradient from rows 0, per, 2 per, ... below nrows, in packed order: [cR | cA | sigma]
+// first when ncoef > 0, then [W0 | b0 | w1 | b1]. kFinishParts threads to an entry, each every
+// kFinishParts-th row in order (eight loads in flight: the kernel is the latency of rows that
+// other dies wrote), then those sums in a fixed order. At most kGradGroups rows.
+constexpr int kFinishParts = 32, kFinishEntries = kBlock / kFinishParts;
+__global__ void __launch_bounds__(kBlock)
+k_grad_finish(GradRows rows, int nrows, int per, int H, int D, int ncoef, double gE, int64_t N,
+              float* __restrict__ grad, int accumulate) {
+  __shared__ double sh[kBlock / 64][kFinishEntries];
+  const int lane_e = threadIdx.x % kFinishEntries, part = threadIdx.x / kFinishEntries;
+  const int e = blockIdx.x * kFinishEntries + lane_e;
+  const int G = H * D + 2 * H + 1;
+  const int u = e - ncoef;  // entry of the network block
+  const int src = u < 0 ? G - 1 + e : u;
+  const bool on = e < ncoef + G - 1;
+  double v[kGradGroups / kFinishParts], sum = 0.0;
+#pragma unroll
+  for (int k = 0; k < kGradGroups / kFinishParts; ++k) {
+    const int r = (part + k * kFinishParts) * per;
+    v[k] = on && r < nrows ? rows.row(r)[src] : 0.0;
+  }
+#pragma unroll
+  for (int k = 0; k < kGradGroups / kFinishParts; ++k) sum += v[k];
+#pragma unroll
+  for (int o = kFinishEntries; o < 64; o <<= 1) sum += __shfl_xor(sum, o, 64);
+  if ((threadIdx.x & 63) < kFinishEntries) sh[threadIdx.x >> 6][lane_e] = sum;
+  __syncthreads();
+  if (threadIdx.x >= kFinishEntries || e >= ncoef + G) return;
+  double out = (sh[0][lane_e] + sh[1][lane_e]) + (sh[2][lane_e] + sh[3][lane_e]);
   if (u >= H * D && u < H * D + H) out = -out;  // dL/db0 = -sum alpha
   if (u == G - 1) out = -gE * (double)N;
   grad[e] = accumulate ? (float)((double)grad[e] + out) : (float)out;
@@ -500,36 +558,45 @@ __global__ void k_adam(float* __restrict__ theta, const float* __restrict__ g, f
 //   8,788                   142    87   125               43    35    48
 //   32,000                  150   168   307               45    43    92
 //   256,000                1081  1244  2359              272   231   623
+// Sixteen lanes need a row for every 16 centers: where the list scratch of a small radial
+// capacity is too short for a model of many coefficients, four lanes, whose rows always fit.
 template <class S>
-int train_lanes(int64_t N) {
+int train_lanes(int64_t N, const GradRows& rows) {
   constexpr int64_t kLanes = 65536;
-  return N * 16 <= kLanes ? 16 : (N * 4 <= kLanes || S::L3 <= 2 ? 4 : 2);
+  if (N * 16 <= kLanes && grid_blocks(N, kBlock / 16) <= rows.end[kGradSegs - 1]) return 16;
+  return N * 4 <= kLanes || S::L3 <= 2 ? 4 : 2;
 }
 
 template <class S, bool MULTI, bool COEF>
-void launch_grad(const ModelDev& m, const TrainBuffers& t, int nrows, hipStream_t st) {
+void launch_grad(const ModelDev& m, const TrainBuffers& t, int L, int nb, const GradRows& rows, hipStream_t st) {
   const float* w = t.gF ? t.w : nullptr;
-  const int L = train_lanes<S>(t.e.N);
-  const dim3 nb(grid_blocks(t.e.N, kBlock / L));
+  const dim3 grid(nb), block(kBlock);
   if (L == 16)
-    hipLaunchKernelGGL((k_train_grad<S, MULTI, COEF, 16>), nb, dim3(kBlock), 0, st, m, t.e, w, t.gE, t.gpart, nrows);
+    hipLaunchKernelGGL((k_train_grad<S, MULTI, COEF, 16>), grid, block, 0, st, m, t.e, w, t.gE, rows);
   else if (L == 4)
-    hipLaunchKernelGGL((k_train_grad<S, MULTI, COEF, 4>), nb, dim3(kBlock), 0, st, m, t.e, w, t.gE, t.gpart, nrows);
+    hipLaunchKernelGGL((k_train_grad<S, MULTI, COEF, 4>), grid, block, 0, st, m, t.e, w, t.gE, rows);
   else if constexpr (S::L3 > 2)
-    hipLaunchKernelGGL((k_train_grad<S, MULTI, COEF, 2>), nb, dim3(kBlock), 0, st, m, t.e, w, t.gE, t.gpart, nrows);
+    hipLaunchKernelGGL((k_train_grad<S, MULTI, COEF, 2>), grid, block, 0, st, m, t.e, w, t.gE, rows);
 }
 
 template <class S, bool COEF>
 hipError_t launch_backward_shape(const ModelDev& m, const TrainBuffers& t, hipStream_t st) {
-  const int nrows = grad_rows(t.e.N);
-  hipLaunchKernelGGL(k_train_prep, dim3(grid_blocks(t.gF ? t.e.N : (int64_t)nrows * kGradStride)), dim3(kBlock), 0, st,
-                     t.e.N, t.perm, t.gF, t.w, t.gpart, (int64_t)nrows * kGradStride);
-  if (m.T > 1) launch_grad<S, true, COEF>(m, t, nrows, st);
-  else launch_grad<S, false, COEF>(m, t, nrows, st);
+  const int64_t N = t.e.N;
   const int ncoef = COEF ? m.T * m.T * (m.nR * m.kR + m.nA * m.kA) + m.D : 0;
-  const int G = m.H * m.D + 2 * m.H + 1;
-  hipLaunchKernelGGL(k_grad_finish, dim3(grid_blocks(ncoef + G, kBlock / 4)), dim3(kBlock), 0, st, t.gpart, nrows,
-                     m.H, m.D, ncoef, t.gE, t.e.N, t.grad, t.accumulate);
+  const int net = m.H * m.D + 2 * m.H;
+  const GradRows rows = grad_rows(t, net + ncoef);
+  const int L = train_lanes<S>(N, rows);
+  const int nb = grid_blocks(N, kBlock / L);
+  if (nb > rows.end[kGradSegs - 1]) return hipErrorInvalidValue;
+  if (t.gF) hipLaunchKernelGGL(k_train_prep, dim3(grid_blocks(N)), dim3(kBlock), 0, st, N, t.perm, t.gF, t.w);
+  if (m.T > 1) launch_grad<S, true, COEF>(m, t, L, nb, rows, st);
+  else launch_grad<S, false, COEF>(m, t, L, nb, rows, st);
+  const int per = (nb + kGradGroups - 1) / kGradGroups;
+  if (per > 1)
+    hipLaunchKernelGGL(k_grad_groups, dim3(grid_blocks(rows.len, kBlock / 4), (nb + per - 1) / per), dim3(kBlock), 0, st,
+                       rows, nb, per);
+  hipLaunchKernelGGL(k_grad_finish, dim3(grid_blocks(ncoef + net + 1, kFinishEntries)), dim3(kBlock), 0, st, rows, nb, per,
+                     m.H, m.D, ncoef, t.gE, N, t.grad, t.accumulate);
   return hipGetLastError();
 }
 
@@ -567,8 +634,6 @@ hipError_t launch_adam(float* theta, const float* g, float* m1, float* m2, int64
                      b2, eps);
   return hipGetLastError();
 }
-
-int train_grad_stride() { return kGradStride; }
 
 hipError_t launch_train_forward(const ModelDev& m, const float* theta, const EvalBuffers& b, hipStream_t st) {
   return launch_eval(with_theta(m, theta), 0, b, st);
