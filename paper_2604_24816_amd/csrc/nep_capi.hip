@@ -859,6 +859,7 @@ int nep_build_neighbors(nep_system* s, double skin) {
   s->have_list = true;
   s->list_skin = skin;
   s->force_valid[0] = s->force_valid[1] = false;
+  s->nhc_ke = false;  // as in a run resumed here: the kinetic energy from the velocities in the new order
   return NEP_OK;
 }
 
@@ -1015,9 +1016,10 @@ int vv_step(nep_system* s, int slot, int prec, double dt, int rebuild_every, dou
 
 // Chain half steps (dt/2): the trailing one of a step and (or) the leading one of the next,
 // from the kinetic energy in the partials or (from_partials false) the one the chain left.
-int nhc_halves(nep_system* s, double dt, bool from_partials, bool trail, bool lead) {
+// early: the step may have rebuilt its lists unscheduled (see launch_nhc).
+int nhc_halves(nep_system* s, double dt, bool from_partials, bool trail, bool lead, bool early) {
   HIPCHK(launch_nhc(s->N, from_partials ? s->partial : nullptr, s->nblocks, s->nhc, s->nvt_M, kBoltzmann * s->nvt_T,
-                    s->nvt_tau, 0.5 * dt, trail, lead, s->st));
+                    s->nvt_tau, 0.5 * dt, trail, lead, early ? s->flags : nullptr, s->v, s->type, s->mt, s->st));
   return NEP_OK;
 }
 
@@ -1077,17 +1079,18 @@ int nep_step(nep_system* s, int64_t n_steps, double dt_fs, int32_t rebuild_every
       const bool stop = last || scheduled || row;
       if (nvt && !led) {
         if (!s->nhc_ke) HIPCHK(launch_kinetic(s->N, s->v, s->type, s->mt, s->partial, s->st));
-        if ((st = nhc_halves(s, dt_fs, !s->nhc_ke, false, true))) return st;
+        if ((st = nhc_halves(s, dt_fs, !s->nhc_ke, false, true, false))) return st;
       }
       link.defer = !nvt && !stop;
       if ((st = vv_step(s, 0, precision, dt_fs, rebuild_every, skin, link))) return st;
       link.pending = link.defer;
       if (nvt) {
-        if ((st = nhc_halves(s, dt_fs, true, true, !stop))) return st;
+        if ((st = nhc_halves(s, dt_fs, true, true, !stop, !scheduled))) return st;
         if (stop) HIPCHK(launch_scale_v(s->N, s->nhc, s->v, s->st));
         led = !stop;
         // the next leading half step takes the kinetic energy from the chain, except after a
         // scheduled rebuild, where a run resumed from a checkpoint takes it from the velocities
+        // (after an early one k_nhc does so)
         s->nhc_ke = !scheduled;
       }
       // the row is queued before the check waits for the stream, and read after it

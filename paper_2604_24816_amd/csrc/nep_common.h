@@ -335,8 +335,11 @@ constexpr int kNhcDoubles = kNhcTrail + 3;
 // Chain half steps of length h, one after the other: the trailing one of a step and (or) the
 // leading one of the next. The kinetic energy is the sum of the nblocks P_KE partials, or
 // (partial null) the one the chain left. The scales of the half steps not taken are 1.
-hipError_t launch_nhc(int64_t N, const double* partial, int nblocks, double* nhc, int M, double kT, double tau,
-                      double h, bool trail, bool lead, hipStream_t st);
+// flags (with a trailing half step and partials; else null): where they say that the step
+// rebuilt its lists, the kinetic energy after that half step is summed from the velocities.
+hipError_t launch_nhc(int64_t N, double* partial, int nblocks, double* nhc, int M, double kT, double tau, double h,
+                      bool trail, bool lead, const int32_t* flags, const double* v, const int32_t* type, MassTable mt,
+                      hipStream_t st);
 // v *= the trailing scale.
 hipError_t launch_scale_v(int64_t N, const double* nhc, double* v, hipStream_t st);
 hipError_t launch_kinetic(int64_t N, const double* v, const int32_t* type, MassTable mt,

@@ -229,34 +229,82 @@ __device__ double nhc_half(double& ke, double* eta, double* ve, int M, double kT
   return sc;
 }
 
+// The kinetic energy from the nblocks P_KE partials, in every thread of a workgroup of
+// kRedBlock; sh holds kRedBlock / 64 doubles.
+__device__ double kinetic_sum(const double* partial, int nblocks, double* sh) {
+  double ke = 0.0;
+#pragma unroll 4
+  for (int b = threadIdx.x; b < nblocks; b += kRedBlock) ke += partial[(int64_t)b * kPartialStride + P_KE];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) ke += __shfl_xor(ke, o, 64);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = ke;
+  __syncthreads();
+  ke = 0.0;
+  for (int k = 0; k < kRedBlock / 64; ++k) ke += sh[k];
+  return ke;
+}
+
+// What k_kinetic leaves in the P_KE partials for the velocities v scale, by one workgroup of
+// kRedBlock threads (the same additions in the same order, four of its workgroups at a time).
+__device__ void kinetic_partials(int64_t N, const double* v, double scale, const int32_t* type, const MassTable& mt,
+                                 double* partial, int nblocks, double* sh) {
+  const int t = threadIdx.x % kBlock, g = threadIdx.x / kBlock;
+  double* s = sh + g * kBlock;
+  for (int b0 = 0; b0 < nblocks; b0 += kRedBlock / kBlock) {
+    const int b = b0 + g;
+    const int64_t p = (int64_t)b * kBlock + t;
+    double ke = 0.0;
+    if (p < N) {
+      const double m = mt.mass[type[p]];
+      for (int c = 0; c < 3; ++c) {
+        const double vv = v[c * N + p] * scale;
+        ke += vv * vv;
+      }
+      ke *= 0.5 * m * 103.642697;
+    }
+    __syncthreads();
+    s[t] = ke;
+    __syncthreads();
+    for (int off = kBlock / 2; off > 0; off >>= 1) {
+      if (t < off) s[t] += s[t + off];
+      __syncthreads();
+    }
+    if (t == 0 && b < nblocks) partial[(int64_t)b * kPartialStride + P_KE] = s[0];
+  }
+  __syncthreads();
+}
+
 // The chain's half steps between two kicks (see launch_nhc): the sum of the kinetic energy's
 // partials and both half steps in one launch, where each half step took four (kinetic
 // energy, its sum, the chain, the scaling of v, which the next kick now does): 36 of the 240 us
-// of a 33,660-atom step.
+// of a 33,660-atom step. flags (nullable): after a step that rebuilt its lists early the
+// kinetic energy is taken from the scaled velocities, as a run resumed from that step takes
+// it, not carried through the scaling (the two differ in the last places); rare, so that
+// this one workgroup may do it.
 __global__ void __launch_bounds__(kRedBlock)
-k_nhc(const double* __restrict__ partial, int nblocks, double* __restrict__ nhc, int M, double kT, double Nf,
-      double tau2, double h, int trail, int lead) {
-  __shared__ double sh[kRedBlock / 64];
-  double ke = 0.0;
-  if (partial) {
-#pragma unroll 4
-    for (int b = threadIdx.x; b < nblocks; b += kRedBlock) ke += partial[(int64_t)b * kPartialStride + P_KE];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) ke += __shfl_xor(ke, o, 64);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = ke;
-    __syncthreads();
-    ke = 0.0;
-    for (int k = 0; k < kRedBlock / 64; ++k) ke += sh[k];
-  } else {
-    ke = nhc[kNhcKe];
-  }
-  if (threadIdx.x != 0) return;
+k_nhc(double* partial, int nblocks, double* __restrict__ nhc, int M, double kT, double Nf, double tau2, double h,
+      int trail, int lead, const int32_t* __restrict__ flags, int64_t N, const double* __restrict__ v,
+      const int32_t* __restrict__ type, MassTable mt) {
+  __shared__ double sh[kRedBlock], scale;
+  const bool rebuilt = flags && flags[FLAG_REBUILD] != 0;
+  double ke = partial ? kinetic_sum(partial, nblocks, sh) : nhc[kNhcKe];
+  if (threadIdx.x != 0 && !rebuilt) return;
   double eta[kMaxChain], ve[kMaxChain];
-  for (int k = 0; k < M; ++k) {
-    eta[k] = nhc[k];
-    ve[k] = nhc[kMaxChain + k];
+  if (threadIdx.x == 0) {
+    for (int k = 0; k < M; ++k) {
+      eta[k] = nhc[k];
+      ve[k] = nhc[kMaxChain + k];
+    }
+    const double s = trail ? nhc_half(ke, eta, ve, M, kT, Nf, tau2, h) : 1.0;
+    nhc[kNhcTrail] = s;
+    scale = s;
   }
-  nhc[kNhcTrail] = trail ? nhc_half(ke, eta, ve, M, kT, Nf, tau2, h) : 1.0;
+  if (rebuilt) {
+    __syncthreads();
+    kinetic_partials(N, v, scale, type, mt, partial, nblocks, sh);
+    ke = kinetic_sum(partial, nblocks, sh);
+    if (threadIdx.x != 0) return;
+  }
   nhc[kNhcLead] = lead ? nhc_half(ke, eta, ve, M, kT, Nf, tau2, h) : 1.0;
   nhc[kNhcKe] = ke;
   for (int k = 0; k < M; ++k) {
@@ -372,10 +420,11 @@ hipError_t launch_kick_drift(int64_t N, double dt, CellGrid g, const float* F, c
   return hipGetLastError();
 }
 
-hipError_t launch_nhc(int64_t N, const double* partial, int nblocks, double* nhc, int M, double kT, double tau,
-                      double h, bool trail, bool lead, hipStream_t st) {
+hipError_t launch_nhc(int64_t N, double* partial, int nblocks, double* nhc, int M, double kT, double tau, double h,
+                      bool trail, bool lead, const int32_t* flags, const double* v, const int32_t* type, MassTable mt,
+                      hipStream_t st) {
   hipLaunchKernelGGL(k_nhc, dim3(1), dim3(kRedBlock), 0, st, partial, nblocks, nhc, M, kT, 3.0 * (double)N - 3.0,
-                     tau * tau, h, trail ? 1 : 0, lead ? 1 : 0);
+                     tau * tau, h, trail ? 1 : 0, lead ? 1 : 0, flags, N, v, type, mt);
   return hipGetLastError();
 }
 
