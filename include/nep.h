@@ -320,6 +320,10 @@ int nep_surrogate_error(nep_system* s, int32_t precision, double* err2);
 int nep_profile(nep_system* s, int32_t enable);
 int nep_profile_read(nep_system* s, double* ms6, int64_t* count6);
 
+/* Whether the system's error words and scalar results come through the pinned host
+ * block: *in_use = 1, or 0 where they are copied (the block holds 256 systems). */
+int nep_host_words(const nep_system* s, int32_t* in_use);
+
 /* Pair counts summed over atoms at the last evaluation: counts3 = {radial pairs
  * (r < rc_radial), angular pairs (r < rc_angular), radial list entries with skin}. */
 int nep_pair_counts(nep_system* s, int64_t* counts3);

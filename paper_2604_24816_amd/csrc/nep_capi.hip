@@ -1423,6 +1423,12 @@ int nep_profile_read(nep_system* s, double* ms6, int64_t* count6) {
   return NEP_OK;
 }
 
+int nep_host_words(const nep_system* s, int32_t* in_use) {
+  if (!s || !in_use) return NEP_ERR_ARG;
+  *in_use = s->host ? 1 : 0;
+  return NEP_OK;
+}
+
 int nep_pair_counts(nep_system* s, int64_t* counts3) {
   if (!s || !counts3) return NEP_ERR_ARG;
   if (!s->force_valid[0] && !s->force_valid[1]) return fail(s, NEP_ERR_STALE_LIST, "no evaluation yet");

@@ -42,7 +42,7 @@ EXPORTED = [
     "nep_train_backward64",
     "nep_adam_update",
     "nep_surrogate_error", "nep_status_string", "nep_last_error", "nep_profile", "nep_profile_read",
-    "nep_pair_counts", "nep_compute_energy_forces_virial_noalloc",
+    "nep_host_words", "nep_pair_counts", "nep_compute_energy_forces_virial_noalloc",
 ]
 
 
@@ -102,6 +102,7 @@ def load_library(path: str = LIB_PATH):
         "nep_surrogate_error": [vp, i32, vp],
         "nep_profile": [vp, i32],
         "nep_profile_read": [vp, vp, vp],
+        "nep_host_words": [vp, vp],
         "nep_pair_counts": [vp, vp],
         "nep_compute_energy_forces_virial_noalloc": [vp, i64, vp, i32, i32, f64, vp, vp, i32, vp, vp, vp, vp, vp],
     }
@@ -337,6 +338,13 @@ class NEPSystem:
         self._check(self.lib.nep_get_stats(self.handle, _np_ptr(s)))
         return {"list_builds": int(s[0]), "mts_blocks": int(s[1]), "fallback_blocks": int(s[2]),
                 "steps": int(s[3])}
+
+    def uses_host_words(self) -> bool:
+        """Whether error words and scalar results come through pinned host memory (a process
+        has words for 256 systems; the others copy them)."""
+        f = ctypes.c_int32()
+        self._check(self.lib.nep_host_words(self.handle, ctypes.byref(f)))
+        return bool(f.value)
 
     def halo_stats(self) -> dict:
         """Force-halo tables of the last list build: tiles, tiles on the global-atomic
