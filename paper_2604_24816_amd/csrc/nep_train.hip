@@ -77,8 +77,8 @@ __global__ void k_train_prep(int64_t N, const int32_t* __restrict__ perm, const 
 }
 
 // The neighbours of one lane of a center: entries l, l + L, ... below k1, each with its FP64
-// position, force weight and species loaded while the entry before is worked on.
-template <bool MULTI, int L, class Body>
+// position, force weight (FORCE) and species loaded while the entry before is worked on.
+template <bool MULTI, bool FORCE, int L, class Body>
 __device__ __forceinline__ void for_each_train(const EvalBuffers& b, const float* __restrict__ w, int64_t i, int l,
                                                int k1, Body&& body) {
   if (k1 <= 0) return;
@@ -94,9 +94,9 @@ __device__ __forceinline__ void for_each_train(const EvalBuffers& b, const float
     q.x = b.x[j];
     q.y = b.x[N + j];
     q.z = b.x[2 * N + j];
-    q.w0 = w ? w[3 * (int64_t)j] : 0.f;
-    q.w1 = w ? w[3 * (int64_t)j + 1] : 0.f;
-    q.w2 = w ? w[3 * (int64_t)j + 2] : 0.f;
+    q.w0 = FORCE ? w[3 * (int64_t)j] : 0.f;
+    q.w1 = FORCE ? w[3 * (int64_t)j + 1] : 0.f;
+    q.w2 = FORCE ? w[3 * (int64_t)j + 2] : 0.f;
     q.t = MULTI ? b.type[j] : 0;
     return q;
   };
@@ -109,7 +109,9 @@ __device__ __forceinline__ void for_each_train(const EvalBuffers& b, const float
 }
 
 // Gradients of the network parameters and, with COEF, of the coefficients and the scaler,
-// each workgroup's sum over its centers into its row. L lanes share a center: one pass over its list gives the
+// each workgroup's sum over its centers into its row. Without a force term (FORCE false) there
+// is no JVP: v, z, E_k, sd and what they enter are left out (a backward call of 37,044 atoms,
+// network: 152 us with them, 76 without). L lanes share a center: one pass over its list gives the
 // basis sums, the accumulators s and their JVP sd together (two accumulators per harmonic
 // and channel: one wavefront per SIMD); the network runs on MFMA with the wavefront's
 // centers as rows, as does the sum of the outer products over them; the angular
@@ -119,7 +121,7 @@ __device__ __forceinline__ void for_each_train(const EvalBuffers& b, const float
 // of their own and the descriptors computed again for the coefficients, took 287 us for
 // the network's gradient of 32,000 atoms and 57 + 89 us for both of 4,000 atoms (l <= 2
 // shape); with sincospi and coefficient gathers per pair in place of the tables.
-template <class S, bool MULTI, bool COEF, int L>
+template <class S, bool MULTI, bool COEF, bool FORCE, int L>
 __global__ void __launch_bounds__(kBlock, 1)
 k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, GradRows rows) {
   constexpr int NR = S::NR, NA = S::NA, NC = S::NC, D = S::D, H = S::H, KR = S::KR, KA = S::KA;
@@ -168,14 +170,14 @@ k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, 
     xi = b.x[i];
     yi = b.x[N + i];
     zi = b.x[2 * N + i];
-    if (w) {
+    if constexpr (FORCE) {
       wi0 = w[3 * i];
       wi1 = w[3 * i + 1];
       wi2 = w[3 * i + 2];
     }
     kA = angular_bound(b, i);
     // Fk, Ek hold sum f_c T_k and sum (f_c T_k)' (u.w) (k >= 1) and the k = 0 sums of f_c
-    for_each_train<MULTI, L>(b, w, i, l, radial_bound(b, i), [&](int p, const auto& e) {
+    for_each_train<MULTI, FORCE, L>(b, w, i, l, radial_bound(b, i), [&](int p, const auto& e) {
       double ex, ey, ez;
       const double r2 = pair_r2_64(e.x, e.y, e.z, xi, yi, zi, Lx, Ly, Lz, iLx, iLy, iLz, ex, ey, ez);
       if (!(r2 < rcR2)) return;
@@ -186,8 +188,8 @@ k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, 
       const float ux = dx * rinv, uy = dy * rinv, uz = dz * rinv;
       const float uw = ux * w0 + uy * w1 + uz * w2;
       {
-        const RadialGeo g = radial_geo<true>(r, cutR);
-        const float df = kDR * g.c * uw, xf = g.fc * (kYR * g.y) * uw;
+        const RadialGeo g = radial_geo<FORCE>(r, cutR);
+        const float df = FORCE ? kDR * g.c * uw : 0.f, xf = FORCE ? g.fc * (kYR * g.y) * uw : 0.f;
         float ft[TT], dt[TT], xt[TT];  // the factors for the neighbour's species, 0 for the others
 #pragma unroll
         for (int t = 0; t < TT; ++t) {
@@ -196,7 +198,7 @@ k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, 
           dt[t] = on ? df : 0.f;
           xt[t] = on ? xf : 0.f;
           Fk[t][0] += ft[t];
-          Ek[t][0] += dt[t];
+          if constexpr (FORCE) Ek[t][0] += dt[t];
         }
         const float x2 = g.x + g.x;
         float Tm = 1.f, T = g.x, Um = 0.f, U = 1.f;  // T_{k-1}, T_k, U_{k-2}, U_{k-1}
@@ -206,7 +208,7 @@ k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, 
 #pragma unroll
           for (int t = 0; t < TT; ++t) {
             Fk[t][k] = fmaf(ft[t], T, Fk[t][k]);
-            Ek[t][k] = fmaf(dt[t], T, fmaf(xt[t], kU, Ek[t][k]));
+            if constexpr (FORCE) Ek[t][k] = fmaf(dt[t], T, fmaf(xt[t], kU, Ek[t][k]));
           }
           const float Tn = fmaf(x2, T, -Tm), Un = fmaf(x2, U, -Um);
           Tm = T;
@@ -217,24 +219,32 @@ k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, 
       }
       if (p < kA && r2 < rcA2) {
         // ds_nlm . w = g_n' (u.w) P_lm + g_n (grad P_lm . w - l P_lm (u.w)) / r
-        const RadialGeo g = radial_geo<true>(r, cutA);
+        const RadialGeo g = radial_geo<FORCE>(r, cutA);
         float gn[NA], gu[NA];
-        if constexpr (MULTI) radial_cd_tab<S, true>(g.x, ang_tab(tab, ti, e.t), gn, gu);
-        else radial_cd_fast<NA, KA>(g.x, uniform_coeffs(m.hA), gn, gu);
-        const float df = kDA * g.c * uw, xf = g.fc * (kYA * g.y) * uw;
+        if constexpr (MULTI) radial_cd_tab<S, FORCE>(g.x, ang_tab(tab, ti, e.t), gn, gu);
+        else if constexpr (FORCE) radial_cd_fast<NA, KA>(g.x, uniform_coeffs(m.hA), gn, gu);
+        else radial_g_fast<NA, KA>(1.f, g.x, uniform_coeffs(m.hA), gn);
+        const float df = FORCE ? kDA * g.c * uw : 0.f, xf = FORCE ? g.fc * (kYA * g.y) * uw : 0.f;
 #pragma unroll
         for (int n = 0; n < NA; ++n) {
-          gu[n] = fmaf(df, gn[n], xf * gu[n]);
+          if constexpr (FORCE) gu[n] = fmaf(df, gn[n], xf * gu[n]);
           gn[n] *= g.fc;
         }
-        for_each_poly_grad<NC>(ux, uy, uz, [&](int lm, float P, auto px, auto py, auto pz) {
-          const float bb = fmac(w0, px, fmac(w1, py, fmac(w2, pz, -(float)comp_l(lm) * P * uw))) * rinv;
+        if constexpr (FORCE) {
+          for_each_poly_grad<NC>(ux, uy, uz, [&](int lm, float P, auto px, auto py, auto pz) {
+            const float bb = fmac(w0, px, fmac(w1, py, fmac(w2, pz, -(float)comp_l(lm) * P * uw))) * rinv;
 #pragma unroll
-          for (int n = 0; n < NA; ++n) {
-            s[n * NC + lm] = fmaf(gn[n], P, s[n * NC + lm]);
-            sd[n * NC + lm] = fmaf(gu[n], P, fmaf(gn[n], bb, sd[n * NC + lm]));
-          }
-        });
+            for (int n = 0; n < NA; ++n) {
+              s[n * NC + lm] = fmaf(gn[n], P, s[n * NC + lm]);
+              sd[n * NC + lm] = fmaf(gu[n], P, fmaf(gn[n], bb, sd[n * NC + lm]));
+            }
+          });
+        } else {
+          for_each_poly<NC>(ux, uy, uz, [&](int lm, float P) {
+#pragma unroll
+            for (int n = 0; n < NA; ++n) s[n * NC + lm] = fmaf(gn[n], P, s[n * NC + lm]);
+          });
+        }
       }
     });
 #pragma unroll
@@ -243,7 +253,7 @@ k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, 
 #pragma unroll
       for (int k = 1; k < KR; ++k) {
         Fk[t][k] = 0.5f * (Fk[t][k] + Fk[t][0]);
-        Ek[t][k] = 0.5f * (Ek[t][k] + Ek[t][0]);
+        if constexpr (FORCE) Ek[t][k] = 0.5f * (Ek[t][k] + Ek[t][0]);
       }
       auto add = [&](auto c) {
 #pragma unroll
@@ -251,7 +261,7 @@ k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, 
 #pragma unroll
           for (int k = 0; k < KR; ++k) {
             q[n] = fmaf(c[n * KR + k], Fk[t][k], q[n]);
-            v[n] = fmaf(c[n * KR + k], Ek[t][k], v[n]);
+            if constexpr (FORCE) v[n] = fmaf(c[n * KR + k], Ek[t][k], v[n]);
           }
       };
       if constexpr (MULTI) add(tab.rad + (ti * kMaxTypes + t) * (NR * KR));
@@ -260,22 +270,24 @@ k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, 
 #pragma unroll
     for (int n = 0; n < NR; ++n) {
       q[n] = lanes_sum<L>(q[n]);
-      v[n] = lanes_sum<L>(v[n]);
+      if constexpr (FORCE) v[n] = lanes_sum<L>(v[n]);
     }
 #pragma unroll
     for (int k = 0; k < NA * NC; ++k) {
       s[k] = lanes_sum<L>(s[k]);
-      sd[k] = lanes_sum<L>(sd[k]);
+      if constexpr (FORCE) sd[k] = lanes_sum<L>(sd[k]);
     }
     desc_finish<S>(s, q);
+    if constexpr (FORCE) {
 #pragma unroll
-    for (int n = 0; n < NA; ++n)
+      for (int n = 0; n < NA; ++n)
 #pragma unroll
-      for (int lm = 0; lm < NC; ++lm) {
-        const int k = NR + (comp_l(lm) - 1) * NA + n;
-        v[k] = fmaf(2.f * kW[lm] * s[n * NC + lm], sd[n * NC + lm], v[k]);
-      }
-    if constexpr (S::FB) {
+        for (int lm = 0; lm < NC; ++lm) {
+          const int k = NR + (comp_l(lm) - 1) * NA + n;
+          v[k] = fmaf(2.f * kW[lm] * s[n * NC + lm], sd[n * NC + lm], v[k]);
+        }
+    }
+    if constexpr (FORCE && S::FB) {
 #pragma unroll
       for (int n = 0; n < NA; ++n) {
         float d4[5];
@@ -296,19 +308,19 @@ k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, 
   for (int k = 0; k < 32; ++k)
     if ((k & (L - 1)) == l) {
       tq[row + k] = k < D ? q[k < D ? k : 0] * net.sigma[k] : 0.f;
-      tv[row + k] = k < D ? v[k < D ? k : 0] * net.sigma[k] : 0.f;
+      if constexpr (FORCE) tv[row + k] = k < D ? v[k < D ? k : 0] * net.sigma[k] : 0.f;
     }
   net_product<RT, true>(tq, ta, net);
-  net_product<RT, true>(tv, tb, net);
+  if constexpr (FORCE) net_product<RT, true>(tv, tb, net);
   const float gEf = (float)gE;
 #pragma unroll
   for (int mu0 = 0; mu0 < 32; mu0 += L) {
     const int mu = mu0 + l;
-    const float t = tanhf(ta[row + mu] - net.b0[mu]), z = tb[row + mu], w1 = net.w1[mu];
+    const float t = tanhf(ta[row + mu] - net.b0[mu]), z = FORCE ? tb[row + mu] : 0.f, w1 = net.w1[mu];
     const float d = 1.f - t * t, w1d = w1 * d;
-    ta[row + mu] = valid ? fmaf(gEf, w1d, 2.f * z * w1 * t * d) : 0.f;
-    tb[row + mu] = valid ? w1d : 0.f;
-    tg[row + mu] = valid ? fmaf(gEf, t, -z * d) : 0.f;
+    ta[row + mu] = valid ? (FORCE ? fmaf(gEf, w1d, 2.f * z * w1 * t * d) : gEf * w1d) : 0.f;
+    if constexpr (FORCE) tb[row + mu] = valid ? w1d : 0.f;
+    tg[row + mu] = valid ? (FORCE ? fmaf(gEf, t, -z * d) : gEf * t) : 0.f;
   }
   wave_lds_sync();
   // sum over the wavefront's centers of alpha q~^T - beta v~^T, and of alpha and gE t - z d
@@ -318,7 +330,7 @@ k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, 
 #pragma unroll
     for (int C = 0; C < 2; ++C) acc[R][C] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int pass = 0; pass < 2; ++pass)
+  for (int pass = 0; pass < (FORCE ? 2 : 1); ++pass)
 #pragma unroll
     for (int kb = 0; kb < CW / 4; ++kb) {
       const int c0 = (4 * kb + lk) * kNetStride;
@@ -356,15 +368,15 @@ k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, 
       }
     };
     net_product<RT, false>(ta, ta, net);
-    net_product<RT, false>(tb, tb, net);
+    if constexpr (FORCE) net_product<RT, false>(tb, tb, net);
     // dL/dq and dU/dq of the lane's center (zero where there is none)
     float rho[D], fp[D];
 #pragma unroll
     for (int k = 0; k < D; ++k) {
-      const float sa = ta[row + k], sb = tb[row + k];
+      const float sa = ta[row + k], sb = FORCE ? tb[row + k] : 0.f;
       rho[k] = net.sigma[k] * sa;
       fp[k] = net.sigma[k] * sb;
-      total((k & (L - 1)) == l ? q[k] * sa - v[k] * sb : 0.f, oS + k);
+      total((k & (L - 1)) == l ? (FORCE ? q[k] * sa - v[k] * sb : q[k] * sa) : 0.f, oS + k);
     }
     // radial coefficients [t_i][t][n][k], linear in the lanes' parts of the basis sums
 #pragma unroll
@@ -373,25 +385,27 @@ k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, 
       for (int n = 0; n < NR; ++n)
 #pragma unroll
         for (int k = 0; k < KR; ++k)
-          total_by_type(rho[n] * Fk[t][k] - fp[n] * Ek[t][k], (t * NR + n) * KR + k, TT * NR * KR);
+          total_by_type(FORCE ? rho[n] * Fk[t][k] - fp[n] * Ek[t][k] : rho[n] * Fk[t][k], (t * NR + n) * KR + k,
+                        TT * NR * KR);
     // angular coefficients A (in place of s) and C (in place of sd)
 #pragma unroll
     for (int n = 0; n < NA; ++n) {
       float d4[5] = {}, h4[5] = {};
       if constexpr (S::FB) {
         fourbody_ds(s + n * NC, d4);
-        fourbody_ds_dir(s + n * NC, sd + n * NC, h4);
+        if constexpr (FORCE) fourbody_ds_dir(s + n * NC, sd + n * NC, h4);
       }
 #pragma unroll
       for (int lm = 0; lm < NC; ++lm) {
         const int k = NR + (comp_l(lm) - 1) * NA + n;
-        float a = 2.f * kW[lm] * fp[k] * s[n * NC + lm];
-        float c = 2.f * kW[lm] * (rho[k] * s[n * NC + lm] - fp[k] * sd[n * NC + lm]);
+        float a = FORCE ? 2.f * kW[lm] * fp[k] * s[n * NC + lm] : 0.f;
+        float c = FORCE ? 2.f * kW[lm] * (rho[k] * s[n * NC + lm] - fp[k] * sd[n * NC + lm])
+                        : 2.f * kW[lm] * (rho[k] * s[n * NC + lm]);
         if constexpr (S::FB) {
           if (comp_l(lm) == 2) {
             const int k4 = NR + S::L3 * NA + n;
-            a = fmaf(fp[k4], d4[lm - 3], a);
-            c += rho[k4] * d4[lm - 3] - fp[k4] * h4[lm - 3];
+            if constexpr (FORCE) a = fmaf(fp[k4], d4[lm - 3], a);
+            c += FORCE ? rho[k4] * d4[lm - 3] - fp[k4] * h4[lm - 3] : rho[k4] * d4[lm - 3];
           }
         }
         s[n * NC + lm] = a;
@@ -403,7 +417,7 @@ k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, 
     for (int t = 0; t < TT; ++t)
 #pragma unroll
       for (int k = 0; k < NA * KA; ++k) gc[t][k] = 0.f;
-    for_each_train<MULTI, L>(b, w, i, l, kA, [&](int, const auto& e) {
+    for_each_train<MULTI, FORCE, L>(b, w, i, l, kA, [&](int, const auto& e) {
       double ex, ey, ez;
       const double r2 = pair_r2_64(e.x, e.y, e.z, xi, yi, zi, Lx, Ly, Lz, iLx, iLy, iLz, ex, ey, ez);
       if (!(r2 < rcA2)) return;
@@ -416,27 +430,34 @@ k_train_grad(ModelDev m, EvalBuffers b, const float* __restrict__ w, double gE, 
       float X[NA], Y[NA], Z[NA];
 #pragma unroll
       for (int n = 0; n < NA; ++n) X[n] = Y[n] = Z[n] = 0.f;
-      for_each_poly_grad<NC>(ux, uy, uz, [&](int lm, float P, auto px, auto py, auto pz) {
-        const float bb = fmac(w0, px, fmac(w1, py, fmac(w2, pz, -(float)comp_l(lm) * P * uw))) * rinv;
+      if constexpr (FORCE) {
+        for_each_poly_grad<NC>(ux, uy, uz, [&](int lm, float P, auto px, auto py, auto pz) {
+          const float bb = fmac(w0, px, fmac(w1, py, fmac(w2, pz, -(float)comp_l(lm) * P * uw))) * rinv;
 #pragma unroll
-        for (int n = 0; n < NA; ++n) {
-          X[n] = fmaf(sd[n * NC + lm], P, X[n]);
-          Y[n] = fmaf(s[n * NC + lm], P, Y[n]);
-          Z[n] = fmaf(s[n * NC + lm], bb, Z[n]);
-        }
-      });
-      const RadialGeo g = radial_geo<true>(r, cutA);
+          for (int n = 0; n < NA; ++n) {
+            X[n] = fmaf(sd[n * NC + lm], P, X[n]);
+            Y[n] = fmaf(s[n * NC + lm], P, Y[n]);
+            Z[n] = fmaf(s[n * NC + lm], bb, Z[n]);
+          }
+        });
+      } else {
+        for_each_poly<NC>(ux, uy, uz, [&](int lm, float P) {
+#pragma unroll
+          for (int n = 0; n < NA; ++n) X[n] = fmaf(sd[n * NC + lm], P, X[n]);
+        });
+      }
+      const RadialGeo g = radial_geo<FORCE>(r, cutA);
       // f_k and f'_k (u.w), from T_k and T_k' = k U_{k-1}
-      const float df = kDA * g.c * uw, xf = g.fc * (kYA * g.y) * uw;
+      const float df = FORCE ? kDA * g.c * uw : 0.f, xf = FORCE ? g.fc * (kYA * g.y) * uw : 0.f;
       const float x2 = g.x + g.x;
       float Tm = 0.f, T = 1.f, Um = 0.f, U = 0.f;
 #pragma unroll
       for (int k = 0; k < KA; ++k) {
         const float f = 0.5f * g.fc * (T + 1.f);
-        const float fd = 0.5f * fmaf(df, T + 1.f, xf * ((float)k * U));
+        const float fd = FORCE ? 0.5f * fmaf(df, T + 1.f, xf * ((float)k * U)) : 0.f;
 #pragma unroll
         for (int n = 0; n < NA; ++n) {
-          const float t1 = fmaf(f, X[n] - Z[n], -fd * Y[n]);
+          const float t1 = FORCE ? fmaf(f, X[n] - Z[n], -fd * Y[n]) : f * X[n];
 #pragma unroll
           for (int t = 0; t < TT; ++t) gc[t][n * KA + k] += !MULTI || e.t == t ? t1 : 0.f;
         }
@@ -567,16 +588,15 @@ int train_lanes(int64_t N, const GradRows& rows) {
   return N * 4 <= kLanes || S::L3 <= 2 ? 4 : 2;
 }
 
-template <class S, bool MULTI, bool COEF>
+template <class S, bool MULTI, bool COEF, bool FORCE>
 void launch_grad(const ModelDev& m, const TrainBuffers& t, int L, int nb, const GradRows& rows, hipStream_t st) {
-  const float* w = t.gF ? t.w : nullptr;
   const dim3 grid(nb), block(kBlock);
   if (L == 16)
-    hipLaunchKernelGGL((k_train_grad<S, MULTI, COEF, 16>), grid, block, 0, st, m, t.e, w, t.gE, rows);
+    hipLaunchKernelGGL((k_train_grad<S, MULTI, COEF, FORCE, 16>), grid, block, 0, st, m, t.e, t.w, t.gE, rows);
   else if (L == 4)
-    hipLaunchKernelGGL((k_train_grad<S, MULTI, COEF, 4>), grid, block, 0, st, m, t.e, w, t.gE, rows);
+    hipLaunchKernelGGL((k_train_grad<S, MULTI, COEF, FORCE, 4>), grid, block, 0, st, m, t.e, t.w, t.gE, rows);
   else if constexpr (S::L3 > 2)
-    hipLaunchKernelGGL((k_train_grad<S, MULTI, COEF, 2>), grid, block, 0, st, m, t.e, w, t.gE, rows);
+    hipLaunchKernelGGL((k_train_grad<S, MULTI, COEF, FORCE, 2>), grid, block, 0, st, m, t.e, t.w, t.gE, rows);
 }
 
 template <class S, bool COEF>
@@ -588,9 +608,14 @@ hipError_t launch_backward_shape(const ModelDev& m, const TrainBuffers& t, hipSt
   const int L = train_lanes<S>(N, rows);
   const int nb = grid_blocks(N, kBlock / L);
   if (nb > rows.end[kGradSegs - 1]) return hipErrorInvalidValue;
-  if (t.gF) hipLaunchKernelGGL(k_train_prep, dim3(grid_blocks(N)), dim3(kBlock), 0, st, N, t.perm, t.gF, t.w);
-  if (m.T > 1) launch_grad<S, true, COEF>(m, t, L, nb, rows, st);
-  else launch_grad<S, false, COEF>(m, t, L, nb, rows, st);
+  if (t.gF) {
+    hipLaunchKernelGGL(k_train_prep, dim3(grid_blocks(N)), dim3(kBlock), 0, st, N, t.perm, t.gF, t.w);
+    if (m.T > 1) launch_grad<S, true, COEF, true>(m, t, L, nb, rows, st);
+    else launch_grad<S, false, COEF, true>(m, t, L, nb, rows, st);
+  } else {
+    if (m.T > 1) launch_grad<S, true, COEF, false>(m, t, L, nb, rows, st);
+    else launch_grad<S, false, COEF, false>(m, t, L, nb, rows, st);
+  }
   const int per = (nb + kGradGroups - 1) / kGradGroups;
   if (per > 1)
     hipLaunchKernelGGL(k_grad_groups, dim3(grid_blocks(rows.len, kBlock / 4), (nb + per - 1) / per), dim3(kBlock), 0, st,
