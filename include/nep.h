@@ -225,11 +225,12 @@ int nep_set_judge(nep_system* s, int32_t relative);
  * from each neighbour j's). deterministic = 0 (the default): each center adds its
  * angular terms to its neighbours with atomic additions, so the order of the FP32
  * sums, and the last bits of the forces, can change from run to run.
- * deterministic = 1: no atomics; every atom sums its own terms and then, in list
- * order, the angular terms of its neighbours, each recomputed from that
- * neighbour's dU/ds; the same list, positions and model then give bitwise the
- * same forces, energy and virial on every run. It costs a second pass over the
- * angular lists in the force kernel. Energies are unchanged; forces agree with
+ * deterministic = 1: no atomics; every atom sums its own terms and then the
+ * angular terms of its neighbours, each recomputed from that neighbour's dU/ds,
+ * in an order that the list, the number of atoms and the model's shape fix; the
+ * same list, positions and model then give bitwise the same forces, energy and
+ * virial on every run. It costs a second pass over the angular lists in the
+ * force kernel. Energies are unchanged; forces agree with
  * the default mode to FP32 rounding. Returns NEP_ERR_ARG for other values.
  * Systems created while the environment variable NEP_DETERMINISTIC is "1" start
  * in deterministic mode. */
@@ -292,8 +293,8 @@ int nep_train_backward_params(nep_system* s, int32_t slot, const float* params, 
  * differences of that evaluation's L check it (Section III.B: the expansion
  * coefficients c are trainable; the descriptor scaler sigma and the network
  * weights likewise). Every descriptor, JVP, network and gradient term is FP64;
- * one thread per center, sums over atoms with FP64 atomics (the last bits
- * depend on their order). gF: [N][3] device FP64 in original order, or NULL
+ * 16 lanes per center, sums over workgroups of 16 centers with FP64 atomics (the
+ * last bits depend on their order). gF: [N][3] device FP64 in original order, or NULL
  * for no force term. grad: device FP64, n_params values in the packed order
  * [cR | cA | sigma | W0 | b0 | w1 | b1], overwritten. Uses the sort scratch and
  * the system's stream; does not synchronise. Returns NEP_ERR_STALE_LIST

@@ -5,8 +5,8 @@
 //   k_desc_net  (256-thread workgroups)
 //     1. radial descriptors q_n = sum_j g_n(r_ij) (Section III.B) and angular
 //        accumulators s_nlm = sum_j g_n(r_ij) P_lm(u_ij) for every channel n in one
-//        pass over the center's list with skin, each visited entry tested against
-//        the true cutoffs in FP64 (Algorithm 1's geometry reuse with the channel tile
+//        pass over the center's list with skin, each visited entry's FP32 r^2 tested
+//        against the true cutoffs (Algorithm 1's geometry reuse with the channel tile
 //        equal to all n_max+1 channels); from them q_nl = sum_m W_lm s_nlm^2 and the
 //        four-body invariant tr(S_n^3);
 //     2. the network U_i = w1 . tanh(W0 q~ - b0) - b1 and its gradient
@@ -708,11 +708,13 @@ __global__ void k_add_late(int64_t n, const double* __restrict__ late, float* __
 
 // DET: the deterministic form. Nothing is scattered: each atom adds, after its own pair
 // terms, the angular forces of the centers that have it as an angular neighbour, each
-// recomputed from that center's dU/ds (atom-major rows) in list order, and stores its
-// force. The sets agree: a pair inside rc_angular lies in both atoms' angular prefixes,
-// and the box-fraction pair vector of (j, i) is the exact negation of that of (i, j), so
-// both sides see the same r^2. The terms are bitwise those the scattering form adds, in
-// a fixed order.
+// recomputed from that center's dU/ds (atom-major rows), and stores its force. With L lanes
+// each takes every L-th list entry and the lanes' sums are added in a fixed order, so the
+// order follows the list and the lane count, that is the system's size and the model's
+// shape. The sets agree: a pair inside rc_angular lies in both atoms' angular prefixes, and
+// the box-fraction pair vector of (j, i) is the exact negation of that of (i, j), so both
+// sides see the same r^2. The terms are bitwise those the scattering form adds, in a fixed
+// order.
 template <class S, bool MULTI, bool DET, int L>
 __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, EvalBuffers b) {
   __shared__ double red[4 * 10];
@@ -856,7 +858,7 @@ __global__ void __launch_bounds__(kBlock, force_waves<S>()) k_force(ModelDev m, 
       for_each_rec_fast<W, 1, 4>(b.nbr, plane, N, i, 0, kR, pair_both);
     nz = lanes_sum<L>(nz);
     if constexpr (DET) {
-      // the neighbours' angular terms on this atom, in list order
+      // the neighbours' angular terms on this atom, the lane's entries in list order
       const uint64_t n64 = (uint64_t)N;
       for (int p = l; p < kA; p += L) {
         const int32_t j = b.nbr[(uint64_t)(uint32_t)p * n64 + i];

@@ -1,9 +1,10 @@
-// Pair arithmetic of the evaluation kernels (k_desc_net, k_force), written for the
-// fewest VALU instructions per pair: the cutoff function from short Taylor series on
+// Pair arithmetic of the evaluation kernels (k_desc_net, k_force) and of the training
+// gradient (k_train_grad), written for the fewest VALU instructions per pair: the cutoff function from short Taylor series on
 // the one interval it needs, the Chebyshev basis through the recurrences of both kinds
 // with model-derived coefficient tables, the radial force by Clenshaw's recurrence, and
 // a neighbour loop whose prefetch buffers rotate without copies.
-// The training kernels keep the direct forms of nep_kernels.h.
+// The direct forms of nep_kernels.h (sincospif, a pair's g_n from its coefficients) remain for
+// the bfloat16 network with two species.
 #pragma once
 
 #include "nep_kernels.h"

@@ -296,8 +296,8 @@ k_scan_scatter(int64_t N, int ncell, const int32_t* __restrict__ count, const in
 // whatever order the scatter's atomics left. The keys are read through LDS kSortMax at a
 // time: once for a cell of up to that many atoms (all cells at metallic densities), once for
 // each 64 atoms of a larger one. By one lane, with an insertion sort, those cost n^2
-// dependent accesses: the list build of 4,000 atoms in one cell took 53 ms (26 so), of 1,200
-// in a 10 A cube 5.3 (1.8).
+// dependent accesses: the list build of 4,000 atoms in one cell took 53 ms (30 so), of 1,200
+// in a 10 A cube 5.3 (1.5).
 constexpr int kSortMax = 256;
 constexpr int kSortWaves = kBlock / 64;
 
